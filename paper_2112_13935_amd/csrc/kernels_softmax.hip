@@ -3,13 +3,12 @@
 // One workgroup (8 waves) per client runs the client's whole round (Algorithm 2,
 // MainComputeNode: s_i recursions).  The replica w_c (C x D weights + C biases) and the
 // gradient sum U stay in registers for the round: thread t owns columns t, t+512, ... of
-// every class row.  Per recursion the only memory traffic is the sampled row (prefetched one
-// recursion ahead: the index hash is a counter, so the next row is known) and its label.
+// every class row.  Per recursion the only memory traffic is the sampled row (fetched three
+// recursions ahead: the index hash is a counter, so the rows are known).
 //
-//   z_o = b_o + sum_k W[o][k] x[k]   per-thread partial sums, DPP reduction inside a wave,
+//   z_o = b_o + sum_k W[o][k] x[k]   per-thread partial sums, lane swaps and DPP inside a wave,
 //                                    one LDS hop across the 8 waves (fixed order)
-//   p = softmax(z), dz = p - onehot  lane o of every 16-lane row handles class o (DPP row
-//                                    reductions); dz is then handed to the matrix cores
+//   p = softmax(z), dz = p - onehot  every lane handles three classes, its quad all of them
 //   W[o][k] -= eta dz_o x[k];  U[o][k] += dz_o x[k]      in registers, as 4 x 4 outer products
 //                                    on the matrix cores (g never stored)
 //
@@ -19,21 +18,10 @@
 
 namespace aet {
 
-constexpr int kSmThreads = 512;
-constexpr int kSmWaves = kSmThreads / 64;
-
-// sum over the 64 lanes of a wave; the total ends up in lane 63
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-    // within quads, then across the halves of 8 and 16 lanes of a row
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
-    // lane 15 of a row to the next row (rows 1 and 3), then lane 31 to rows 2 and 3
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x142, 0xA, 0xF, false));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x143, 0xC, 0xF, false));
-    return v;
-}
+constexpr int kSmWaves = 8;
+constexpr int kSmThreads = 64 * kSmWaves;
+constexpr int kSmDepth = 4;    // rows in registers: at work, just done with, and two on the way
+constexpr int kSmBlock = 48;   // recursions per block of row numbers; a multiple of kSmDepth
 
 // Sums of N values over the 64 lanes of a wave, several values per instruction.  The lane
 // swaps of gfx950 exchange half-waves (rows of 16 lanes) between two registers, so that one
@@ -71,19 +59,15 @@ __device__ __forceinline__ void wave_sum_rows(const float (&v)[N], float (&out)[
     for (int k = 0; k < NQ; ++k) out[k] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, out[k]), 0x140, 0xF, 0xF, true));
 }
 
-// sum / max over each row of 16 lanes (every lane of the row gets the result)
-__device__ __forceinline__ float row_sum_dpp(float v) {
+// sum / max over each quad (every lane of it gets the result)
+__device__ __forceinline__ float quad_sum_dpp(float v) {
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
     return v;
 }
-__device__ __forceinline__ float row_max_dpp(float v) {
+__device__ __forceinline__ float quad_max_dpp(float v) {
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true)));
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)));
     return v;
 }
 
@@ -98,105 +82,197 @@ __device__ __forceinline__ float row_max_dpp(float v) {
 // owns columns t, t+512, ... of every class row), so the logits still need no other lane's
 // data, and three instructions per 64 columns cover classes 0..11 (rows 10 and 11 stay
 // zero).  The vector ALU is left with the dot products, the reductions and the softmax.
+//
+// What bounds it: with many clients instruction issue (two waves per SIMD, some 150 vector and 36
+// matrix instructions each per recursion at D = 3072), with few clients the chain dots - wave
+// reduction - LDS hop - softmax - update, the same for every width.  So what need not be on that
+// chain is off it: U of a recursion is added while the next one's partial logits travel through
+// LDS; a lane softmaxes just the three classes whose dz it hands to the matrix core (no lane
+// exchange after it); row numbers are hashed 48 recursions at a time; rows are asked for three
+// recursions ahead, and no load stands behind a branch or goes through the scalar cache, so
+// that nothing waits for more than the row it needs.  Measured, 1,024 clients x 3,072 columns, 40
+// rounds: 23.8 -> 19.9 ms (2.6 -> 3.1 TB/s of rows); 4 clients x 784 columns, 20 rounds: 1.79
+// -> 1.64 ms.  Four waves with twice the columns each: 21.8 and 1.75 ms; two rows ahead 20.0,
+// five no better.
 // NC columns per thread; EXACT: D == 512 * NC, no column guards.
+// dword 3 of a raw buffer descriptor for 32-bit untyped accesses on this part
+constexpr int kBufferFlags = 0x00020000;
+
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 template <int NC, bool EXACT>
 __global__ void __launch_bounds__(kSmThreads, 1)
 k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
     constexpr int C = 10, Q = 3;   // classes, groups of four class rows
+    constexpr int NW = kSmWaves, T = kSmThreads, DEPTH = kSmDepth;
     const RoundParams p = rp[blockIdx.x];
-    const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, cls = lane & 15;
+    const int tid = threadIdx.x, lane = tid & 63, l4 = lane & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    __shared__ float zpart[2][kSmWaves][16];
+    // partial logits [parity][class][wave]: a lane reads the eight waves' sums of one class as
+    // two 16-byte pieces; classes 10 and 11 stay zero
+    __shared__ __attribute__((aligned(16))) float zpart[2][4 * Q][NW];
+    if (tid < 2 * 2 * NW) zpart[tid / (2 * NW)][C + (tid / NW) % 2][tid % NW] = 0.f;
 
-    if (!Wg) Wg = p.W;
+    const gcf_ptr W0 = as_global(Wg ? Wg : p.W);
     f4v W[NC][Q], U[NC][Q];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-        const int k = tid + kSmThreads * j;
+        const int k = tid + T * j;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int o = 4 * q + r;
-                W[j][q][r] = (o < C && (EXACT || k < D)) ? Wg[(int64_t)o * D + k] : 0.f;
+                W[j][q][r] = (o < C && (EXACT || k < D)) ? W0[(int64_t)o * D + k] : 0.f;
                 U[j][q][r] = 0.f;
             }
     }
-    float bias = cls < C ? Wg[(int64_t)C * D + cls] : 0.f, Ub = 0.f;
+    // lane l looks after classes l%4, 4 + l%4, 8 + l%4 (every quad has a copy); the two that do
+    // not exist have a bias that keeps them out of the maximum and the sum
+    float bias[Q], Ub[Q], dz[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        bias[q] = 4 * q + l4 < C ? W0[(int64_t)C * D + 4 * q + l4] : -3.0e38f;
+        Ub[q] = 0.f;
+        dz[q] = 0.f;
+    }
     float loss_acc = 0.f;
 
-    auto load_row = [&](uint32_t row, float (&x)[NC], int &lab) {
+    // Row numbers and labels come a block of kSmBlock recursions at a time: lane l hashes
+    // recursion l of the block (the lanes beyond it the rows that are fetched ahead), and each
+    // recursion picks its own with a lane read: the hash of one recursion alone is a chain of
+    // some forty scalar instructions.  Beyond the round's end the last row stands.
+    uint32_t rowv = 0, rown = 0;
+    int labv = 0, labn = 0;
+    auto next_block = [&](int u) {
+        rown = sample_row(p.key, (uint64_t)(p.q0 + min(u + lane, p.m - 1)), p.n_samples);
+        labn = yg[rown];
+    };
+    // The loads of a row have no branches, so that the compiler can count them and wait for the
+    // one row it needs: a range-checked buffer per row (columns beyond D read zero).
+    auto load_row = [&](int i, float (&x)[NC]) {
+        const uint32_t row = __builtin_amdgcn_readlane(rowv, i);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(p.X) + (int64_t)row * D, 0, 4 * D, kBufferFlags);
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            const int k = tid + kSmThreads * j;
-            x[j] = (EXACT || k < D) ? Xg[(int64_t)row * D + k] : 0.f;
-        }
-        lab = yg[row];
+        for (int j = 0; j < NC; ++j)
+            x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * (tid + T * j), 0, 0));
+    };
+    // U <- U + dz x^T of one recursion
+    auto add_U = [&](const float (&x)[NC]) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) U[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(dz[q], x[j], U[j][q], 0, 0, 0);
     };
 
-    auto recursion = [&](int u, const float (&x)[NC], int lab, float (&xn)[NC], int &labn) {
-        // prefetch (Algorithm 2, sampling step; the index is a counter hash)
-        if (u + 1 < p.m) load_row(sample_row(p.key, (uint64_t)(p.q0 + u + 1), p.n_samples), xn, labn);
-        float(*zp)[16] = zpart[u & 1];
-        float s[C];
+    // x: this recursion's row; xp: the row of the recursion before, whose dz is still in dz[];
+    // that row's registers then take the row of recursion u + DEPTH - 1.  The loads stand
+    // outside of the branches on `live` (false for the up to DEPTH - 1 steps that fill the last
+    // group): between two of them the same number of loads is issued on every way.
+    auto recursion = [&](int u, int i, const float (&x)[NC], float (&xp)[NC]) {
+        const bool live = u < p.m;
+        const int lab = __builtin_amdgcn_readlane(labv, i);
+        f4v za[Q][NW / 4];
+        if (live) {
+            float(*zp)[NW] = zpart[u & 1];
+            float s[C];
 #pragma unroll
-        for (int o = 0; o < C; ++o) {
-            s[o] = 0.f;
+            for (int o = 0; o < C; ++o) {
+                s[o] = 0.f;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) s[o] += W[j][o >> 2][o & 3] * x[j];
-        }
-        float t[(C + 3) / 4];
-        wave_sum_rows<C>(s, t);
-        if (cls == 0) {
-            const int row = lane >> 4, o0 = ((row & 1) << 1) | (row >> 1);
-#pragma unroll
-            for (int k = 0; k < (C + 3) / 4; ++k)
-                if (4 * k + o0 < C) zp[wave][4 * k + o0] = t[k];
-        }
-        __syncthreads();
-        float z = bias;
-#pragma unroll
-        for (int w = 0; w < kSmWaves; ++w) z += zp[w][cls];
-        const bool live = cls < C;
-        const float zmax = row_max_dpp(live ? z : -3.0e38f);
-        const float ex = live ? __expf(z - zmax) : 0.f;
-        const float lse = zmax + __logf(row_sum_dpp(ex));
-        const float dzl = live ? __expf(z - lse) - (cls == lab ? 1.f : 0.f) : 0.f;
-        if (cls == lab) loss_acc += lse - z;
-        bias -= p.eta * dzl;
-        Ub += dzl;
-        // w <- w - eta g, U <- U + g with g = dz x^T: lane l hands the matrix core entry
-        // 4q + l%4 of dz (lanes 10..15 of a row hold zeros) and its own x
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const float a = __shfl(dzl, 4 * q + (lane & 3), 64);
-            const float na = -p.eta * a;
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                W[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(na, x[j], W[j][q], 0, 0, 0);
-                U[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, x[j], U[j][q], 0, 0, 0);
+                for (int j = 0; j < NC; ++j) s[o] += W[j][o >> 2][o & 3] * x[j];
             }
+            float t[(C + 3) / 4];
+            wave_sum_rows<C>(s, t);
+            if ((lane & 15) == 0) {
+                const int row = lane >> 4, o0 = ((row & 1) << 1) | (row >> 1);
+#pragma unroll
+                for (int k = 0; k < (C + 3) / 4; ++k)
+                    if (4 * k + o0 < C) zp[4 * k + o0][wave] = t[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int h = 0; h < NW / 4; ++h) za[q][h] = *reinterpret_cast<const f4v *>(&zp[4 * q + l4][4 * h]);
+        }
+        // while those travel: the sum U of the recursion before (not on the way to the next
+        // logits), and the row that is needed DEPTH - 1 recursions from now
+        __builtin_amdgcn_sched_barrier(0);
+        add_U(xp);
+        __builtin_amdgcn_sched_barrier(0);
+        load_row(i + DEPTH - 1, xp);
+        if (live) {
+            float z[Q], ex[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const f4v v = za[q][0] + za[q][1];
+                z[q] = bias[q] + ((v[0] + v[1]) + (v[2] + v[3]));
+            }
+            const float zmax = quad_max_dpp(fmaxf(fmaxf(z[0], z[1]), z[2]));
+#pragma unroll
+            for (int q = 0; q < Q; ++q) ex[q] = __expf(z[q] - zmax);
+            const float sum = quad_sum_dpp(ex[0] + ex[1] + ex[2]);
+            const float inv = __builtin_amdgcn_rcpf(sum);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) dz[q] = ex[q] * inv - (4 * q + l4 == lab ? 1.f : 0.f);
+            // w <- w - eta g with g = dz x^T: lane l hands the matrix core entry 4q + l%4 of
+            // dz and its own x
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const float na = -p.eta * dz[q];
+#pragma unroll
+                for (int j = 0; j < NC; ++j) W[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(na, x[j], W[j][q], 0, 0, 0);
+                bias[q] += na;
+                Ub[q] += dz[q];
+            }
+            if (wave == NW - 1) {
+                const float lse = zmax + __logf(sum);
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (4 * q + l4 == lab) loss_acc += lse - z[q];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) dz[q] = 0.f;
         }
     };
 
-    float xa[NC], xb[NC];
-    int la = 0, lb = 0;
-    if (p.m > 0) load_row(sample_row(p.key, (uint64_t)p.q0, p.n_samples), xa, la);
-    int u = 0;
-    for (; u + 1 < p.m; u += 2) {
-        recursion(u, xa, la, xb, lb);
-        recursion(u + 1, xb, lb, xa, la);
+    // DEPTH rows live in registers: the one at work, the one before it and DEPTH - 2 on the way
+    float x[DEPTH][NC];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) x[i][j] = 0.f;
     }
-    if (u < p.m) recursion(u, xa, la, xb, lb);
+    __syncthreads();   // the zeros of zpart
+    if (p.m > 0) {
+        next_block(0);
+        rowv = rown;
+#pragma unroll
+        for (int i = 0; i < DEPTH - 1; ++i) load_row(i, x[i]);
+        // everything has arrived when the loop starts: what is in flight at its head is then
+        // the same on the way in and on the way round, and the compiler waits for a count
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        for (int u0 = 0; u0 < p.m; u0 += kSmBlock) {
+            rowv = rown;
+            labv = labn;
+            next_block(u0 + kSmBlock);
+            const int n = min(kSmBlock, p.m - u0);
+            for (int i0 = 0; i0 < n; i0 += DEPTH)
+#pragma unroll
+                for (int i = 0; i < DEPTH; ++i) recursion(u0 + i0 + i, i0 + i, x[i], x[(i + DEPTH - 1) % DEPTH]);
+        }
+        add_U(x[DEPTH - 1]);   // the last recursion's, unless a filling step has done it
+    }
 
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-        const int k = tid + kSmThreads * j;
+        const int k = tid + T * j;
         if (EXACT || k < D) {
 #pragma unroll
             for (int o = 0; o < C; ++o) {
@@ -205,14 +281,17 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
             }
         }
     }
-    if (tid < C) {
-        Wc[(int64_t)C * D + tid] = bias;
-        Uc[(int64_t)C * D + tid] = Ub;
+    if (tid < 4) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (4 * q + tid < C) {
+                Wc[(int64_t)C * D + 4 * q + tid] = bias[q];
+                Uc[(int64_t)C * D + 4 * q + tid] = Ub[q];
+            }
     }
-    if (wave == 0) {
-        float l = lane < 16 ? loss_acc : 0.f;
-        l = wave_sum_dpp(l);
-        if (lane == 63) *as_global(p.loss) = l;
+    if (wave == NW - 1) {
+        const float l = quad_sum_dpp(loss_acc);
+        if (lane == 0) *as_global(p.loss) = l;
     }
 }
 
