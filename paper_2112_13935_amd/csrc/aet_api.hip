@@ -137,10 +137,19 @@ enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENE
 // aet_test_select_kernels: which kernel set contexts created from now on use
 int g_force_layer_engine = 0, g_plain_layers = 0;
 
-Engine pick_engine(const LayerGeom *lay, int L, int B) {
+// Padded forms of the fused rounds (widths or mini-batches that do not fill their tiles) go to
+// the layer engine beyond this many clients: their exchange records take up to 384 KB per
+// client, which is more than a small model's own state, and with so many clients the layer
+// engine's launches are full.
+constexpr int kPaddedClients = 256;
+
+// padded_ok: the caller has room for the records of a padded form
+Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = true) {
     if (g_force_layer_engine) return ENGINE_LAYERS;
+    const bool padded = padded_ok && n <= kPaddedClients;
     if (L == 2 && lay[0].type == AET_DENSE && lay[1].type == AET_DENSE && lay[0].relu &&
-        mlp_round_supported((int)lay[0].in_size, lay[0].oc, lay[1].oc, B))
+        mlp_round_supported((int)lay[0].in_size, lay[0].oc, lay[1].oc, B) &&
+        (padded || mlp_round_exact(lay[0].oc, B)))
         return ENGINE_MLP;
     if (L == 1 && lay[0].type == AET_DENSE && softmax_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX;
@@ -149,7 +158,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B) {
 }
 
 bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int inflight, int rounds,
-                 Layout *lo) {
+                 Layout *lo, Engine eng) {
     if (n < 1 || inflight < 1 || rounds < 1) return false;
     const size_t Ps = (size_t)((P + 63) / 64 * 64);
     size_t off = 0;
@@ -164,7 +173,6 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     lo->debug = take((size_t)kDebugIdx * 4);
     lo->labels = take((size_t)n * B * 4);
     // exchange records of the fused dense-ReLU-dense engine, only for models it runs
-    const Engine eng = pick_engine(lay, L, B);
     lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n) : 0);
     size_t wg_floats = 0;
     for (int l = 0; l < L; ++l)
@@ -308,7 +316,8 @@ size_t aet_workspace_bytes(const aet_model_desc *model, int32_t n_clients, int32
     std::string why;
     Layout lo;
     if (!resolve(model, lay, &P, &why)) return 0;
-    if (!make_layout(lay, model->n_layers, P, model->batch, n_clients, max_inflight, max_rounds, &lo))
+    if (!make_layout(lay, model->n_layers, P, model->batch, n_clients, max_inflight, max_rounds, &lo,
+                     pick_engine(lay, model->n_layers, model->batch, n_clients)))
         return 0;
     return lo.total;
 }
@@ -354,7 +363,13 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     ctx->seed = seed;
     ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
     ctx->ws = static_cast<char *>(workspace);
-    make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo);
+    Engine engine = pick_engine(ctx->lay, ctx->L, ctx->B, ctx->n);
+    make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine);
+    if (workspace_bytes < ctx->lo.total) {   // a padded form's records are an option, not a need
+        engine = pick_engine(ctx->lay, ctx->L, ctx->B, ctx->n, false);
+        make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine);
+    }
+    ctx->engine = engine;
     if (workspace_bytes < ctx->lo.total) {
         const size_t need = ctx->lo.total;
         delete ctx;
@@ -385,7 +400,6 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     ctx->sc.labels = reinterpret_cast<int32_t *>(ctx->ws + ctx->lo.labels);
     ctx->sc.wgrad = reinterpret_cast<float *>(ctx->ws + ctx->lo.wgrad);
     ctx->sc.plain = g_plain_layers != 0;
-    ctx->engine = pick_engine(ctx->lay, ctx->L, ctx->B);
 
     hipError_t e = hipSuccess;
     if (static_ws) {

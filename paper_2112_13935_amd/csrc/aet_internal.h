@@ -122,6 +122,7 @@ hipError_t launch_softmax_round(hipStream_t s, Profiler *prof, const RoundParams
                                 const float *Wg, int D, int C);
 // fused round of dense-ReLU-dense models (kernels_mlp.hip)
 bool mlp_round_supported(int D, int H, int C, int B);
+bool mlp_round_exact(int H, int B);   // no padded units or samples
 size_t mlp_round_scratch_bytes(int n_clients, int B);
 // hp: HOST array of the tick's round records (they are passed on in kernel arguments)
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact,

@@ -1,7 +1,7 @@
-// Fused local round for dense-ReLU-dense models (D -> H -> C, mini-batch B = 16 or 32).
+// Fused local round for dense-ReLU-dense models (D -> H -> C, mini-batch up to 32).
 //
 // One launch runs the whole round (Algorithm 2, MainComputeNode: all s_i/B recursions) of
-// every active client.  A client is handled by a cluster of G = H/16 workgroups; workgroup
+// every active client.  A client is handled by a cluster of G = ceil(H/16) workgroups; workgroup
 // g owns hidden units 16g..16g+15: its slice of the first layer (16 x D weights, 16
 // biases) and of the second layer (C x 16 weights), together with the matching slices of
 // U, stay in registers / LDS for the whole round, so the per-recursion traffic is the
@@ -32,6 +32,12 @@
 // hidden sums through a second tagged exchange and then compute the same h, logits and
 // second-layer updates side by side.  16 clients x 8 unit groups then occupy all 256
 // compute units instead of 128.
+//
+// Widths and mini-batches that do not fill the 16 x 16 tiles are padded: hidden units beyond H
+// have zero weights, samples beyond the mini-batch repeat its last row with d logits of zero
+// (never a row that was not drawn: it could hold a value that is not finite).  12 clients, 784 ->
+// 100 -> 10, mini-batch 20: 6.3 us per recursion here, 28.7 us as seven launches of the
+// layer-by-layer engine.
 //
 // All workgroups of a client must be resident together: the launcher never has more
 // working workgroups in flight than the device holds (1 per compute unit with this LDS
@@ -122,7 +128,7 @@ struct MlpPack {
 template <int NBT, int TPW, bool FAST, bool FULL, int HF>
 __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
-            int D, int H, int C, int G, unsigned long long *__restrict__ xrec,
+            int D, int H, int C, int G, int Br, unsigned long long *__restrict__ xrec,
             unsigned long long *__restrict__ prec, uint32_t tag0, int *__restrict__ errflag) {
     constexpr int B = 16 * NBT;
     // workgroup -> (client, unit group, half): consecutive workgroup ids go round the 8 XCDs,
@@ -176,7 +182,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     float *Xs = reinterpret_cast<float *>(labs + B); // [B][ld]
 
     const int64_t b1_off = (int64_t)H * D, w2_off = b1_off + H, b2_off = w2_off + (int64_t)C * H;
-    const float invB = 1.0f / (float)B;
+    const float invB = 1.0f / (float)Br;
 
     // The mini-batch travels global -> registers -> matrix core / LDS in the A-operand layout
     // of the forward product: lane (li, lg) holds, for batch tile bt and K tile tt, the four
@@ -203,12 +209,16 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL:
     // peer-to-peer form): own slice into registers / LDS; U = 0 -------------------------
     if (!Wg) Wg = p.W;
+    // own unit of this lane in the first layer; the last group may have units that do not exist:
+    // they carry zero weights, so h, dh and every update of theirs is zero
+    const bool unit_ok = 16 * g + li < H;
+    const int unit = unit_ok ? 16 * g + li : 0;
     f4 W1r[TPW], U1r[TPW];
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
         f4 w = {0.f, 0.f, 0.f, 0.f};
-        if (tt < nt) {
-            const float *src = Wg + (int64_t)(16 * g + li) * D + gcol0 + 16 * tt + 4 * lg;
+        if (tt < nt && unit_ok) {
+            const float *src = Wg + (int64_t)unit * D + gcol0 + 16 * tt + 4 * lg;
             if constexpr (FAST) {   // D a multiple of 16: the four values are one aligned piece
                 w = *reinterpret_cast<const f4 *>(src);
             } else {
@@ -223,12 +233,12 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     {
         const int o = tid >> 4, j = tid & 15;  // threads 0..255 = 16 x 16
         if (tid < 256) {
-            W2s[tid] = (o < C) ? Wg[w2_off + (int64_t)o * H + 16 * g + j] : 0.f;
+            W2s[tid] = (o < C && 16 * g + j < H) ? Wg[w2_off + (int64_t)o * H + 16 * g + j] : 0.f;
             U2s[tid] = 0.f;
         }
         for (int i = tid; i < B * 16; i += kMlpThreads) zs[i] = 0.f;
         if (tid < 16) {
-            b1s[tid] = Wg[b1_off + 16 * g + tid];
+            b1s[tid] = 16 * g + tid < H ? Wg[b1_off + 16 * g + tid] : 0.f;
             Ub1s[tid] = 0.f;
             b2s[tid] = (tid < C) ? Wg[b2_off + tid] : 0.f;
             Ub2s[tid] = 0.f;
@@ -244,7 +254,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         for (int tt = 0; tt < TPW; ++tt) xreg[bt][tt] = f4{0.f, 0.f, 0.f, 0.f};
     if (p.m > 0) {
         uint32_t rowv = 0;
-        if (lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + lane), p.n_samples);
+        if (lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + min(lane, Br - 1)), p.n_samples);
         if (wave == 0 && lane < B) labs[lane] = yg[rowv];
 #pragma unroll
         for (int bt = 0; bt < NBT; ++bt) {
@@ -301,7 +311,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         uint32_t rowv = 0;
         const bool more = u + 1 < p.m;
         auto next_rows = [&]() {
-            if (more && lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)(u + 1) * B + lane), p.n_samples);
+            if (more && lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)(u + 1) * Br + min(lane, Br - 1)), p.n_samples);
         };
         // ---- h = relu(z1 + b1) ----------------------------------------------------------
         const uint32_t tag = tag0 + (uint32_t)u;
@@ -466,7 +476,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                 const float lse = zmax + __logf(row16_sum(ex));
                 const int lab = labs[b];
                 if (o == lab) lossb[b] = lse - z;
-                zs[b * 16 + o] = o < C ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+                zs[b * 16 + o] = o < C && b < Br ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
             }
         }
         __syncthreads();
@@ -499,7 +509,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             }
         } else if (wave == 4) {
             // the recursion's mean loss
-            const float s = row16_sum(fold_rows(lane < B ? lossb[lane] : 0.f));
+            const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
             if (lane == 0) lossacc[0] += s * invB;
         }
         __syncthreads();
@@ -571,8 +581,8 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     // ---- end of round: the replica and the message payload go to HBM ---------------------
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-        if (tt < nt) {
-            const int64_t base = (int64_t)(16 * g + li) * D + gcol0 + 16 * tt + 4 * lg;
+        if (tt < nt && unit_ok) {
+            const int64_t base = (int64_t)unit * D + gcol0 + 16 * tt + 4 * lg;
             if constexpr (FAST) {
                 *reinterpret_cast<f4 __attribute__((address_space(1))) *>(Wc + base) = W1r[tt];
                 *reinterpret_cast<f4 __attribute__((address_space(1))) *>(Uc + base) = U1r[tt];
@@ -589,13 +599,15 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     __syncthreads();
     if (hf == 0) {
         const int o = tid >> 4, j = tid & 15;
-        if (tid < 256 && o < C) {
+        if (tid < 256 && o < C && 16 * g + j < H) {
             Wc[w2_off + (int64_t)o * H + 16 * g + j] = W2s[tid];
             Uc[w2_off + (int64_t)o * H + 16 * g + j] = U2s[tid];
         }
         if (tid < 16) {
-            Wc[b1_off + 16 * g + tid] = b1s[tid];
-            Uc[b1_off + 16 * g + tid] = Ub1s[tid];
+            if (16 * g + tid < H) {
+                Wc[b1_off + 16 * g + tid] = b1s[tid];
+                Uc[b1_off + 16 * g + tid] = Ub1s[tid];
+            }
             if (g == 0 && tid < C) {
                 Wc[b2_off + tid] = b2s[tid];
                 Uc[b2_off + tid] = Ub2s[tid];
@@ -620,11 +632,13 @@ static size_t mlp_lds_bytes_tpw(int tpw, int B) {
 static size_t mlp_lds_bytes(int D, int B) { return mlp_lds_bytes_tpw(mlp_tpw(D), B); }
 
 bool mlp_round_supported(int D, int H, int C, int B) {
-    if (!(B == 16 || B == 32)) return false;
-    if (H % 16 || H / 16 > kMlpMaxG || C < 1 || C > 16) return false;
+    if (B < 1 || B > 32) return false;
+    if (H < 1 || H > 16 * kMlpMaxG || C < 1 || C > 16) return false;
     if (D < 1 || (D + 15) / 16 > kMlpWaves * kMlpMaxTPW) return false;
-    return mlp_lds_bytes(D, B) <= 160 * 1024;
+    return mlp_lds_bytes(D, B <= 16 ? 16 : 32) <= 160 * 1024;
 }
+
+bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0; }
 
 // exchange records [client][2][kMlpMaxG][kMlpRec] 64-bit words, the pair records
 // [client][kMlpMaxG][2][2][kMlpPair], then the error flag
@@ -661,10 +675,10 @@ static hipError_t mlp_capacity(size_t lds, int *cap) {
 // launch that way; otherwise *declined is set and nothing is launched.
 template <int NBT, int TPW, bool FAST, bool FULL, int HF>
 static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact, int max_m,
-                             const float *Wg, int D, int H, int C, void *scratch, int n_clients,
+                             const float *Wg, int D, int H, int C, int Br, void *scratch, int n_clients,
                              uint32_t *epoch, bool *declined = nullptr) {
     constexpr int B = 16 * NBT;
-    const int G = H / 16;
+    const int G = (H + 15) / 16;
     const size_t lds = mlp_lds_bytes_tpw(TPW, B);
     int cap = 0;
     hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF>(lds, &cap);
@@ -698,7 +712,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, xrec, prec, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, tag0, errflag);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -718,19 +732,19 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     if (!small && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW) {
         bool declined = false;
         hipError_t e;
-        if (B == 16) e = fast ? mlp_launch<1, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch, &declined)
-                              : mlp_launch<1, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch, &declined);
-        else e = fast ? mlp_launch<2, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch, &declined)
-                      : mlp_launch<2, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch, &declined);
+        if (B <= 16) e = fast ? mlp_launch<1, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined)
+                              : mlp_launch<1, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined);
+        else e = fast ? mlp_launch<2, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined)
+                      : mlp_launch<2, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined);
         if (e != hipSuccess || !declined) return e;
     }
 #define AET_MLP_CASE(nbt, tpw)                                                                        \
     do {                                                                                              \
-        if (full) return mlp_launch<nbt, tpw, true, true, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch);   \
-        if (fast) return mlp_launch<nbt, tpw, true, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch);  \
-        return mlp_launch<nbt, tpw, false, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, scratch, n_clients, epoch);           \
+        if (full) return mlp_launch<nbt, tpw, true, true, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);   \
+        if (fast) return mlp_launch<nbt, tpw, true, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);  \
+        return mlp_launch<nbt, tpw, false, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);           \
     } while (0)
-    if (B == 16) {
+    if (B <= 16) {
         if (small) AET_MLP_CASE(1, 2);
         AET_MLP_CASE(1, kMlpMaxTPW);
     }

@@ -34,3 +34,34 @@ def test_softmax_round_lengths(gpu, oracle_libs, d, s0):
     """Round lengths s0, s0+1, ... s0+3: every remainder of the recursions in a group of four, a
     block of 48 recursions met exactly, missed by one and passed by one, and the empty round."""
     _lockstep(gpu, W.config1(n_clients=2, n_per=40, d=d, rounds=4, a=1, b=s0))
+
+
+@pytest.mark.parametrize("n,d,hidden,batch", [
+    (3, 30, 10, 4),      # one unit group, one sample tile, both padded
+    (2, 17, 1, 1),       # one unit, one sample
+    (3, 112, 17, 20),    # the second group holds one unit, the second sample tile four
+    (3, 784, 100, 20),   # two workgroups per unit group
+    (2, 777, 255, 31),   # ragged columns, one unit and one sample short of full tiles
+    (257, 12, 5, 3),     # one client more than the padded form takes: the layer engine
+])
+def test_mlp_padded_tiles(gpu, oracle_libs, n, d, hidden, batch):
+    wl = W.config2(n_clients=n, n_total=n * 60, d=d, hidden=hidden, batch=batch, rounds=3, a=batch, b=batch)
+    if n == 3:
+        wl.compute_factor = np.array([1, 2, 1], dtype=np.int32)
+    _lockstep(gpu, wl)
+
+
+@pytest.fixture
+def layer_engine():
+    """Contexts of one test on the layer engine; the default choice comes back afterwards."""
+    from paper_2112_13935_amd import load_library
+    lib = load_library()
+    lib.aet_test_select_kernels(1, 0)
+    yield
+    lib.aet_test_select_kernels(0, 0)
+
+
+@pytest.mark.parametrize("n,d,hidden,batch", [(5, 50, 24, 4), (3, 52, 24, 32), (2, 36, 40, 64), (3, 256, 120, 16),
+                                              (3, 784, 100, 20)])
+def test_dense_layers_on_the_layer_engine(gpu, oracle_libs, layer_engine, n, d, hidden, batch):
+    _lockstep(gpu, W.config2(n_clients=n, n_total=n * 80, d=d, hidden=hidden, batch=batch, rounds=3, a=batch, b=batch))
