@@ -132,7 +132,8 @@ bool resolve(const aet_model_desc *m, LayerGeom *lay, int64_t *P, std::string *w
 }
 
 // which engine runs the local rounds of this model
-enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENET = 3 };
+enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENET = 3,
+              ENGINE_SOFTMAX_BATCH = 4 };
 
 // aet_test_select_kernels: which kernel set contexts created from now on use
 int g_force_layer_engine = 0, g_plain_layers = 0;
@@ -143,7 +144,7 @@ int g_force_layer_engine = 0, g_plain_layers = 0;
 // engine's launches are full.
 constexpr int kPaddedClients = 256;
 
-// padded_ok: the caller has room for the records of a padded form
+// padded_ok: the caller has room for the records of a padded form (or of mini-batch softmax)
 Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = true) {
     if (g_force_layer_engine) return ENGINE_LAYERS;
     const bool padded = padded_ok && n <= kPaddedClients;
@@ -153,6 +154,8 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
         return ENGINE_MLP;
     if (L == 1 && lay[0].type == AET_DENSE && softmax_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX;
+    if (L == 1 && lay[0].type == AET_DENSE && padded_ok && softmax_batch_round_supported((int)lay[0].in_size, lay[0].oc, B))
+        return ENGINE_SOFTMAX_BATCH;
     if (lenet_round_supported(lay, L, B)) return ENGINE_LENET;
     return ENGINE_LAYERS;
 }
@@ -173,7 +176,8 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     lo->debug = take((size_t)kDebugIdx * 4);
     lo->labels = take((size_t)n * B * 4);
     // exchange records of the fused dense-ReLU-dense engine, only for models it runs
-    lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n) : 0);
+    lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n)
+                     : eng == ENGINE_SOFTMAX_BATCH ? softmax_batch_scratch_bytes(n, (int)lay[0].in_size, B) : 0);
     size_t wg_floats = 0;
     for (int l = 0; l < L; ++l)
         if (lay[l].type == AET_CONV && conv_wgrad_mfma_supported(lay[l], B))
@@ -420,6 +424,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_LENET)
         e = lenet_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients);
+    if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
+        e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0
     if (e == hipSuccess) e = hipMemcpyAsync(ctx->W0(), w0, (size_t)ctx->P * 4, static_ws ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);  // w0 is the caller's; do not keep reading it
@@ -512,9 +518,9 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
     if (nact > 0) {
         // staging: the layer engine copies the records to the device from a pinned ring; the
         // dense-ReLU-dense engine takes them in its kernel arguments from plain host memory; the
-        // other two fused engines read them where they are, in the pinned ring (every workgroup
+        // other fused engines read them where they are, in the pinned ring (every workgroup
         // reads its own record once, at its start: no copy in the stream ahead of the kernel)
-        const bool direct = !ctx->static_ws && (ctx->engine == ENGINE_SOFTMAX || ctx->engine == ENGINE_LENET);
+        const bool direct = !ctx->static_ws && (ctx->engine == ENGINE_SOFTMAX || ctx->engine == ENGINE_LENET || ctx->engine == ENGINE_SOFTMAX_BATCH);
         const int ring = ctx->ring_p;
         RoundParams *hp = ctx->static_ws ? ctx->v_params.data() : ctx->h_params[ring];
         if (ctx->engine != ENGINE_MLP && !ctx->static_ws) {
@@ -559,6 +565,9 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
                                           ctx->lay[0].oc, ctx->lay[1].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
         } else if (ctx->engine == ENGINE_SOFTMAX) {
             AET_HIP(ctx, launch_softmax_round(ctx->stream, ctx->profp(), dp, nact, start, (int)ctx->lay[0].in_size, ctx->lay[0].oc));
+        } else if (ctx->engine == ENGINE_SOFTMAX_BATCH) {
+            AET_HIP(ctx, launch_softmax_batch_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
+                                                    ctx->lay[0].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
         } else if (ctx->engine == ENGINE_LENET) {
             AET_HIP(ctx, launch_lenet_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
                                             ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
@@ -760,10 +769,12 @@ aet_status aet_receive(aet_ctx *ctx, float scale, int32_t *n_applied, int32_t *a
 
 // After a synchronisation: did a fused kernel give up waiting for its cluster peers?
 static aet_status check_device_flag(aet_ctx *ctx) {
-    if (ctx->engine != ENGINE_MLP && ctx->engine != ENGINE_LENET) return AET_OK;
+    if (ctx->engine != ENGINE_MLP && ctx->engine != ENGINE_LENET && ctx->engine != ENGINE_SOFTMAX_BATCH) return AET_OK;
     int flag = 0;
-    const int *dflag = ctx->engine == ENGINE_MLP ? mlp_error_flag_ptr(ctx->ws + ctx->lo.fused, ctx->n, ctx->B)
-                                                 : lenet_error_flag_ptr(ctx->ws + ctx->lo.fused, ctx->n);
+    char *fused = ctx->ws + ctx->lo.fused;
+    const int *dflag = ctx->engine == ENGINE_MLP     ? mlp_error_flag_ptr(fused, ctx->n, ctx->B)
+                       : ctx->engine == ENGINE_LENET ? lenet_error_flag_ptr(fused, ctx->n)
+                                                     : softmax_batch_error_flag_ptr(fused, ctx->n, (int)ctx->lay[0].in_size, ctx->B);
     AET_HIP(ctx, hipMemcpyAsync(&flag, dflag, 4, hipMemcpyDeviceToHost, ctx->stream));
     AET_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (flag) {

@@ -120,6 +120,13 @@ hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const Roun
 bool softmax_round_supported(int D, int C, int B);
 hipError_t launch_softmax_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact,
                                 const float *Wg, int D, int C);
+// ... with mini-batches (kernels_softmax_batch.hip)
+bool softmax_batch_round_supported(int D, int C, int B);
+size_t softmax_batch_scratch_bytes(int n_clients, int D, int B);
+hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
+                                      const float *Wg, int D, int C, int B, void *scratch, int n_clients, uint32_t *epoch);
+hipError_t softmax_batch_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int D, int B);
+const int *softmax_batch_error_flag_ptr(void *scratch, int n_clients, int D, int B);
 // fused round of dense-ReLU-dense models (kernels_mlp.hip)
 bool mlp_round_supported(int D, int H, int C, int B);
 bool mlp_round_exact(int H, int B);   // no padded units or samples

@@ -65,3 +65,19 @@ def layer_engine():
                                               (3, 784, 100, 20)])
 def test_dense_layers_on_the_layer_engine(gpu, oracle_libs, layer_engine, n, d, hidden, batch):
     _lockstep(gpu, W.config2(n_clients=n, n_total=n * 80, d=d, hidden=hidden, batch=batch, rounds=3, a=batch, b=batch))
+
+
+@pytest.mark.parametrize("n,d,batch", [
+    (1, 3, 2),           # the smallest: three columns, two samples
+    (3, 512, 8),         # one column per thread, full; mini-batch at its bound
+    (2, 513, 33),        # one column beyond, one sample beyond 32: a cluster of two
+    (3, 1537, 16),       # three columns per thread, one column in the second workgroup
+    (2, 3072, 64),       # widest and largest: a cluster of six
+    (130, 1600, 20),     # more workgroups (4 x 130) than are resident: three columns per thread
+    (300, 700, 50),      # a cluster of two that takes three launches
+])
+def test_softmax_mini_batches(gpu, oracle_libs, n, d, batch):
+    wl = W.config5(n_clients=n, n_per=70, d=d, rounds=3)
+    wl.model.batch = batch
+    wl.a = wl.b = batch
+    _lockstep(gpu, wl)
