@@ -139,9 +139,9 @@ enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENE
 int g_force_layer_engine = 0, g_plain_layers = 0;
 
 // Padded forms of the fused rounds (widths or mini-batches that do not fill their tiles) go to
-// the layer engine beyond this many clients: their exchange records take up to 384 KB per
-// client, which is more than a small model's own state, and with so many clients the layer
-// engine's launches are full.
+// the layer engine beyond this many clients: their exchange records take 0.4 MB per
+// client (dense-ReLU-dense) to 2.6 MB (LeNet, mini-batch over 16), which is more than such a
+// model's own state, and with so many clients the layer engine's launches are full.
 constexpr int kPaddedClients = 256;
 
 // padded_ok: the caller has room for the records of a padded form (or of mini-batch softmax)
@@ -156,7 +156,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
         return ENGINE_SOFTMAX;
     if (L == 1 && lay[0].type == AET_DENSE && padded_ok && softmax_batch_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX_BATCH;
-    if (lenet_round_supported(lay, L, B)) return ENGINE_LENET;
+    if (lenet_round_supported(lay, L, B) && (padded || lenet_round_exact(B))) return ENGINE_LENET;
     return ENGINE_LAYERS;
 }
 
@@ -176,7 +176,7 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     lo->debug = take((size_t)kDebugIdx * 4);
     lo->labels = take((size_t)n * B * 4);
     // exchange records of the fused dense-ReLU-dense engine, only for models it runs
-    lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n)
+    lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n, B)
                      : eng == ENGINE_SOFTMAX_BATCH ? softmax_batch_scratch_bytes(n, (int)lay[0].in_size, B) : 0);
     size_t wg_floats = 0;
     for (int l = 0; l < L; ++l)
@@ -423,7 +423,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     if (e == hipSuccess && ctx->engine == ENGINE_MLP)
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_LENET)
-        e = lenet_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients);
+        e = lenet_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
         e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0
@@ -773,7 +773,7 @@ static aet_status check_device_flag(aet_ctx *ctx) {
     int flag = 0;
     char *fused = ctx->ws + ctx->lo.fused;
     const int *dflag = ctx->engine == ENGINE_MLP     ? mlp_error_flag_ptr(fused, ctx->n, ctx->B)
-                       : ctx->engine == ENGINE_LENET ? lenet_error_flag_ptr(fused, ctx->n)
+                       : ctx->engine == ENGINE_LENET ? lenet_error_flag_ptr(fused, ctx->n, ctx->B)
                                                      : softmax_batch_error_flag_ptr(fused, ctx->n, (int)ctx->lay[0].in_size, ctx->B);
     AET_HIP(ctx, hipMemcpyAsync(&flag, dflag, 4, hipMemcpyDeviceToHost, ctx->stream));
     AET_HIP(ctx, hipStreamSynchronize(ctx->stream));

@@ -139,11 +139,12 @@ hipError_t mlp_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int
 const int *mlp_error_flag_ptr(void *scratch, int n_clients, int B);
 // fused round of LeNet-5-style models (kernels_lenet.hip); dp: DEVICE array of round records
 bool lenet_round_supported(const LayerGeom *lay, int L, int B);
-size_t lenet_round_scratch_bytes(int n_clients);
+bool lenet_round_exact(int B);   // no padded samples, one cluster per client
+size_t lenet_round_scratch_bytes(int n_clients, int B);
 hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
                               const float *Wg, const LayerGeom *lay, int L, int B, void *scratch,
                               int n_clients, uint32_t *epoch);
-hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients);
-const int *lenet_error_flag_ptr(void *scratch, int n_clients);
+hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B);
+const int *lenet_error_flag_ptr(void *scratch, int n_clients, int B);
 
 }  // namespace aet

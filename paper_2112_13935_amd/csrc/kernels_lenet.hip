@@ -1,6 +1,6 @@
 // Fused local round for LeNet-5-style models:
 //   conv 5x5 (1 -> 6, ReLU), 2x2 max pool, conv 5x5 (6 -> 16, ReLU), 2x2 max pool,
-//   dense F0 -> 120 (ReLU), dense 120 -> 84 (ReLU), dense 84 -> 10, mini-batch B = 16.
+//   dense F0 -> 120 (ReLU), dense 120 -> 84 (ReLU), dense 84 -> 10, mini-batch up to 32.
 //
 // One launch runs the whole round (Algorithm 2, MainComputeNode: all s_i/B recursions) of
 // every active client.  A client is a cluster of 4 workgroups.  Workgroup g
@@ -33,6 +33,14 @@
 // hidden dense layers (forward, backward-data, weight gradient) run on the matrix cores
 // (fp32 16 x 16 x 4 products); the first convolution (6 channels) and the 10-class layer on
 // the vector ALU.
+//
+// Mini-batches other than 16.  Fewer samples: the missing ones repeat the last row with d logits of
+// zero.  17 .. 32: a second cluster of four runs samples 16 .. 31 in the same way; the two add
+// their gradients of all layers (each workgroup with its counterpart for the dense slices, all
+// eight for the filter banks) through records that alternate between two sets (a workgroup can be
+// a recursion ahead of its counterpart: they meet only here), and both apply the same update.
+// 32 clients, 28 x 28, mini-batch 32: 53 us per recursion, 192 us as 22 launches of the
+// layer-by-layer engine.
 //
 // All workgroups of a client must be resident together; the wait for a peer's word is
 // bounded and raises an error flag instead of hanging (every workgroup still runs to the end).
@@ -67,6 +75,13 @@ constexpr int kXB1 = 7680;           // [4][16][128]   partial d loss / d (outpu
 constexpr int kXB2 = 15872;          // [4][16][256]   partial d loss / d (pooled output of conv 2)
 constexpr int kXB3 = 32256;          // [4][2576]      partial filter-bank gradients
 constexpr int kXWords = 43008;
+// two clusters per client: kXB3 words of the above each, then two sets of
+constexpr int kXB3s = 8 * 2576;      // [8][2576]      partial filter-bank gradients
+constexpr int kXDw = 26 * 512 + 128; // one workgroup's dense gradients, as its threads own them:
+                                     // 16 of dense 1, 8 of dense 2, 2 of dense 3 per thread, then
+                                     // the biases (32 + 32 + 16) and the loss sum
+constexpr int kXSet = kXB3s + 8 * kXDw;
+constexpr int kXWords2 = 2 * kXB3 + 2 * kXSet;
 
 struct LenetDims {
     int H0, P1, H2, P2, F0, lgF0;    // input side, sides after pool 1 / conv 2 / pool 2, F0 = 16 P2^2 = 2^lgF0
@@ -165,14 +180,17 @@ __device__ __forceinline__ float relu_pool(const float (&acc)[4], int &which) {
 // G28: the geometry of the 28 x 28 input (12 x 12 pooled maps, 8 x 8 conv-2 maps, 256 features)
 // as compile-time constants, so that the operand addresses of the convolution phases are
 // immediates; other input sizes take the sizes from d.
-template <bool G28>
+// S: clusters of four workgroups per client; PAD: the mini-batch does not fill the S x 16 samples.
+template <bool G28, int S, bool PAD>
 __global__ void __launch_bounds__(kLnThreads, 1)
-k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, const LenetDims d,
+k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, const LenetDims d, int Brun,
               u64 *__restrict__ xrec, uint32_t tag0, int *__restrict__ errflag) {
     // consecutive workgroup ids go round the 8 XCDs: the four workgroups of a client get ids
     // that land on the same XCD and exchange through its L2
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int a = xcd + 8 * (slot / kLnG), g = slot % kLnG;
+    const int a = xcd + 8 * (slot / (kLnG * S)), gs = slot % (kLnG * S);
+    const int g = S == 1 ? gs : gs % kLnG, sub = S == 1 ? 0 : gs / kLnG;   // workgroup of the cluster, cluster (samples 16 sub ..)
+    const int Br = PAD ? Brun : kLnB * S;       // samples of the mini-batch
     if (a >= nhere) return;
     const RoundParams p = rp[a];
     const gcf_ptr Xg = as_global(p.X);
@@ -184,7 +202,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     const int nwin1 = P1 * P1, nwin2 = P2 * P2, npix = H0 * H0;
     const int P1S = 6 * nwin1 + 8;       // per-sample stride of the pooled conv-1 maps
     const int F0P = F0 + 4;              // row stride of arrays with F0 columns
-    const float invB = 1.0f / (float)kLnB;
+    const float invB = 1.0f / (float)Br;
     const float eta = p.eta;
 
     extern __shared__ __align__(16) float smem[];
@@ -222,7 +240,8 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     float *dp1 = h1;                               // [4][P1S]        delta at the pooled conv-1 outputs
     float *dpart = gsum;                           // [8][kDP]        partial sums of the dense forward products, one [32 units][17] slice per wave (over gsum, c1part)
 
-    u64 *rec = xrec + (int64_t)(rec0 + a) * kXWords;
+    u64 *const rec = xrec + (int64_t)(rec0 + a) * (S == 1 ? kXWords : kXWords2) + sub * kXB3;
+    u64 *const set0 = xrec + (int64_t)(rec0 + a) * kXWords2 + 2 * kXB3;   // S = 2
     Waiter wt{tag0, errflag, false};
 
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL) ----
@@ -257,6 +276,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 
     // the own samples' rows travel global -> registers (one recursion ahead) -> LDS
     const int nq = npix >> 2;   // 16-byte pieces per row
+    auto sample_of = [&](int b) { return PAD ? min(kLnB * sub + b, Br - 1) : kLnB * sub + b; };
     auto load_rows = [&](int u, f4 (&xr)[2], int &lab) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -264,12 +284,12 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             xr[j] = f4{0.f, 0.f, 0.f, 0.f};
             if (e < 4 * nq) {
                 const int s = e / nq, q = e % nq;
-                const uint32_t row = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * kLnB + 4 * g + s), p.n_samples);
+                const uint32_t row = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * Br + sample_of(4 * g + s)), p.n_samples);
                 xr[j] = *reinterpret_cast<const f4 __attribute__((address_space(1))) *>(Xg + (int64_t)row * npix + 4 * q);
             }
         }
         lab = 0;
-        if (tid < kLnB) lab = yg[sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * kLnB + tid), p.n_samples)];
+        if (tid < kLnB) lab = yg[sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * Br + sample_of(tid)), p.n_samples)];
     };
     auto store_rows = [&](const f4 (&xr)[2], int lab) {
 #pragma unroll
@@ -292,6 +312,11 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         // the whole recursion
         int tq = opaque(tid);
         wt.tag = tag0 + (uint32_t)u;
+        // filter-bank and (S = 2) dense gradients: this recursion's records
+        u64 *const set = set0 + (u & 1) * kXSet, *const recd = set + kXB3s;
+        auto rec3 = [&](int i) { return S == 1 ? rec + kXB3 + i * 2576 : set + i * 2576; };   // of workgroup i
+        constexpr int NP = kLnG * S;   // partials per filter-bank entry
+        float gd1[S > 1 ? 16 : 1], gd2[S > 1 ? 8 : 1], gd3[S > 1 ? 2 : 1], gdb1 = 0.f, gdb2 = 0.f, gdb3 = 0.f, gloss = 0.f;   // S = 2: kept until the counterpart's are there
         const bool more = u + 1 < p.m;
         if (more) load_rows(u + 1, xr, labr);   // Algorithm 2, sampling step: a counter hash, known ahead
 
@@ -636,8 +661,9 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             const float ex = o < kNC ? __expf(z - zmax) : 0.f;
             const float lse = zmax + __logf(row16_sum_ln(ex));
             const int lab = labs[b];
-            if (o == lab) lossb[b] = lse - z;
-            dz[b * 16 + o] = o < kNC ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+            const bool real = !PAD || kLnB * sub + b < Br;
+            if (o == lab) lossb[b] = real ? lse - z : 0.f;
+            dz[b * 16 + o] = o < kNC && real ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
         }
         __syncthreads();
 
@@ -657,7 +683,12 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         if (g == 0 && tq == 511) {
             float s = 0.f;
             for (int b = 0; b < kLnB; ++b) s += lossb[b];
-            lossacc[0] += s * invB;
+            if constexpr (S == 1) {
+                lossacc[0] += s * invB;
+            } else {
+                gloss = s;
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 96, wt.tag, s);
+            }
         }
         __syncthreads();
 
@@ -693,18 +724,28 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 float s = 0.f;
 #pragma unroll
                 for (int b = 0; b < kLnB; ++b) s += dz[b * 16 + o] * h2[b * kS2 + k];
-                const float gv = s * invB;
-                w3s[o * kS2 + k] -= eta * gv;
-                U3[j] += gv;
+                if constexpr (S == 1) {
+                    const float gv = s * invB;
+                    w3s[o * kS2 + k] -= eta * gv;
+                    U3[j] += gv;
+                } else {
+                    gd3[j] = s;
+                    xpost(recd + (int64_t)gs * kXDw + (24 + j) * 512 + tq, wt.tag, s);
+                }
             }
         }
         if (tq < kNC) {
             float s = 0.f;
 #pragma unroll
             for (int b = 0; b < kLnB; ++b) s += dz[b * 16 + tq];
-            const float gv = s * invB;
-            b3s[tq] -= eta * gv;
-            U3b += gv;
+            if constexpr (S == 1) {
+                const float gv = s * invB;
+                b3s[tq] -= eta * gv;
+                U3b += gv;
+            } else {
+                gdb3 = s;
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 64 + tq, wt.tag, s);
+            }
         }
         __syncthreads();
         // dense 2: g^T = delta^T h1 on the matrix cores (rows = the own units in two tiles, columns =
@@ -732,10 +773,15 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int ul = 16 * mt + 4 * kq + r;
-                        if (ul < kU2) {
-                            const float gv = acc[mt][r] * invB;
-                            w2s[ul * kS1 + k] -= eta * gv;
-                            U2[4 * mt + r] += gv;
+                        if constexpr (S == 1) {
+                            if (ul < kU2) {
+                                const float gv = acc[mt][r] * invB;
+                                w2s[ul * kS1 + k] -= eta * gv;
+                                U2[4 * mt + r] += gv;
+                            }
+                        } else {
+                            gd2[4 * mt + r] = acc[mt][r];
+                            if (ul < kU2) xpost(recd + (int64_t)gs * kXDw + (16 + 4 * mt + r) * 512 + tq, wt.tag, acc[mt][r]);
                         }
                     }
             }
@@ -744,9 +790,14 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             float s = 0.f;
 #pragma unroll
             for (int b = 0; b < kLnB; ++b) s += d2own[b * 24 + tq];
-            const float gv = s * invB;
-            b2s[tq] -= eta * gv;
-            U2b += gv;
+            if constexpr (S == 1) {
+                const float gv = s * invB;
+                b2s[tq] -= eta * gv;
+                U2b += gv;
+            } else {
+                gdb2 = s;
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 32 + tq, wt.tag, s);
+            }
         }
         // delta of the own units of dense 1: the four partials in workgroup order
         {
@@ -855,10 +906,15 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int ul = 16 * mt + 4 * kq + r;
-                            if (ul < kU1) {
-                                const float gv = acc[nl][mt][r] * invB;
-                                w1s[ul * F0P + k] -= eta * gv;
-                                U1[(2 * nl + mt) * 4 + r] += gv;
+                            if constexpr (S == 1) {
+                                if (ul < kU1) {
+                                    const float gv = acc[nl][mt][r] * invB;
+                                    w1s[ul * F0P + k] -= eta * gv;
+                                    U1[(2 * nl + mt) * 4 + r] += gv;
+                                }
+                            } else {
+                                gd1[(2 * nl + mt) * 4 + r] = acc[nl][mt][r];
+                                if (ul < kU1) xpost(recd + (int64_t)gs * kXDw + ((2 * nl + mt) * 4 + r) * 512 + tq, wt.tag, acc[nl][mt][r]);
                             }
                         }
                 }
@@ -868,9 +924,14 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             float s = 0.f;
 #pragma unroll
             for (int b = 0; b < kLnB; ++b) s += d1own[tq * 16 + b];
-            const float gv = s * invB;
-            b1s[tq] -= eta * gv;
-            U1b += gv;
+            if constexpr (S == 1) {
+                const float gv = s * invB;
+                b1s[tq] -= eta * gv;
+                U1b += gv;
+            } else {
+                gdb1 = s;
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + tq, wt.tag, s);
+            }
         }
         // delta at the own samples' pooled conv-2 outputs (masked by the ReLU): both elements of
         // a thread in one batch of loads
@@ -1015,7 +1076,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int e = 156 + tq + kLnThreads * j;
-            if (e < kConvP) xpost(rec + kXB3 + g * 2576 + e, wt.tag, gsum[e]);
+            if (e < kConvP) xpost(rec3(S == 1 ? g : gs) + e, wt.tag, gsum[e]);
         }
         // delta at the pooled conv-1 outputs (dense correlation with the flipped filters), masked
         // by the ReLU.
@@ -1211,15 +1272,15 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         __syncthreads();
 
         tq = opaque(tq);
-        // the four partial conv-2 gradients were posted before the last phase: ask for them now, the
+        // the partial conv-2 gradients were posted before the last phase: ask for them now, the
         // words are looked at after the conv-1 gradient below (thread: elements 156 + tq + 512 j)
-        u64 early[5][4];
+        u64 early[5][NP];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int e = 156 + tq + kLnThreads * j;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                early[j][i] = __hip_atomic_load(rec + kXB3 + i * 2576 + (e < kConvP ? e : 156), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < NP; ++i)
+                early[j][i] = __hip_atomic_load(rec3(i) + (e < kConvP ? e : 156), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // ---- conv-1 filter gradient over the own samples: thread = (window group, channel,
         // filter row); one position per window; the bias gradient is the sum of the deltas the
@@ -1270,26 +1331,25 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             float s = 0.f;
 #pragma unroll
             for (int grp = 0; grp < 14; ++grp) s += c1part[grp * 160 + tq];
-            xpost(rec + kXB3 + g * 2576 + tq, wt.tag, s);
+            xpost(rec3(gs) + tq, wt.tag, s);
         }
         // the next recursion's rows and labels (xs and labs are not read any more)
         if (more) store_rows(xr, labr);
         {   // the conv-1 part: threads 0 .. 155
             const bool act = tq < 156;
-            const u64 *ptr[4];
-            bool need[4];
-            float val[4];
+            const u64 *ptr[NP];
+            bool need[NP];
+            float val[NP];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ptr[i] = rec + kXB3 + i * 2576 + (act ? tq : 0);
+            for (int i = 0; i < NP; ++i) {
+                ptr[i] = rec3(i) + (act ? tq : 0);
                 need[i] = act;
             }
-            xfetch<4>(ptr, need, val, wt);
+            xfetch<NP>(ptr, need, val, wt);
             if (act) {
                 float t = val[0];
-                t += val[1];
-                t += val[2];
-                t += val[3];
+#pragma unroll
+                for (int i = 1; i < NP; ++i) t += val[i];
                 const float gv = t * invB;
                 wc1[tq] -= eta * gv;
                 UC[0] += gv;
@@ -1299,38 +1359,128 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         for (int j = 0; j < 5; ++j) {   // the conv-2 part and its biases: the words asked for earlier
             const int e = 156 + tq + kLnThreads * j;
             const bool act = e < kConvP;
-            float val[4];
+            float val[NP];
             bool ok = true;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < NP; ++i) {
                 ok = ok && (uint32_t)(early[j][i] >> 32) == wt.tag;
                 val[i] = __uint_as_float((uint32_t)early[j][i]);
             }
             if (act && !ok) {   // not there yet when asked: fetch again (rare)
-                const u64 *ptr[4];
-                bool need[4];
+                const u64 *ptr[NP];
+                bool need[NP];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    ptr[i] = rec + kXB3 + i * 2576 + e;
+                for (int i = 0; i < NP; ++i) {
+                    ptr[i] = rec3(i) + e;
                     need[i] = true;
                 }
-                xfetch<4>(ptr, need, val, wt);
+                xfetch<NP>(ptr, need, val, wt);
             }
             if (act) {
                 float t = val[0];
-                t += val[1];
-                t += val[2];
-                t += val[3];
+#pragma unroll
+                for (int i = 1; i < NP; ++i) t += val[i];
                 const float gv = t * invB;
                 float *w = e < 2556 ? wc2 + ((e - 156) / 150) * kWS + (e - 156) % 150 : wc2b + (e - 2556);
                 *w -= eta * gv;
                 UC[1 + j] += gv;
             }
         }
+        if constexpr (S > 1) {
+            // dense slices: the counterpart's gradients, the two clusters' added in cluster order,
+            // so that both copies get the same update
+            const u64 *theirs = recd + (int64_t)(gs ^ kLnG) * kXDw;
+            auto both = [&](float own, float other) { return (sub == 0 ? own + other : other + own) * invB; };
+            const int wave = __builtin_amdgcn_readfirstlane(tq >> 6), n = tq & 15, kq = (tq & 63) >> 4;
+            const int ntile = F0 >> 4;
+#pragma unroll
+            for (int nl = 0; nl < 2; ++nl) {
+                const int nt = wave + 8 * nl;
+                if (nt >= ntile) break;
+                const u64 *ptr[8];
+                bool need[8];
+                float val[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    need[i] = 16 * (i >> 2) + 4 * kq + (i & 3) < kU1;
+                    ptr[i] = theirs + (8 * nl + i) * 512 + tq;
+                }
+                xfetch<8>(ptr, need, val, wt);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (need[i]) {
+                        const float gv = both(gd1[8 * nl + i], val[i]);
+                        w1s[(16 * (i >> 2) + 4 * kq + (i & 3)) * F0P + 16 * nt + n] -= eta * gv;
+                        U1[8 * nl + i] += gv;
+                    }
+            }
+            {
+                const int k = 16 * wave + n;
+                const u64 *ptr[8];
+                bool need[8];
+                float val[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    need[i] = k < kF1 && 16 * (i >> 2) + 4 * kq + (i & 3) < kU2;
+                    ptr[i] = theirs + (16 + i) * 512 + tq;
+                }
+                xfetch<8>(ptr, need, val, wt);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (need[i]) {
+                        const float gv = both(gd2[i], val[i]);
+                        w2s[(16 * (i >> 2) + 4 * kq + (i & 3)) * kS1 + k] -= eta * gv;
+                        U2[i] += gv;
+                    }
+            }
+            {   // dense 3, the biases, the loss
+                const u64 *ptr[6];
+                bool need[6];
+                float val[6];
+                need[0] = tq < kNC * kF2;
+                need[1] = tq + kLnThreads < kNC * kF2;
+                need[2] = tq < kU1;
+                need[3] = tq < kU2;
+                need[4] = tq < kNC;
+                need[5] = g == 0 && tq == 511;
+                ptr[0] = theirs + 24 * 512 + tq;
+                ptr[1] = theirs + 25 * 512 + tq;
+                ptr[2] = theirs + 26 * 512 + (tq & 31);
+                ptr[3] = theirs + 26 * 512 + 32 + (tq & 31);
+                ptr[4] = theirs + 26 * 512 + 64 + (tq & 15);
+                ptr[5] = theirs + 26 * 512 + 96;
+                xfetch<6>(ptr, need, val, wt);
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    if (need[j]) {
+                        const int e = tq + kLnThreads * j;
+                        const float gv = both(gd3[j], val[j]);
+                        w3s[(e / kF2) * kS2 + e % kF2] -= eta * gv;
+                        U3[j] += gv;
+                    }
+                if (need[2]) {
+                    const float gv = both(gdb1, val[2]);
+                    b1s[tq] -= eta * gv;
+                    U1b += gv;
+                }
+                if (need[3]) {
+                    const float gv = both(gdb2, val[3]);
+                    b2s[tq] -= eta * gv;
+                    U2b += gv;
+                }
+                if (need[4]) {
+                    const float gv = both(gdb3, val[4]);
+                    b3s[tq] -= eta * gv;
+                    U3b += gv;
+                }
+                if (need[5]) lossacc[0] += both(gloss, val[5]);
+            }
+        }
         __syncthreads();
     }
 
     // ---- end of round: the replica and the message payload go to HBM ------------------------------
+    if (S > 1 && sub != 0) return;   // the clusters' copies are the same
     {   // dense 1 in the ownership of its update: lane (n, kq) of wave w, input tiles w and w + 8
         const int wave = tid >> 6, n = tid & 15, kq = (tid & 63) >> 4, ntile = F0 >> 4;
 #pragma unroll
@@ -1413,7 +1563,7 @@ __global__ void k_zero_words_ln(u64 *p, size_t n) {
 }
 
 bool lenet_dims(const LayerGeom *lay, int L, int B, LenetDims *d) {
-    if (L != 7 || B != kLnB) return false;
+    if (L != 7 || B < 1 || B > 2 * kLnB) return false;
     const LayerGeom &c1 = lay[0], &q1 = lay[1], &c2 = lay[2], &q2 = lay[3], &f1 = lay[4], &f2 = lay[5], &f3 = lay[6];
     if (c1.type != 0 || q1.type != 1 || c2.type != 0 || q2.type != 1 || f1.type != 2 || f2.type != 2 || f3.type != 2) return false;
     if (c1.k != 5 || c1.pad != 0 || !c1.relu || c1.ic != 1 || c1.oc != 6 || c1.ih != c1.iw) return false;
@@ -1440,7 +1590,15 @@ size_t lenet_lds_bytes(const LenetDims &d) {
     return fl * 4;
 }
 
-int g_lenet_per_cu[2] = {0, 0};
+// the instantiations: 28 x 28 or any geometry; one or two clusters; exact or padded
+typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, uint32_t, int *);
+LenetKernel lenet_kernel(bool g28, int S, bool pad) {
+    if (S == 2) return g28 ? k_lenet_round<true, 2, true> : k_lenet_round<false, 2, true>;
+    if (pad) return g28 ? k_lenet_round<true, 1, true> : k_lenet_round<false, 1, true>;
+    return g28 ? k_lenet_round<true, 1, false> : k_lenet_round<false, 1, false>;
+}
+int lenet_clusters(int B) { return B > kLnB ? 2 : 1; }
+size_t lenet_words(int n_clients, int B) { return (size_t)n_clients * (lenet_clusters(B) == 1 ? kXWords : kXWords2); }
 
 }  // namespace
 
@@ -1454,16 +1612,18 @@ bool lenet_round_supported(const LayerGeom *lay, int L, int B) {
     return lenet_lds_bytes(d) <= 160 * 1024;
 }
 
-size_t lenet_round_scratch_bytes(int n_clients) { return (size_t)n_clients * kXWords * 8 + 256; }
+bool lenet_round_exact(int B) { return B == kLnB; }
 
-hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients) {
+size_t lenet_round_scratch_bytes(int n_clients, int B) { return lenet_words(n_clients, B) * 8 + 256; }
+
+hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B) {
     u64 *xrec = static_cast<u64 *>(scratch);
-    k_zero_words_ln<<<1, 64, 0, s>>>(xrec + (size_t)n_clients * kXWords, 1);
+    k_zero_words_ln<<<1, 64, 0, s>>>(xrec + lenet_words(n_clients, B), 1);
     return hipGetLastError();
 }
 
-const int *lenet_error_flag_ptr(void *scratch, int n_clients) {
-    return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + (size_t)n_clients * kXWords);
+const int *lenet_error_flag_ptr(void *scratch, int n_clients, int B) {
+    return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + lenet_words(n_clients, B));
 }
 
 hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
@@ -1475,29 +1635,31 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     const size_t lds = lenet_lds_bytes(d);
     hipError_t e;
     const bool g28 = d.H0 == 28 && d.P1 == 12 && d.H2 == 8 && d.P2 == 4 && d.F0 == 256 && d.lgF0 == 8;
-    const void *fn = g28 ? reinterpret_cast<const void *>(k_lenet_round<true>) : reinterpret_cast<const void *>(k_lenet_round<false>);
-    if (g_lenet_per_cu[g28] == 0) {
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const int S = lenet_clusters(B);
+    const LenetKernel kernel = lenet_kernel(g28, S, !lenet_round_exact(B));
+    static bool sized[2][3] = {};   // a property of the function: set once
+    bool &done = sized[g28][S == 2 ? 2 : lenet_round_exact(B) ? 0 : 1];
+    if (!done) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
+        done = true;
     }
     int dev = 0, cus = 0, per_cu = 0;
     e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    e = g28 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_lenet_round<true>, kLnThreads, lds)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_lenet_round<false>, kLnThreads, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kLnThreads, lds);
     if (e != hipSuccess) return e;
-    g_lenet_per_cu[g28] = per_cu;
     // clusters per launch: every workgroup that polls must be resident together with its peers
-    const int per_launch = cus * per_cu / kLnG;
+    const int per_launch = cus * per_cu / (kLnG * S);
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     u64 *xrec = static_cast<u64 *>(scratch);
-    int *errflag = reinterpret_cast<int *>(xrec + (size_t)n_clients * kXWords);
+    const size_t words = lenet_words(n_clients, B);
+    int *errflag = reinterpret_cast<int *>(xrec + words);
     // step tags of this launch: never 0 (the cleared state) and never a tag that an earlier
     // launch may have left in the records
     if (*epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u) {
-        const size_t words = (size_t)n_clients * kXWords;
         k_zero_words_ln<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(xrec, words);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1507,10 +1669,9 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     *epoch += (uint32_t)max_m + 1u;
     for (int a0 = 0; a0 < nact; a0 += per_launch) {
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
-        const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * kLnG);
+        const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * kLnG * S);
         if (prof && prof->on[F_LENET_ROUND]) prof->before(F_LENET_ROUND, s);
-        if (g28) k_lenet_round<true><<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, xrec, tag0, errflag);
-        else k_lenet_round<false><<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, xrec, tag0, errflag);
+        kernel<<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, B, xrec, tag0, errflag);
         if (prof && prof->on[F_LENET_ROUND]) prof->after(F_LENET_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -81,3 +81,23 @@ def test_softmax_mini_batches(gpu, oracle_libs, n, d, batch):
     wl.model.batch = batch
     wl.a = wl.b = batch
     _lockstep(gpu, wl)
+
+
+@pytest.mark.parametrize("n,hw,batch", [
+    (3, 16, 1),          # one real sample of sixteen
+    (5, 28, 4),
+    (2, 20, 15),         # one sample short
+    (3, 28, 17),         # a second cluster with one real sample
+    (9, 16, 32),         # both clusters full; more than one client per XCD
+    (33, 28, 32),        # one client more than is resident: two launches
+])
+def test_lenet_mini_batches(gpu, oracle_libs, n, hw, batch):
+    wl = W.config3(n_clients=n, n_per=60, hw=hw, batch=batch, rounds=3 if n < 33 else 2, a=batch, b=batch)
+    if n == 5:
+        wl.compute_factor = np.array([1, 2, 1, 3, 1], dtype=np.int32)
+    _lockstep(gpu, wl)
+
+
+@pytest.mark.parametrize("hw,batch", [(16, 4), (28, 20)])
+def test_lenet_on_the_layer_engine(gpu, oracle_libs, layer_engine, hw, batch):
+    _lockstep(gpu, W.config3(n_clients=3, n_per=40, hw=hw, batch=batch, rounds=3, a=batch, b=batch))
