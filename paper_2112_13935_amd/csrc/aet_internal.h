@@ -116,6 +116,10 @@ hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundPara
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,
                              int u, int B, int K, int O, int64_t w_off, int64_t b_off, int relu,
                              const float *x, const float *y, float *z, const float *mask_src);
+// the whole last dense layer (logits, softmax cross-entropy, d(input), update) in one launch
+bool dense_head_supported(const LayerGeom &L, int B);
+hipError_t launch_dense_head(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                             const LayerGeom &L, const float *in, const int32_t *labels, float *din, bool masked);
 // fused round of softmax regression, per-sample SGD (kernels_softmax.hip)
 bool softmax_round_supported(int D, int C, int B);
 hipError_t launch_softmax_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact,

@@ -451,6 +451,226 @@ k_dense_fwd_direct(const RoundParams *__restrict__ rp, int u, int B, int K, int 
     }
 }
 
+// The last dense layer (O <= 16 outputs, its mini-batch and weights fit in LDS) in one launch, one
+// workgroup of 8 waves per client: logits, softmax cross-entropy, d(input) and the update.
+//   logits   M = b, N = o, contraction over k dealt to the waves, partial tiles added in wave order
+//   d(input) M = b, N = k, contraction over o (the weights as they were), masked by the ReLU below
+//   g        M = o, N = k, contraction over b;  w <- w - eta g,  U <- U + g
+// Inputs, weights and d(logits) are read once and stay in LDS (rows 4 mod 32 banks apart: operand
+// reads are conflict-free); rows and columns that do not exist are zeros.  As four launches (forward,
+// softmax, backward-data, backward-weight) this layer was a chain of dependent trips through
+// memory and launch boundaries: on 6 clients x (64 -> 10, mini-batch 16) 23 us of a recursion's
+// 158, now 7 us of it: the job of 45 recursions went from 6.60 to 6.29 ms.
+constexpr int kHeadWaves = 8;
+
+struct HeadGeom {
+    int B, K, O;
+    int BT, KT;            // tiles of 16 samples / inputs
+    int KA;                // LDS row stride of inputs and weights
+    int64_t w_off, b_off;
+};
+
+static size_t head_lds_bytes(const HeadGeom &g) {
+    return 4 * ((size_t)16 * g.BT * g.KA + 16 * g.KA + (size_t)kHeadWaves * 16 * g.BT * 17 + (size_t)16 * g.BT * 20 + 32 * g.BT);
+}
+
+static HeadGeom head_geom(const LayerGeom &L, int B) {
+    HeadGeom g;
+    g.B = B; g.K = (int)L.in_size; g.O = L.oc;
+    g.BT = (B + 15) / 16;
+    g.KT = (g.K + 15) / 16;
+    g.KA = (16 * g.KT + 31) / 32 * 32 + 4;
+    g.w_off = L.w_off; g.b_off = L.b_off;
+    return g;
+}
+
+// VEC: rows of inputs and weights are 16-byte aligned
+template <bool VEC>
+__global__ void __launch_bounds__(64 * kHeadWaves)
+k_dense_head(const RoundParams *__restrict__ rp, int u, HeadGeom g, const float *__restrict__ in,
+             const int32_t *__restrict__ labels, float *__restrict__ din, int masked) {
+    const RoundParams p = rp[blockIdx.x];
+    if (u >= p.m) return;
+    constexpr int T = 64 * kHeadWaves;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int B16 = 16 * g.BT, K16 = 16 * g.KT;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    float *As = smem;                          // [B16][KA]   inputs
+    float *Ws = As + B16 * g.KA;               // [16][KA]    weights
+    float *part = Ws + 16 * g.KA;              // [8][B16][17] partial logits
+    float *dz = part + kHeadWaves * B16 * 17;  // [B16][20]   d loss / d logits
+    float *lossb = dz + B16 * 20;              // [B16]
+    int *labs = reinterpret_cast<int *>(lossb + B16);   // [B16]
+    const int64_t cb = (int64_t)blockIdx.x * g.B;
+    const gcf_ptr ain = as_global(in) + cb * g.K;
+    const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
+
+    // what is needed later and can be asked for now: labels, the bias of this thread's class, U of
+    // the wave's first two tiles (lane: outputs 4 lg .. 4 lg + 3, input 16 t + li)
+    for (int b = tid; b < g.B; b += T) labs[b] = labels[cb + b];
+    const float bias = (tid & 15) < g.O ? Wc[g.b_off + (tid & 15)] : 0.f;
+    auto fetch_U = [&](int t, float (&uv)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k = 16 * t + li, o = 4 * lg + r;
+            uv[r] = Uc[k < g.K && o < g.O ? g.w_off + (int64_t)o * g.K + k : g.w_off];
+        }
+    };
+    float u0[4], u1[4];
+    fetch_U(wave, u0);
+    fetch_U(wave + kHeadWaves, u1);
+    // rows of both in pieces of four, eight pieces of a thread in flight; the weights are the rows
+    // behind the samples
+    const int K4 = K16 >> 2, np = (B16 + 16) * K4;
+    for (int q0 = tid; q0 < np; q0 += 8 * T) {
+        f4 v[8];
+        int dst[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int q = min(q0 + T * i, np - 1), row = q / K4, k = 4 * (q - row * K4), o = row - B16;
+            const bool real = o < 0 ? row < g.B : o < g.O;
+            const gcf_ptr src = o < 0 ? ain + (int64_t)(real ? row : 0) * g.K : (gcf_ptr)Wc + g.w_off + (int64_t)(real ? o : 0) * g.K;
+            if (VEC) {
+                const bool ok = real && k < g.K;
+                v[i] = *reinterpret_cast<const f4 __attribute__((address_space(1))) *>(src + (ok ? k : 0));
+                if (!ok) v[i] = f4{0.f, 0.f, 0.f, 0.f};
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool ok = real && k + r < g.K;
+                    v[i][r] = src[ok ? k + r : 0];
+                    if (!ok) v[i][r] = 0.f;
+                }
+            }
+            dst[i] = row * g.KA + k;   // (Ws follows As)
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (q0 + T * i < np) *reinterpret_cast<f4 *>(As + dst[i]) = v[i];
+    }
+    __syncthreads();
+    // logits: wave w contracts the tiles w, w + 8, ... of inputs for all samples
+    for (int bt = 0; bt < g.BT; ++bt) {
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+        const float *ap = As + (16 * bt + li) * g.KA + lg, *wp = Ws + li * g.KA + lg;
+        for (int t = wave; t < g.KT; t += kHeadWaves)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ap[16 * t + 4 * s], wp[16 * t + 4 * s], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(wave * B16 + 16 * bt + 4 * lg + r) * 17 + li] = acc[r];
+    }
+    __syncthreads();
+    // softmax, d logits and loss: 16 lanes per sample
+    for (int e = tid; e < 16 * B16; e += T) {
+        const int b = e >> 4, o = e & 15;
+        const bool live = b < g.B && o < g.O;
+        float z = bias;
+#pragma unroll
+        for (int w = 0; w < kHeadWaves; ++w) z += part[(w * B16 + b) * 17 + o];
+        float zmax = live ? z : -3.4e38f;
+#pragma unroll
+        for (int d = 1; d < 16; d <<= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
+        float sum = live ? expf(z - zmax) : 0.f;
+#pragma unroll
+        for (int d = 1; d < 16; d <<= 1) sum += __shfl_xor(sum, d, 64);
+        const float lse = zmax + logf(sum);
+        float dv = 0.f;
+        if (live) {
+            const int lab = labs[b];
+            dv = expf(z - lse) - (o == lab ? 1.f : 0.f);
+            if (o == lab) lossb[b] = lse - z;
+        }
+        dz[b * 20 + o] = dv;
+    }
+    __syncthreads();
+    const float invB = 1.0f / (float)g.B;
+    const int bsteps = 4 * g.BT;
+    for (int t = wave; t < g.KT; t += kHeadWaves) {
+        const int k = 16 * t + li;
+        const bool kok = k < g.K;
+        float uv[4];
+        if (t >= 2 * kHeadWaves) {
+            fetch_U(t, uv);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) uv[r] = t < kHeadWaves ? u0[r] : u1[r];
+        }
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int s = 0; s < bsteps; ++s)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(dz[(4 * s + lg) * 20 + li], As[(4 * s + lg) * g.KA + k], acc, 0, 0, 0);
+        for (int bt = 0; bt < g.BT; ++bt) {
+            f4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(dz[(16 * bt + li) * 20 + 4 * s + lg], Ws[(4 * s + lg) * g.KA + k], d, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = 16 * bt + 4 * lg + r;
+                if (kok && b < g.B)
+                    as_global(din)[(cb + b) * g.K + k] = !masked || As[b * g.KA + k] > 0.f ? d[r] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int o = 4 * lg + r;
+            if (kok && o < g.O) {
+                const float gv = acc[r] * invB;
+                const int64_t wi = g.w_off + (int64_t)o * g.K + k;
+                Wc[wi] = Ws[o * g.KA + k] - p.eta * gv;
+                Uc[wi] = uv[r] + gv;
+            }
+        }
+    }
+    if (wave == kHeadWaves - 1) {   // bias: lane group lg adds the samples lg, lg + 4, ...
+        float s = 0.f;
+#pragma unroll 8
+        for (int b = lg; b < B16; b += 4) s += dz[b * 20 + li];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        s *= invB;
+        if (lane < g.O) {
+            Wc[g.b_off + lane] -= p.eta * s;
+            Uc[g.b_off + lane] += s;
+        }
+    } else if (wave == kHeadWaves - 2) {
+        float s = 0.f;
+        for (int b = lane; b < g.B; b += 64) s += lossb[b];
+        s = wave_sum(s);
+        if (lane == 0) *as_global(p.loss) += s / (float)g.B;
+    }
+}
+
+bool dense_head_supported(const LayerGeom &L, int B) {
+    return L.oc <= 16 && head_lds_bytes(head_geom(L, B)) <= 160 * 1024;
+}
+
+hipError_t launch_dense_head(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                             const LayerGeom &L, const float *in, const int32_t *labels, float *din, bool masked) {
+    const HeadGeom g = head_geom(L, B);
+    const size_t lds = head_lds_bytes(g);
+    static bool sized = false;   // a property of the function: set once
+    if (!sized) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<true>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<false>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        sized = true;
+    }
+    const bool timed = prof && prof->on[F_SOFTMAX_CE];
+    if (timed) prof->before(F_SOFTMAX_CE, s);
+    if ((g.K & 3) == 0 && (g.w_off & 3) == 0)
+        k_dense_head<true><<<(unsigned)nact, 64 * kHeadWaves, lds, s>>>(dp, u, g, in, labels, din, masked ? 1 : 0);
+    else
+        k_dense_head<false><<<(unsigned)nact, 64 * kHeadWaves, lds, s>>>(dp, u, g, in, labels, din, masked ? 1 : 0);
+    if (timed) prof->after(F_SOFTMAX_CE, s);
+    return hipGetLastError();
+}
+
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,
                              int u, int B, int K, int O, int64_t w_off, int64_t b_off, int relu,
                              const float *x, const float *y, float *z, const float *mask_src) {

@@ -6,7 +6,8 @@
 // One recursion (Algorithm 2, MainComputeNode, body of the while loop), for client c:
 //   draw B sample indices and gather the rows      -> k_gather
 //   forward pass, layer by layer                   -> k_conv_fwd / k_pool_fwd / k_dense_fwd
-//   softmax cross-entropy, d loss / d logits       -> k_softmax_ce
+//   softmax cross-entropy, d loss / d logits       -> k_softmax_ce (k_dense_head: the whole last
+//                                                     layer, where it fits)
 //   backward pass; each parameter layer first hands the gradient to the layer below
 //   (k_*_bwd_data, which reads the not-yet-updated weights) and then forms its own
 //   gradient g and applies  w <- w - eta g,  U <- U + g  in the same kernel
@@ -637,7 +638,10 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         AET_TIMED(F_GATHER, k_gather<<<grid, 256, 0, s>>>(dp, u, B, D, sc.act[0], sc.labels));
         AET_RETURN_IF(hipGetLastError());
     }
-    for (int l = 0; l < L; ++l) {
+    // the last layer, forward to update, in one launch where it fits
+    const bool head = !sc.plain && L > 1 && dense_head_supported(lay[L - 1], B);
+    const int LF = head ? L - 1 : L;
+    for (int l = 0; l < LF; ++l) {
         const LayerGeom &g = lay[l];
         if (g.type == 0) {
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 0, sc.act[l], nullptr,
@@ -661,9 +665,13 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
             AET_RETURN_IF(hipGetLastError());
         }
     }
-    AET_TIMED(F_SOFTMAX_CE, k_softmax_ce<<<nact, 256, 0, s>>>(dp, u, B, lay[L - 1].oc, sc.act[L], sc.labels, sc.del[L]));
-    AET_RETURN_IF(hipGetLastError());
-    for (int l = L - 1; l >= 0; --l) {
+    if (head) {
+        AET_RETURN_IF(launch_dense_head(s, prof, dp, nact, u, B, lay[L - 1], sc.act[L - 1], sc.labels, sc.del[L - 1], lay[L - 2].relu != 0));
+    } else {
+        AET_TIMED(F_SOFTMAX_CE, k_softmax_ce<<<nact, 256, 0, s>>>(dp, u, B, lay[L - 1].oc, sc.act[L], sc.labels, sc.del[L]));
+        AET_RETURN_IF(hipGetLastError());
+    }
+    for (int l = LF - 1; l >= 0; --l) {
         const LayerGeom &g = lay[l];
         // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
         const float *mask = (l > 0 && lay[l - 1].relu) ? sc.act[l] : nullptr;

@@ -101,3 +101,14 @@ def test_lenet_mini_batches(gpu, oracle_libs, n, hw, batch):
 @pytest.mark.parametrize("hw,batch", [(16, 4), (28, 20)])
 def test_lenet_on_the_layer_engine(gpu, oracle_libs, layer_engine, hw, batch):
     _lockstep(gpu, W.config3(n_clients=3, n_per=40, hw=hw, batch=batch, rounds=3, a=batch, b=batch))
+
+
+@pytest.mark.parametrize("n,hw,width,fc,batch", [
+    (1, 4, 3, 5, 1),       # one sample, fewer inputs of the last layer than a tile
+    (2, 8, 6, 17, 5),      # one input more than a tile
+    (3, 8, 16, 256, 64),   # the largest mini-batch whose last layer is one launch at this width
+    (2, 8, 4, 40, 80),     # more samples than the unrolled tiles, still one launch
+    (2, 8, 4, 300, 64),    # too wide for it: forward, softmax, backward as launches of their own
+])
+def test_cnn_last_layer_and_rows(gpu, oracle_libs, n, hw, width, fc, batch):
+    _lockstep(gpu, W.config4(n_clients=n, n_per=90, hw=hw, width=width, fc=fc, batch=batch, rounds=2, a=batch, b=batch))
