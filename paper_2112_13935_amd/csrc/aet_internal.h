@@ -112,6 +112,10 @@ size_t conv_wgrad_partial_floats(const LayerGeom &L, int B, int n_clients);
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
                                   float *partial);
+// backward-data and backward-weight of a layer in one launch where both are small
+hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                                const LayerGeom &L, const float *dout, float *din, const float *mask_src,
+                                const float *in, float *partial, bool *taken);
 // dense layers on the matrix cores (kernels_dense_mfma.hip); mode 0 fwd, 1 bwd-data, 2 bwd-weight
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,
                              int u, int B, int K, int O, int64_t w_off, int64_t b_off, int relu,

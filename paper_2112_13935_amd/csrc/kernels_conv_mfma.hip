@@ -75,12 +75,11 @@ struct ConvDir {
 // row and walks channels; for the weights to four consecutive elements of the memory run and
 // walks destination channels (forward) or source channels (backward-data).  The tile's halo
 // columns never change and are zeroed once.
+// (bx, by, bz): row and channel block, sample, client.
 template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC>
-__global__ void __launch_bounds__(256, VEC ? 4 : 1)   // VEC: at most 128 registers, 4 workgroups per CU
-k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const float *__restrict__ src,
-            float *__restrict__ dst, const float *__restrict__ mask_src) {
-    const RoundParams p = rp[blockIdx.z];
-    if (u >= p.m) return;
+__device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, const ConvDir &g, const float *__restrict__ src,
+                                               float *__restrict__ dst, const float *__restrict__ mask_src,
+                                               int bx, int by, int bz, float *smem) {
     constexpr int KSQ = KS * KS;
     constexpr int KCHR = CCH * KSQ;          // K elements per chunk
     constexpr int KCH = (KCHR + 3) / 4 * 4;  // ... rounded up to whole contraction steps (zero weights)
@@ -89,10 +88,10 @@ k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const f
     constexpr bool CF = CCH >= 4;            // channels fastest
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int nblocks = (g.DC + 16 * NT - 1) / (16 * NT);
-    const int nblk = blockIdx.x % nblocks, rblk = blockIdx.x / nblocks;
+    const int nblk = bx % nblocks, rblk = bx / nblocks;
     const int y0 = rblk * g.R;
     const int dc0 = nblk * 16 * NT;
-    const int64_t sample = (int64_t)blockIdx.z * B + blockIdx.y;
+    const int64_t sample = (int64_t)bz * B + by;
     // range-checked buffers: the sample's source planes and the layer's weights; an offset
     // beyond them (kNowhere, or a channel beyond the last) reads zero without touching memory
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -106,7 +105,6 @@ k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const f
         return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 0));
     };
 
-    extern __shared__ float smem[];
     const int tile_plane = g.rowsT * g.SWP;
     const int PL = g.PL;                        // plane stride: 16 mod 32, so that the four lane
     float *Ssm = smem;                          // groups of an A operand fall into distinct banks
@@ -410,6 +408,16 @@ k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const f
     }
 }
 
+template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC>
+__global__ void __launch_bounds__(256, VEC ? 4 : 1)   // VEC: at most 128 registers, 4 workgroups per CU
+k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const float *__restrict__ src,
+            float *__restrict__ dst, const float *__restrict__ mask_src) {
+    const RoundParams p = rp[blockIdx.z];
+    if (u >= p.m) return;
+    extern __shared__ float smem[];
+    conv_mfma_body<KS, BWD, CCH, NT, NPOS, VEC>(p, B, g, src, dst, mask_src, blockIdx.x, blockIdx.y, blockIdx.z, smem);
+}
+
 static int device_cus() {
     static int cus = 0;
     if (cus == 0) {
@@ -550,20 +558,16 @@ constexpr int kPreD = 16;   // the same for the d(output) tile
 // Staging: a thread is tied to one position of the tile (row, column) and walks the channels,
 // so the loop has no index arithmetic and no branches; the next work item's elements are
 // fetched into registers before the products of the current one start and go to LDS after them.
+// (sl, bz): slice, client.
 template <int KS, int MT, int NTW, int WM, bool VEC>
-__global__ void __launch_bounds__(256)
-k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
-                  const float *__restrict__ in, const float *__restrict__ dout,
-                  float *__restrict__ partial) {
-    const RoundParams p = rp[blockIdx.z];
-    if (u >= p.m) return;
+__device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const float *__restrict__ in,
+                                                const float *__restrict__ dout, float *__restrict__ partial,
+                                                int sl, int bz, float *smem) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
-    const int sl = blockIdx.x;
     const int m0 = WM == 1 ? 0 : (wave >> 1);   // first M tile of the wave, stride WM
     const int n0 = WM == 1 ? wave : (wave & 1);  // first N tile of the wave, stride NS
     constexpr int NS = 4 / WM;
 
-    extern __shared__ float smem[];
     const int plane = g.rowsT * g.SWP;
     const int CP = VEC ? g.gin4 * g.nq_in4 : g.gin * g.nq_in_all;   // channel planes the staging threads write (>= IC)
     const int DR = VEC ? g.gd4 * g.nq_d4 : g.gd * g.nq_d_all;       // d(output) rows they write (>= 16*MTS)
@@ -643,7 +647,7 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
     auto fetch = [&](int it) {
         const int b = it / g.items_per_sample, rb = it - b * g.items_per_sample;
         const int y0 = rb * g.R;
-        const int64_t sample = (int64_t)blockIdx.z * B + b;
+        const int64_t sample = (int64_t)bz * B + b;
         const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(in) + sample * g.in_size, 0, (int)(4 * g.in_size), kBufferFlags);
         const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
@@ -739,7 +743,7 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
     }
     // partial[a][slice][co][k]: lane holds k = 16*nt + li, co = 16*mt + 4*lg + r
     const int KP = 16 * g.NTT, OCP = 16 * g.MTT;
-    const gf_ptr pg = as_global(partial) + ((int64_t)blockIdx.z * g.S + sl) * OCP * KP;
+    const gf_ptr pg = as_global(partial) + ((int64_t)bz * g.S + sl) * OCP * KP;
 #pragma unroll
     for (int j = 0; j < NTW; ++j) {
         const int nt = n0 + NS * j;
@@ -751,6 +755,38 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
 #pragma unroll
             for (int r = 0; r < 4; ++r) pg[(int64_t)(16 * mt + 4 * lg + r) * KP + 16 * nt + li] = acc[m][j][r];
         }
+    }
+}
+
+template <int KS, int MT, int NTW, int WM, bool VEC>
+__global__ void __launch_bounds__(256)
+k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
+                  const float *__restrict__ in, const float *__restrict__ dout,
+                  float *__restrict__ partial) {
+    if (u >= rp[blockIdx.z].m) return;
+    extern __shared__ float smem[];
+    conv_wgrad_body<KS, MT, NTW, WM, VEC>(B, g, in, dout, partial, blockIdx.x, blockIdx.z, smem);
+}
+
+// Backward-data and backward-weight of one layer in one launch, for launches too small to fill
+// the GPU: both read d(output) and neither reads what the other writes (the weights are updated
+// by the finish kernel).  Workgroups 0 .. nd-1 are backward-data blocks, the rest slices.
+template <int NT, bool VECD, int MT, int NTW, bool VECW>
+__global__ void __launch_bounds__(256)
+k_conv_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, ConvDir d, int nd, int dx, WgradGeom w,
+                const float *__restrict__ dout, float *__restrict__ din, const float *__restrict__ mask_src,
+                const float *__restrict__ in, float *__restrict__ partial) {
+    extern __shared__ float smem[];
+    const int id = blockIdx.x;
+    if (id < nd) {
+        const int bx = id % dx, r = id / dx, by = r % B, bz = r / B;
+        const RoundParams p = rp[bz];
+        if (u >= p.m) return;
+        conv_mfma_body<3, true, kCch, NT, 1, VECD>(p, B, d, dout, din, mask_src, bx, by, bz, smem);
+    } else {
+        const int sl = (id - nd) % w.S, bz = (id - nd) / w.S;
+        if (u >= rp[bz].m) return;
+        conv_wgrad_body<3, MT, NTW, 1, VECW>(B, w, in, dout, partial, sl, bz, smem);
     }
 }
 
@@ -942,6 +978,71 @@ static int wgrad_dispatch(int which, hipStream_t s, dim3 grid, size_t lds, int m
 }
 
 
+// Slices per client: all workgroups of the launch resident at once (a few workgroups more
+// than fit would cost a whole second pass), never more than the partial-sum scratch holds
+// (wgrad_target + n_clients slices), and the output rows of the work items spread evenly.
+static void wgrad_slices(const LayerGeom &L, int B, int nact, int cap, WgradGeom *g) {
+    const int units = B * g->items_per_sample * g->R;
+    if (cap > wgrad_target(L)) cap = wgrad_target(L);
+    int S = cap / nact;
+    if (S < 1) S = 1;
+    if (S > units) S = units;
+    g->U = (units + S - 1) / S;
+    g->S = (units + g->U - 1) / g->U;  // the fewest slices with the same longest share
+}
+
+static hipError_t wgrad_finish(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L,
+                               const WgradGeom &g, const float *partial) {
+    // thread groups per workgroup: a chain of at most about twelve slices each
+    const int sg = g.S <= 8 ? 1 : g.S <= 48 ? 4 : 16;
+    const int runs = g.OC * 4 * g.NTT;   // of four entries
+    dim3 fgrid((unsigned)((runs + 256 / sg - 1) / (256 / sg)), 1, (unsigned)nact);
+    if (sg == 1) k_conv_wgrad_finish<1><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
+    else if (sg == 4) k_conv_wgrad_finish<4><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
+    else k_conv_wgrad_finish<16><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
+    return hipGetLastError();
+}
+
+// Both backward kernels of a layer in one launch (and the finish).  *taken = false: nothing was
+// launched, the caller runs them one after the other.  The rule: the backward-data blocks take at
+// most one workgroup per compute unit and the slices get as many again, so that all of both are
+// resident together; beyond that each fills the GPU by itself.  3 x 3 layers of up to 32
+// channels on both sides (the instantiations that exist).
+hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                                const LayerGeom &L, const float *dout, float *din, const float *mask_src,
+                                const float *in, float *partial, bool *taken) {
+    *taken = false;
+    ConvDir d;
+    WgradGeom w;
+    if (L.k != 3 || !conv_mfma_supported(L, true) || !conv_wgrad_mfma_supported(L, B)) return hipSuccess;
+    if (!conv_dir(L, true, &d, 2) || !wgrad_geom(L, B, nact, &w)) return hipSuccess;
+    const int cus = device_cus();
+    const int dx = (d.DC + 16 * d.NT - 1) / (16 * d.NT) * ((d.DH + d.R - 1) / d.R);
+    if ((int64_t)dx * B * nact > cus) return hipSuccess;
+    const int mt = wgrad_mt(w), ntw = wgrad_ntw(w);
+    if (d.CCH != kCch || (!d.vec && d.npos != 1) || wgrad_wm(w) != 1 || mt > 2) return hipSuccess;
+    wgrad_slices(L, B, nact, cus, &w);
+    const int nd = dx * B * nact;
+    const size_t la = conv_lds_bytes(d, 3), lb = wgrad_lds_bytes(w), lds = la > lb ? la : lb;
+    void (*kernel)(const RoundParams *, int, int, ConvDir, int, int, WgradGeom, const float *, float *, const float *,
+                   const float *, float *) = nullptr;
+#define AET_PAIR(nt, m, n)                                                                              \
+    if (d.NT == nt && mt == m && ntw == n)                                                              \
+        kernel = d.vec ? (w.vec ? k_conv_bwd_pair<nt, true, m, n, true> : nullptr)                      \
+                       : (w.vec ? k_conv_bwd_pair<nt, false, m, n, true> : k_conv_bwd_pair<nt, false, m, n, false>);
+    AET_PAIR(1, 1, 2) AET_PAIR(1, 2, 2) AET_PAIR(1, 1, 5) AET_PAIR(1, 2, 5) AET_PAIR(2, 1, 5) AET_PAIR(2, 2, 5)
+#undef AET_PAIR
+    if (!kernel) return hipSuccess;
+    *taken = true;
+    const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
+    if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
+    kernel<<<(unsigned)(nd + w.S * nact), 256, lds, s>>>(dp, u, B, d, nd, dx, w, dout, din, mask_src, in, partial);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, w, partial);
+    if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
+    return e;
+}
+
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
                                   float *partial) {
@@ -953,34 +1054,14 @@ hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundPara
     const int per_cu = L.k == 3 ? wgrad_dispatch<3>(0, s, none, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial)
                                 : wgrad_dispatch<5>(0, s, none, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial);
     if (per_cu < 1) return hipErrorInvalidValue;
-    // Slices per client: all workgroups of the launch resident at once (a few workgroups more
-    // than fit would cost a whole second pass), never more than the partial-sum scratch holds
-    // (wgrad_target + n_clients slices), and the output rows of the work items spread evenly.
-    const int units = B * g.items_per_sample * g.R;
-    int cap = per_cu * device_cus();
-    if (cap > wgrad_target(L)) cap = wgrad_target(L);
-    int S = cap / nact;
-    if (S < 1) S = 1;
-    if (S > units) S = units;
-    g.U = (units + S - 1) / S;
-    S = (units + g.U - 1) / g.U;  // the fewest slices with the same longest share
-    g.S = S;
+    wgrad_slices(L, B, nact, per_cu * device_cus(), &g);
     const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
     if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
     dim3 grid((unsigned)g.S, 1, (unsigned)nact);
     if (L.k == 3) wgrad_dispatch<3>(1, s, grid, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial);
     else wgrad_dispatch<5>(1, s, grid, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        // thread groups per workgroup: a chain of at most about twelve slices each
-        const int sg = g.S <= 8 ? 1 : g.S <= 48 ? 4 : 16;
-        const int runs = g.OC * 4 * g.NTT;   // of four entries
-        dim3 fgrid((unsigned)((runs + 256 / sg - 1) / (256 / sg)), 1, (unsigned)nact);
-        if (sg == 1) k_conv_wgrad_finish<1><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
-        else if (sg == 4) k_conv_wgrad_finish<4><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
-        else k_conv_wgrad_finish<16><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, g, partial);
     if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
     return e;
 }

@@ -676,6 +676,10 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
         const float *mask = (l > 0 && lay[l - 1].relu) ? sc.act[l] : nullptr;
         if (g.type == 0) {
+            bool taken = false;
+            if (l > 0 && !sc.plain && !conv_wgrad_direct_ok(g))
+                AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad, &taken));
+            if (taken) continue;
             if (l > 0)
                 AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 1, sc.del[l + 1], nullptr,
                                             sc.del[l], mask, !sc.plain));

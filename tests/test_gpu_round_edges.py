@@ -112,3 +112,13 @@ def test_lenet_on_the_layer_engine(gpu, oracle_libs, layer_engine, hw, batch):
 ])
 def test_cnn_last_layer_and_rows(gpu, oracle_libs, n, hw, width, fc, batch):
     _lockstep(gpu, W.config4(n_clients=n, n_per=90, hw=hw, width=width, fc=fc, batch=batch, rounds=2, a=batch, b=batch))
+
+
+@pytest.mark.parametrize("n,hw,width,batch", [
+    (1, 8, 5, 2),        # fewest slices; channels that fill no tile
+    (2, 12, 14, 4),      # rows of 12 and 6: staged by four pixels and one by one
+    (6, 16, 16, 16),     # as many backward-data blocks as a launch of both may have
+    (7, 16, 16, 32),     # more: one launch each
+])
+def test_conv_backward_in_one_launch(gpu, oracle_libs, n, hw, width, batch):
+    _lockstep(gpu, W.config4(n_clients=n, n_per=50, hw=hw, width=width, fc=20, batch=batch, rounds=2, a=0, b=batch))
