@@ -106,7 +106,9 @@ hipError_t launch_debug_indices(hipStream_t s, uint64_t key, int64_t q0, int cou
 bool conv_mfma_supported(const LayerGeom &L, bool bwd);
 hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, bool bwd, const float *src, float *dst,
-                            const float *mask_src);
+                            const float *mask_src, uint8_t *amax = nullptr);
+// amax != NULL (forward only): dst is the output of the 2 x 2 pooling layer behind it, amax its winners
+bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool);
 bool conv_wgrad_mfma_supported(const LayerGeom &L, int B);
 size_t conv_wgrad_partial_floats(const LayerGeom &L, int B, int n_clients);
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,

@@ -55,6 +55,8 @@ struct ConvDir {
     int64_t w_off, b_off;
     int ic, oc;          // the layer's own channel counts (weight layout W[oc][ic][K][K])
     int relu;
+    int pool;            // forward: 2 x 2 maxima (and where they were) are stored, not the map
+    int64_t pool_size;   // floats per sample of the pooled map
 };
 
 // CCH: source channels per K chunk (1, 2, 4 or 8: the smallest that holds the layer's source
@@ -79,7 +81,7 @@ struct ConvDir {
 template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC>
 __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, const ConvDir &g, const float *__restrict__ src,
                                                float *__restrict__ dst, const float *__restrict__ mask_src,
-                                               int bx, int by, int bz, float *smem) {
+                                               uint8_t *__restrict__ amax, int bx, int by, int bz, float *smem) {
     constexpr int KSQ = KS * KS;
     constexpr int KCHR = CCH * KSQ;          // K elements per chunk
     constexpr int KCH = (KCHR + 3) / 4 * 4;  // ... rounded up to whole contraction steps (zero weights)
@@ -110,12 +112,20 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     float *Ssm = smem;                          // groups of an A operand fall into distinct banks
     float *Wsm = Ssm + CCH * PL;                // [16*NT][KCHP]
 
-    // the wave's two M tiles: (row, column chunk) inside the workgroup's block
-    int abase[2];
+    // the wave's two M tiles: (row, column chunk) inside the workgroup's block.  In front of a
+    // pooling layer they are the two rows of the same windows, so that a lane holds whole windows.
+    int trow[2], tcch[2];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         const int mt = 2 * wave + m;
-        const int row = mt / g.MPR, cch = mt - row * g.MPR;
+        const bool pool = !BWD && g.pool;
+        trow[m] = pool ? 2 * (wave / g.MPR) + m : mt / g.MPR;
+        tcch[m] = pool ? wave % g.MPR : mt - trow[m] * g.MPR;
+    }
+    int abase[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int row = trow[m], cch = tcch[m];
         abase[m] = row * g.SWP + 16 * cch + li + (CF ? lg * PL : 0);
     }
     int ko[CF ? 1 : STEPS];
@@ -362,10 +372,52 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     const gf_ptr dg = as_global(dst) + sample * g.dst_size;
     const gcf_ptr mg = mask_src ? as_global(mask_src) + sample * g.dst_size : nullptr;
     const bool vec = (g.DW & 3) == 0;   // whole groups of 4 pixels, 16-byte aligned
+    if (!BWD && g.pool) {
+        // the map itself is not stored: nobody reads it (the backward pass takes the winners, and
+        // the ReLU mask of a winner from the pooled value)
+        const int row = trow[0], y = y0 + row, x0 = 16 * tcch[0] + 4 * lg;
+        if (row >= g.R || y >= g.DH) return;
+        const int PW = g.DW >> 1, PH = g.DH >> 1;
+        const gf_ptr pg = as_global(dst) + sample * g.pool_size;
+        uint8_t *am = amax + sample * g.pool_size;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            const int dc = dc0 + 16 * n + li;
+            if (dc >= g.DC) continue;
+            const float bias = as_global(p.W)[g.b_off + dc];
+            float best[2];
+            int which[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                which[h] = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {   // row-major: the first maximum wins
+                    float v = acc[i >> 1][n][2 * h + (i & 1)] + bias;
+                    if (g.relu && !(v > 0.f)) v = 0.f;
+                    if (i == 0 || v > best[h]) { best[h] = v; which[h] = i; }
+                }
+            }
+            const int64_t o = ((int64_t)dc * PH + (y >> 1)) * PW + (x0 >> 1);
+            if (vec) {
+                if (x0 < g.DW) {
+                    typedef float f2 __attribute__((ext_vector_type(2)));
+                    *reinterpret_cast<f2 __attribute__((address_space(1))) *>(pg + o) = f2{best[0], best[1]};
+                    *reinterpret_cast<uint16_t *>(am + o) = (uint16_t)(which[0] | which[1] << 8);
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (x0 + 2 * h < g.DW) {
+                        pg[o + h] = best[h];
+                        am[o + h] = (uint8_t)which[h];
+                    }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-        const int mt = 2 * wave + m;
-        const int row = mt / g.MPR, cch = mt - row * g.MPR;
+        const int row = trow[m], cch = tcch[m];
         const int y = y0 + row;
         if (row >= g.R || y >= g.DH) continue;
 #pragma unroll
@@ -411,11 +463,11 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
 template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC>
 __global__ void __launch_bounds__(256, VEC ? 4 : 1)   // VEC: at most 128 registers, 4 workgroups per CU
 k_conv_mfma(const RoundParams *__restrict__ rp, int u, int B, ConvDir g, const float *__restrict__ src,
-            float *__restrict__ dst, const float *__restrict__ mask_src) {
+            float *__restrict__ dst, const float *__restrict__ mask_src, uint8_t *__restrict__ amax) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
     extern __shared__ float smem[];
-    conv_mfma_body<KS, BWD, CCH, NT, NPOS, VEC>(p, B, g, src, dst, mask_src, blockIdx.x, blockIdx.y, blockIdx.z, smem);
+    conv_mfma_body<KS, BWD, CCH, NT, NPOS, VEC>(p, B, g, src, dst, mask_src, amax, blockIdx.x, blockIdx.y, blockIdx.z, smem);
 }
 
 static int device_cus() {
@@ -433,6 +485,8 @@ static bool conv_dir(const LayerGeom &L, bool bwd, ConvDir *d, int nt_max = 4) {
     const int KS = L.k;
     if (!(KS == 3 || KS == 5)) return false;
     d->ic = L.ic; d->oc = L.oc; d->relu = L.relu;
+    d->pool = 0;
+    d->pool_size = L.out_size / 4;
     d->w_off = L.w_off; d->b_off = L.b_off;
     if (!bwd) {
         d->SC = L.ic; d->DC = L.oc; d->SH = L.ih; d->SW = L.iw; d->DH = L.oh; d->DW = L.ow; d->P = L.pad;
@@ -481,9 +535,18 @@ bool conv_mfma_supported(const LayerGeom &L, bool bwd) {
     return conv_lds_bytes(d, L.k) <= 64 * 1024;
 }
 
+// A pooling layer behind a convolution on the matrix cores is done in its epilogue: the block's
+// rows come in pairs (R is even) and the pooling covers the whole map.  Launch and map fall away: the
+// map of 4 x the pooled size was written, read by the pooling kernel and read again as its ReLU mask.
+bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool) {
+    ConvDir d;
+    return conv_mfma_supported(L, false) && conv_dir(L, false, &d) && (d.R & 1) == 0 &&
+           2 * pool.oh == L.oh && 2 * pool.ow == L.ow && pool.oc == L.oc;
+}
+
 hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, bool bwd, const float *src, float *dst,
-                            const float *mask_src) {
+                            const float *mask_src, uint8_t *amax) {
     ConvDir d;
     if (!conv_dir(L, bwd, &d)) return hipErrorInvalidValue;
     // A launch of the widest tiling (4 N tiles, 4 resident workgroups per compute unit) that
@@ -493,6 +556,7 @@ hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp
     if (d.NT == 4 && (int64_t)((d.DH + d.R - 1) / d.R) * ((d.DC + 63) / 64) * B * nact < (int64_t)8 * device_cus() &&
         !conv_dir(L, bwd, &d, 2))
         return hipErrorInvalidValue;
+    d.pool = amax != nullptr;
     const size_t lds = conv_lds_bytes(d, L.k);
     const int nblocks = (d.DC + 16 * d.NT - 1) / (16 * d.NT);
     const int rblocks = (d.DH + d.R - 1) / d.R;
@@ -502,13 +566,13 @@ hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp
     if (timed) prof->before(fam, s);
 #define AET_CONV(KSv, CCHv, NTv, NPv)                                                                                \
     if (L.k == KSv && d.CCH == CCHv && d.NT == NTv && np == NPv) {                                                  \
-        if (bwd) k_conv_mfma<KSv, true, CCHv, NTv, NPv, false><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src);  \
-        else k_conv_mfma<KSv, false, CCHv, NTv, NPv, false><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src);     \
+        if (bwd) k_conv_mfma<KSv, true, CCHv, NTv, NPv, false><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src, amax);  \
+        else k_conv_mfma<KSv, false, CCHv, NTv, NPv, false><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src, amax);     \
     }
 #define AET_CONV_VEC(NTv)                                                                                            \
     if (np == 0 && d.NT == NTv) {                                                                                    \
-        if (bwd) k_conv_mfma<3, true, 8, NTv, 1, true><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src);    \
-        else k_conv_mfma<3, false, 8, NTv, 1, true><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src);       \
+        if (bwd) k_conv_mfma<3, true, 8, NTv, 1, true><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src, amax);    \
+        else k_conv_mfma<3, false, 8, NTv, 1, true><<<grid, 256, lds, s>>>(dp, u, B, d, src, dst, mask_src, amax);       \
     }
 #define AET_CONV_NT(KSv, CCHv, NPv) AET_CONV(KSv, CCHv, 1, NPv) AET_CONV(KSv, CCHv, 2, NPv) AET_CONV(KSv, CCHv, 4, NPv)
     // tiles of up to 256 positions and at least 4 channels per chunk get the one-position kernel
@@ -771,6 +835,9 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
 // Backward-data and backward-weight of one layer in one launch, for launches too small to fill
 // the GPU: both read d(output) and neither reads what the other writes (the weights are updated
 // by the finish kernel).  Workgroups 0 .. nd-1 are backward-data blocks, the rest slices.
+// What bounds such launches is their latency (a few dependent trips through memory each, half of
+// the compute units idle), not work: 6 clients, 16 x 16 half-width CNN, 45 recursions: 6.30 ->
+// 5.82 ms; 3 clients, 12 x 12, 27 recursions: 3.28 -> 2.93 ms.
 template <int NT, bool VECD, int MT, int NTW, bool VECW>
 __global__ void __launch_bounds__(256)
 k_conv_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, ConvDir d, int nd, int dx, WgradGeom w,
@@ -782,7 +849,7 @@ k_conv_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, ConvDir d, int
         const int bx = id % dx, r = id / dx, by = r % B, bz = r / B;
         const RoundParams p = rp[bz];
         if (u >= p.m) return;
-        conv_mfma_body<3, true, kCch, NT, 1, VECD>(p, B, d, dout, din, mask_src, bx, by, bz, smem);
+        conv_mfma_body<3, true, kCch, NT, 1, VECD>(p, B, d, dout, din, mask_src, nullptr, bx, by, bz, smem);
     } else {
         const int sl = (id - nd) % w.S, bz = (id - nd) / w.S;
         if (u >= rp[bz].m) return;

@@ -247,7 +247,10 @@ k_conv_bwd_weight(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
     }
 }
 
-// 2x2 / stride 2 max pooling; the first maximum in row-major window order wins
+// 2x2 / stride 2 max pooling; the first maximum in row-major window order wins.  (Behind a
+// convolution on the matrix cores the forward part is that kernel's epilogue.)  The backward part
+// takes the ReLU mask of the layer below from the pooled values: a winner's value is the pooled
+// one, and the others get no gradient; the map itself, four times as large, is not read.
 __global__ void __launch_bounds__(256)
 k_pool_fwd(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
            const float *__restrict__ in, float *__restrict__ out, uint8_t *__restrict__ amax) {
@@ -270,22 +273,20 @@ k_pool_fwd(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
 __global__ void __launch_bounds__(256)
 k_pool_bwd(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
            const float *__restrict__ dout, const uint8_t *__restrict__ amax,
-           float *__restrict__ din, const float *__restrict__ mask_src) {
+           float *__restrict__ din, const float *__restrict__ pooled) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= g.oc * g.oh * g.ow) return;
     const int ox = idx % g.ow, oy = (idx / g.ow) % g.oh, c = idx / (g.ow * g.oh);
     const int64_t sample = (int64_t)blockIdx.z * B + blockIdx.y;
-    const float d = dout[sample * g.out_size + idx];
+    float d = dout[sample * g.out_size + idx];
     const int which = amax[sample * g.out_size + idx];
+    if (pooled && !(pooled[sample * g.out_size + idx] > 0.f)) d = 0.f;
     const int64_t base = sample * g.in_size + ((int64_t)c * g.ih + 2 * oy) * g.iw + 2 * ox;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int64_t i = base + (j >> 1) * g.iw + (j & 1);
-        float v = (j == which) ? d : 0.f;
-        if (mask_src && !(mask_src[i] > 0.f)) v = 0.f;
-        din[i] = v;
+        din[base + (j >> 1) * g.iw + (j & 1)] = (j == which) ? d : 0.f;
     }
 }
 
@@ -326,7 +327,7 @@ k_pool_fwd_pair(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
 __global__ void __launch_bounds__(256)
 k_pool_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
                 const float *__restrict__ dout, const uint8_t *__restrict__ amax,
-                float *__restrict__ din, const float *__restrict__ mask_src) {
+                float *__restrict__ din, const float *__restrict__ pooled) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -335,7 +336,13 @@ k_pool_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
     const int oxp = idx % owh, oy = (idx / owh) % g.oh, c = idx / (owh * g.oh);
     const int64_t sample = (int64_t)blockIdx.z * B + blockIdx.y;
     const int64_t o = sample * g.out_size + 2 * (int64_t)idx;
-    const pf2 d = *reinterpret_cast<const pf2 *>(dout + o);
+    pf2 d = *reinterpret_cast<const pf2 *>(dout + o);
+    if (pooled) {
+        const pf2 k = *reinterpret_cast<const pf2 *>(pooled + o);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (!(k[h] > 0.f)) d[h] = 0.f;
+    }
     const unsigned which2 = *reinterpret_cast<const uint16_t *>(amax + o);
     const int64_t base = sample * g.in_size + ((int64_t)c * g.ih + 2 * oy) * g.iw + 4 * oxp;
 #pragma unroll
@@ -346,14 +353,7 @@ k_pool_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
             const int h = e >> 1, j = 2 * r + (e & 1);
             v[e] = ((which2 >> (8 * h)) & 0xffu) == (unsigned)j ? d[h] : 0.f;
         }
-        const int64_t i = base + (int64_t)r * g.iw;
-        if (mask_src) {
-            const pf4 k = *reinterpret_cast<const pf4 *>(mask_src + i);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (!(k[e] > 0.f)) v[e] = 0.f;
-        }
-        *reinterpret_cast<pf4 *>(din + i) = v;
+        *reinterpret_cast<pf4 *>(din + base + (int64_t)r * g.iw) = v;
     }
 }
 
@@ -643,7 +643,10 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
     const int LF = head ? L - 1 : L;
     for (int l = 0; l < LF; ++l) {
         const LayerGeom &g = lay[l];
-        if (g.type == 0) {
+        if (g.type == 0 && !sc.plain && l + 1 < L && lay[l + 1].type == 1 && conv_pool_fused(g, lay[l + 1])) {
+            AET_RETURN_IF(launch_conv_mfma(s, prof, dp, nact, u, B, g, false, sc.act[l], sc.act[l + 2], nullptr, sc.amax[l + 1]));
+            ++l;   // the pooling layer
+        } else if (g.type == 0) {
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 0, sc.act[l], nullptr,
                                         sc.act[l + 1], nullptr, !sc.plain));
         } else if (g.type == 1) {
@@ -687,12 +690,14 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
                                         sc.wgrad, nullptr, !sc.plain));
         } else if (g.type == 1) {
             if (l > 0) {
+                // the ReLU below, at the winners: their value is the pooled one
+                const float *pooled = mask ? sc.act[l + 1] : nullptr;
                 if (pool_pairs(g)) {
                     dim3 grid((unsigned)((g.out_size / 2 + 255) / 256), B, nact);
-                    AET_TIMED(F_POOL_BWD, k_pool_bwd_pair<<<grid, 256, 0, s>>>(dp, u, B, g, sc.del[l + 1], sc.amax[l], sc.del[l], mask));
+                    AET_TIMED(F_POOL_BWD, k_pool_bwd_pair<<<grid, 256, 0, s>>>(dp, u, B, g, sc.del[l + 1], sc.amax[l], sc.del[l], pooled));
                 } else {
                     dim3 grid((unsigned)((g.out_size + 255) / 256), B, nact);
-                    AET_TIMED(F_POOL_BWD, k_pool_bwd<<<grid, 256, 0, s>>>(dp, u, B, g, sc.del[l + 1], sc.amax[l], sc.del[l], mask));
+                    AET_TIMED(F_POOL_BWD, k_pool_bwd<<<grid, 256, 0, s>>>(dp, u, B, g, sc.del[l + 1], sc.amax[l], sc.del[l], pooled));
                 }
                 AET_RETURN_IF(hipGetLastError());
             }
