@@ -450,17 +450,26 @@ static hipError_t conv_step(hipStream_t s, Profiler *prof, const RoundParams *dp
 // of the window in registers (one new input value and one d(output) value per pixel feed KS
 // FMAs).  The per-row sums are added in fixed order (sample slot, then y), scaled by 1/B and
 // applied:  w <- w - eta g,  U <- U + g.  Stride 1, zero padding.
+//
+// The 256 threads are repeated in up to kDirectGroups groups that take turns of samples (group j
+// the j-th SPW samples, then every G-th turn after it); their row sums are added in group order.
+// Launches are small (a workgroup per filter plane and client), so what bounds them is the chain
+// of turns: one group walked a mini-batch of 16 in four turns (6 clients x 48 planes of 16 x 16:
+// 12.4 -> 9.7 us a launch with four groups and one staging position per thread; 3 clients, 12 x
+// 12, mini-batch 5: 10.0 -> 5.8 us).
 // ---------------------------------------------------------------------------------------
 constexpr int kDirectPos = 4;   // tile positions one thread stages, at most
-constexpr int kDirectSlots = 4; // samples in flight, at most
+constexpr int kDirectSlots = 4; // samples in flight per group, at most
+constexpr int kDirectGroups = 4;
 
-template <int KS>
-__global__ void __launch_bounds__(256)
+// NP: tile positions one thread stages (planes of up to 256 NP values)
+template <int KS, int NP>
+__global__ void __launch_bounds__(256 * kDirectGroups)
 k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom g,
                     const float *__restrict__ in, const float *__restrict__ dout) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
-    const int oc = blockIdx.x, ic = blockIdx.y, tid = threadIdx.x;
+    const int oc = blockIdx.x, ic = blockIdx.y, tid = threadIdx.x & 255, grp = threadIdx.x >> 8, G = blockDim.x >> 8;
     const int IWP = (g.iw + 2 * g.pad) | 1, IHP = g.ih + 2 * g.pad;   // padded plane, odd row stride
     const int OWS = g.ow | 1;
     const int rows = KS * g.oh;              // threads per sample in flight
@@ -468,18 +477,18 @@ k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom 
     const int iplane = IHP * IWP, dplane = g.oh * OWS;
     const int ihw = g.ih * g.iw, ohw = g.oh * g.ow;
     extern __shared__ float sm[];
-    float *Ism = sm;                         // [SPW][IHP][IWP], borders zero
-    float *Dsm = Ism + SPW * iplane;         // [SPW][oh][OWS]
-    float *red = Dsm + SPW * dplane;         // [SPW * rows][KS + 1]: row sums per kx, and of d(output)
+    float *Ism = sm + grp * SPW * (iplane + dplane);   // per group: [SPW][IHP][IWP], borders zero
+    float *Dsm = Ism + SPW * iplane;                   // ... and [SPW][oh][OWS]
+    float *red = sm + G * SPW * (iplane + dplane);     // [G][SPW * rows][KS + 1]: row sums per kx, and of d(output)
     const int slot = tid / rows, rem = tid - slot * rows;
     const int ky = rem / g.oh, y = rem - ky * g.oh;
     const bool active = slot < SPW;
     const int64_t cb = (int64_t)blockIdx.z * B;
 
-    // staging: a thread is tied to up to kDirectPos positions of each plane
-    int igo[kDirectPos], ilo[kDirectPos], dgo[kDirectPos], dlo[kDirectPos];
+    // staging: a thread is tied to up to NP positions of each plane
+    int igo[NP], ilo[NP], dgo[NP], dlo[NP];
 #pragma unroll
-    for (int i = 0; i < kDirectPos; ++i) {
+    for (int i = 0; i < NP; ++i) {
         const int e = tid + 256 * i;
         const int yi = e / g.iw, xi = e - yi * g.iw;
         igo[i] = e < ihw ? e : -1;
@@ -496,7 +505,7 @@ k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom 
 
     // the planes of the next samples are fetched into registers before the products of the
     // current ones start and go to LDS after them
-    float vi[kDirectSlots][kDirectPos], vd[kDirectSlots][kDirectPos];
+    float vi[kDirectSlots][NP], vd[kDirectSlots][NP];
     auto fetch = [&](int b0) {
 #pragma unroll
         for (int sl = 0; sl < kDirectSlots; ++sl) {
@@ -505,7 +514,7 @@ k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom 
                 const float *ib = in + (cb + b) * g.in_size + (int64_t)ic * ihw;
                 const float *db = dout + (cb + b) * g.out_size + (int64_t)oc * ohw;
 #pragma unroll
-                for (int i = 0; i < kDirectPos; ++i) {
+                for (int i = 0; i < NP; ++i) {
                     vi[sl][i] = ib[igo[i] >= 0 ? igo[i] : 0];
                     vd[sl][i] = db[dgo[i] >= 0 ? dgo[i] : 0];
                 }
@@ -514,22 +523,23 @@ k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom 
     };
     constexpr int CH = 2 * KS;   // pixels per step of the row walk (a multiple of KS: the window's
                                  // registers keep their places)
-    fetch(0);
-    for (int b0 = 0; b0 < B; b0 += SPW) {
+    fetch(grp * SPW);
+    for (int t0 = 0; t0 < B; t0 += G * SPW) {
+        const int b0 = t0 + grp * SPW;   // a group beyond the mini-batch adds zeros
         __syncthreads();   // the products of the previous samples are done (first pass: borders are zero)
 #pragma unroll
         for (int sl = 0; sl < kDirectSlots; ++sl) {
             if (sl < SPW) {
                 const bool bok = b0 + sl < B;
 #pragma unroll
-                for (int i = 0; i < kDirectPos; ++i) {
+                for (int i = 0; i < NP; ++i) {
                     if (igo[i] >= 0) Ism[sl * iplane + ilo[i]] = bok ? vi[sl][i] : 0.f;
                     if (dgo[i] >= 0) Dsm[sl * dplane + dlo[i]] = bok ? vd[sl][i] : 0.f;
                 }
             }
         }
         __syncthreads();
-        if (b0 + SPW < B) fetch(b0 + SPW);
+        if (t0 + G * SPW < B) fetch(b0 + G * SPW);
         if (active) {
             const float *Irow = Ism + slot * iplane + (y + ky) * IWP;
             const float *Drow = Dsm + slot * dplane + y * OWS;
@@ -555,38 +565,45 @@ k_conv_wgrad_direct(const RoundParams *__restrict__ rp, int u, int B, LayerGeom 
             }
         }
     }
+    const int nrow = SPW * rows;
     if (active) {
+        float *rr = red + (grp * nrow + tid) * (KS + 1);
 #pragma unroll
-        for (int kx = 0; kx < KS; ++kx) red[tid * (KS + 1) + kx] = acc[kx];
-        red[tid * (KS + 1) + KS] = dsum;
+        for (int kx = 0; kx < KS; ++kx) rr[kx] = acc[kx];
+        rr[KS] = dsum;
     }
     __syncthreads();
     const float invB = 1.0f / (float)B;
-    if (tid < KS * KS) {
-        const int fy = tid / KS, fx = tid - fy * KS;
+    // 8 threads per output (25 or 9 filter entries and the bias), rows dealt over them; lanes of one
+    // output are neighbours: their sums are folded with shuffles
+    constexpr int NOUT = KS * KS + 1;
+    const int out = threadIdx.x >> 3, part = threadIdx.x & 7;
+    if (out < NOUT) {
+        const int fy = out < KS * KS ? out / KS : 0, fx = out < KS * KS ? out - fy * KS : KS;
         float sum = 0.f;
-        for (int sl = 0; sl < SPW; ++sl)
-            for (int yy = 0; yy < g.oh; ++yy) sum += red[(sl * rows + fy * g.oh + yy) * (KS + 1) + fx];
+        for (int j = part; j < G * SPW * g.oh; j += 8) {
+            const int sl = j / g.oh, yy = j - sl * g.oh;   // (group, slot) and row
+            sum += red[(sl * rows + fy * g.oh + yy) * (KS + 1) + fx];
+        }
+        sum += __shfl_xor(sum, 1, 64);
+        sum += __shfl_xor(sum, 2, 64);
+        sum += __shfl_xor(sum, 4, 64);
         sum *= invB;
-        const int64_t wi = g.w_off + ((int64_t)(oc * g.ic + ic) * KS + fy) * KS + fx;
-        p.W[wi] -= p.eta * sum;
-        p.U[wi] += sum;
-    } else if (tid == KS * KS && ic == 0) {
-        float sum = 0.f;
-        for (int sl = 0; sl < SPW; ++sl)
-            for (int yy = 0; yy < g.oh; ++yy) sum += red[(sl * rows + yy) * (KS + 1) + KS];
-        sum *= invB;
-        p.W[g.b_off + oc] -= p.eta * sum;
-        p.U[g.b_off + oc] += sum;
+        if (part == 0 && (out < KS * KS || ic == 0)) {
+            const int64_t wi = out < KS * KS ? g.w_off + ((int64_t)(oc * g.ic + ic) * KS + fy) * KS + fx : g.b_off + oc;
+            p.W[wi] -= p.eta * sum;
+            p.U[wi] += sum;
+        }
     }
 }
 
-static size_t conv_wgrad_direct_lds(const LayerGeom &g) {
-    const int IWP = (g.iw + 2 * g.pad) | 1, IHP = g.ih + 2 * g.pad, OWS = g.ow | 1;
+static int conv_wgrad_direct_spw(const LayerGeom &g) {   // samples in flight per group
     const int rows = g.k * g.oh;
-    if (rows > 256) return 0;
-    const int SPW = 256 / rows < kDirectSlots ? 256 / rows : kDirectSlots;
-    return sizeof(float) * ((size_t)SPW * (IHP * IWP + g.oh * OWS) + (size_t)SPW * rows * (g.k + 1));
+    return rows > 256 ? 0 : 256 / rows < kDirectSlots ? 256 / rows : kDirectSlots;
+}
+static size_t conv_wgrad_direct_lds(const LayerGeom &g, int G) {
+    const int IWP = (g.iw + 2 * g.pad) | 1, IHP = g.ih + 2 * g.pad, OWS = g.ow | 1, SPW = conv_wgrad_direct_spw(g);
+    return sizeof(float) * (size_t)G * ((size_t)SPW * (IHP * IWP + g.oh * OWS) + (size_t)SPW * g.k * g.oh * (g.k + 1));
 }
 
 // few channels (the matrix tiles of the MFMA kernel would be mostly padding), small planes
@@ -595,7 +612,7 @@ static bool conv_wgrad_direct_ok(const LayerGeom &g) {
     if (g.ic * g.k * g.k + 1 > 32 || g.oc > 16) return false;
     if (g.ih * g.iw > 256 * kDirectPos || g.oh * g.ow > 256 * kDirectPos) return false;
     if (g.ow != g.iw + 2 * g.pad - g.k + 1 || g.oh != g.ih + 2 * g.pad - g.k + 1) return false;
-    const size_t lds = conv_wgrad_direct_lds(g);
+    const size_t lds = conv_wgrad_direct_lds(g, 1);
     return lds > 0 && lds <= 64 * 1024;
 }
 
@@ -603,11 +620,17 @@ static hipError_t launch_conv_wgrad_direct(hipStream_t s, Profiler *prof, const 
                                            int u, int B, const LayerGeom &g, const float *in,
                                            const float *dout) {
     dim3 grid((unsigned)g.oc, (unsigned)g.ic, (unsigned)nact);
-    const size_t lds = conv_wgrad_direct_lds(g);
-    if (g.k == 3)
-        AET_TIMED(F_CONV_BWD_WEIGHT, k_conv_wgrad_direct<3><<<grid, 256, lds, s>>>(dp, u, B, g, in, dout));
-    else
-        AET_TIMED(F_CONV_BWD_WEIGHT, k_conv_wgrad_direct<5><<<grid, 256, lds, s>>>(dp, u, B, g, in, dout));
+    // as many groups as the mini-batch has turns for and 64 KB of LDS hold; one when the workgroups
+    // fill the GPU anyway (two per compute unit)
+    int G = 1;
+    while (G < kDirectGroups && G * conv_wgrad_direct_spw(g) < B && conv_wgrad_direct_lds(g, G + 1) <= 64 * 1024 &&
+           (int64_t)g.oc * g.ic * nact < 512)
+        ++G;
+    const size_t lds = conv_wgrad_direct_lds(g, G);
+    const bool one = g.ih * g.iw <= 256 && g.oh * g.ow <= 256;
+    auto kernel = g.k == 3 ? (one ? k_conv_wgrad_direct<3, 1> : k_conv_wgrad_direct<3, kDirectPos>)
+                           : (one ? k_conv_wgrad_direct<5, 1> : k_conv_wgrad_direct<5, kDirectPos>);
+    AET_TIMED(F_CONV_BWD_WEIGHT, kernel<<<grid, 256 * G, lds, s>>>(dp, u, B, g, in, dout));
     return hipGetLastError();
 }
 
