@@ -79,7 +79,8 @@ struct RoundRec {
 };
 
 struct Layout {
-    size_t w0, Wg, W, U, loss, params, arrivals, debug, labels, fused, wgrad;
+    size_t w0, Wg, W, U, loss, params, arrivals, debug, labels, fused, wgrad[AET_MAX_LAYERS];
+    bool wgrad_apart;
     size_t act[AET_MAX_LAYERS + 1], del[AET_MAX_LAYERS + 1], amax[AET_MAX_LAYERS];
     size_t total;
 };
@@ -161,7 +162,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
 }
 
 bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int inflight, int rounds,
-                 Layout *lo, Engine eng) {
+                 Layout *lo, Engine eng, bool apart = true) {
     if (n < 1 || inflight < 1 || rounds < 1) return false;
     const size_t Ps = (size_t)((P + 63) / 64 * 64);
     size_t off = 0;
@@ -178,11 +179,19 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     // exchange records of the fused dense-ReLU-dense engine, only for models it runs
     lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n, B)
                      : eng == ENGINE_SOFTMAX_BATCH ? softmax_batch_scratch_bytes(n, (int)lay[0].in_size, B) : 0);
+    // partial sums of the convolutions' weight gradients: apart (so that one launch can finish all
+    // layers), or in turns in the same place where the workspace is too small for that
+    apart = apart && eng == ENGINE_LAYERS;
+    lo->wgrad_apart = apart;
     size_t wg_floats = 0;
-    for (int l = 0; l < L; ++l)
-        if (lay[l].type == AET_CONV && conv_wgrad_mfma_supported(lay[l], B))
-            wg_floats = std::max(wg_floats, conv_wgrad_partial_floats(lay[l], B, n));
-    lo->wgrad = take(wg_floats * 4);
+    for (int l = 0; l < L; ++l) {
+        lo->wgrad[l] = off;
+        if (lay[l].type != AET_CONV || !conv_wgrad_mfma_supported(lay[l], B)) continue;
+        const size_t floats = conv_wgrad_partial_floats(lay[l], B, n);
+        if (apart) take(floats * 4);
+        wg_floats = std::max(wg_floats, floats);
+    }
+    if (!apart) take(wg_floats * 4);
     const size_t samples = (size_t)n * B;
     lo->act[0] = take(samples * lay[0].in_size * 4);
     lo->del[0] = 0;
@@ -369,9 +378,11 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     ctx->ws = static_cast<char *>(workspace);
     Engine engine = pick_engine(ctx->lay, ctx->L, ctx->B, ctx->n);
     make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine);
-    if (workspace_bytes < ctx->lo.total) {   // a padded form's records are an option, not a need
+    if (workspace_bytes < ctx->lo.total) {   // a padded form's records are an option, not a need; so are partial sums apart
         engine = pick_engine(ctx->lay, ctx->L, ctx->B, ctx->n, false);
         make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine);
+        if (workspace_bytes < ctx->lo.total)
+            make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine, false);
     }
     ctx->engine = engine;
     if (workspace_bytes < ctx->lo.total) {
@@ -402,7 +413,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     for (int l = 0; l < ctx->L; ++l)
         ctx->sc.amax[l] = ctx->lay[l].type == AET_POOL ? reinterpret_cast<uint8_t *>(ctx->ws + ctx->lo.amax[l]) : nullptr;
     ctx->sc.labels = reinterpret_cast<int32_t *>(ctx->ws + ctx->lo.labels);
-    ctx->sc.wgrad = reinterpret_cast<float *>(ctx->ws + ctx->lo.wgrad);
+    for (int l = 0; l < ctx->L; ++l) ctx->sc.wgrad[l] = reinterpret_cast<float *>(ctx->ws + ctx->lo.wgrad[l]);
+    ctx->sc.wgrad_apart = ctx->lo.wgrad_apart;
     ctx->sc.plain = g_plain_layers != 0;
 
     hipError_t e = hipSuccess;

@@ -50,7 +50,8 @@ struct LayerScratch {
     float *del[17];     // d loss / d act[l] (l >= 1)
     uint8_t *amax[16];  // pool layers: which of the 4 window elements was the maximum
     int32_t *labels;    // [n_clients][batch]
-    float *wgrad;       // partial sums of the convolution weight gradients
+    float *wgrad[16];   // convolutions: partial sums of the weight gradient
+    bool wgrad_apart;   // ... each layer's in a place of its own (else all in the same)
     bool plain;         // use the plain (non matrix-core) layer kernels
 };
 
@@ -111,13 +112,20 @@ hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp
 bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool);
 bool conv_wgrad_mfma_supported(const LayerGeom &L, int B);
 size_t conv_wgrad_partial_floats(const LayerGeom &L, int B, int n_clients);
+// weight updates of convolutions that wait for the recursion's end, when one launch does them all
+struct FinishList {
+    alignas(8) unsigned char bytes[1024] = {};
+    int blocks = 0;
+};
+hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                                    const FinishList &later);
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial);
+                                  float *partial, FinishList *later);
 // backward-data and backward-weight of a layer in one launch where both are small
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                                 const LayerGeom &L, const float *dout, float *din, const float *mask_src,
-                                const float *in, float *partial, bool *taken);
+                                const float *in, float *partial, FinishList *later, bool *taken);
 // dense layers on the matrix cores (kernels_dense_mfma.hip); mode 0 fwd, 1 bwd-data, 2 bwd-weight
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,
                              int u, int B, int K, int O, int64_t w_off, int64_t b_off, int relu,

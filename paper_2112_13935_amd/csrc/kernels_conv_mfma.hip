@@ -857,25 +857,40 @@ k_conv_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, ConvDir d, int
     }
 }
 
-// g = (sum of the partials) / B;  w <- w - eta g;  U <- U + g.  A workgroup owns 256 / SG runs of
-// four entries; its SG thread groups each sum a contiguous part of the slices in order (eight
-// 16-byte loads in flight), the group sums are added in group order in LDS.  What bounds it is
-// the chain of loads down the slices (a launch of few clients has up to 256 of them): with one
-// thread per entry walking all of them a finish took 8.5 us in the middle and 15.5 us at most on
-// 6 clients x 16 channels, longer than the products themselves.  45 recursions of it: 7.10 -> 6.57 ms.
-template <int SG>
+// g = (sum of the partials) / B;  w <- w - eta g;  U <- U + g, for up to kFinishLayers layers in one
+// launch.  A workgroup owns 256 / SG runs of four entries of one layer; its SG thread groups each
+// sum a contiguous part of the slices in order (eight 16-byte loads in flight), the group sums are
+// added in group order in LDS.  What bounds it is the chain of loads down the slices (a launch of
+// few clients has up to 256 of them): with one thread per entry walking all of them a finish took
+// 8.5 us in the middle and 15.5 us at most on 6 clients x 16 channels, longer than the products
+// themselves.  45 recursions of it: 7.10 -> 6.57 ms.
+constexpr int kFinishLayers = 8;
+struct FinishLayer {
+    const float *partial;
+    int64_t w_off, b_off;
+    int KTOT, KP, OC, ICK;      // columns, padded columns, channels, filter entries per channel (IC k k)
+    int64_t stride;             // floats per slice
+    int S, lgsg;                // slices; log2 of the thread groups
+    int block0;                 // first workgroup of the layer
+};
+struct FinishPack {
+    FinishLayer l[kFinishLayers];
+    int n;
+};
+
 __global__ void __launch_bounds__(256)
-k_conv_wgrad_finish(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g, int KSQ,
-                    const float *__restrict__ partial) {
+k_conv_wgrad_finish(const RoundParams *__restrict__ rp, int u, int B, FinishPack pack) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
-    constexpr int COLS = 256 / SG;
-    const int tid = threadIdx.x, col = tid % COLS, grp = tid / COLS;
-    const int KP = 16 * g.NTT, OCP = 16 * g.MTT;
-    const int e = 4 * (blockIdx.x * COLS + col);   // first of the four entries, [co][k]
-    const int co = e / KP, k = e - co * KP;
-    const bool act = co < g.OC;
-    const int64_t wrow = g.w_off + (int64_t)co * g.IC * KSQ;
+    int li = 0;
+    while (li + 1 < pack.n && (int)blockIdx.x >= pack.l[li + 1].block0) ++li;
+    const FinishLayer f = pack.l[li];
+    const int lgc = 8 - f.lgsg, COLS = 1 << lgc;
+    const int tid = threadIdx.x, col = tid & (COLS - 1), grp = tid >> lgc;
+    const int e = 4 * ((((int)blockIdx.x - f.block0) << lgc) + col);   // first of the four entries, [co][k]
+    const int co = e / f.KP, k = e - co * f.KP;
+    const bool act = co < f.OC;
+    const int64_t wrow = f.w_off + (int64_t)co * f.ICK;
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
     // the four entries' places; the last column of a row is the bias, beyond it there is padding
     int64_t wi[4];
@@ -883,32 +898,30 @@ k_conv_wgrad_finish(const RoundParams *__restrict__ rp, int u, int B, WgradGeom 
     float wv[4], uv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        ok[i] = act && grp == 0 && k + i < g.KTOT;
-        wi[i] = k + i < g.KTOT - 1 ? wrow + k + i : g.b_off + co;
+        ok[i] = act && grp == 0 && k + i < f.KTOT;
+        wi[i] = k + i < f.KTOT - 1 ? wrow + k + i : f.b_off + co;
         wv[i] = ok[i] ? Wc[wi[i]] : 0.f;
         uv[i] = ok[i] ? Uc[wi[i]] : 0.f;
     }
     typedef const f4 __attribute__((address_space(1))) *gv4;
-    const int64_t stride = (int64_t)OCP * KP;
-    const gcf_ptr pg = as_global(partial) + (int64_t)blockIdx.z * g.S * stride + (act ? e : 0);
-    const int per = (g.S + SG - 1) / SG;
-    const int s0 = grp * per, s1 = min(s0 + per, g.S);
+    const gcf_ptr pg = as_global(f.partial) + (int64_t)blockIdx.z * f.S * f.stride + (act ? e : 0);
+    const int per = (f.S + (1 << f.lgsg) - 1) >> f.lgsg;
+    const int s0 = grp * per, s1 = min(s0 + per, f.S);
     f4 sum = {0.f, 0.f, 0.f, 0.f};
     for (int sl = s0; sl < s1; sl += 8) {
         f4 v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<gv4>(pg + (int64_t)(sl + i < s1 ? sl + i : sl) * stride);
+        for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<gv4>(pg + (int64_t)(sl + i < s1 ? sl + i : sl) * f.stride);
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (sl + i < s1) sum += v[i];
     }
-    if constexpr (SG > 1) {
-        __shared__ f4 red[SG][COLS];
-        red[grp][col] = sum;
+    __shared__ f4 red[256];
+    if (f.lgsg > 0) {
+        red[tid] = sum;
         __syncthreads();
         if (grp != 0) return;
-#pragma unroll
-        for (int i = 1; i < SG; ++i) sum += red[i][col];
+        for (int i = 1; i < 1 << f.lgsg; ++i) sum += red[(i << lgc) + col];
     }
     const float invB = 1.0f / (float)B;
 #pragma unroll
@@ -1058,15 +1071,46 @@ static void wgrad_slices(const LayerGeom &L, int B, int nact, int cap, WgradGeom
     g->S = (units + g->U - 1) / g->U;  // the fewest slices with the same longest share
 }
 
+// Finish of one layer: put on the list when that is wanted and the layer's partial sums are small
+// (they stay in the caches until the recursion's end; a layer of a full launch is finished at
+// once, while its sums are still there), else launched now.
+constexpr int64_t kFinishLaterBytes = 24 << 20;
 static hipError_t wgrad_finish(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L,
-                               const WgradGeom &g, const float *partial) {
-    // thread groups per workgroup: a chain of at most about twelve slices each
-    const int sg = g.S <= 8 ? 1 : g.S <= 48 ? 4 : 16;
-    const int runs = g.OC * 4 * g.NTT;   // of four entries
-    dim3 fgrid((unsigned)((runs + 256 / sg - 1) / (256 / sg)), 1, (unsigned)nact);
-    if (sg == 1) k_conv_wgrad_finish<1><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
-    else if (sg == 4) k_conv_wgrad_finish<4><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
-    else k_conv_wgrad_finish<16><<<fgrid, 256, 0, s>>>(dp, u, B, g, L.k * L.k, partial);
+                               const WgradGeom &g, const float *partial, FinishList *later) {
+    FinishLayer f;
+    f.partial = partial;
+    f.w_off = g.w_off; f.b_off = g.b_off;
+    f.KTOT = g.KTOT; f.KP = 16 * g.NTT; f.OC = g.OC; f.ICK = g.IC * L.k * L.k;
+    f.stride = (int64_t)16 * g.MTT * f.KP;
+    f.S = g.S;
+    f.lgsg = g.S <= 8 ? 0 : g.S <= 48 ? 2 : 4;   // thread groups: a chain of at most about twelve slices each
+    const int runs = g.OC * 4 * g.NTT;           // of four entries
+    const int blocks = (runs + (256 >> f.lgsg) - 1) / (256 >> f.lgsg);
+    FinishPack one;
+    FinishPack &pack = later ? *reinterpret_cast<FinishPack *>(later->bytes) : one;
+    if (later && pack.n < kFinishLayers && 4 * f.stride * g.S * nact <= kFinishLaterBytes) {
+        f.block0 = later->blocks;
+        pack.l[pack.n++] = f;
+        later->blocks += blocks;
+        return hipSuccess;
+    }
+    f.block0 = 0;
+    one.l[0] = f;
+    one.n = 1;
+    k_conv_wgrad_finish<<<dim3((unsigned)blocks, 1, (unsigned)nact), 256, 0, s>>>(dp, u, B, one);
+    return hipGetLastError();
+}
+
+static_assert(sizeof(FinishPack) <= sizeof(FinishList::bytes), "FinishList holds a FinishPack");
+
+hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                                    const FinishList &later) {
+    if (later.blocks == 0) return hipSuccess;
+    const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
+    if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
+    k_conv_wgrad_finish<<<dim3((unsigned)later.blocks, 1, (unsigned)nact), 256, 0, s>>>(
+        dp, u, B, *reinterpret_cast<const FinishPack *>(later.bytes));
+    if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
     return hipGetLastError();
 }
 
@@ -1077,7 +1121,7 @@ static hipError_t wgrad_finish(hipStream_t s, const RoundParams *dp, int nact, i
 // channels on both sides (the instantiations that exist).
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                                 const LayerGeom &L, const float *dout, float *din, const float *mask_src,
-                                const float *in, float *partial, bool *taken) {
+                                const float *in, float *partial, FinishList *later, bool *taken) {
     *taken = false;
     ConvDir d;
     WgradGeom w;
@@ -1105,14 +1149,14 @@ hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams
     if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
     kernel<<<(unsigned)(nd + w.S * nact), 256, lds, s>>>(dp, u, B, d, nd, dx, w, dout, din, mask_src, in, partial);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, w, partial);
+    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, w, partial, later);
     if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
     return e;
 }
 
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial) {
+                                  float *partial, FinishList *later) {
     WgradGeom g;
     if (!wgrad_geom(L, B, nact, &g)) return hipErrorInvalidValue;
     const size_t lds = wgrad_lds_bytes(g);
@@ -1128,7 +1172,7 @@ hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundPara
     if (L.k == 3) wgrad_dispatch<3>(1, s, grid, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial);
     else wgrad_dispatch<5>(1, s, grid, lds, mt, ntw, wm, dp, u, B, g, in, dout, partial);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, g, partial);
+    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, g, partial, later);
     if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
     return e;
 }

@@ -636,13 +636,13 @@ static hipError_t launch_conv_wgrad_direct(hipStream_t s, Profiler *prof, const 
 
 static hipError_t conv_dispatch(int ks, hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                 int B, const LayerGeom &g, int which, const float *a,
-                                const float *b, float *c, const float *mask, bool mfma) {
+                                const float *b, float *c, const float *mask, bool mfma, FinishList *later = nullptr) {
     if (which < 2 && mfma && conv_mfma_supported(g, which == 1))
         return launch_conv_mfma(s, prof, dp, nact, u, B, g, which == 1, a, c, mask);
     if (which == 2 && mfma && conv_wgrad_direct_ok(g))
         return launch_conv_wgrad_direct(s, prof, dp, nact, u, B, g, a, b);
     if (which == 2 && mfma && c && conv_wgrad_mfma_supported(g, B))
-        return launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, a, b, c);
+        return launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, a, b, c, later);
     switch (ks) {
         case 1: return conv_step<1>(s, prof, dp, nact, u, B, g, which, a, b, c, mask);
         case 2: return conv_step<2>(s, prof, dp, nact, u, B, g, which, a, b, c, mask);
@@ -697,6 +697,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         AET_TIMED(F_SOFTMAX_CE, k_softmax_ce<<<nact, 256, 0, s>>>(dp, u, B, lay[L - 1].oc, sc.act[L], sc.labels, sc.del[L]));
         AET_RETURN_IF(hipGetLastError());
     }
+    FinishList list, *later = sc.wgrad_apart ? &list : nullptr;
     for (int l = LF - 1; l >= 0; --l) {
         const LayerGeom &g = lay[l];
         // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
@@ -704,13 +705,13 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         if (g.type == 0) {
             bool taken = false;
             if (l > 0 && !sc.plain && !conv_wgrad_direct_ok(g))
-                AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad, &taken));
+                AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad[l], later, &taken));
             if (taken) continue;
             if (l > 0)
                 AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 1, sc.del[l + 1], nullptr,
                                             sc.del[l], mask, !sc.plain));
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 2, sc.act[l], sc.del[l + 1],
-                                        sc.wgrad, nullptr, !sc.plain));
+                                        sc.wgrad[l], nullptr, !sc.plain, later));
         } else if (g.type == 1) {
             if (l > 0) {
                 // the ReLU below, at the winners: their value is the pooled one
@@ -743,7 +744,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
             AET_RETURN_IF(hipGetLastError());
         }
     }
-    return hipSuccess;
+    return launch_conv_wgrad_finish(s, prof, dp, nact, u, B, list);
 }
 
 __global__ void k_debug_indices(uint64_t key, int64_t q0, int count, uint32_t n_samples,

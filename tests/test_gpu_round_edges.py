@@ -122,3 +122,30 @@ def test_cnn_last_layer_and_rows(gpu, oracle_libs, n, hw, width, fc, batch):
 ])
 def test_conv_backward_in_one_launch(gpu, oracle_libs, n, hw, width, batch):
     _lockstep(gpu, W.config4(n_clients=n, n_per=50, hw=hw, width=width, fc=20, batch=batch, rounds=2, a=0, b=batch))
+
+
+@pytest.mark.parametrize("make", [
+    lambda: W.config4(n_clients=3, n_per=40, hw=8, width=8, fc=32, batch=4, rounds=3, a=4, b=8),
+    lambda: W.config2(n_clients=3, n_total=150, d=50, hidden=24, batch=4, rounds=3, a=4, b=8),
+    lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=20, rounds=2, a=20, b=20),
+], ids=["cnn", "mlp", "lenet"])
+def test_smallest_workspace(gpu, oracle_libs, monkeypatch, make):
+    """A workspace that holds the layer engine's needs and nothing more is still accepted: the
+    exchange records of the padded rounds and the partial sums of every layer apart are taken
+    only where there is room."""
+    import re
+    from paper_2112_13935_amd.binding import AetError
+    run = gpu(make())
+    full, lib = run.lib.workspace_bytes, run.lib.lib
+    run.close()
+    size = [256]
+    monkeypatch.setattr(lib, "aet_workspace_bytes", lambda *a: size[0])
+    with pytest.raises(AetError) as err:
+        gpu(make())
+    need = int(re.search(r"(\d+) needed", str(err.value)).group(1))
+    assert need < full
+    size[0] = need - 256
+    with pytest.raises(AetError):
+        gpu(make())
+    size[0] = need
+    _lockstep(gpu, make())
