@@ -282,15 +282,15 @@ k_dense_wgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, in
 //   din^T[k][b] = sum_o W[o][k] dout[b][o],             M = k, N = b, contraction over o,
 // so that W is staged as it lies in memory (rows of consecutive k) and a lane ends up with
 // four consecutive k of one sample: float4 stores (and float4 loads of the ReLU mask).
-// A workgroup owns 64 k x 16*NBT samples; wave w owns the k tile 16w.. and all sample tiles.
+// A workgroup owns 64 k x 64 samples; wave w owns the k tile 16w.. and all sample tiles.  (Layers
+// with mini-batches of up to 64 run k_dense_bwd.)
 // dout is staged transposed ([o][b], odd row stride); chunks of 32 output units.
-template <int NBT>
 __global__ void __launch_bounds__(256)
 k_dense_dgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, int64_t w_off,
               const float *__restrict__ y, float *__restrict__ z, const float *__restrict__ mask_src) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
-    constexpr int BS = NBT == 4 ? 81 : 49;   // row stride of the transposed dout tile
+    constexpr int NBT = 4, BS = 81;   // sample tiles; row stride of the transposed dout tile
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int kbase = blockIdx.x * kDT, bbase = blockIdx.y * 16 * NBT;
     const int64_t cb = (int64_t)blockIdx.z * B;
@@ -361,6 +361,192 @@ k_dense_dgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, in
             }
         }
     }
+}
+
+// Both backward products of a hidden dense layer in one launch (mini-batches up to 64): a workgroup
+// owns 64 inputs k of one client for all outputs and samples; wave w owns the k tile 16 w.. .
+//   d(input)^T[k][b] = sum_o W[o][k] dout[b][o]     M = k, N = b, contraction over o, accumulated
+//                                                   over the chunks of 32 outputs
+//   g^T[k][o]        = sum_b in[b][k] dout[b][o]    M = k, N = o, contraction over b, per chunk;
+//                                                   then w <- w - eta g,  U <- U + g
+// W is read once (it was read by both), dout once per 64 inputs, the inputs once; a lane ends up
+// with four consecutive k of one output, so W and U move as float4 (VEC: rows 16-byte aligned).
+// The next chunk is fetched into registers while a chunk's products run.  Bound by the traffic of
+// W and U (read and written) where the layer is large, by its trips through memory where it
+// is small: 6 clients, 512 -> 64, mini-batch 16: 9.2 -> 6.3 us against the two kernels it takes the
+// place of (and a launch boundary less); 11 clients, 4,096 -> 256, mini-batch 64: 81 -> 77 us.
+template <int NBT, bool VEC>
+__global__ void __launch_bounds__(256)
+k_dense_bwd(const RoundParams *__restrict__ rp, int u, int B, int K, int O, int64_t w_off, int64_t b_off,
+            const float *__restrict__ in, const float *__restrict__ dout, float *__restrict__ din, int masked) {
+    const RoundParams p = rp[blockIdx.z];
+    if (u >= p.m) return;
+    constexpr int B16 = 16 * NBT, DS = 36;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int kbase = blockIdx.x * kDT;
+    const int64_t cb = (int64_t)blockIdx.z * B;
+    const gcf_ptr xin = as_global(in) + cb * K, yd = as_global(dout) + cb * O;
+    const gf_ptr Wc = as_global(p.W) + w_off, Uc = as_global(p.U) + w_off;
+    typedef const f4 __attribute__((address_space(1))) *gv4;
+    typedef f4 __attribute__((address_space(1))) *gw4;
+
+    __shared__ __attribute__((aligned(16))) float Is[B16 * kWS];    // in[b][k]
+    __shared__ __attribute__((aligned(16))) float Ws[kDK * kWS];    // W[o][k] of the chunk
+    __shared__ float Ds[B16 * DS];                                  // dout[b][o] of the chunk
+
+    // four consecutive k of a row, zeros outside
+    auto piece = [&](gcf_ptr row, bool rok, int k) -> f4 {
+        f4 v;
+        if (VEC) {
+            const bool ok = rok && k < K;
+            v = *reinterpret_cast<gv4>(row + (ok ? k : 0));
+            if (!ok) v = f4{0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool ok = rok && k + r < K;
+                v[r] = row[ok ? k + r : 0];
+                if (!ok) v[r] = 0.f;
+            }
+        }
+        return v;
+    };
+    const int srow = tid >> 4, sc4 = 4 * (tid & 15), sk = kbase + sc4;   // rows srow + 16 i, 4 columns from sc4
+    const int oo = tid & 31, brow = tid >> 5;                            // dout: output oo of the chunk, samples brow + 8 i
+    f4 wn[2];
+    float dn[2 * NBT];
+    auto fetch = [&](int o0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int o = o0 + srow + 16 * i;
+            wn[i] = piece(Wc + (int64_t)(o < O ? o : 0) * K, o < O, sk);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * NBT; ++i) {
+            const int b = brow + 8 * i;
+            const bool ok = o0 + oo < O && b < B;
+            dn[i] = yd[ok ? (int64_t)b * O + o0 + oo : 0];
+            if (!ok) dn[i] = 0.f;
+        }
+    };
+    {
+        f4 v[NBT];
+#pragma unroll
+        for (int i = 0; i < NBT; ++i) {
+            const int b = srow + 16 * i;
+            v[i] = piece(xin + (int64_t)(b < B ? b : 0) * K, b < B, sk);
+        }
+        fetch(0);
+#pragma unroll
+        for (int i = 0; i < NBT; ++i) *reinterpret_cast<f4 *>(&Is[(srow + 16 * i) * kWS + sc4]) = v[i];
+    }
+    f4 acc[NBT];
+#pragma unroll
+    for (int n = 0; n < NBT; ++n) acc[n] = f4{0.f, 0.f, 0.f, 0.f};
+    const float invB = 1.0f / (float)B;
+    const int kl = 16 * wave + 4 * lg, k = kbase + kl;   // the lane's four inputs
+
+    for (int o0 = 0; o0 < O; o0 += kDK) {
+        __syncthreads();   // the products of the previous chunk are done with the tiles
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *reinterpret_cast<f4 *>(&Ws[(srow + 16 * i) * kWS + sc4]) = wn[i];
+#pragma unroll
+        for (int i = 0; i < 2 * NBT; ++i) Ds[(brow + 8 * i) * DS + oo] = dn[i];
+        __syncthreads();
+        // U of this chunk (lane: outputs o0 + 16 t + li) and the next chunk
+        f4 uv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int o = o0 + 16 * t + li;
+            uv[t] = piece(Uc + (int64_t)(o < O ? o : 0) * K, o < O, k);
+        }
+        if (o0 + kDK < O) fetch(o0 + kDK);
+#pragma unroll
+        for (int s = 0; s < kDK / 4; ++s) {
+            const float a = Ws[(4 * s + lg) * kWS + 16 * wave + li];
+#pragma unroll
+            for (int n = 0; n < NBT; ++n)
+                acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ds[(16 * n + li) * DS + 4 * s + lg], acc[n], 0, 0, 0);
+        }
+        f4 g[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < 4 * NBT; ++s) {
+            const float a = Is[(4 * s + lg) * kWS + 16 * wave + li];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                g[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Ds[(4 * s + lg) * DS + 16 * t + li], g[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int o = o0 + 16 * t + li;
+            if (o >= O || k >= K) continue;
+            const f4 gv = g[t] * invB;
+            const f4 wv = *reinterpret_cast<const f4 *>(&Ws[(16 * t + li) * kWS + kl]);
+            const int64_t wi = (int64_t)o * K + k;
+            const f4 w1 = wv - p.eta * gv, u1 = uv[t] + gv;
+            if (VEC) {
+                *reinterpret_cast<gw4>(Wc + wi) = w1;
+                *reinterpret_cast<gw4>(Uc + wi) = u1;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (k + r < K) {
+                        Wc[wi + r] = w1[r];
+                        Uc[wi + r] = u1[r];
+                    }
+            }
+        }
+        if (blockIdx.x == 0 && wave == 0) {   // bias: column sums of dout, two lanes per output
+            float s = 0.f;
+#pragma unroll
+            for (int b = 0; b < B16; b += 2) s += Ds[(b + (lane >> 5)) * DS + (lane & 31)];
+            s = (s + __shfl_xor(s, 32, 64)) * invB;
+            const int o = o0 + lane;
+            if (lane < kDK && o < O) {
+                as_global(p.W)[b_off + o] -= p.eta * s;
+                as_global(p.U)[b_off + o] += s;
+            }
+        }
+    }
+    if (k < K) {
+        const gf_ptr dg = as_global(din) + cb * K + k;
+#pragma unroll
+        for (int n = 0; n < NBT; ++n) {
+            const int b = 16 * n + li;
+            if (b >= B) continue;
+            f4 v = acc[n];
+            if (masked) {
+                const f4 a = *reinterpret_cast<const f4 *>(&Is[b * kWS + kl]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (!(a[r] > 0.f)) v[r] = 0.f;
+            }
+            if (VEC) {
+                *reinterpret_cast<gw4>(dg + (int64_t)b * K) = v;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (k + r < K) dg[(int64_t)b * K + r] = v[r];
+            }
+        }
+    }
+}
+
+bool dense_bwd_supported(int B) { return B <= 64; }
+
+hipError_t launch_dense_bwd(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                            const LayerGeom &L, const float *in, const float *dout, float *din, bool masked) {
+    const int K = (int)L.in_size, O = L.oc;
+    const bool vec = (K & 3) == 0 && (L.w_off & 3) == 0;
+    dim3 grid((unsigned)((K + kDT - 1) / kDT), 1, (unsigned)nact);
+    const bool timed = prof && prof->on[F_DENSE_BWD_WEIGHT];
+    if (timed) prof->before(F_DENSE_BWD_WEIGHT, s);
+    auto kernel = B <= 16 ? (vec ? k_dense_bwd<1, true> : k_dense_bwd<1, false>)
+                : B <= 32 ? (vec ? k_dense_bwd<2, true> : k_dense_bwd<2, false>)
+                          : (vec ? k_dense_bwd<4, true> : k_dense_bwd<4, false>);
+    kernel<<<grid, 256, 0, s>>>(dp, u, B, K, O, L.w_off, L.b_off, in, dout, din, masked ? 1 : 0);
+    if (timed) prof->after(F_DENSE_BWD_WEIGHT, s);
+    return hipGetLastError();
 }
 
 // Forward pass of a layer with few output tiles (small mini-batch, moderate width): one
@@ -702,11 +888,8 @@ hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const Roun
     } else if (mode == DENSE_FWD)
         k_dense_mfma<DENSE_FWD, 4><<<grid, 256, 0, s>>>(dp, u, B, K, O, w_off, b_off, relu, x, y, z, mask_src);
     else if (mode == DENSE_BWD_DATA && (K & 3) == 0 && (w_off & 3) == 0) {
-        const int nbt = B <= 16 ? 1 : B <= 32 ? 2 : 4;
-        dim3 dgrid((unsigned)((K + kDT - 1) / kDT), (unsigned)((B + 16 * nbt - 1) / (16 * nbt)), (unsigned)nact);
-        if (nbt == 1) k_dense_dgrad<1><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
-        else if (nbt == 2) k_dense_dgrad<2><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
-        else k_dense_dgrad<4><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
+        dim3 dgrid((unsigned)((K + kDT - 1) / kDT), (unsigned)((B + 63) / 64), (unsigned)nact);
+        k_dense_dgrad<<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
     } else if (mode == DENSE_BWD_DATA)
         k_dense_mfma<DENSE_BWD_DATA, 4><<<grid, 256, 0, s>>>(dp, u, B, K, O, w_off, b_off, relu, x, y, z, mask_src);
     else if ((K & 3) == 0 && (w_off & 3) == 0) {

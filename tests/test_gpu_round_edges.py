@@ -149,3 +149,17 @@ def test_smallest_workspace(gpu, oracle_libs, monkeypatch, make):
         gpu(make())
     size[0] = need
     _lockstep(gpu, make())
+
+
+@pytest.mark.parametrize("n,d,hidden,batch", [
+    (2, 900, 70, 1),      # one sample, two outputs more than two chunks of 32 in the hidden layer
+    (3, 897, 66, 33),     # rows that are not 16-byte aligned, one sample beyond 32
+    (2, 1000, 300, 64),   # several input blocks, the last ragged; all four sample tiles
+    (2, 900, 40, 65),     # one sample too many for both products in one launch
+])
+def test_hidden_dense_backward(gpu, oracle_libs, n, d, hidden, batch):
+    """Two hidden dense layers (the fused rounds take one), so that one of them has both products."""
+    wl = W.config2(n_clients=n, n_total=n * 90, d=d, hidden=hidden, batch=batch, rounds=2, a=0, b=batch)
+    wl.model.layers.insert(1, W.Layer(W.DENSE, hidden + 3, relu=1))
+    wl.w0 = W.init_weights(wl.model, 5)
+    _lockstep(gpu, wl)
