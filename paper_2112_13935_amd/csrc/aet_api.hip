@@ -148,6 +148,7 @@ constexpr int kPaddedClients = 256;
 // padded_ok: the caller has room for the records of a padded form (or of mini-batch softmax)
 Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = true) {
     if (g_force_layer_engine) return ENGINE_LAYERS;
+    padded_ok = padded_ok && !g_plain_layers;   // the plain layer kernels are asked for
     const bool padded = padded_ok && n <= kPaddedClients;
     if (L == 2 && lay[0].type == AET_DENSE && lay[1].type == AET_DENSE && lay[0].relu &&
         mlp_round_supported((int)lay[0].in_size, lay[0].oc, lay[1].oc, B) &&
