@@ -284,7 +284,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
 #pragma unroll
                     for (int q = 0; q < Q; ++q) G[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[q][r], x[b + r][j], G[q], 0, 0, 0);
             }
-            load_col(j);
+            if (u + 1 < p.m) load_col(j);
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
 #pragma unroll
