@@ -53,6 +53,14 @@ struct ArrivalsPut { Arrival a[kPutArrivals]; };
 __global__ void k_put_arrivals(const ArrivalsPut pack, int count, Arrival *__restrict__ dst) {
     if ((int)threadIdx.x < count) dst[threadIdx.x] = pack.a[threadIdx.x];
 }
+// Records in a pinned ring that many workgroups read: this brings them into device memory once.  A
+// kernel and not hipMemcpyAsync: the copy operation and the event behind it each put a barrier
+// into the stream, some 5.5 us of idle GPU apiece, between kernels that otherwise follow each
+// other without a gap.
+__global__ void k_fetch_words(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
 __global__ void k_clear_bytes16(uint4 *__restrict__ p, size_t n16) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n16) p[i] = uint4{0u, 0u, 0u, 0u};
@@ -60,7 +68,12 @@ __global__ void k_clear_bytes16(uint4 *__restrict__ p, size_t n16) {
 
 namespace {
 
-constexpr int kRing = 4;            // pinned staging buffers in flight
+// Pinned staging: a ring of up to kRingSlots slots (as many as kRingBytes hold, at least 4), one per
+// tick.  The ring has two halves with an event each, recorded after the last kernel that reads
+// the half and waited for before its first slot is written again: an event costs the stream a
+// gap of 5.5 us, so it is not recorded on every tick.
+constexpr int kRingSlots = 32;
+constexpr size_t kRingBytes = 1 << 20;
 constexpr int kDebugIdx = 65536;    // capacity of the debug index buffer
 constexpr uint64_t kTagSample = 0;  // stream purposes of the counter hash
 constexpr uint64_t kTagNet = 1;
@@ -223,10 +236,38 @@ struct aet_ctx {
     std::vector<Msg> queue;
     std::vector<int> free_slots;
     int64_t tick = 0;
-    RoundParams *h_params[kRing] = {};
-    Arrival *h_arr[kRing] = {};
-    hipEvent_t ev_params[kRing] = {}, ev_arr[kRing] = {};
-    int ring_p = 0, ring_a = 0;
+    struct Ring {
+        char *mem = nullptr;
+        size_t slot_bytes = 0;
+        int half = 0, next = 0;      // slots per half, next slot
+        hipEvent_t ev[2] = {};
+        hipError_t create(size_t bytes) {
+            slot_bytes = bytes;
+            size_t slots = kRingBytes / bytes;
+            slots = slots < 4 ? 4 : slots > kRingSlots ? kRingSlots : slots;
+            half = (int)(slots / 2);
+            hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&mem), 2 * half * bytes, hipHostMallocDefault);
+            for (int h = 0; h < 2 && e == hipSuccess; ++h) e = hipEventCreateWithFlags(&ev[h], hipEventDisableTiming);
+            return e;
+        }
+        // the next slot, free to write (an event that was never recorded counts as complete)
+        hipError_t acquire(void **slot) {
+            *slot = mem + (size_t)next * slot_bytes;
+            return next % half == 0 ? hipEventSynchronize(ev[next / half]) : hipSuccess;
+        }
+        // the kernels that read the acquired slot are in the stream
+        hipError_t release(hipStream_t s) {
+            const int slot = next;
+            next = (slot + 1) % (2 * half);
+            return slot % half == half - 1 ? hipEventRecord(ev[slot / half], s) : hipSuccess;
+        }
+        void destroy() {
+            if (mem) (void)hipHostFree(mem);
+            for (int h = 0; h < 2; ++h)
+                if (ev[h]) (void)hipEventDestroy(ev[h]);
+        }
+    };
+    Ring ring_p, ring_a;     // round records, arrival lists
     // a context on the library's own workspace has no pinned rings: its records reach the
     // device through kernel arguments, staged in these host vectors
     bool static_ws = false;
@@ -424,15 +465,13 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         const size_t n16 = (ctx->lo.total + 15) / 16;
         k_clear_bytes16<<<(unsigned)((n16 + 255) / 256), 256, 0, ctx->stream>>>(reinterpret_cast<uint4 *>(ctx->ws), n16);
         e = hipGetLastError();
-        ctx->v_params.resize(n_clients);
         ctx->v_arr.resize((size_t)n_clients * max_inflight);
     }
-    for (int r = 0; r < kRing && e == hipSuccess && !static_ws; ++r) {
-        e = hipHostMalloc(reinterpret_cast<void **>(&ctx->h_params[r]), (size_t)n_clients * sizeof(RoundParams), hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&ctx->h_arr[r]), (size_t)n_clients * max_inflight * sizeof(Arrival), hipHostMallocDefault);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_params[r], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_arr[r], hipEventDisableTiming);
+    if (e == hipSuccess && !static_ws) {
+        e = ctx->ring_p.create((size_t)n_clients * sizeof(RoundParams));
+        if (e == hipSuccess) e = ctx->ring_a.create((size_t)n_clients * max_inflight * sizeof(Arrival));
     }
+    ctx->v_params.resize(n_clients);
     if (e == hipSuccess && ctx->engine == ENGINE_MLP)
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_LENET)
@@ -529,17 +568,15 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
         return fail(ctx, AET_ENOMEM, "no free U slot: more than max_inflight messages of a client in flight");
 
     if (nact > 0) {
-        // staging: the layer engine copies the records to the device from a pinned ring; the
+        // staging: for the layer engine one small kernel brings the records from a pinned ring to the device; the
         // dense-ReLU-dense engine takes them in its kernel arguments from plain host memory; the
         // other fused engines read them where they are, in the pinned ring (every workgroup
         // reads its own record once, at its start: no copy in the stream ahead of the kernel)
         const bool direct = !ctx->static_ws && (ctx->engine == ENGINE_SOFTMAX || ctx->engine == ENGINE_LENET || ctx->engine == ENGINE_SOFTMAX_BATCH);
-        const int ring = ctx->ring_p;
-        RoundParams *hp = ctx->static_ws ? ctx->v_params.data() : ctx->h_params[ring];
-        if (ctx->engine != ENGINE_MLP && !ctx->static_ws) {
-            ctx->ring_p = (ring + 1) % kRing;
-            AET_HIP(ctx, hipEventSynchronize(ctx->ev_params[ring]));
-        }
+        const bool ring = ctx->engine != ENGINE_MLP && !ctx->static_ws;
+        void *slot = ctx->v_params.data();
+        if (ring) AET_HIP(ctx, ctx->ring_p.acquire(&slot));
+        RoundParams *hp = static_cast<RoundParams *>(slot);
         std::vector<int> slots(nact);
         for (int a = 0; a < nact; ++a) {
             const int c = act[a];
@@ -566,8 +603,10 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
                     AET_HIP(ctx, hipGetLastError());
                 }
             } else {
-                AET_HIP(ctx, hipMemcpyAsync(dp, hp, (size_t)nact * sizeof(RoundParams), hipMemcpyHostToDevice, ctx->stream));
-                AET_HIP(ctx, hipEventRecord(ctx->ev_params[ring], ctx->stream));
+                static_assert(sizeof(RoundParams) % 8 == 0, "records are copied in 8-byte words");
+                const int words = (int)((size_t)nact * sizeof(RoundParams) / 8);
+                k_fetch_words<<<(words + 255) / 256, 256, 0, ctx->stream>>>(reinterpret_cast<const uint64_t *>(hp), reinterpret_cast<uint64_t *>(dp), words);
+                AET_HIP(ctx, hipGetLastError());
             }
         }
         // server form: every round starts from the global model; peer-to-peer form: from the
@@ -589,7 +628,7 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
             for (int64_t u = 0; u < max_m; ++u)
                 AET_HIP(ctx, launch_layer_step(ctx->stream, ctx->profp(), dp, nact, (int)u, ctx->lay, ctx->L, ctx->B, ctx->sc));
         }
-        if (direct) AET_HIP(ctx, hipEventRecord(ctx->ev_params[ring], ctx->stream));   // the ring slot is free after the kernel
+        if (ring) AET_HIP(ctx, ctx->ring_p.release(ctx->stream));
         for (int a = 0; a < nact; ++a) {
             const int c = act[a];
             Msg msg;
@@ -620,27 +659,24 @@ static aet_status stage_arrivals(aet_ctx *ctx, float scale, std::vector<Msg> *ar
     *pack_out = nullptr;
     *dev_out = nullptr;
     if (na == 0) return AET_OK;
-    Arrival *dst = pack->a;
-    int ring = -1;
-    if (na > kArrivalPack && ctx->static_ws) {
-        ring = kRing;  // no ring: staged in host memory, handed over in kernel arguments
-        dst = ctx->v_arr.data();
-    } else if (na > kArrivalPack) {
-        ring = ctx->ring_a;
-        ctx->ring_a = (ring + 1) % kRing;
-        AET_HIP(ctx, hipEventSynchronize(ctx->ev_arr[ring]));
-        dst = ctx->h_arr[ring];
+    void *slot = pack->a;
+    const bool by_value = na <= kArrivalPack;
+    if (!by_value && ctx->static_ws) {
+        slot = ctx->v_arr.data();   // no ring: staged in host memory, handed over in kernel arguments
+    } else if (!by_value) {
+        AET_HIP(ctx, ctx->ring_a.acquire(&slot));
     }
+    Arrival *dst = static_cast<Arrival *>(slot);
     for (int j = 0; j < na; ++j) {
         dst[j].U = ctx->Uslot(arr[j].slot);
         dst[j].scale = (float)((double)scale * (double)arr[j].eta);
         dst[j].sender = arr[j].c;
     }
-    if (ring < 0) {
+    if (by_value) {
         *pack_out = pack;
     } else {
         Arrival *da = reinterpret_cast<Arrival *>(ctx->ws + ctx->lo.arrivals);
-        if (ring == kRing) {
+        if (ctx->static_ws) {
             for (int a0 = 0; a0 < na; a0 += kPutArrivals) {
                 const int here = std::min(kPutArrivals, na - a0);
                 ArrivalsPut put;
@@ -649,8 +685,11 @@ static aet_status stage_arrivals(aet_ctx *ctx, float scale, std::vector<Msg> *ar
                 AET_HIP(ctx, hipGetLastError());
             }
         } else {
-            AET_HIP(ctx, hipMemcpyAsync(da, dst, (size_t)na * sizeof(Arrival), hipMemcpyHostToDevice, ctx->stream));
-            AET_HIP(ctx, hipEventRecord(ctx->ev_arr[ring], ctx->stream));
+            static_assert(sizeof(Arrival) % 8 == 0, "records are copied in 8-byte words");
+            const int words = (int)((size_t)na * sizeof(Arrival) / 8);
+            k_fetch_words<<<(words + 255) / 256, 256, 0, ctx->stream>>>(reinterpret_cast<const uint64_t *>(dst), reinterpret_cast<uint64_t *>(da), words);
+            AET_HIP(ctx, hipGetLastError());
+            AET_HIP(ctx, ctx->ring_a.release(ctx->stream));
         }
         *dev_out = da;
     }
@@ -912,7 +951,7 @@ aet_status aet_reset(aet_ctx *ctx) {
     if (!ctx) return AET_EINVAL;
     if (ctx->dead) return fail(ctx, AET_ESTATE, "context is unusable after a HIP error");
     // server form: the replicas need no copy, every round starts by adopting the global model
-    AET_HIP(ctx, hipMemcpyAsync(ctx->Wg(), ctx->W0(), (size_t)ctx->P * 4, hipMemcpyDeviceToDevice, ctx->stream));
+    AET_HIP(ctx, launch_broadcast_model(ctx->stream, ctx->Wg(), ctx->Ps, 1, ctx->W0()));
     if (ctx->p2p) AET_HIP(ctx, launch_broadcast_model(ctx->stream, ctx->Wc(0), ctx->Ps, ctx->n, ctx->W0()));
     std::fill(ctx->i_c.begin(), ctx->i_c.end(), 0);
     std::fill(ctx->t_c.begin(), ctx->t_c.end(), 0);
@@ -957,12 +996,8 @@ void aet_destroy(aet_ctx *ctx) {
     if (!ctx) return;
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->static_ws && ctx->device >= 0 && g_scratch_owner[ctx->device] == ctx) g_scratch_owner[ctx->device] = nullptr;
-    for (int r = 0; r < kRing; ++r) {
-        if (ctx->h_params[r]) (void)hipHostFree(ctx->h_params[r]);
-        if (ctx->h_arr[r]) (void)hipHostFree(ctx->h_arr[r]);
-        if (ctx->ev_params[r]) (void)hipEventDestroy(ctx->ev_params[r]);
-        if (ctx->ev_arr[r]) (void)hipEventDestroy(ctx->ev_arr[r]);
-    }
+    ctx->ring_p.destroy();
+    ctx->ring_a.destroy();
     delete ctx;
 }
 
