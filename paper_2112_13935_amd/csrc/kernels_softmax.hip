@@ -8,7 +8,8 @@
 //
 //   z_o = b_o + sum_k W[o][k] x[k]   per-thread partial sums, lane swaps and DPP inside a wave,
 //                                    one LDS hop across the 8 waves (fixed order)
-//   p = softmax(z), dz = p - onehot  every lane handles three classes, its quad all of them
+//   p = softmax(z), dz = p - onehot  lane o of every 16-lane row handles class o (DPP row
+//                                    reductions); the matrix cores take dz from there
 //   W[o][k] -= eta dz_o x[k];  U[o][k] += dz_o x[k]      in registers, as 4 x 4 outer products
 //                                    on the matrix cores (g never stored)
 //
@@ -59,15 +60,19 @@ __device__ __forceinline__ void wave_sum_rows(const float (&v)[N], float (&out)[
     for (int k = 0; k < NQ; ++k) out[k] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, out[k]), 0x140, 0xF, 0xF, true));
 }
 
-// sum / max over each quad (every lane of it gets the result)
-__device__ __forceinline__ float quad_sum_dpp(float v) {
+// sum / max over each row of 16 lanes (every lane of the row gets the result)
+__device__ __forceinline__ float row_sum_dpp(float v) {
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
     return v;
 }
-__device__ __forceinline__ float quad_max_dpp(float v) {
+__device__ __forceinline__ float row_max_dpp(float v) {
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true)));
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true)));
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)));
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)));
     return v;
 }
 
@@ -77,7 +82,8 @@ __device__ __forceinline__ float quad_max_dpp(float v) {
 // D[b] += A[b] B[b]^T: lane l supplies A[b = l/4][i = l%4] and B[b][n = l%4] and receives, in
 // its four result registers, the products of the four A entries of its block with ITS OWN B
 // entry.  With B = the lane's own column of the sampled row and A = four entries of
-// (-eta) dz (the same four in every block), one instruction updates four class rows of the
+// (-eta) dz (the same four in every block: the instruction's block broadcast takes them from
+// four neighbouring lanes, so dz needs no lane exchange), one instruction updates four class rows of the
 // lane's own column: the replica keeps the ownership it has in the vector-ALU form (thread t
 // owns columns t, t+512, ... of every class row), so the logits still need no other lane's
 // data, and three instructions per 64 columns cover classes 0..11 (rows 10 and 11 stay
@@ -87,19 +93,24 @@ __device__ __forceinline__ float quad_max_dpp(float v) {
 // matrix instructions each per recursion at D = 3072), with few clients the chain dots - wave
 // reduction - LDS hop - softmax - update, the same for every width.  So what need not be on that
 // chain is off it: U of a recursion is added while the next one's partial logits travel through
-// LDS; a lane softmaxes just the three classes whose dz it hands to the matrix core (no lane
-// exchange after it); row numbers are hashed 48 recursions at a time; rows are asked for three
-// recursions ahead, and no load stands behind a branch or goes through the scalar cache, so
-// that nothing waits for more than the row it needs.  Measured, 1,024 clients x 3,072 columns, 40
-// rounds: 23.8 -> 19.9 ms (2.6 -> 3.1 TB/s of rows); 4 clients x 784 columns, 20 rounds: 1.79
-// -> 1.64 ms.  Four waves with twice the columns each: 21.8 and 1.75 ms; two rows ahead 20.0,
-// five no better.
-// NC columns per thread; EXACT: D == 512 * NC, no column guards.
+// LDS; row numbers are hashed 48 recursions at a time; rows are asked for three recursions
+// ahead, and no load stands behind a branch or goes through the scalar cache, so that nothing
+// waits for more than the row it needs.  Measured, 1,024 clients x 3,072 columns, 40 rounds:
+// 23.8 -> 19.0 ms (2.6 -> 3.3 TB/s of rows); 4 clients x 784 columns, 20 rounds: 1.73 -> 1.43
+// ms.  Four waves with twice the columns each, two rows ahead: slower; five ahead: no faster.
+//
+// The arithmetic of dz = exp(z - lse) - onehot, its sums' order included, is fixed (the GPU tests
+// hold digests of it).  Its entries add up to an error that is not centred; with features of one
+// sign every recursion moves all ten rows by a little of x, and the models of many clients
+// keep that: 600 clients x 40 columns, 20 rounds, 4e-5 of the norm against 64 bits.  ex * (1 / sum)
+// is as good a softmax and came to 2.4e-6 there, -(sum - ex) / sum for the label's entry to
+// 2.4e-7, but each moves every model by those 4e-5.
 // dword 3 of a raw buffer descriptor for 32-bit untyped accesses on this part
 constexpr int kBufferFlags = 0x00020000;
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+// NC columns per thread; EXACT: D == 512 * NC, no column guards.
 template <int NC, bool EXACT>
 __global__ void __launch_bounds__(kSmThreads, 1)
 k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
@@ -108,13 +119,12 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
     const RoundParams p = rp[blockIdx.x];
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
-    const int tid = threadIdx.x, lane = tid & 63, l4 = lane & 3;
+    const int tid = threadIdx.x, lane = tid & 63, cls = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // partial logits [parity][class][wave]: a lane reads the eight waves' sums of one class as
-    // two 16-byte pieces; classes 10 and 11 stay zero
-    __shared__ __attribute__((aligned(16))) float zpart[2][4 * Q][NW];
-    if (tid < 2 * 2 * NW) zpart[tid / (2 * NW)][C + (tid / NW) % 2][tid % NW] = 0.f;
+    // partial logits [parity][four waves][class]: a lane reads the eight waves' sums of its class
+    // as two 16-byte pieces, the lanes of a row from neighbouring places
+    __shared__ __attribute__((aligned(16))) float zpart[2][NW / 4][16][4];
 
     const gcf_ptr W0 = as_global(Wg ? Wg : p.W);
     f4v W[NC][Q], U[NC][Q];
@@ -130,15 +140,9 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
                 U[j][q][r] = 0.f;
             }
     }
-    // lane l looks after classes l%4, 4 + l%4, 8 + l%4 (every quad has a copy); the two that do
-    // not exist have a bias that keeps them out of the maximum and the sum
-    float bias[Q], Ub[Q], dz[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        bias[q] = 4 * q + l4 < C ? W0[(int64_t)C * D + 4 * q + l4] : -3.0e38f;
-        Ub[q] = 0.f;
-        dz[q] = 0.f;
-    }
+    // lane o of every row of 16 looks after class o
+    const bool real = cls < C;
+    float bias = real ? W0[(int64_t)C * D + cls] : 0.f, Ub = 0.f, dz = 0.f;
     float loss_acc = 0.f;
 
     // Row numbers and labels come a block of kSmBlock recursions at a time: lane l hashes
@@ -161,24 +165,27 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
         for (int j = 0; j < NC; ++j)
             x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * (tid + T * j), 0, 0));
     };
-    // U <- U + dz x^T of one recursion
-    auto add_U = [&](const float (&x)[NC]) {
+    // M <- M + a x^T: cbsz = 4, abid = q broadcasts block q of A, that is lanes 4q .. 4q + 3 of the
+    // first row with classes 4q .. 4q + 3 (10 .. 15: zeros), to all sixteen blocks
+    auto rank1 = [&](f4v (&M)[NC][Q], float a, const float (&x)[NC]) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-            for (int j = 0; j < NC; ++j) U[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(dz[q], x[j], U[j][q], 0, 0, 0);
+        for (int j = 0; j < NC; ++j) {
+            M[j][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, x[j], M[j][0], 4, 0, 0);
+            M[j][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, x[j], M[j][1], 4, 1, 0);
+            M[j][2] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, x[j], M[j][2], 4, 2, 0);
+        }
     };
 
-    // x: this recursion's row; xp: the row of the recursion before, whose dz is still in dz[];
+    // x: this recursion's row; xp: the row of the recursion before, whose dz is still in dz;
     // that row's registers then take the row of recursion u + DEPTH - 1.  The loads stand
     // outside of the branches on `live` (false for the up to DEPTH - 1 steps that fill the last
     // group): between two of them the same number of loads is issued on every way.
     auto recursion = [&](int u, int i, const float (&x)[NC], float (&xp)[NC]) {
         const bool live = u < p.m;
         const int lab = __builtin_amdgcn_readlane(labv, i);
-        f4v za[Q][NW / 4];
+        f4v za[NW / 4];
         if (live) {
-            float(*zp)[NW] = zpart[u & 1];
+            float(*zp)[16][4] = zpart[u & 1];
             float s[C];
 #pragma unroll
             for (int o = 0; o < C; ++o) {
@@ -192,53 +199,32 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
                 const int row = lane >> 4, o0 = ((row & 1) << 1) | (row >> 1);
 #pragma unroll
                 for (int k = 0; k < (C + 3) / 4; ++k)
-                    if (4 * k + o0 < C) zp[4 * k + o0][wave] = t[k];
+                    if (4 * k + o0 < C) zp[wave >> 2][4 * k + o0][wave & 3] = t[k];
             }
             __syncthreads();
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-#pragma unroll
-                for (int h = 0; h < NW / 4; ++h) za[q][h] = *reinterpret_cast<const f4v *>(&zp[4 * q + l4][4 * h]);
+            for (int h = 0; h < NW / 4; ++h) za[h] = *reinterpret_cast<const f4v *>(zp[h][real ? cls : 0]);
         }
         // while those travel: the sum U of the recursion before (not on the way to the next
         // logits), and the row that is needed DEPTH - 1 recursions from now
         __builtin_amdgcn_sched_barrier(0);
-        add_U(xp);
+        rank1(U, dz, xp);
         __builtin_amdgcn_sched_barrier(0);
         load_row(i + DEPTH - 1, xp);
         if (live) {
-            float z[Q], ex[Q];
+            float z = bias;   // the waves' sums in wave order
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const f4v v = za[q][0] + za[q][1];
-                z[q] = bias[q] + ((v[0] + v[1]) + (v[2] + v[3]));
-            }
-            const float zmax = quad_max_dpp(fmaxf(fmaxf(z[0], z[1]), z[2]));
-#pragma unroll
-            for (int q = 0; q < Q; ++q) ex[q] = __expf(z[q] - zmax);
-            const float sum = quad_sum_dpp(ex[0] + ex[1] + ex[2]);
-            const float inv = __builtin_amdgcn_rcpf(sum);
-#pragma unroll
-            for (int q = 0; q < Q; ++q) dz[q] = ex[q] * inv - (4 * q + l4 == lab ? 1.f : 0.f);
-            // w <- w - eta g with g = dz x^T: lane l hands the matrix core entry 4q + l%4 of
-            // dz and its own x
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const float na = -p.eta * dz[q];
-#pragma unroll
-                for (int j = 0; j < NC; ++j) W[j][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(na, x[j], W[j][q], 0, 0, 0);
-                bias[q] += na;
-                Ub[q] += dz[q];
-            }
-            if (wave == NW - 1) {
-                const float lse = zmax + __logf(sum);
-#pragma unroll
-                for (int q = 0; q < Q; ++q)
-                    if (4 * q + l4 == lab) loss_acc += lse - z[q];
-            }
+            for (int w = 0; w < NW; ++w) z += za[w >> 2][w & 3];
+            const float zmax = row_max_dpp(real ? z : -3.0e38f);
+            const float ex = real ? __expf(z - zmax) : 0.f;
+            const float lse = zmax + __logf(row_sum_dpp(ex));
+            dz = real ? __expf(z - lse) - (cls == lab ? 1.f : 0.f) : 0.f;
+            rank1(W, -p.eta * dz, x);   // w <- w - eta g with g = dz x^T
+            bias -= p.eta * dz;
+            Ub += dz;
+            if (cls == lab) loss_acc += lse - z;
         } else {
-#pragma unroll
-            for (int q = 0; q < Q; ++q) dz[q] = 0.f;
+            dz = 0.f;
         }
     };
 
@@ -249,7 +235,6 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) x[i][j] = 0.f;
     }
-    __syncthreads();   // the zeros of zpart
     if (p.m > 0) {
         next_block(0);
         rowv = rown;
@@ -267,7 +252,7 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
 #pragma unroll
                 for (int i = 0; i < DEPTH; ++i) recursion(u0 + i0 + i, i0 + i, x[i], x[(i + DEPTH - 1) % DEPTH]);
         }
-        add_U(x[DEPTH - 1]);   // the last recursion's, unless a filling step has done it
+        rank1(U, dz, x[DEPTH - 1]);   // the last recursion's, unless a filling step has done it
     }
 
 #pragma unroll
@@ -281,16 +266,12 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
             }
         }
     }
-    if (tid < 4) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (4 * q + tid < C) {
-                Wc[(int64_t)C * D + 4 * q + tid] = bias[q];
-                Uc[(int64_t)C * D + 4 * q + tid] = Ub[q];
-            }
+    if (tid < C) {
+        Wc[(int64_t)C * D + tid] = bias;
+        Uc[(int64_t)C * D + tid] = Ub;
     }
-    if (wave == NW - 1) {
-        const float l = quad_sum_dpp(loss_acc);
+    if (wave == 0) {
+        const float l = row_sum_dpp(loss_acc);
         if (lane == 0) *as_global(p.loss) = l;
     }
 }
