@@ -1,0 +1,53 @@
+"""Clusters per launch (csrc/cluster_plan.h): every workgroup of a launch has a place on its own
+XCD.  The header is plain host code; a small C++ program prints its answers and the launch is
+laid out here the way the round kernels number their workgroups."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2112_13935_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = str(d / "plan.cpp"), str(d / "plan")
+    with open(src, "w") as f:
+        f.write('#include "cluster_plan.h"\n#include <cstdio>\nint main() {\n'
+                "    int c, x, s;\n"
+                '    while (scanf("%d %d %d", &c, &x, &s) == 3) printf("%d\\n", aet::resident_clusters(c, x, s));\n}\n')
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", exe, src], check=True)
+
+    def ask(rows):
+        text = "\n".join(" ".join(map(str, r)) for r in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [int(v) for v in out.split()]
+    return ask
+
+
+def most_on_one_xcd(clients, size, xcds):
+    """Working workgroups per XCD: workgroup id -> (client, member) as the kernels do it."""
+    on = [0] * xcds
+    for block in range(8 * ((clients + 7) // 8) * size):
+        client = (block & 7) + 8 * ((block >> 3) // size)
+        if client < clients:
+            on[block % xcds] += 1
+    return max(on)
+
+
+@pytest.mark.parametrize("cus,xcds", [(256, 8), (512, 8), (128, 4), (64, 2), (32, 1)])
+def test_every_workgroup_of_a_launch_has_a_place(plan, cus, xcds):
+    sizes = list(range(1, 33))
+    for size, n in zip(sizes, plan([(cus, xcds, s) for s in sizes])):
+        assert n >= xcds, f"clusters of {size} fit every XCD"
+        for clients in {1, 7, 8, 9, n - 1, n} - {0}:
+            if clients <= n:
+                assert most_on_one_xcd(clients, size, xcds) <= cus // xcds, (size, clients)
+        # and no smaller than it has to be: eight clients more overfill some XCD
+        assert most_on_one_xcd(n + 8, size, xcds) > cus // xcds, size
+
+
+def test_a_cluster_larger_than_an_xcd_has_no_place(plan):
+    assert plan([(256, 8, 33)]) == [0]

@@ -75,6 +75,9 @@ def test_dense_layers_on_the_layer_engine(gpu, oracle_libs, layer_engine, n, d, 
     (2, 3072, 64),       # widest and largest: a cluster of six
     (130, 1600, 20),     # more workgroups (4 x 130) than are resident: three columns per thread
     (300, 700, 50),      # a cluster of two that takes three launches
+    (40, 3072, 20),      # as many clusters of six as the XCDs hold: one column per thread
+    (41, 3072, 20),      # one client more: three columns per thread, clusters of two
+    (43, 3072, 50),      # clusters of six for 40 clients, then for three
 ])
 def test_softmax_mini_batches(gpu, oracle_libs, n, d, batch):
     wl = W.config5(n_clients=n, n_per=70, d=d, rounds=3)
