@@ -25,7 +25,6 @@ using namespace aet;
 // clears get.
 static constexpr size_t kStaticBytes = (size_t)AET_STATIC_WORKSPACE_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
-static constexpr int kMaxDevices = 64;
 static void *g_scratch_ptr[kMaxDevices] = {};
 static const aet_ctx *g_scratch_owner[kMaxDevices] = {};
 

@@ -5,6 +5,8 @@
 
 #include <vector>
 
+#include "per_device.h"
+
 namespace aet {
 
 // Resolved geometry of one layer (activations are C,H,W per sample).

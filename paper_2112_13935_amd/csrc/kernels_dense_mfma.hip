@@ -837,16 +837,18 @@ hipError_t launch_dense_head(hipStream_t s, Profiler *prof, const RoundParams *d
                              const LayerGeom &L, const float *in, const int32_t *labels, float *din, bool masked) {
     const HeadGeom g = head_geom(L, B);
     const size_t lds = head_lds_bytes(g);
-    static bool sized = false;   // a property of the function: set once
-    if (!sized) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        sized = true;
-    }
+    int dev = 0, sized = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    static PerDevice lds_allowed;
+    e = lds_allowed.get(dev, &sized, [](int *done) {
+        *done = 1;
+        const hipError_t e0 = hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<true>),
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        return e0 != hipSuccess ? e0 : hipFuncSetAttribute(reinterpret_cast<const void *>(k_dense_head<false>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    if (e != hipSuccess) return e;
     const bool timed = prof && prof->on[F_SOFTMAX_CE];
     if (timed) prof->before(F_SOFTMAX_CE, s);
     if ((g.K & 3) == 0 && (g.w_off & 3) == 0)

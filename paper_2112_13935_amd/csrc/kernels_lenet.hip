@@ -1637,15 +1637,14 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     const bool g28 = d.H0 == 28 && d.P1 == 12 && d.H2 == 8 && d.P2 == 4 && d.F0 == 256 && d.lgF0 == 8;
     const int S = lenet_clusters(B);
     const LenetKernel kernel = lenet_kernel(g28, S, !lenet_round_exact(B));
-    static bool sized[2][3] = {};   // a property of the function: set once
-    bool &done = sized[g28][S == 2 ? 2 : lenet_round_exact(B) ? 0 : 1];
-    if (!done) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        done = true;
-    }
-    int dev = 0, cus = 0, per_cu = 0;
+    int dev = 0, cus = 0, per_cu = 0, sized = 0;
     e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    static PerDevice lds_allowed[2][3];
+    e = lds_allowed[g28][S == 2 ? 2 : lenet_round_exact(B) ? 0 : 1].get(dev, &sized, [kernel](int *done) {
+        *done = 1;
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
     if (e != hipSuccess) return e;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;

@@ -650,25 +650,23 @@ size_t mlp_round_scratch_bytes(int n_clients, int B) {
     return mlp_all_words(n_clients) * 8 + 256;
 }
 
-static int g_mlp_capacity[2][3][3] = {};  // resident workgroups, per instantiation
-
 template <int NBT, int TPW, bool FAST, bool FULL, int HF>
-static hipError_t mlp_capacity(size_t lds, int *cap) {
-    int &cached = g_mlp_capacity[NBT - 1][HF == 2 ? 2 : TPW == kMlpMaxTPW ? 1 : 0][FAST ? (FULL ? 2 : 1) : 0];
-    if (cached > 0) { *cap = cached; return hipSuccess; }
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    int dev = 0, cus = 0, per_cu = 0;
-    e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF>, kMlpThreads, lds);
-    if (e != hipSuccess) return e;
-    *cap = cus * per_cu;
-    cached = *cap;
-    return hipSuccess;
+static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
+    int dev = 0;
+    const hipError_t e0 = hipGetDevice(&dev);
+    if (e0 != hipSuccess) return e0;
+    static PerDevice capacity;   // of this instantiation
+    return capacity.get(dev, cap, [lds, dev](int *found) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        int cus = 0, per_cu = 0;
+        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF>, kMlpThreads, lds);
+        *found = cus * per_cu;
+        return e;
+    });
 }
 
 // HF = 2 (two workgroups per unit group) is taken only when all active clients fit one
