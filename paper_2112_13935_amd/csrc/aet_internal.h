@@ -9,6 +9,15 @@
 
 namespace aet {
 
+// XCDs of the current GPU
+inline hipError_t device_xcds(int *xcds) {
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    static PerDevice known;
+    return known.get(dev, xcds, [dev](int *n) { return hipDeviceGetAttribute(n, hipDeviceAttributeNumberOfXccs, dev); });
+}
+
 // Resolved geometry of one layer (activations are C,H,W per sample).
 struct LayerGeom {
     int type, relu, k, pad;

@@ -48,6 +48,7 @@
 
 #include "aet_device.h"
 #include "aet_internal.h"
+#include "cluster_plan.h"
 
 namespace aet {
 
@@ -1651,7 +1652,10 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kLnThreads, lds);
     if (e != hipSuccess) return e;
     // clusters per launch: every workgroup that polls must be resident together with its peers
-    const int per_launch = cus * per_cu / (kLnG * S);
+    int xcds = 0;
+    e = device_xcds(&xcds);
+    if (e != hipSuccess) return e;
+    const int per_launch = resident_clusters(cus * per_cu, xcds, kLnG * S);
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     u64 *xrec = static_cast<u64 *>(scratch);
     const size_t words = lenet_words(n_clients, B);

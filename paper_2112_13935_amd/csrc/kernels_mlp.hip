@@ -39,12 +39,13 @@
 // 100 -> 10, mini-batch 20: 6.3 us per recursion here, 28.7 us as seven launches of the
 // layer-by-layer engine.
 //
-// All workgroups of a client must be resident together: the launcher never has more
-// working workgroups in flight than the device holds (1 per compute unit with this LDS
-// footprint).  The poll is bounded: on expiry an error flag is raised and every workgroup
+// All workgroups of a client must be resident together: the launcher never puts more
+// working workgroups on an XCD than it holds (cluster_plan.h; 1 per compute unit with this
+// LDS footprint).  The poll is bounded: on expiry an error flag is raised and every workgroup
 // still runs to the end, so the grid always drains.
 #include "aet_device.h"
 #include "aet_internal.h"
+#include "cluster_plan.h"
 
 namespace aet {
 
@@ -678,13 +679,15 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     constexpr int B = 16 * NBT;
     const int G = (H + 15) / 16;
     const size_t lds = mlp_lds_bytes_tpw(TPW, B);
-    int cap = 0;
+    int cap = 0, xcds = 0;
     hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF>(lds, &cap);
+    if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
     // Clusters per launch: every workgroup that polls must be resident together with its
     // peers.  Workgroups of unused slots exit at once and free their compute unit, so only
     // the working ones count.
-    const int per_launch = cap / (G * HF) < kMlpPack ? cap / (G * HF) : kMlpPack;
+    const int fit = resident_clusters(cap, xcds, G * HF);
+    const int per_launch = fit < kMlpPack ? fit : kMlpPack;
     if (HF == 2 && per_launch < nact) {
         *declined = true;
         return hipSuccess;

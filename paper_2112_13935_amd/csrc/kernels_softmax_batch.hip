@@ -397,7 +397,7 @@ hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const Round
     int dev = 0, cus = 0, xcds = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&xcds, hipDeviceAttributeNumberOfXccs, dev);
+    if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
     // One column per thread (more workgroups per client) for mini-batches whose rows would not
     // fit the registers otherwise, and for mini-batches of more than 16 when all clusters are

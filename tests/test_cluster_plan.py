@@ -51,3 +51,9 @@ def test_every_workgroup_of_a_launch_has_a_place(plan, cus, xcds):
 
 def test_a_cluster_larger_than_an_xcd_has_no_place(plan):
     assert plan([(256, 8, 33)]) == [0]
+
+
+@pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet"])
+def test_the_launchers_take_their_clusters_from_the_plan(kernel):
+    text = open(os.path.join(CSRC, f"kernels_{kernel}.hip")).read()
+    assert "per_launch" in text and "resident_clusters(" in text

@@ -42,6 +42,9 @@ def test_softmax_round_lengths(gpu, oracle_libs, d, s0):
     (3, 112, 17, 20),    # the second group holds one unit, the second sample tile four
     (3, 784, 100, 20),   # two workgroups per unit group
     (2, 777, 255, 31),   # ragged columns, one unit and one sample short of full tiles
+    (16, 784, 100, 20),  # as many clusters of 2 x 7 workgroups as the XCDs hold
+    (17, 784, 100, 20),  # one client more: clusters of 7
+    (33, 784, 170, 20),  # clusters of 11, two per XCD: three launches
     (257, 12, 5, 3),     # one client more than the padded form takes: the layer engine
 ])
 def test_mlp_padded_tiles(gpu, oracle_libs, n, d, hidden, batch):
