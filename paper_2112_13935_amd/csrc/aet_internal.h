@@ -141,9 +141,9 @@ hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,
                              int u, int B, int K, int O, int64_t w_off, int64_t b_off, int relu,
                              const float *x, const float *y, float *z, const float *mask_src);
-// d(input) and update of a dense layer that is not the first, in one launch; masked: the input went
-// through a ReLU
-bool dense_bwd_supported(int B);
+// d(input) and update of a dense layer that is not the first, in one launch, where that is faster
+// than two; masked: the input went through a ReLU
+bool dense_bwd_pays(const LayerGeom &L, int B, int nact);
 hipError_t launch_dense_bwd(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, const float *in, const float *dout, float *din, bool masked);
 // the whole last dense layer (logits, softmax cross-entropy, d(input), update) in one launch

@@ -282,15 +282,15 @@ k_dense_wgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, in
 //   din^T[k][b] = sum_o W[o][k] dout[b][o],             M = k, N = b, contraction over o,
 // so that W is staged as it lies in memory (rows of consecutive k) and a lane ends up with
 // four consecutive k of one sample: float4 stores (and float4 loads of the ReLU mask).
-// A workgroup owns 64 k x 64 samples; wave w owns the k tile 16w.. and all sample tiles.  (Layers
-// with mini-batches of up to 64 run k_dense_bwd.)
+// A workgroup owns 64 k x 16*NBT samples; wave w owns the k tile 16w.. and all sample tiles.
 // dout is staged transposed ([o][b], odd row stride); chunks of 32 output units.
+template <int NBT>
 __global__ void __launch_bounds__(256)
 k_dense_dgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, int64_t w_off,
               const float *__restrict__ y, float *__restrict__ z, const float *__restrict__ mask_src) {
     const RoundParams p = rp[blockIdx.z];
     if (u >= p.m) return;
-    constexpr int NBT = 4, BS = 81;   // sample tiles; row stride of the transposed dout tile
+    constexpr int BS = NBT == 4 ? 81 : 49;   // row stride of the transposed dout tile
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int kbase = blockIdx.x * kDT, bbase = blockIdx.y * 16 * NBT;
     const int64_t cb = (int64_t)blockIdx.z * B;
@@ -363,7 +363,7 @@ k_dense_dgrad(const RoundParams *__restrict__ rp, int u, int B, int K, int O, in
     }
 }
 
-// Both backward products of a hidden dense layer in one launch (mini-batches up to 64): a workgroup
+// Both backward products of a hidden dense layer in one launch (where dense_bwd_pays): a workgroup
 // owns 64 inputs k of one client for all outputs and samples; wave w owns the k tile 16 w.. .
 //   d(input)^T[k][b] = sum_o W[o][k] dout[b][o]     M = k, N = b, contraction over o, accumulated
 //                                                   over the chunks of 32 outputs
@@ -532,7 +532,22 @@ k_dense_bwd(const RoundParams *__restrict__ rp, int u, int B, int K, int O, int6
     }
 }
 
-bool dense_bwd_supported(int B) { return B <= 64; }
+// One launch instead of two saves some 3 us; but its workgroups walk all outputs, the update of
+// a chunk included, where k_dense_wgrad spreads them: 1 us per chunk beyond the second, until
+// there are enough workgroups to hide that.  Measured per recursion (one launch - two), 1 to 128
+// clients, mini-batches of 16 and 64:
+//   up to 96 outputs             -1.0 .. -64 us, every size
+//   128 outputs, 1,024 inputs    1 client -0.5 and +0.5, 8 clients -0.3 and +1.3, 32 clients -2.4 and -3.3
+//   256 -> 1,024                 8 clients (32 workgroups) +36 of 74 us, 128 (512) +10 of 281
+//   1,024 -> 512                 8 clients (128) +16 of 62, 32 (512) -5 of 120 us
+//   1,024 -> 1,024               32 clients (512) +9 of 376, 128 (2,048) -13 of 970
+// Where rows are not 16-byte aligned the two are the general tiles, which walk the outputs more
+// slowly: 255 -> 257, 1 client -18 of 75 us, 128 clients -34 of 195.
+bool dense_bwd_pays(const LayerGeom &L, int B, int nact) {
+    const int64_t wgs = (L.in_size + kDT - 1) / kDT * nact;
+    const bool vec = (L.in_size & 3) == 0 && (L.w_off & 3) == 0;
+    return B <= 64 && (!vec || L.oc <= 3 * kDK || (wgs >= 512 && L.oc <= 512) || wgs >= 2048);
+}
 
 hipError_t launch_dense_bwd(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, const float *in, const float *dout, float *din, bool masked) {
@@ -890,8 +905,11 @@ hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const Roun
     } else if (mode == DENSE_FWD)
         k_dense_mfma<DENSE_FWD, 4><<<grid, 256, 0, s>>>(dp, u, B, K, O, w_off, b_off, relu, x, y, z, mask_src);
     else if (mode == DENSE_BWD_DATA && (K & 3) == 0 && (w_off & 3) == 0) {
-        dim3 dgrid((unsigned)((K + kDT - 1) / kDT), (unsigned)((B + 63) / 64), (unsigned)nact);
-        k_dense_dgrad<<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
+        const int nbt = B <= 16 ? 1 : B <= 32 ? 2 : 4;
+        dim3 dgrid((unsigned)((K + kDT - 1) / kDT), (unsigned)((B + 16 * nbt - 1) / (16 * nbt)), (unsigned)nact);
+        if (nbt == 1) k_dense_dgrad<1><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
+        else if (nbt == 2) k_dense_dgrad<2><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
+        else k_dense_dgrad<4><<<dgrid, 256, 0, s>>>(dp, u, B, K, O, w_off, x, z, mask_src);
     } else if (mode == DENSE_BWD_DATA)
         k_dense_mfma<DENSE_BWD_DATA, 4><<<grid, 256, 0, s>>>(dp, u, B, K, O, w_off, b_off, relu, x, y, z, mask_src);
     else if ((K & 3) == 0 && (w_off & 3) == 0) {

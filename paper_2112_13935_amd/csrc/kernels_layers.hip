@@ -725,7 +725,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
                 }
                 AET_RETURN_IF(hipGetLastError());
             }
-        } else if (!sc.plain && l > 0 && dense_bwd_supported(B)) {
+        } else if (!sc.plain && l > 0 && dense_bwd_pays(g, B, nact)) {
             AET_RETURN_IF(launch_dense_bwd(s, prof, dp, nact, u, B, g, sc.act[l], sc.del[l + 1], sc.del[l], mask != nullptr));
         } else if (!sc.plain) {
             const int K = (int)g.in_size;

@@ -162,6 +162,12 @@ def test_smallest_workspace(gpu, oracle_libs, monkeypatch, make):
     (3, 897, 66, 33),     # rows that are not 16-byte aligned, one sample beyond 32
     (2, 1000, 300, 64),   # several input blocks, the last ragged; all four sample tiles
     (2, 900, 40, 65),     # one sample too many for both products in one launch
+    (2, 50, 92, 16),      # 95 outputs, rows 16-byte aligned: always one launch
+    (2, 50, 92, 64),      # the same with four sample tiles
+    (2, 50, 96, 16),      # 99: two launches for few clients, one sample tile
+    (3, 50, 200, 32),     # two launches, two sample tiles
+    (3, 50, 198, 33),     # 201 outputs, rows not aligned: one launch
+    (128, 20, 200, 20),   # one launch again: 512 workgroups
 ])
 def test_hidden_dense_backward(gpu, oracle_libs, n, d, hidden, batch):
     """Two hidden dense layers (the fused rounds take one), so that one of them has both products."""
@@ -169,3 +175,22 @@ def test_hidden_dense_backward(gpu, oracle_libs, n, d, hidden, batch):
     wl.model.layers.insert(1, W.Layer(W.DENSE, hidden + 3, relu=1))
     wl.w0 = W.init_weights(wl.model, 5)
     _lockstep(gpu, wl)
+
+
+@pytest.mark.parametrize("n,inputs,outputs,batch,launches", [
+    (1, 64, 96, 16, 1), (1, 64, 97, 16, 2), (2, 64, 1024, 64, 2), (8, 1024, 512, 16, 2), (32, 1024, 97, 16, 1),
+    (1, 64, 32, 65, 2), (1, 66, 257, 16, 1),
+])
+def test_wide_hidden_layers_are_not_walked_by_few_workgroups(gpu, n, inputs, outputs, batch, launches):
+    """How many launches the backward pass of a hidden dense layer takes: one (d(input) in the
+    update's kernel) only where its workgroups do not walk many outputs in a chain."""
+    wl = W.config2(n_clients=n, n_total=n * 70, d=20, hidden=inputs, batch=batch, rounds=1, a=0, b=2 * batch)
+    wl.model.layers.insert(1, W.Layer(W.DENSE, outputs, relu=1))
+    wl.w0 = W.init_weights(wl.model, 5)
+    run = gpu(wl)
+    fam = run.lib.profile_family_names().index("k_dense_bwd_data")
+    run.lib.aet_profile_enable(fam, True)
+    run.run_all()
+    # two recursions; the last layer's own backward pass is part of other kernels at these sizes
+    assert run.lib.aet_profile_read(fam)[0] == 2 * (launches - 1)
+    run.close()
