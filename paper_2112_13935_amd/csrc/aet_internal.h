@@ -146,8 +146,9 @@ hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const Roun
 bool dense_bwd_pays(const LayerGeom &L, int B, int nact);
 hipError_t launch_dense_bwd(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, const float *in, const float *dout, float *din, bool masked);
-// the whole last dense layer (logits, softmax cross-entropy, d(input), update) in one launch
-bool dense_head_supported(const LayerGeom &L, int B);
+// the whole last dense layer (logits, softmax cross-entropy, d(input), update) in one launch, where it
+// fits and is faster
+bool dense_head_pays(const LayerGeom &L, int B, int nact);
 hipError_t launch_dense_head(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                              const LayerGeom &L, const float *in, const int32_t *labels, float *din, bool masked);
 // fused round of softmax regression, per-sample SGD (kernels_softmax.hip)

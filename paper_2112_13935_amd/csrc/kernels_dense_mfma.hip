@@ -844,8 +844,18 @@ k_dense_head(const RoundParams *__restrict__ rp, int u, HeadGeom g, const float 
     }
 }
 
-bool dense_head_supported(const LayerGeom &L, int B) {
-    return L.oc <= 16 && head_lds_bytes(head_geom(L, B)) <= 160 * 1024;
+// One workgroup per client does what three launches (five without k_dense_bwd, mini-batches over
+// 64) spread over the GPU, so it pays where its tiles are few or the clients fill the GPU.
+// Measured per recursion, one launch - several, 10 classes:
+//   tiles = (sample tiles + 1) x input tiles
+//   mini-batch 16: 300 inputs (38 tiles)  1 client -0.3, 64 clients -3.1; 1,024 (128): +6.5, +5.2, 256 clients -4.1 us
+//   mini-batch 32: 256 (48)  0.0, -1.7; 300 (57)  +0.7, -2.7; 700 (132): +9.0, +6.9, 256 clients -6.1
+//   mini-batch 64: 128 (40)  0.0, -2.2; 256 (80)  +4.6, +2.9, 256 clients -6.9
+//   mini-batch 128: 128 (72)  -2.6, -6.6, 256 clients -28 (all that fits in LDS)
+bool dense_head_pays(const LayerGeom &L, int B, int nact) {
+    if (L.oc > 16) return false;
+    const HeadGeom g = head_geom(L, B);
+    return head_lds_bytes(g) <= 160 * 1024 && (B > 64 || nact >= 256 || (g.BT + 1) * g.KT <= 48);
 }
 
 hipError_t launch_dense_head(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,

@@ -661,8 +661,8 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         AET_TIMED(F_GATHER, k_gather<<<grid, 256, 0, s>>>(dp, u, B, D, sc.act[0], sc.labels));
         AET_RETURN_IF(hipGetLastError());
     }
-    // the last layer, forward to update, in one launch where it fits
-    const bool head = !sc.plain && L > 1 && dense_head_supported(lay[L - 1], B);
+    // the last layer, forward to update, in one launch
+    const bool head = !sc.plain && L > 1 && dense_head_pays(lay[L - 1], B, nact);
     const int LF = head ? L - 1 : L;
     for (int l = 0; l < LF; ++l) {
         const LayerGeom &g = lay[l];

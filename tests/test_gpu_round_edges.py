@@ -112,7 +112,7 @@ def test_lenet_on_the_layer_engine(gpu, oracle_libs, layer_engine, hw, batch):
 @pytest.mark.parametrize("n,hw,width,fc,batch", [
     (1, 4, 3, 5, 1),       # one sample, fewer inputs of the last layer than a tile
     (2, 8, 6, 17, 5),      # one input more than a tile
-    (3, 8, 16, 256, 64),   # the largest mini-batch whose last layer is one launch at this width
+    (3, 8, 16, 256, 64),   # many tiles for three clients: launches of their own
     (2, 8, 4, 40, 80),     # more samples than the unrolled tiles, still one launch
     (2, 8, 4, 300, 64),    # too wide for it: forward, softmax, backward as launches of their own
 ])
@@ -194,3 +194,30 @@ def test_wide_hidden_layers_are_not_walked_by_few_workgroups(gpu, n, inputs, out
     # two recursions; the last layer's own backward pass is part of other kernels at these sizes
     assert run.lib.aet_profile_read(fam)[0] == 2 * (launches - 1)
     run.close()
+
+
+@pytest.mark.parametrize("n,inputs,batch,one", [
+    (1, 304, 16, True), (1, 400, 16, False), (2, 1024, 16, False), (256, 400, 16, True), (1, 128, 64, True),
+    (1, 256, 64, False), (2, 128, 128, True), (2, 600, 128, False),
+])
+def test_last_layer_in_one_launch_where_its_tiles_are_few(gpu, n, inputs, batch, one):
+    """One workgroup per client for the whole last layer, or forward, softmax and backward as
+    launches of their own: the forward launches of a recursion tell which."""
+    wl = W.config2(n_clients=n, n_total=n * 130, d=20, hidden=24, batch=batch, rounds=1, a=0, b=2 * batch)
+    wl.model.layers.insert(1, W.Layer(W.DENSE, inputs, relu=1))
+    wl.w0 = W.init_weights(wl.model, 5)
+    run = gpu(wl)
+    fam = run.lib.profile_family_names().index("k_dense_fwd")
+    run.lib.aet_profile_enable(fam, True)
+    run.run_all()
+    assert run.lib.aet_profile_read(fam)[0] == 2 * (2 if one else 3)
+    run.close()
+
+
+@pytest.mark.parametrize("n,inputs,batch", [(1, 304, 16), (1, 305, 17), (1, 400, 16), (256, 400, 16), (2, 256, 64),
+                                            (256, 272, 64), (2, 128, 128)])
+def test_last_layer_both_ways(gpu, oracle_libs, n, inputs, batch):
+    wl = W.config2(n_clients=n, n_total=n * 130, d=20, hidden=24, batch=batch, rounds=2, a=0, b=batch)
+    wl.model.layers.insert(1, W.Layer(W.DENSE, inputs, relu=1))
+    wl.w0 = W.init_weights(wl.model, 5)
+    _lockstep(gpu, wl)
