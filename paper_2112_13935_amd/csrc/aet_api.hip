@@ -152,9 +152,11 @@ enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENE
 int g_force_layer_engine = 0, g_plain_layers = 0;
 
 // Padded forms of the fused rounds (widths or mini-batches that do not fill their tiles) go to
-// the layer engine beyond this many clients: their exchange records take 0.4 MB per
-// client (dense-ReLU-dense) to 2.6 MB (LeNet, mini-batch over 16), which is more than such a
-// model's own state, and with so many clients the layer engine's launches are full.
+// the layer engine beyond this many clients for their memory: the exchange records take 0.4 MB
+// per client (dense-ReLU-dense) to 2.6 MB (LeNet, mini-batch over 16), which is more than such
+// a model's own state.  (In time the line is not here: 1,024 clients x 784 -> 100 take 0.5 of
+// the layer engine's time, 30 -> 100 2.2 times.)  Up to it mlp_padded_pays and lenet_padded_pays
+// say which engine is the faster one.
 constexpr int kPaddedClients = 256;
 
 // padded_ok: the caller has room for the records of a padded form (or of mini-batch softmax)
@@ -164,13 +166,13 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
     const bool padded = padded_ok && n <= kPaddedClients;
     if (L == 2 && lay[0].type == AET_DENSE && lay[1].type == AET_DENSE && lay[0].relu &&
         mlp_round_supported((int)lay[0].in_size, lay[0].oc, lay[1].oc, B) &&
-        (padded || mlp_round_exact(lay[0].oc, B)))
+        (mlp_round_exact(lay[0].oc, B) || (padded && mlp_padded_pays((int)lay[0].in_size, lay[0].oc, n))))
         return ENGINE_MLP;
     if (L == 1 && lay[0].type == AET_DENSE && softmax_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX;
     if (L == 1 && lay[0].type == AET_DENSE && padded_ok && softmax_batch_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX_BATCH;
-    if (lenet_round_supported(lay, L, B) && (padded || lenet_round_exact(B))) return ENGINE_LENET;
+    if (lenet_round_supported(lay, L, B) && (lenet_round_exact(B) || (padded && lenet_padded_pays(lay[0], B, n)))) return ENGINE_LENET;
     return ENGINE_LAYERS;
 }
 

@@ -165,6 +165,7 @@ const int *softmax_batch_error_flag_ptr(void *scratch, int n_clients, int D, int
 // fused round of dense-ReLU-dense models (kernels_mlp.hip)
 bool mlp_round_supported(int D, int H, int C, int B);
 bool mlp_round_exact(int H, int B);   // no padded units or samples
+bool mlp_padded_pays(int D, int H, int n_clients);   // else: faster than the layer engine
 size_t mlp_round_scratch_bytes(int n_clients, int B);
 // hp: HOST array of the tick's round records (they are passed on in kernel arguments)
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact,
@@ -175,6 +176,7 @@ const int *mlp_error_flag_ptr(void *scratch, int n_clients, int B);
 // fused round of LeNet-5-style models (kernels_lenet.hip); dp: DEVICE array of round records
 bool lenet_round_supported(const LayerGeom *lay, int L, int B);
 bool lenet_round_exact(int B);   // no padded samples, one cluster per client
+bool lenet_padded_pays(const LayerGeom &conv1, int B, int n_clients);   // else: faster than the layer engine
 size_t lenet_round_scratch_bytes(int n_clients, int B);
 hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
                               const float *Wg, const LayerGeom *lay, int L, int B, void *scratch,

@@ -1615,6 +1615,18 @@ bool lenet_round_supported(const LayerGeom *lay, int L, int B) {
 
 bool lenet_round_exact(int B) { return B == kLnB; }
 
+// Padded samples cost as much as real ones; with many clients (launches of 64 or, two clusters
+// each, 32) the layer engine wins where they are most of the tile.  Time here / there per
+// recursion for mini-batches of 1, 4, 8, 15 | 17, 24, 32:
+//   128 clients  16 x 16  0.79 0.71 0.57 0.43 | 0.89 0.76 0.63   28 x 28  0.87 0.70 0.52 0.37 | 0.79 0.65 0.52
+//   192          20 x 20  1.18 1.00 0.75 0.57 | 1.14 0.95 0.78   28 x 28  1.09 0.79 0.59 0.40 | 0.86 0.68 0.53
+//   256          20 x 20  1.27 1.04 0.80 0.61 | 1.26 1.03 0.84   28 x 28  1.00 0.75 0.57 0.39 | 0.84 0.65 0.52
+bool lenet_padded_pays(const LayerGeom &conv1, int B, int n_clients) {
+    if (n_clients <= 128) return true;
+    if (conv1.ih >= 28) return B >= 4;
+    return B <= kLnB ? B >= 8 : B >= 28;
+}
+
 size_t lenet_round_scratch_bytes(int n_clients, int B) { return lenet_words(n_clients, B) * 8 + 256; }
 
 hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B) {

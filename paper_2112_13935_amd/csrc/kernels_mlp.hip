@@ -641,6 +641,26 @@ bool mlp_round_supported(int D, int H, int C, int B) {
 
 bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0; }
 
+// The layer engine's launches take all clients, these as many as are resident (at most kMlpPack)
+// and follow one another, so it catches up with many clients, the sooner the smaller the
+// model.  Time here / there per recursion at mini-batches of 1 to 31, launches in brackets:
+//              30 inputs              100                    300                    784
+//   10 units   96 (2)  0.43 .. 0.48   0.51 .. 0.56           0.64 .. 0.76
+//             192 (4)  0.74 .. 0.86   0.86 .. 0.93           1.03 .. 1.13
+//             256 (6)  1.03 .. 1.25   1.20 .. 1.27           1.37 .. 1.48           0.88 .. 0.99
+//   100 units 128 (4)  0.63 .. 0.75   0.67 .. 0.70           0.75 .. 0.78
+//             256 (8)  0.99 .. 1.26   0.76 .. 0.88           0.65 .. 0.77           0.30 .. 0.36
+//   130 units 256 (11) 1.28 .. 1.65   1.05 .. 1.15           0.83 .. 0.96
+//   250 units  96 (6)  0.87 .. 1.09   0.95 .. 0.99           0.91 .. 0.96
+//             256 (16) 1.76 .. 2.10   1.29 .. 1.42           0.93 .. 1.10           0.37 .. 0.46
+// (256 inputs, 250 units, 256 clients: 0.82 .. 0.89; 400: 0.67 .. 0.79.)
+bool mlp_padded_pays(int D, int H, int n_clients) {
+    const int G = (H + 15) / 16, fit = resident_clusters(256, 8, G), per = fit < kMlpPack ? fit : kMlpPack;
+    const int launches = (n_clients + per - 1) / per;
+    if (launches <= 3 || D >= 768) return true;
+    return G > 1 && (launches <= 5 || D >= 384 || (D >= 256 && launches <= 12) || (D >= 100 && launches <= 8));
+}
+
 // exchange records [client][2][kMlpMaxG][kMlpRec] 64-bit words, the pair records
 // [client][kMlpMaxG][2][2][kMlpPair], then the error flag
 static size_t mlp_rec_words(int n_clients) { return (size_t)n_clients * 2 * kMlpMaxG * kMlpRec; }

@@ -221,3 +221,34 @@ def test_last_layer_both_ways(gpu, oracle_libs, n, inputs, batch):
     wl.model.layers.insert(1, W.Layer(W.DENSE, inputs, relu=1))
     wl.w0 = W.init_weights(wl.model, 5)
     _lockstep(gpu, wl)
+
+
+def _launches(gpu, wl, family):
+    run = gpu(wl)
+    fam = run.lib.profile_family_names().index(family)
+    run.lib.aet_profile_enable(fam, True)
+    run.run_all()
+    n = run.lib.aet_profile_read(fam)[0]
+    run.close()
+    return n
+
+
+@pytest.mark.parametrize("n,d,hidden,launches", [
+    (144, 30, 10, 3), (145, 30, 10, 0),          # 48 clients per launch; one group of units: up to 3 launches
+    (80, 30, 250, 5), (81, 30, 250, 0),          # 16 per launch: up to 5 with few inputs
+    (128, 100, 250, 8), (129, 100, 250, 0),      # ... up to 8 with 100
+    (192, 300, 250, 12), (193, 300, 250, 0),     # ... up to 12 with 256
+    (256, 384, 250, 16), (256, 784, 10, 6), (257, 784, 10, 0),
+])
+def test_padded_mlp_where_it_is_the_faster_engine(gpu, n, d, hidden, launches):
+    wl = W.config2(n_clients=n, n_total=n * 8, d=d, hidden=hidden, batch=4, rounds=1, a=0, b=4)
+    assert _launches(gpu, wl, "k_mlp_round") == launches
+
+
+@pytest.mark.parametrize("n,hw,batch,launches", [
+    (128, 16, 1, 2), (129, 16, 1, 0), (129, 16, 8, 3), (129, 20, 17, 0), (129, 16, 28, 5), (129, 28, 4, 3), (129, 28, 3, 0),
+    (129, 28, 17, 5), (257, 28, 4, 0),
+])
+def test_padded_lenet_where_it_is_the_faster_engine(gpu, n, hw, batch, launches):
+    wl = W.config3(n_clients=n, n_per=10, hw=hw, batch=batch, rounds=1, a=0, b=batch)
+    assert _launches(gpu, wl, "k_lenet_round") == launches
