@@ -11,7 +11,10 @@
 //   - HF > 1: the sums of the workgroup's columns go to the cluster's exchange record as
 //     64-bit {step tag, value} words; every workgroup reads the others' and adds in cluster
 //     order (two records alternate: nobody can post step u + 2 before everybody has read u);
-//   - softmax and dz = p - onehot with 16 lanes per sample, dz^T to LDS;
+//   - softmax and dz = p - onehot with 16 lanes per sample, dz^T to LDS.  (expf and logf as in the
+//     layer engine: with __expf and __logf, 1 % faster, the entries of dz add up to more, and
+//     with features of one sign models come out 1.4 times as far from 64 bits: 600 clients x 40
+//     columns, mini-batch 8, 12 rounds 1.3e-5 against 1.8e-5 of the norm);
 //   - g^T = sum_b x_b dz_b^T as 4 x 4 outer products on the matrix cores (see k_softmax_round:
 //     the lane's own column is the B operand), then W -= eta g and U += g in place.  When a
 //     column is done its registers take the next recursion's rows.
@@ -88,7 +91,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
     const gcf_ptr W0 = as_global(Wg ? Wg : p.W);
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, l4 = lane & 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const float invB = 1.0f / (float)Br, ginv = p.eta * invB;
+    const float invB = 1.0f / (float)Br;
 
     __shared__ float part[NW][BC * kSbPS];
     __shared__ __attribute__((aligned(16))) float dzT[kSbC * DZ];
@@ -251,11 +254,11 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
             const bool live = b < Br && o < C;
             const float zz = z[e] + bs[o];
             const float zmax = max16(live ? zz : -3.0e38f);
-            const float ex = live ? __expf(zz - zmax) : 0.f;
-            const float lse = zmax + __logf(sum16(ex));
+            const float ex = live ? expf(zz - zmax) : 0.f;
+            const float lse = zmax + logf(sum16(ex));
             const int lab = labs[min(b, BC - 1)];
             if (live && o == lab) loss_acc += lse - zz;
-            if (b < BC && o < kSbC) dzT[o * DZ + b] = live ? __expf(zz - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+            if (b < BC && o < kSbC) dzT[o * DZ + b] = live ? expf(zz - lse) - (o == lab ? 1.f : 0.f) : 0.f;
         }
         __syncthreads();
         if (wave == 0 && lane < BC) labs[lane] = labn;
@@ -266,8 +269,9 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                 const f4 v = *reinterpret_cast<const f4 *>(&dzT[lane * DZ + b]);
                 s += (v[0] + v[1]) + (v[2] + v[3]);
             }
-            bs[lane] -= ginv * s;
-            Ubs[lane] += invB * s;
+            s *= invB;
+            bs[lane] -= p.eta * s;
+            Ubs[lane] += s;
         }
         // ---- g, update, the next recursion's rows ------------------------------------------------
 #pragma unroll
@@ -289,8 +293,11 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) W[j][q][r] = kok[j] ? W[j][q][r] - ginv * G[q][r] : 0.f;
-                U[j][q] += invB * G[q];
+                for (int r = 0; r < 4; ++r) {
+                    const float gv = G[q][r] * invB;
+                    W[j][q][r] = kok[j] ? W[j][q][r] - p.eta * gv : 0.f;
+                    U[j][q][r] += gv;
+                }
             }
         }
     }
