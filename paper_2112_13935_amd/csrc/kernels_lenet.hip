@@ -659,12 +659,14 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 z = (part[0] + part[1]) + (part[2] + part[3]);
             }
             const float zmax = row16_max_ln(o < kNC ? z : -3.0e38f);
-            const float ex = o < kNC ? __expf(z - zmax) : 0.f;
-            const float lse = zmax + __logf(row16_sum_ln(ex));
+            // PAD: expf and logf as in the layer engine, where these models ran before
+            const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
+            const float ex = o < kNC ? exp_of(z - zmax) : 0.f;
+            const float sum = row16_sum_ln(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
             const int lab = labs[b];
             const bool real = !PAD || kLnB * sub + b < Br;
             if (o == lab) lossb[b] = real ? lse - z : 0.f;
-            dz[b * 16 + o] = o < kNC && real ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+            dz[b * 16 + o] = o < kNC && real ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
         }
         __syncthreads();
 

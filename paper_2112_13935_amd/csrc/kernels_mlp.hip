@@ -126,12 +126,14 @@ struct MlpPack {
 // partial hidden sums through a second tagged exchange (pair records `prec`) and from
 // there on compute the same numbers side by side; half 0 posts the logits and stores the
 // second layer at the end.
-template <int NBT, int TPW, bool FAST, bool FULL, int HF>
+// PAD: the width or the mini-batch does not fill its tiles.
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
 __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
-            int D, int H, int C, int G, int Br, unsigned long long *__restrict__ xrec,
+            int D, int H, int C, int G, int Brun, unsigned long long *__restrict__ xrec,
             unsigned long long *__restrict__ prec, uint32_t tag0, int *__restrict__ errflag) {
     constexpr int B = 16 * NBT;
+    const int Br = PAD ? Brun : B;   // samples of the mini-batch
     // workgroup -> (client, unit group, half): consecutive workgroup ids go round the 8 XCDs,
     // so the workgroups of one client get ids that land on the same XCD and share its L2
     // for the mini-batch rows and the exchanges.
@@ -212,7 +214,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     if (!Wg) Wg = p.W;
     // own unit of this lane in the first layer; the last group may have units that do not exist:
     // they carry zero weights, so h, dh and every update of theirs is zero
-    const bool unit_ok = 16 * g + li < H;
+    const bool unit_ok = !PAD || 16 * g + li < H;
     const int unit = unit_ok ? 16 * g + li : 0;
     f4 W1r[TPW], U1r[TPW];
 #pragma unroll
@@ -234,12 +236,12 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     {
         const int o = tid >> 4, j = tid & 15;  // threads 0..255 = 16 x 16
         if (tid < 256) {
-            W2s[tid] = (o < C && 16 * g + j < H) ? Wg[w2_off + (int64_t)o * H + 16 * g + j] : 0.f;
+            W2s[tid] = (o < C && (!PAD || 16 * g + j < H)) ? Wg[w2_off + (int64_t)o * H + 16 * g + j] : 0.f;
             U2s[tid] = 0.f;
         }
         for (int i = tid; i < B * 16; i += kMlpThreads) zs[i] = 0.f;
         if (tid < 16) {
-            b1s[tid] = 16 * g + tid < H ? Wg[b1_off + 16 * g + tid] : 0.f;
+            b1s[tid] = !PAD || 16 * g + tid < H ? Wg[b1_off + 16 * g + tid] : 0.f;
             Ub1s[tid] = 0.f;
             b2s[tid] = (tid < C) ? Wg[b2_off + tid] : 0.f;
             Ub2s[tid] = 0.f;
@@ -473,11 +475,13 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             }
             if (b < B) {
                 const float zmax = row16_max(o < C ? z : -3.0e38f);
-                const float ex = o < C ? __expf(z - zmax) : 0.f;
-                const float lse = zmax + __logf(row16_sum(ex));
+                // PAD: expf and logf as in the layer engine, where these models run otherwise
+                const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
+                const float ex = o < C ? exp_of(z - zmax) : 0.f;
+                const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
                 const int lab = labs[b];
                 if (o == lab) lossb[b] = lse - z;
-                zs[b * 16 + o] = o < C && b < Br ? __expf(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+                zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
             }
         }
         __syncthreads();
@@ -600,12 +604,12 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     __syncthreads();
     if (hf == 0) {
         const int o = tid >> 4, j = tid & 15;
-        if (tid < 256 && o < C && 16 * g + j < H) {
+        if (tid < 256 && o < C && (!PAD || 16 * g + j < H)) {
             Wc[w2_off + (int64_t)o * H + 16 * g + j] = W2s[tid];
             Uc[w2_off + (int64_t)o * H + 16 * g + j] = U2s[tid];
         }
         if (tid < 16) {
-            if (16 * g + tid < H) {
+            if (!PAD || 16 * g + tid < H) {
                 Wc[b1_off + 16 * g + tid] = b1s[tid];
                 Uc[b1_off + 16 * g + tid] = Ub1s[tid];
             }
@@ -671,20 +675,20 @@ size_t mlp_round_scratch_bytes(int n_clients, int B) {
     return mlp_all_words(n_clients) * 8 + 256;
 }
 
-template <int NBT, int TPW, bool FAST, bool FULL, int HF>
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
 static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
     int dev = 0;
     const hipError_t e0 = hipGetDevice(&dev);
     if (e0 != hipSuccess) return e0;
     static PerDevice capacity;   // of this instantiation
     return capacity.get(dev, cap, [lds, dev](int *found) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         int cus = 0, per_cu = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF>, kMlpThreads, lds);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD>, kMlpThreads, lds);
         *found = cus * per_cu;
         return e;
     });
@@ -692,7 +696,7 @@ static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
 
 // HF = 2 (two workgroups per unit group) is taken only when all active clients fit one
 // launch that way; otherwise *declined is set and nothing is launched.
-template <int NBT, int TPW, bool FAST, bool FULL, int HF>
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
 static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact, int max_m,
                              const float *Wg, int D, int H, int C, int Br, void *scratch, int n_clients,
                              uint32_t *epoch, bool *declined = nullptr) {
@@ -700,7 +704,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     const int G = (H + 15) / 16;
     const size_t lds = mlp_lds_bytes_tpw(TPW, B);
     int cap = 0, xcds = 0;
-    hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF>(lds, &cap);
+    hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF, PAD>(lds, &cap);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
     // Clusters per launch: every workgroup that polls must be resident together with its
@@ -733,7 +737,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, tag0, errflag);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -750,20 +754,22 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     const bool full = D == 16 * kMlpWaves * mlp_tpw(D);   // no pad tiles
     // wide inputs: two workgroups per unit group, half of the columns each, when every active
     // client gets its 2 G workgroups resident in one launch
+    const bool pad = !mlp_round_exact(H, B);
+#define AET_MLP(nbt, tpw, fast_, full_, hf, ...)                                                                            \
+    (pad ? mlp_launch<nbt, tpw, fast_, full_, hf, true>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)   \
+         : mlp_launch<nbt, tpw, fast_, full_, hf, false>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__))
     if (!small && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW) {
         bool declined = false;
         hipError_t e;
-        if (B <= 16) e = fast ? mlp_launch<1, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined)
-                              : mlp_launch<1, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined);
-        else e = fast ? mlp_launch<2, kMlpHalfTPW, true, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined)
-                      : mlp_launch<2, kMlpHalfTPW, false, false, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, &declined);
+        if (B <= 16) e = fast ? AET_MLP(1, kMlpHalfTPW, true, false, 2, &declined) : AET_MLP(1, kMlpHalfTPW, false, false, 2, &declined);
+        else e = fast ? AET_MLP(2, kMlpHalfTPW, true, false, 2, &declined) : AET_MLP(2, kMlpHalfTPW, false, false, 2, &declined);
         if (e != hipSuccess || !declined) return e;
     }
-#define AET_MLP_CASE(nbt, tpw)                                                                        \
-    do {                                                                                              \
-        if (full) return mlp_launch<nbt, tpw, true, true, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);   \
-        if (fast) return mlp_launch<nbt, tpw, true, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);  \
-        return mlp_launch<nbt, tpw, false, false, 1>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch);           \
+#define AET_MLP_CASE(nbt, tpw)                                        \
+    do {                                                              \
+        if (full) return AET_MLP(nbt, tpw, true, true, 1);            \
+        if (fast) return AET_MLP(nbt, tpw, true, false, 1);           \
+        return AET_MLP(nbt, tpw, false, false, 1);                    \
     } while (0)
     if (B <= 16) {
         if (small) AET_MLP_CASE(1, 2);
@@ -772,6 +778,7 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     if (small) AET_MLP_CASE(2, 2);
     AET_MLP_CASE(2, kMlpMaxTPW);
 #undef AET_MLP_CASE
+#undef AET_MLP
 }
 
 hipError_t mlp_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B) {
