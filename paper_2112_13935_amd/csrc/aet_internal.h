@@ -18,6 +18,17 @@ inline hipError_t device_xcds(int *xcds) {
     return known.get(dev, xcds, [dev](int *n) { return hipDeviceGetAttribute(n, hipDeviceAttributeNumberOfXccs, dev); });
 }
 
+// Is the stream under graph capture?  (An error is no answer: the default stream may not be asked
+// while another stream is captured.)
+inline bool stream_is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 // Resolved geometry of one layer (activations are C,H,W per sample).
 struct LayerGeom {
     int type, relu, k, pad;

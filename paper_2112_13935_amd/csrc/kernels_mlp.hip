@@ -722,12 +722,15 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     int *errflag = reinterpret_cast<int *>(xrec + mlp_all_words(n_clients));
     // step tags of this launch: never 0 (the cleared state) and never a tag that an
     // earlier launch may have left in the records
-    if (*epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u) {
+    // A captured launch carries its tags into every replay, where the records still hold words
+    // of the replay before with the same tags: there the records are cleared ahead of it.
+    const bool spent = *epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u;
+    if (spent || stream_is_capturing(s)) {
         k_zero_words<<<(unsigned)((mlp_all_words(n_clients) + 255) / 256), 256, 0, s>>>(xrec, mlp_all_words(n_clients));
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        *epoch = 1;
     }
+    if (spent) *epoch = 1;
     const uint32_t tag0 = *epoch;
     *epoch += (uint32_t)max_m + 1u;
     for (int a0 = 0; a0 < nact; a0 += per_launch) {

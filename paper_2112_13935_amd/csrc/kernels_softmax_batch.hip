@@ -391,14 +391,15 @@ hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const Round
     if (nact <= 0) return hipSuccess;
     const size_t words = (size_t)n_clients * rec_words(D, B);
     // step tags of this launch: never 0 and never one that an earlier launch may have left
-    if (*epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u) {
-        if (words > 0) {
-            k_sb_zero<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(static_cast<u64 *>(scratch), words);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        *epoch = 1;
+    // A captured launch carries its tags into every replay, where the records still hold words
+    // of the replay before with the same tags: there the records are cleared ahead of it.
+    const bool spent = *epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u;
+    if (words > 0 && (spent || stream_is_capturing(s))) {
+        k_sb_zero<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(static_cast<u64 *>(scratch), words);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
+    if (spent) *epoch = 1;
     const uint32_t tag0 = *epoch;
     *epoch += (uint32_t)max_m + 1u;
     int dev = 0, cus = 0, xcds = 0;
