@@ -15,6 +15,7 @@
 #include "../../include/aet_sgd.h"
 #include "aet_device.h"
 #include "aet_internal.h"
+#include "cluster_turns.h"
 
 using namespace aet;
 
@@ -27,6 +28,9 @@ static constexpr size_t kStaticBytes = (size_t)AET_STATIC_WORKSPACE_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 static void *g_scratch_ptr[kMaxDevices] = {};
 static const aet_ctx *g_scratch_owner[kMaxDevices] = {};
+
+// contexts whose rounds run in clusters of workgroups, per GPU
+static ClusterTurns<hipStream_t> g_turns[kMaxDevices];
 
 static hipError_t scratch_address(int dev, void **ptr) {
     if (!g_scratch_ptr[dev]) {
@@ -288,6 +292,27 @@ struct aet_ctx {
     std::vector<std::vector<int64_t>> setup_share;  // [round][node] recursions
     int engine = 0;
     uint32_t epoch = 0;  // step-tag base of the fused kernels' exchange records
+    // a context whose rounds run in clusters: its place among those of its GPU
+    struct Turn : ClusterTurns<hipStream_t>::Member {
+        ClusterTurns<hipStream_t> *among = nullptr;
+        hipEvent_t ev = nullptr;   // none in a context on the library's own workspace
+    };
+    Turn turn;
+    // The cluster launch, behind those that other contexts made on other streams.  (Under capture
+    // there is no order to other streams: a replay beside other cluster launches is the caller's
+    // to prevent.)
+    template <class Launch>
+    hipError_t clustered(Launch launch) {
+        if (!turn.among) return launch();
+        const bool captured = stream_is_capturing(stream);
+        return turn.among->take(&turn, [&](ClusterTurns<hipStream_t>::Member *m) -> hipError_t {
+            if (captured || stream_is_capturing(m->stream)) return hipSuccess;
+            // only one context of a GPU has no event, so one of the two has
+            const hipEvent_t own = static_cast<Turn *>(m)->ev, ev = own ? own : turn.ev;
+            const hipError_t e = hipEventRecord(ev, m->stream);
+            return e != hipSuccess ? e : hipStreamWaitEvent(stream, ev, 0);
+        }, launch);
+    }
     std::string err;
     Profiler prof;
     Profiler *profp() { return prof.any ? &prof : nullptr; }
@@ -473,6 +498,13 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         if (e == hipSuccess) e = ctx->ring_a.create((size_t)n_clients * max_inflight * sizeof(Arrival));
     }
     ctx->v_params.resize(n_clients);
+    const bool clusters = ctx->engine == ENGINE_MLP || ctx->engine == ENGINE_LENET ||
+                          (ctx->engine == ENGINE_SOFTMAX_BATCH && softmax_batch_in_clusters((int)ctx->lay[0].in_size));
+    if (clusters && !static_ws) {
+        if (e == hipSuccess) e = hipGetDevice(&dev);
+        if (e == hipSuccess && (dev < 0 || dev >= kMaxDevices)) e = hipErrorInvalidDevice;
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->turn.ev, hipEventDisableTiming);
+    }
     if (e == hipSuccess && ctx->engine == ENGINE_MLP)
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_LENET)
@@ -490,6 +522,11 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         return st;
     }
     if (static_ws) g_scratch_owner[dev] = ctx;
+    if (clusters) {
+        ctx->turn.stream = ctx->stream;
+        ctx->turn.among = &g_turns[dev];
+        ctx->turn.among->join(&ctx->turn);
+    }
     *out = ctx;
     return AET_OK;
 }
@@ -614,16 +651,22 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
         // client's own replica
         const float *start = ctx->p2p ? nullptr : ctx->Wg();
         if (ctx->engine == ENGINE_MLP) {
-            AET_HIP(ctx, launch_mlp_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
-                                          ctx->lay[0].oc, ctx->lay[1].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
+            AET_HIP(ctx, ctx->clustered([&] {
+                return launch_mlp_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
+                                        ctx->lay[0].oc, ctx->lay[1].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+            }));
         } else if (ctx->engine == ENGINE_SOFTMAX) {
             AET_HIP(ctx, launch_softmax_round(ctx->stream, ctx->profp(), dp, nact, start, (int)ctx->lay[0].in_size, ctx->lay[0].oc));
         } else if (ctx->engine == ENGINE_SOFTMAX_BATCH) {
-            AET_HIP(ctx, launch_softmax_batch_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
-                                                    ctx->lay[0].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
+            AET_HIP(ctx, ctx->clustered([&] {
+                return launch_softmax_batch_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
+                                                  ctx->lay[0].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+            }));
         } else if (ctx->engine == ENGINE_LENET) {
-            AET_HIP(ctx, launch_lenet_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
-                                            ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch));
+            AET_HIP(ctx, ctx->clustered([&] {
+                return launch_lenet_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
+                                          ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+            }));
         } else {
             AET_HIP(ctx, launch_begin_round(ctx->stream, ctx->profp(), dp, nact, start, ctx->P));
             for (int64_t u = 0; u < max_m; ++u)
@@ -996,6 +1039,8 @@ const char *aet_last_error(const aet_ctx *ctx) { return ctx ? ctx->err.c_str() :
 void aet_destroy(aet_ctx *ctx) {
     if (!ctx) return;
     (void)hipStreamSynchronize(ctx->stream);
+    if (ctx->turn.among) ctx->turn.among->leave(&ctx->turn);
+    if (ctx->turn.ev) (void)hipEventDestroy(ctx->turn.ev);
     if (ctx->static_ws && ctx->device >= 0 && g_scratch_owner[ctx->device] == ctx) g_scratch_owner[ctx->device] = nullptr;
     ctx->ring_p.destroy();
     ctx->ring_a.destroy();

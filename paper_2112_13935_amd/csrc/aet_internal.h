@@ -168,6 +168,7 @@ hipError_t launch_softmax_round(hipStream_t s, Profiler *prof, const RoundParams
                                 const float *Wg, int D, int C);
 // ... with mini-batches (kernels_softmax_batch.hip)
 bool softmax_batch_round_supported(int D, int C, int B);
+bool softmax_batch_in_clusters(int D);   // more than one workgroup per client
 size_t softmax_batch_scratch_bytes(int n_clients, int D, int B);
 hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
                                       const float *Wg, int D, int C, int B, void *scratch, int n_clients, uint32_t *epoch);

@@ -351,6 +351,8 @@ bool softmax_batch_round_supported(int D, int C, int B) {
     return B >= 2 && B <= kSbMaxB && C == 10 && D >= 1 && D <= kSbMaxD;
 }
 
+bool softmax_batch_in_clusters(int D) { return D > kSbThreads; }
+
 size_t softmax_batch_scratch_bytes(int n_clients, int D, int B) {
     return (size_t)n_clients * rec_words(D, B) * 8 + 256;
 }

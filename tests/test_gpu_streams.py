@@ -1,0 +1,83 @@
+"""Several contexts on one GPU, each on a stream and in a host thread of its own, whose rounds run
+in clusters of workgroups that wait for each other: their launches take turns, none gives up
+waiting, and every context gets the bits it gets alone.  Run with  -m gpu  on an MI355X."""
+import threading
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def softmax_batch(n, d, batch):
+    wl = W.config5(n_clients=n, n_per=40, d=d, rounds=4)
+    wl.model.batch = batch
+    wl.a = wl.b = batch
+    return wl
+
+
+MIXES = {
+    # clusters of 32 workgroups: one of them fills an XCD
+    "two padded MLPs": lambda: [W.config2(n_clients=3, n_total=180, d=784, hidden=250, batch=20, rounds=6, a=20, b=40) for _ in range(2)],
+    "exact and padded MLP": lambda: [W.config2(n_clients=8, n_total=480, d=784, hidden=256, batch=16, rounds=6, a=16, b=32),
+                                     W.config2(n_clients=8, n_total=480, d=784, hidden=250, batch=20, rounds=6, a=20, b=40)],
+    "four engines": lambda: [W.config2(n_clients=5, n_total=300, d=784, hidden=100, batch=20, rounds=6, a=20, b=40),
+                             W.config3(n_clients=9, n_per=40, hw=16, batch=20, rounds=4, a=20, b=40),
+                             softmax_batch(20, 3072, 50), softmax_batch(9, 400, 20)],
+}
+
+
+@pytest.mark.parametrize("mix", sorted(MIXES))
+def test_contexts_on_their_own_streams(mix):
+    import torch
+    from paper_2112_13935_amd.binding import AetSgd
+    from paper_2112_13935_amd.runner import upload
+    jobs = []
+    for wl in MIXES[mix]():
+        wl.compute_factor = wl.is_straggler = None
+        wl.delay_min = wl.delay_max = 0
+        X, y = upload(wl)
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()     # the shards are there
+        jobs.append((wl, AetSgd(wl.model, X, y, wl.w0, wl.seed, max_inflight=1, max_rounds=wl.rounds, stream=stream), stream))
+
+    def job(wl, lib, stream):
+        with torch.cuda.stream(stream):
+            lib.aet_reset()
+            lib.aet_run_ticks(wl.a, wl.b, wl.rounds, wl.eta0, wl.beta, wl.power, wl.agg_scale)
+            return lib.aet_get_weights_device(-1)
+
+    alone = []
+    for j in jobs:
+        w = job(*j)
+        torch.cuda.synchronize()
+        alone.append(w.cpu())
+    # from one thread, the streams in turn, nothing waited for in between
+    mixed = [[job(*j) for j in jobs] for _ in range(3)]
+    torch.cuda.synchronize()
+    for row in mixed:
+        for a, b in zip(row, alone):
+            assert torch.equal(a.cpu(), b)
+    # from a thread each
+    got, errors = [None] * len(jobs), []
+
+    def work(i):
+        try:
+            for _ in range(6):
+                got[i] = job(*jobs[i])
+        except Exception as e:   # noqa: BLE001 (handed to the test's own thread)
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for (wl, lib, stream), a, b in zip(jobs, got, alone):
+        lib.aet_synchronize()    # raises if a wait had run out
+        assert torch.equal(a.cpu(), b)
+        assert np.isfinite(b.numpy()).all()
+        lib.aet_destroy()
