@@ -148,8 +148,9 @@ aet_status aet_init(aet_ctx **out, const aet_model_desc *model, int32_t n_client
  * through pinned staging buffers.
  *   w0_dev   DEVICE, P floats, canonical layout (read before the call returns)
  *   the other arguments as for aet_init; the context lives on the current device.
- * AET_ENOMEM (with the two sizes in aet_last_error(NULL)) when
- * aet_workspace_bytes(model, n_clients, max_inflight, max_rounds) exceeds
+ * AET_ENOMEM (with the two sizes in aet_last_error(NULL)) when what the context cannot do
+ * without (aet_workspace_bytes(model, n_clients, max_inflight, max_rounds) less the records
+ * of padded rounds and the separate places of partial sums, which are optional) exceeds
  * AET_STATIC_WORKSPACE_BYTES.  Every such context on one GPU uses the same array, which
  * keeps what the last one left (the part the new context uses is cleared by this call):
  * only ONE may be alive per GPU at a time -- a second aet_init_static on that GPU before
@@ -284,20 +285,29 @@ aet_status aet_reset(aet_ctx *ctx);
 
 /* Which engine runs the local rounds, and what it needs from the device.
  *   - softmax regression (one dense layer, batch 1, 10 classes, up to 3072 inputs): one
- *     workgroup per client runs the whole round with the replica in registers;
- *   - dense-ReLU-dense models (batch 16 or 32, hidden width a multiple of 16 up to 256, up
- *     to 896 inputs): a CLUSTER of workgroups per client runs the whole round and
- *     exchanges partial sums through tagged records in the workspace.  PRECONDITION: all
- *     workgroups of a cluster must be resident on the GPU together.  The launcher sizes its
- *     launches from the occupancy the device reports for an otherwise idle GPU; if other
- *     work occupies compute units at the same time (another stream, process or a
- *     compute-unit mask) a cluster may not become resident.  The wait of a workgroup for
+ *     workgroup per client runs the whole round with the replica in registers; the same
+ *     with batch 2 to 64 and up to 512 inputs;
+ *   - softmax regression with batch 2 to 64 and more inputs (up to 3072), dense-ReLU-dense
+ *     models (batch up to 32, hidden width up to 256, up to 896 inputs, up to 16 classes)
+ *     and LeNet-5-style models (28 x 28, 20 x 20 or 16 x 16 images, batch up to 32): a CLUSTER of workgroups
+ *     per client runs the whole round and exchanges partial sums through tagged records in
+ *     the workspace.  Widths that are no multiple of 16 and batches other than 16 (and 32,
+ *     dense-ReLU-dense) are padded: for up to 256 clients, where that is faster, and where
+ *     the workspace has room (aet_workspace_bytes counts it); else they run as below.
+ *     PRECONDITION: all workgroups of a cluster must be resident on the GPU together.  The
+ *     launcher sizes its launches for an otherwise idle GPU; contexts of one process on
+ *     several streams take turns with these launches.  If other work occupies compute
+ *     units at the same time for seconds (a long kernel, a compute-unit mask), or waits in
+ *     the same way (another process with such a context, a graph of captured rounds replayed
+ *     beside other rounds), a cluster may not become resident.  The wait of a workgroup for
  *     its peers is bounded: when it expires the kernel raises an error flag and still runs
  *     to its end (nothing hangs), the results of that launch are invalid, and the next call
  *     that synchronises (aet_synchronize, any getter with on_host != 0, aet_get_round_info)
- *     returns AET_EHIP; from then on every call on the context returns AET_ESTATE.  There
- *     is no fall-back to another engine inside a context: create a new one (after
- *     aet_test_select_kernels(1, 0) it runs on the layer-by-layer engine);
+ *     returns AET_EHIP; from then on every call on the context returns AET_ESTATE.  A getter
+ *     with on_host == 0 only enqueues a copy and cannot tell: call aet_synchronize before
+ *     its result is relied on.  There is no fall-back to another engine inside a context:
+ *     create a new one (after aet_test_select_kernels(1, 0) it runs on the layer-by-layer
+ *     engine);
  *   - every other model: one short kernel sequence per recursion (layer-by-layer engine).
  *
  * Test hook: contexts created after this call use the layer-by-layer engine for every
