@@ -1,11 +1,12 @@
-// Fused local round for softmax regression with mini-batches (one dense layer D -> C <= 12,
+// Fused local round for softmax regression with mini-batches (one dense layer D -> 10 classes,
 // 2 <= B <= 64).  One launch runs the whole round (Algorithm 2, MainComputeNode: all s_i/B
 // recursions) of every active client.
 //
 // A client is a cluster of HF workgroups (8 waves), each owning a run of 512 * NC columns:
 // thread t owns columns t, t + 512, ... of the run for every class row of W and U and, one
-// recursion at a time, of the mini-batch.  All three stay in registers, so the only memory
-// traffic is the sampled rows.  Per recursion:
+// recursion at a time, of the mini-batch.  All three stay in registers, so the memory traffic is
+// the sampled rows.  (The form with three columns and 32 samples spills eight registers, all
+// ahead of the loop over recursions; one pair of them is read back in it.)  Per recursion:
 //   - partial logits: dot products over the thread's columns, two samples (20 sums) at a time
 //     folded over the wave with lane swaps and DPP steps, added over the waves through LDS;
 //   - HF > 1: the sums of the workgroup's columns go to the cluster's exchange record as
@@ -43,8 +44,10 @@ typedef unsigned long long u64;
 
 constexpr int kSbWaves = 8;
 constexpr int kSbThreads = 64 * kSbWaves;
+constexpr int kSbClasses = 10;         // the forward part sums two samples' classes as 20 values
 constexpr int kSbQ = 3;                // groups of four class rows
 constexpr int kSbC = 4 * kSbQ;         // class slots
+static_assert(2 * kSbClasses == 20 && kSbClasses <= kSbC, "five registers of four sums hold two samples' classes");
 constexpr int kSbMaxD = 6 * kSbThreads;
 constexpr int kSbMaxB = 64;
 constexpr int kSbPS = 13;              // LDS stride of a sample's partial logits
@@ -160,13 +163,13 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
             float res[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int c = 0; c < GS / 2; ++c) {
-                float s[20];
+                float s[2 * kSbClasses];
 #pragma unroll
-                for (int i = 0; i < 20; ++i) {
-                    const int o = i % 10;
-                    s[i] = W[0][o >> 2][o & 3] * x[b0 + 2 * c + i / 10][0];
+                for (int i = 0; i < 2 * kSbClasses; ++i) {
+                    const int o = i % kSbClasses, b = b0 + 2 * c + i / kSbClasses;
+                    s[i] = W[0][o >> 2][o & 3] * x[b][0];
 #pragma unroll
-                    for (int j = 1; j < NC; ++j) s[i] += W[j][o >> 2][o & 3] * x[b0 + 2 * c + i / 10][j];
+                    for (int j = 1; j < NC; ++j) s[i] += W[j][o >> 2][o & 3] * x[b][j];
                 }
                 // row r of register kk ends up with the total of sum 4 kk + {0, 2, 1, 3}[r]
                 float t[5];
@@ -190,8 +193,8 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                 const int row = lane >> 4, o0 = ((row & 1) << 1) | (row >> 1);
 #pragma unroll
                 for (int kk = 0; kk < 5; ++kk) {
-                    const int i = 4 * kk + o0, second = i >= 10 ? 1 : 0;
-                    part[wave][(b0 + 2 * li + second) * kSbPS + i - 10 * second] = res[kk];
+                    const int i = 4 * kk + o0, second = i >= kSbClasses ? 1 : 0;
+                    part[wave][(b0 + 2 * li + second) * kSbPS + i - kSbClasses * second] = res[kk];
                 }
             }
         }
@@ -348,7 +351,7 @@ int rec_words(int D, int B) {
 }  // namespace
 
 bool softmax_batch_round_supported(int D, int C, int B) {
-    return B >= 2 && B <= kSbMaxB && C == 10 && D >= 1 && D <= kSbMaxD;
+    return B >= 2 && B <= kSbMaxB && C == kSbClasses && D >= 1 && D <= kSbMaxD;
 }
 
 bool softmax_batch_in_clusters(int D) { return D > kSbThreads; }

@@ -78,15 +78,23 @@ def test_dense_layers_on_the_layer_engine(gpu, oracle_libs, layer_engine, n, d, 
     (2, 3072, 64),       # widest and largest: a cluster of six
     (130, 1600, 20),     # more workgroups (4 x 130) than are resident: three columns per thread
     (300, 700, 50),      # a cluster of two that takes three launches
+    (2, 500, 13),        # one workgroup per client, mini-batches up to 16 and up to 32
+    (3, 400, 20),
+    (3, 3000, 29),       # clusters of six, one column per thread
+    (2, 1540, 7),        # three columns per thread, mini-batches up to 8
     (40, 3072, 20),      # as many clusters of six as the XCDs hold: one column per thread
     (41, 3072, 20),      # one client more: three columns per thread, clusters of two
     (43, 3072, 50),      # clusters of six for 40 clients, then for three
 ])
 def test_softmax_mini_batches(gpu, oracle_libs, n, d, batch):
+    _lockstep(gpu, _mini_batch_softmax(n, d, batch))
+
+
+def _mini_batch_softmax(n, d, batch):
     wl = W.config5(n_clients=n, n_per=70, d=d, rounds=3)
     wl.model.batch = batch
     wl.a = wl.b = batch
-    _lockstep(gpu, wl)
+    return wl
 
 
 @pytest.mark.parametrize("n,hw,batch", [
@@ -134,7 +142,8 @@ def test_conv_backward_in_one_launch(gpu, oracle_libs, n, hw, width, batch):
     lambda: W.config4(n_clients=3, n_per=40, hw=8, width=8, fc=32, batch=4, rounds=3, a=4, b=8),
     lambda: W.config2(n_clients=3, n_total=150, d=50, hidden=24, batch=4, rounds=3, a=4, b=8),
     lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=20, rounds=2, a=20, b=20),
-], ids=["cnn", "mlp", "lenet"])
+    lambda: _mini_batch_softmax(n=3, d=1100, batch=20),
+], ids=["cnn", "mlp", "lenet", "softmax"])
 def test_smallest_workspace(gpu, oracle_libs, monkeypatch, make):
     """A workspace that holds the layer engine's needs and nothing more is still accepted: the
     exchange records of the padded rounds and the partial sums of every layer apart are taken
