@@ -414,8 +414,10 @@ hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const Round
     if (e != hipSuccess) return e;
     // One column per thread (more workgroups per client) for mini-batches whose rows would not
     // fit the registers otherwise, and for mini-batches of more than 16 when all clusters are
-    // resident that way (3,072 columns, mini-batch 32, 21 recursions: 40 clients 279 us, 41 with
-    // three columns 382 us); else three columns.
+    // resident that way; else three columns, which take more clients per launch.  21 recursions of 3,072
+    // columns, one column and three: mini-batch 32, 40 clients 281 and 386 us, 8 clients 234 and
+    // 356; mini-batch 17, 40 clients 269 and 381.  (Mini-batches of up to 16 could use one column
+    // there as well: 16 samples, 40 clients 198 and 261 us, 784 columns, 100 clients 185 and 236.)
     const int hf1 = (D + kSbThreads - 1) / kSbThreads, hf3 = (D + 3 * kSbThreads - 1) / (3 * kSbThreads);
     // (one workgroup per compute unit is sure to be resident)
     const int r1 = resident_clusters(cus, xcds, hf1), r3 = resident_clusters(cus, xcds, hf3);
