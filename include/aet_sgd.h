@@ -313,8 +313,10 @@ aet_status aet_reset(aet_ctx *ctx);
  * Test hook: contexts created after this call use the layer-by-layer engine for every
  * model (force_layer_engine != 0) and / or its plain-FMA kernels instead of the matrix-core
  * ones (plain_layers != 0), so that the kernel sets can be checked against each other and
- * against the oracle.  Process-wide; (0, 0) restores the defaults.  It also changes what
- * aet_workspace_bytes returns. */
+ * against the oracle.  force_layer_engine == 2 keeps the choice of kernels and, for every round
+ * launched until the next call, sends the words that the workgroups of a client exchange
+ * through memory even where all of them run on one XCD.  Process-wide; (0, 0) restores the
+ * defaults.  It also changes what aet_workspace_bytes returns. */
 void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers);
 
 /* Optional kernel timing for measurement harnesses.  The library's kernels are grouped

@@ -376,10 +376,13 @@ const std::vector<int64_t> &setup_shares(aet_ctx *ctx, int64_t i, int64_t a, int
 
 }  // namespace
 
+bool aet::g_posts_to_memory = false;
+
 extern "C" {
 
 void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers) {
-    g_force_layer_engine = force_layer_engine != 0;
+    g_force_layer_engine = force_layer_engine != 0 && force_layer_engine != 2;
+    g_posts_to_memory = force_layer_engine == 2;
     g_plain_layers = plain_layers != 0;
 }
 

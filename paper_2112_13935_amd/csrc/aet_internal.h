@@ -29,6 +29,9 @@ inline bool stream_is_capturing(hipStream_t s) {
     return status == hipStreamCaptureStatusActive;
 }
 
+// Test hook: the exchange words of clusters always go through memory (see cluster_post.h).
+extern bool g_posts_to_memory;
+
 // Resolved geometry of one layer (activations are C,H,W per sample).
 struct LayerGeom {
     int type, relu, k, pad;

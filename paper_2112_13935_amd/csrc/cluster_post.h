@@ -1,0 +1,60 @@
+// Exchange words of a cluster of workgroups: 64-bit {step tag, value} words that validate
+// themselves, written by one workgroup and polled by its peers.
+//
+// What bounds an exchange is how soon a posted word can be read.  A store of agent scope is
+// written through the XCD's L2 to memory; a store of workgroup scope stays in that L2 (the L1
+// is written through either way), where a peer on the same XCD finds it with an agent-scope load,
+// which passes the L1 by.  Ping-pong of two workgroups of one XCD, shader clocks per round trip:
+// 2,065 with agent-scope stores, 1,125 with workgroup-scope stores; a peer on another XCD never
+// sees the latter.  So the workgroups of a cluster first tell each other which XCD they run on
+// (agent scope, once per launch, while the replica is loaded), and only where it is one and the
+// same do the words stay in its L2.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace aet {
+
+constexpr int kClusterMax = 32;   // workgroups of a cluster, at most
+
+__device__ __forceinline__ int xcc_id() {   // hardware register 20, bits 0 .. 3
+    return (int)__builtin_amdgcn_s_getreg(20 | (3 << 11));
+}
+
+// places: one word per workgroup of the cluster (NULL: words always go to memory); tag: not in
+// any word of an earlier launch
+__device__ __forceinline__ void cluster_announce(unsigned long long *places, int me, uint32_t tag) {
+    if (places && threadIdx.x == 0)
+        __hip_atomic_store(places + me, ((unsigned long long)tag << 32) | (unsigned)xcc_id(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Do all n workgroups of the cluster run on one XCD?  Every wave asks for itself.  The wait is
+// bounded: on expiry (or once another workgroup's has expired) *dead is set and the answer is no.
+__device__ __forceinline__ bool cluster_on_one_xcd(const unsigned long long *places, int n, uint32_t tag,
+                                                   int spin_limit, int *errflag, bool *dead) {
+    if (!places) return false;
+    const int lane = threadIdx.x & 63;
+    unsigned long long v = 0;
+    int spins = 0;
+    for (;;) {
+        v = __hip_atomic_load(places + min(lane, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__all((uint32_t)(v >> 32) == tag)) break;
+        if (*dead) return false;
+        __builtin_amdgcn_s_sleep(1);
+        if ((++spins & 255) == 0 &&
+            (spins >= spin_limit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+            __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *dead = true;
+        }
+    }
+    return __all((int)(uint32_t)v == xcc_id());
+}
+
+// one_xcd: what cluster_on_one_xcd said (the same for all lanes)
+__device__ __forceinline__ void cluster_post(unsigned long long *p, uint32_t tag, float v, bool one_xcd) {
+    const unsigned long long word = ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(v);
+    if (one_xcd) __hip_atomic_store(p, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(p, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+}  // namespace aet

@@ -49,6 +49,7 @@
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "cluster_plan.h"
+#include "cluster_post.h"
 
 namespace aet {
 
@@ -110,15 +111,14 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
-__device__ __forceinline__ void xpost(u64 *p, uint32_t tag, float v) {
-    __hip_atomic_store(p, ((u64)tag << 32) | (u64)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 struct Waiter {
     uint32_t tag;
     int *errflag;
     bool dead;
+    bool one_xcd;   // all workgroups of the client run on one XCD
 };
+
+__device__ __forceinline__ void xpost(u64 *p, const Waiter &w, float v) { cluster_post(p, w.tag, v, w.one_xcd); }
 
 // N words at once (the loads are in flight together); repeated until every needed word shows
 // the current step.  Words that are not needed still point at valid memory.
@@ -185,7 +185,7 @@ __device__ __forceinline__ float relu_pool(const float (&acc)[4], int &which) {
 template <bool G28, int S, bool PAD>
 __global__ void __launch_bounds__(kLnThreads, 1)
 k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, const LenetDims d, int Brun,
-              u64 *__restrict__ xrec, uint32_t tag0, int *__restrict__ errflag) {
+              u64 *__restrict__ xrec, u64 *__restrict__ places, uint32_t tag0, int *__restrict__ errflag) {
     // consecutive workgroup ids go round the 8 XCDs: the four workgroups of a client get ids
     // that land on the same XCD and exchange through its L2
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -193,6 +193,8 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     const int g = S == 1 ? gs : gs % kLnG, sub = S == 1 ? 0 : gs / kLnG;   // workgroup of the cluster, cluster (samples 16 sub ..)
     const int Br = PAD ? Brun : kLnB * S;       // samples of the mini-batch
     if (a >= nhere) return;
+    if (places) places += (int64_t)(rec0 + a) * (kLnG * S);
+    cluster_announce(places, gs, tag0);
     const RoundParams p = rp[a];
     const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
@@ -243,7 +245,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 
     u64 *const rec = xrec + (int64_t)(rec0 + a) * (S == 1 ? kXWords : kXWords2) + sub * kXB3;
     u64 *const set0 = xrec + (int64_t)(rec0 + a) * kXWords2 + 2 * kXB3;   // S = 2
-    Waiter wt{tag0, errflag, false};
+    Waiter wt{tag0, errflag, false, false};
 
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL) ----
     const float *src = Wg ? Wg : p.W;
@@ -305,6 +307,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     if (p.m > 0) {
         load_rows(0, xr, labr);
         store_rows(xr, labr);
+        wt.one_xcd = cluster_on_one_xcd(places, kLnG * S, tag0, kLnSpin, errflag, &wt.dead);
     }
     __syncthreads();
 
@@ -480,7 +483,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                     a0[(4 * g + sl) * F0P + f] = best;
                     off2[sl * F0 + f] = (uint16_t)(wy * P1 + wx);
                     pos2[sl * F0 + f] = (uint8_t)(wy * H2 + wx);
-                    xpost(rec + kXA1 + (4 * g + sl) * 256 + f, wt.tag, best);
+                    xpost(rec + kXA1 + (4 * g + sl) * 256 + f, wt, best);
                 }
             }
         }
@@ -556,7 +559,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             for (int w = 0; w < kLnThreads / 64; ++w) acc += dpart[w * kDP + ul * 17 + b];
             const float h = acc > 0.f ? acc : 0.f;
             h1[b * kS1 + kU1 * g + ul] = h;
-            xpost(rec + kXA2 + b * 128 + kU1 * g + ul, wt.tag, h);
+            xpost(rec + kXA2 + b * 128 + kU1 * g + ul, wt, h);
         }
         for (int e0 = tq; e0 < 16 * kF1; e0 += 4 * kLnThreads) {
             const u64 *ptr[4];
@@ -620,7 +623,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             for (int w = 0; w < kLnThreads / 64; ++w) acc += dpart[w * kDP + ul * 17 + b];
             const float h = acc > 0.f ? acc : 0.f;
             h2[b * kS2 + kU2 * g + ul] = h;
-            xpost(rec + kXA3 + b * 96 + kU2 * g + ul, wt.tag, h);
+            xpost(rec + kXA3 + b * 96 + kU2 * g + ul, wt, h);
         }
         for (int e0 = tq; e0 < 16 * kF2; e0 += 4 * kLnThreads) {
             const u64 *ptr[4];
@@ -690,7 +693,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 lossacc[0] += s * invB;
             } else {
                 gloss = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 96, wt.tag, s);
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 96, wt, s);
             }
         }
         __syncthreads();
@@ -715,7 +718,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             for (int t = 0; t < 6; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], bv[t], acc, 0, 0, 0);
             if (k < kF1) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) xpost(rec + kXB1 + g * 2048 + (4 * kq + r) * 128 + k, wt.tag, acc[r]);
+                for (int r = 0; r < 4; ++r) xpost(rec + kXB1 + g * 2048 + (4 * kq + r) * 128 + k, wt, acc[r]);
             }
         }
         // dense 3: w <- w - eta g, U <- U + g (the same in every workgroup)
@@ -733,7 +736,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                     U3[j] += gv;
                 } else {
                     gd3[j] = s;
-                    xpost(recd + (int64_t)gs * kXDw + (24 + j) * 512 + tq, wt.tag, s);
+                    xpost(recd + (int64_t)gs * kXDw + (24 + j) * 512 + tq, wt, s);
                 }
             }
         }
@@ -747,7 +750,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U3b += gv;
             } else {
                 gdb3 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 64 + tq, wt.tag, s);
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 64 + tq, wt, s);
             }
         }
         __syncthreads();
@@ -784,7 +787,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                             }
                         } else {
                             gd2[4 * mt + r] = acc[mt][r];
-                            if (ul < kU2) xpost(recd + (int64_t)gs * kXDw + (16 + 4 * mt + r) * 512 + tq, wt.tag, acc[mt][r]);
+                            if (ul < kU2) xpost(recd + (int64_t)gs * kXDw + (16 + 4 * mt + r) * 512 + tq, wt, acc[mt][r]);
                         }
                     }
             }
@@ -799,7 +802,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U2b += gv;
             } else {
                 gdb2 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 32 + tq, wt.tag, s);
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 32 + tq, wt, s);
             }
         }
         // delta of the own units of dense 1: the four partials in workgroup order
@@ -856,8 +859,8 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 // lane: feature n of the tile, samples 4 kq .. 4 kq + 3
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    xpost(rec + kXB2 + g * 4096 + (4 * kq + r) * 256 + 16 * wave + n, wt.tag, acc0[r]);
-                    if (two) xpost(rec + kXB2 + g * 4096 + (4 * kq + r) * 256 + 16 * (wave + 8) + n, wt.tag, acc1[r]);
+                    xpost(rec + kXB2 + g * 4096 + (4 * kq + r) * 256 + 16 * wave + n, wt, acc0[r]);
+                    if (two) xpost(rec + kXB2 + g * 4096 + (4 * kq + r) * 256 + 16 * (wave + 8) + n, wt, acc1[r]);
                 }
             }
         }
@@ -917,7 +920,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                                 }
                             } else {
                                 gd1[(2 * nl + mt) * 4 + r] = acc[nl][mt][r];
-                                if (ul < kU1) xpost(recd + (int64_t)gs * kXDw + ((2 * nl + mt) * 4 + r) * 512 + tq, wt.tag, acc[nl][mt][r]);
+                                if (ul < kU1) xpost(recd + (int64_t)gs * kXDw + ((2 * nl + mt) * 4 + r) * 512 + tq, wt, acc[nl][mt][r]);
                             }
                         }
                 }
@@ -933,7 +936,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U1b += gv;
             } else {
                 gdb1 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + tq, wt.tag, s);
+                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + tq, wt, s);
             }
         }
         // delta at the own samples' pooled conv-2 outputs (masked by the ReLU): both elements of
@@ -1079,7 +1082,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int e = 156 + tq + kLnThreads * j;
-            if (e < kConvP) xpost(rec3(S == 1 ? g : gs) + e, wt.tag, gsum[e]);
+            if (e < kConvP) xpost(rec3(S == 1 ? g : gs) + e, wt, gsum[e]);
         }
         // delta at the pooled conv-1 outputs (dense correlation with the flipped filters), masked
         // by the ReLU.
@@ -1334,7 +1337,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             float s = 0.f;
 #pragma unroll
             for (int grp = 0; grp < 14; ++grp) s += c1part[grp * 160 + tq];
-            xpost(rec3(gs) + tq, wt.tag, s);
+            xpost(rec3(gs) + tq, wt, s);
         }
         // the next recursion's rows and labels (xs and labs are not read any more)
         if (more) store_rows(xr, labr);
@@ -1594,14 +1597,16 @@ size_t lenet_lds_bytes(const LenetDims &d) {
 }
 
 // the instantiations: 28 x 28 or any geometry; one or two clusters; exact or padded
-typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, uint32_t, int *);
+typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, u64 *, uint32_t, int *);
 LenetKernel lenet_kernel(bool g28, int S, bool pad) {
     if (S == 2) return g28 ? k_lenet_round<true, 2, true> : k_lenet_round<false, 2, true>;
     if (pad) return g28 ? k_lenet_round<true, 1, true> : k_lenet_round<false, 1, true>;
     return g28 ? k_lenet_round<true, 1, false> : k_lenet_round<false, 1, false>;
 }
 int lenet_clusters(int B) { return B > kLnB ? 2 : 1; }
-size_t lenet_words(int n_clients, int B) { return (size_t)n_clients * (lenet_clusters(B) == 1 ? kXWords : kXWords2); }
+size_t lenet_rec_words(int n_clients, int B) { return (size_t)n_clients * (lenet_clusters(B) == 1 ? kXWords : kXWords2); }
+// the records of all clients, then their workgroups' places
+size_t lenet_words(int n_clients, int B) { return lenet_rec_words(n_clients, B) + (size_t)n_clients * kLnG * lenet_clusters(B); }
 
 }  // namespace
 
@@ -1673,6 +1678,7 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     u64 *xrec = static_cast<u64 *>(scratch);
     const size_t words = lenet_words(n_clients, B);
+    u64 *places = g_posts_to_memory ? nullptr : xrec + lenet_rec_words(n_clients, B);
     int *errflag = reinterpret_cast<int *>(xrec + words);
     // step tags of this launch: never 0 (the cleared state) and never a tag that an earlier
     // launch may have left in the records
@@ -1691,7 +1697,7 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
         const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * kLnG * S);
         if (prof && prof->on[F_LENET_ROUND]) prof->before(F_LENET_ROUND, s);
-        kernel<<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, B, xrec, tag0, errflag);
+        kernel<<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, B, xrec, places, tag0, errflag);
         if (prof && prof->on[F_LENET_ROUND]) prof->after(F_LENET_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -46,6 +46,7 @@
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "cluster_plan.h"
+#include "cluster_post.h"
 
 namespace aet {
 
@@ -131,7 +132,8 @@ template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
 __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             int D, int H, int C, int G, int Brun, unsigned long long *__restrict__ xrec,
-            unsigned long long *__restrict__ prec, uint32_t tag0, int *__restrict__ errflag) {
+            unsigned long long *__restrict__ prec, unsigned long long *__restrict__ places,
+            uint32_t tag0, int *__restrict__ errflag) {
     constexpr int B = 16 * NBT;
     const int Br = PAD ? Brun : B;   // samples of the mini-batch
     // workgroup -> (client, unit group, half): consecutive workgroup ids go round the 8 XCDs,
@@ -141,6 +143,8 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     const int a = xcd + 8 * (slot / (G * HF));  // index into this launch's records
     const int g = (slot % (G * HF)) / HF, hf = slot % HF;
     if (a >= nhere) return;
+    if (places) places += (int64_t)(rec0 + a) * kClusterMax;
+    cluster_announce(places, g * HF + hf, tag0);
     const RoundParams p = pack.p[a];
     const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
@@ -270,6 +274,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     // pair records [client][unit group][step parity][half][B * 16]
     unsigned long long *prec_base = prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair;
     bool dead = false;  // the poll expired: keep going, the host will see the flag
+    const bool one_xcd = cluster_on_one_xcd(places, G * HF, tag0, kSpinLimit, errflag, &dead);
     __syncthreads();
 
     auto park_rows = [&]() {
@@ -334,8 +339,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             if (i < B * 16) {
 #pragma unroll
                 for (int w = 0; w < kMlpWaves; ++w) own += red[w * B * 16 + i];
-                const unsigned long long word = ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(own);
-                __hip_atomic_store(pr + hf * kMlpPair + i, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                cluster_post(pr + hf * kMlpPair + i, tag, own, one_xcd);
             }
             park_rows();
             next_rows();
@@ -372,8 +376,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int b = 16 * bt + 4 * lg + r;
-                    const unsigned long long word = ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(acc[r]);
-                    __hip_atomic_store(rec + (int64_t)g * kMlpRec + b * C + li, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cluster_post(rec + (int64_t)g * kMlpRec + b * C + li, tag, acc[r], one_xcd);
                 }
             }
         }
@@ -400,54 +403,31 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             xreg[i % NBT][i / NBT] = load_piece(myrow[i % NBT], i / NBT);
         };
         // ---- logits, softmax, d logits: thread (b, o) = (tid / 16, tid % 16) ------------
-        // Every thread with o < C fetches its own logit: the G tagged words of element
-        // (b, o).  Polling loads slow the peers' stores down (they meet in the same memory
-        // channels: a variant in which every thread polls its own words ran a quarter slower), so
-        // while the peers are still computing only wave 0 looks, and only at one word per
-        // record and batch tile (the last one its owner stores); the other waves wait at a
-        // workgroup barrier.  The elements are fetched when those words show the current tag;
-        // the element tags are still checked, and the fetch repeated if one is stale.  (A
-        // separate flag word per poster, stored after the logits, overtakes them on the way
-        // and makes the fetch fail: the watched word has to be one of the data words.)
+        // Every thread with o < C polls the G tagged words of its own element (b, o): an exchange
+        // is then one trip.  (While the words went through memory such polls slowed the peers'
+        // stores down, and one wave watched one word per record before anybody fetched; with the
+        // words in the XCD's L2 the watch costs more than it saves: 16 clients, 784 -> 128, 50
+        // rounds 7.61 ms with it, 7.47 without; through memory, and watched, 8.77.)
         {
             const int b = tid >> 4, o = tid & 15;
             const bool mine = b < B && o < C;
             float z = 0.f;
             int spins = 0;
-            if (wave == 0) {
-                // lane -> (record, batch tile); the word of sample 16*bt+15, class C-1
-                const int gg = lane % G, bt = lane / G;
-                const bool watch = bt < NBT;
-                const unsigned long long *w = rec + (int64_t)gg * kMlpRec + (16 * min(bt, NBT - 1) + 15) * C + (C - 1);
-                for (;;) {
-                    bool ok = true;
-                    if (watch) ok = (uint32_t)(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == tag;
-                    if (__all(ok) || dead) break;
-                    __builtin_amdgcn_s_sleep(2);
-                    if ((++spins & 255) == 0) {
-                        if (spins >= kSpinLimit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                            __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            dead = true;
-                        }
-                    }
-                }
-            }
-            __syncthreads();
             if (mine) {
                 const unsigned long long *src = rec + b * C + o;
                 constexpr int GC = 8;  // records fetched per batch of loads
                 for (;;) {
                     bool ok = true;
                     z = b2s[o];
-                    if (G == GC) {   // the common cluster size: one unguarded batch
+                    if (G <= GC) {   // one batch; records beyond the last stand for it
                         unsigned long long v[GC];
 #pragma unroll
                         for (int gg = 0; gg < GC; ++gg)
-                            v[gg] = __hip_atomic_load(src + gg * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            v[gg] = __hip_atomic_load(src + min(gg, G - 1) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                         for (int gg = 0; gg < GC; ++gg) {
                             ok = ok && (uint32_t)(v[gg] >> 32) == tag;
-                            z += __uint_as_float((uint32_t)v[gg]);
+                            if (gg < G) z += __uint_as_float((uint32_t)v[gg]);
                         }
                     } else {
                         for (int g0 = 0; g0 < G; g0 += GC) {
@@ -464,7 +444,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                         }
                     }
                     if (ok || dead) break;
-                    __builtin_amdgcn_s_sleep(2);
+                    if (!one_xcd) __builtin_amdgcn_s_sleep(2);
                     if ((++spins & 255) == 0) {
                         if (spins >= kSpinLimit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
                             __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -666,9 +646,11 @@ bool mlp_padded_pays(int D, int H, int n_clients) {
 }
 
 // exchange records [client][2][kMlpMaxG][kMlpRec] 64-bit words, the pair records
-// [client][kMlpMaxG][2][2][kMlpPair], then the error flag
+// [client][kMlpMaxG][2][2][kMlpPair], the workgroups' places [client][kClusterMax], then the error flag
 static size_t mlp_rec_words(int n_clients) { return (size_t)n_clients * 2 * kMlpMaxG * kMlpRec; }
-static size_t mlp_all_words(int n_clients) { return mlp_rec_words(n_clients) + (size_t)n_clients * kMlpMaxG * 4 * kMlpPair; }
+static size_t mlp_pair_words(int n_clients) { return (size_t)n_clients * kMlpMaxG * 4 * kMlpPair; }
+static size_t mlp_all_words(int n_clients) { return mlp_rec_words(n_clients) + mlp_pair_words(n_clients) + (size_t)n_clients * kClusterMax; }
+static_assert(2 * kMlpMaxG <= kClusterMax, "a place for every workgroup");
 
 size_t mlp_round_scratch_bytes(int n_clients, int B) {
     (void)B;
@@ -718,7 +700,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     }
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     unsigned long long *xrec = static_cast<unsigned long long *>(scratch);
-    unsigned long long *prec = xrec + mlp_rec_words(n_clients);
+    unsigned long long *prec = xrec + mlp_rec_words(n_clients), *places = g_posts_to_memory ? nullptr : prec + mlp_pair_words(n_clients);
     int *errflag = reinterpret_cast<int *>(xrec + mlp_all_words(n_clients));
     // step tags of this launch: never 0 (the cleared state) and never a tag that an
     // earlier launch may have left in the records
@@ -740,7 +722,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, tag0, errflag);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

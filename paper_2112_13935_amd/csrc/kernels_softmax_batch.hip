@@ -34,6 +34,7 @@
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "cluster_plan.h"
+#include "cluster_post.h"
 
 namespace aet {
 
@@ -48,7 +49,8 @@ constexpr int kSbClasses = 10;         // the forward part sums two samples' cla
 constexpr int kSbQ = 3;                // groups of four class rows
 constexpr int kSbC = 4 * kSbQ;         // class slots
 static_assert(2 * kSbClasses == 20 && kSbClasses <= kSbC, "five registers of four sums hold two samples' classes");
-constexpr int kSbMaxD = 6 * kSbThreads;
+constexpr int kSbMaxHF = 6;            // workgroups of a cluster, at most
+constexpr int kSbMaxD = kSbMaxHF * kSbThreads;
 constexpr int kSbMaxB = 64;
 constexpr int kSbPS = 13;              // LDS stride of a sample's partial logits
 constexpr int kSbSpin = 1 << 22;       // bounded wait of the exchange poll
@@ -79,7 +81,7 @@ __device__ __forceinline__ float fold16(float a, float b) {
 template <int NC, int BC>
 __global__ void __launch_bounds__(kSbThreads, 1)
 k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, int D, int C,
-                      int HF, int Br, int rec_words, u64 *__restrict__ xrec, uint32_t tag0, int *__restrict__ errflag) {
+                      int HF, int Br, int rec_words, u64 *__restrict__ xrec, u64 *__restrict__ places, uint32_t tag0, int *__restrict__ errflag) {
     constexpr int Q = kSbQ, T = kSbThreads, NW = kSbWaves;
     constexpr int GS = BC < 32 ? BC : 32;   // samples whose logits are collected before a store
     constexpr int DZ = BC + 4;              // LDS stride of a class row of dz^T
@@ -88,6 +90,8 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int a = xcd + 8 * (slot / HF), h = slot % HF;
     if (a >= nhere) return;
+    if (places) places += (int64_t)(rec0 + a) * kSbMaxHF;
+    if (HF > 1) cluster_announce(places, h, tag0);
     const RoundParams p = rp[a];
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
@@ -146,13 +150,14 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
     };
     float loss_acc = 0.f;
     u64 *rec_base = xrec + (int64_t)(rec0 + a) * rec_words;
-    bool dead = false;
+    bool dead = false, one_xcd = false;
 
     if (p.m > 0) {
         next_rows(0);
 #pragma unroll
         for (int j = 0; j < NC; ++j) load_col(j);
         if (wave == 0 && lane < BC) labs[lane] = labn;
+        if (HF > 1) one_xcd = cluster_on_one_xcd(places, HF, tag0, kSbSpin, errflag, &dead);
     }
     for (int u = 0; u < p.m; ++u) {
         int lio = li;   // compared where it is needed: 16 masks kept in scalar registers would spill
@@ -210,9 +215,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
             if (b < Br && o < C) {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) z[e] += part[w][b * kSbPS + o];
-                if (HF > 1)
-                    __hip_atomic_store(rec + ((int64_t)h * Br + b) * kSbC + o, ((u64)tag << 32) | (u64)__float_as_uint(z[e]),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (HF > 1) cluster_post(rec + ((int64_t)h * Br + b) * kSbC + o, tag, z[e], one_xcd);
             }
         }
         next_rows(u + 1);   // the hash runs while the words travel
@@ -347,6 +350,11 @@ int rec_words(int D, int B) {
     const int hf = (D + kSbThreads - 1) / kSbThreads;
     return hf > 1 ? 2 * hf * B * kSbC : 0;
 }
+// the records of all clients, then the workgroups' places [client][kSbMaxHF]; the error flag follows
+size_t all_words(int n_clients, int D, int B) {
+    const int words = rec_words(D, B);
+    return words > 0 ? (size_t)n_clients * (words + kSbMaxHF) : 0;
+}
 
 }  // namespace
 
@@ -357,15 +365,15 @@ bool softmax_batch_round_supported(int D, int C, int B) {
 bool softmax_batch_in_clusters(int D) { return D > kSbThreads; }
 
 size_t softmax_batch_scratch_bytes(int n_clients, int D, int B) {
-    return (size_t)n_clients * rec_words(D, B) * 8 + 256;
+    return all_words(n_clients, D, B) * 8 + 256;
 }
 
 const int *softmax_batch_error_flag_ptr(void *scratch, int n_clients, int D, int B) {
-    return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + (size_t)n_clients * rec_words(D, B));
+    return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + all_words(n_clients, D, B));
 }
 
 hipError_t softmax_batch_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int D, int B) {
-    k_sb_zero<<<1, 64, 0, s>>>(static_cast<u64 *>(scratch) + (size_t)n_clients * rec_words(D, B), 1);
+    k_sb_zero<<<1, 64, 0, s>>>(static_cast<u64 *>(scratch) + all_words(n_clients, D, B), 1);
     return hipGetLastError();
 }
 
@@ -374,7 +382,8 @@ static hipError_t sb_launch(hipStream_t s, Profiler *prof, const RoundParams *dp
                             int D, int C, int B, int HF, int n_clients, void *scratch, uint32_t tag0) {
     u64 *xrec = static_cast<u64 *>(scratch);
     const int words = rec_words(D, B);
-    int *errflag = reinterpret_cast<int *>(xrec + (size_t)n_clients * words);
+    u64 *places = g_posts_to_memory ? nullptr : xrec + (size_t)n_clients * words;
+    int *errflag = reinterpret_cast<int *>(xrec + all_words(n_clients, D, B));
     // a cluster of one never waits: any number of clients per launch; else as many clusters as
     // are resident together
     const int per_launch = HF == 1 ? nact : resident;
@@ -383,7 +392,7 @@ static hipError_t sb_launch(hipStream_t s, Profiler *prof, const RoundParams *dp
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
         const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * HF);
         if (prof && prof->on[F_SOFTMAX_ROUND]) prof->before(F_SOFTMAX_ROUND, s);
-        k_softmax_batch_round<NC, BC><<<grid, kSbThreads, 0, s>>>(dp + a0, here, a0, Wg, D, C, HF, B, words, xrec, tag0, errflag);
+        k_softmax_batch_round<NC, BC><<<grid, kSbThreads, 0, s>>>(dp + a0, here, a0, Wg, D, C, HF, B, words, xrec, places, tag0, errflag);
         if (prof && prof->on[F_SOFTMAX_ROUND]) prof->after(F_SOFTMAX_ROUND, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -394,7 +403,7 @@ static hipError_t sb_launch(hipStream_t s, Profiler *prof, const RoundParams *dp
 hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m,
                                       const float *Wg, int D, int C, int B, void *scratch, int n_clients, uint32_t *epoch) {
     if (nact <= 0) return hipSuccess;
-    const size_t words = (size_t)n_clients * rec_words(D, B);
+    const size_t words = all_words(n_clients, D, B);
     // step tags of this launch: never 0 and never one that an earlier launch may have left
     // A captured launch carries its tags into every replay, where the records still hold words
     // of the replay before with the same tags: there the records are cleared ahead of it.
