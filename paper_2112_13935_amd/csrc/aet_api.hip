@@ -97,6 +97,8 @@ struct RoundRec {
 struct Layout {
     size_t w0, Wg, W, U, loss, params, arrivals, debug, labels, fused, wgrad[AET_MAX_LAYERS];
     bool wgrad_apart;
+    size_t split;                // bf16 parts of the convolutions' weights; split_off as in SplitWeights
+    int64_t split_stride, split_off[AET_MAX_LAYERS][2];
     size_t act[AET_MAX_LAYERS + 1], del[AET_MAX_LAYERS + 1], amax[AET_MAX_LAYERS];
     size_t total;
 };
@@ -181,7 +183,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
 }
 
 bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int inflight, int rounds,
-                 Layout *lo, Engine eng, bool apart = true) {
+                 Layout *lo, Engine eng, bool apart = true, bool split = true) {
     if (n < 1 || inflight < 1 || rounds < 1) return false;
     const size_t Ps = (size_t)((P + 63) / 64 * 64);
     size_t off = 0;
@@ -211,6 +213,16 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
         wg_floats = std::max(wg_floats, floats);
     }
     if (!apart) take(wg_floats * 4);
+    // bf16 parts of the convolutions' weights, where the workspace has room for them
+    int64_t sp = 0;
+    for (int l = 0; l < L; ++l)
+        for (int bwd = 0; bwd < 2; ++bwd) {
+            const size_t bytes = split && eng == ENGINE_LAYERS && lay[l].type == AET_CONV && (l > 0 || !bwd) ? conv_split_weight_bytes(lay[l], bwd) : 0;
+            lo->split_off[l][bwd] = bytes ? sp : -1;
+            sp += (int64_t)bytes;
+        }
+    lo->split_stride = sp / 16;
+    lo->split = take((size_t)sp * n);
     const size_t samples = (size_t)n * B;
     lo->act[0] = take(samples * lay[0].in_size * 4);
     lo->del[0] = 0;
@@ -452,8 +464,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     if (workspace_bytes < ctx->lo.total) {   // a padded form's records are an option, not a need; so are partial sums apart
         engine = pick_engine(ctx->lay, ctx->L, ctx->B, ctx->n, false);
         make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine);
-        if (workspace_bytes < ctx->lo.total)
-            make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine, false);
+        for (int apart = 1; apart >= 0 && workspace_bytes < ctx->lo.total; --apart)
+            make_layout(ctx->lay, ctx->L, ctx->P, ctx->B, ctx->n, max_inflight, max_rounds, &ctx->lo, engine, apart != 0, false);
     }
     ctx->engine = engine;
     if (workspace_bytes < ctx->lo.total) {
@@ -487,6 +499,10 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     for (int l = 0; l < ctx->L; ++l) ctx->sc.wgrad[l] = reinterpret_cast<float *>(ctx->ws + ctx->lo.wgrad[l]);
     ctx->sc.wgrad_apart = ctx->lo.wgrad_apart;
     ctx->sc.plain = g_plain_layers != 0;
+    ctx->sc.split.base = ctx->lo.split_stride > 0 ? ctx->ws + ctx->lo.split : nullptr;
+    ctx->sc.split.stride = ctx->lo.split_stride;
+    for (int l = 0; l < ctx->L; ++l)
+        for (int bwd = 0; bwd < 2; ++bwd) ctx->sc.split.off[l][bwd] = ctx->lo.split_off[l][bwd];
 
     hipError_t e = hipSuccess;
     if (static_ws) {

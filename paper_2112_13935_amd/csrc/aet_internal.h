@@ -69,6 +69,13 @@ struct ArrivalPack {
     Arrival a[kArrivalPack];
 };
 
+// The convolutions' weights of the current recursion as bf16 parts (kernels_conv_split.hip).
+struct SplitWeights {
+    char *base = nullptr;          // NULL: not kept
+    int64_t stride = 0;            // between clients, in 16-byte pieces
+    int64_t off[16][2] = {};       // [layer][forward, backward-data], in bytes; < 0: no such form
+};
+
 // Device scratch of the layer-by-layer engine; all sized for n_clients * batch samples.
 struct LayerScratch {
     float *act[17];     // act[0] = gathered inputs, act[l+1] = output of layer l
@@ -77,6 +84,7 @@ struct LayerScratch {
     int32_t *labels;    // [n_clients][batch]
     float *wgrad[16];   // convolutions: partial sums of the weight gradient
     bool wgrad_apart;   // ... each layer's in a place of its own (else all in the same)
+    SplitWeights split;
     bool plain;         // use the plain (non matrix-core) layer kernels
 };
 
@@ -133,6 +141,16 @@ bool conv_mfma_supported(const LayerGeom &L, bool bwd);
 hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                             const LayerGeom &L, bool bwd, const float *src, float *dst,
                             const float *mask_src, uint8_t *amax = nullptr);
+// the same on the bf16 matrix cores (kernels_conv_split.hip), where that is faster
+size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd);   // 0: no such form
+bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, const SplitWeights &sw);
+// the weights of this recursion for every layer and direction that is used
+hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
+                                const SplitWeights &sw);
+// off: of the layer's weights in this direction, in sw
+hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                             const LayerGeom &L, bool bwd, const SplitWeights &sw, int64_t off, const float *src, float *dst,
+                             const float *mask_src, uint8_t *amax);
 // amax != NULL (forward only): dst is the output of the 2 x 2 pooling layer behind it, amax its winners
 bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool);
 bool conv_wgrad_mfma_supported(const LayerGeom &L, int B);

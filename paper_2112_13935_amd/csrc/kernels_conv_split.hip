@@ -1,0 +1,437 @@
+// 3 x 3 convolutions of the layer-by-layer engine with padding 1 on the bf16 matrix cores, fp32
+// values split in three bf16 parts (split_bf16.h), as implicit GEMMs over tiles staged in LDS.
+//
+// Forward and backward-data are the same kernel (as in kernels_conv_mfma.hip):
+//   dst[dc][y][x] = sum_{sc,ky,kx} src[sc][y+ky-1][x+kx-1] * Wt[dc][sc][ky][kx]
+//   forward:        Wt[dc][sc][ky][kx] = W[dc][sc][ky][kx], then bias and ReLU (and pooling);
+//   backward-data:  Wt[dc][sc][ky][kx] = W[sc][dc][2-ky][2-kx], then the ReLU mask of the layer below.
+// GEMM view: M = 32 destination channels, N = pixels in tiles of 32 (whole rows of 8, 16 or 32),
+// K = (tap, sc) in chunks of 16 source channels.  A workgroup owns 256 pixels (rows of one sample, or
+// several samples of 8 x 8) and 32 destination channels; each of its 4 waves owns two pixel tiles.
+//
+// What bounds it: the clock that the power limit leaves while the matrix cores run (1.6 GHz in a
+// loop of these launches; the products alone would take 126 us of the 204 of a 64 -> 64 layer, 32
+// clients x 64 samples of 16 x 16), then reading the maps (backward-data of 32 -> 32 channels at 32 x 32
+// moves 0.87 GB in 0.27 ms).  Unlike the fp32 matrix instructions these leave the vector ALU free
+// for the splitting.  CNN on 32 x 32, 32 clients, 4 rounds: forward and backward-data together 24
+// -> 16 ms, the job 48.9 -> 40.1.
+#include "aet_device.h"
+#include "aet_internal.h"
+#include "split_bf16.h"
+
+namespace aet {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// dword 3 of a raw buffer descriptor for 32-bit untyped accesses on this part
+constexpr int kBufferFlags = 0x00020000;
+constexpr uint32_t kNowhere = 0x80000000u;   // a byte offset no buffer here reaches: reads as zero
+
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef const u4 __attribute__((address_space(1))) *gu4_ptr;
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+
+struct SplitDir {
+    int SC, DC;          // source / destination channels
+    int H;               // rows of the maps (both sides; the width is the template's)
+    int lgRW;            // R W = 2^lgRW
+    int R, NS;           // rows and samples per workgroup: R * W * NS = 128 MT pixels (NS > 1: R = H)
+    int rblocks;         // row blocks per sample
+    int64_t w_off, b_off;
+    int ic, oc;          // the layer's own channel counts (weight layout W[oc][ic][3][3])
+    int relu, pool;
+};
+
+// LDS, in 16-byte pieces (8 channels of one bf16 part): the source tile [part][octet][position],
+// the weights [part][tap][octet][32]
+template <int LGW, int MT>
+struct SplitTile {
+    static constexpr int W = 1 << LGW, PX = 128 * MT, ROWS = PX / W;   // rows over all samples
+    static constexpr int SMALL = W;                                    // square maps of several samples: H = W
+    // positions of the padded tile: NS (R + 2) (W + 2); NS = 1: R = ROWS; else R = W, NS = ROWS / W
+    static constexpr int NSMAX = ROWS / SMALL > 1 ? ROWS / SMALL : 1;
+    static constexpr int POS1 = (ROWS + 2) * (W + 2), POSN = NSMAX > 1 ? NSMAX * (SMALL + 2) * (W + 2) : 0;
+    static constexpr int POS = (POS1 > POSN ? POS1 : POSN) | 1;        // odd: see the staging
+    static constexpr int LDS = (6 * POS + 6 * 9 * 32) * 16;            // bytes
+};
+
+template <int LGW, int MT, bool BWD>
+__global__ void __launch_bounds__(256, 2)
+k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const u4 *__restrict__ wsplit, int64_t wstride,
+             const float *__restrict__ src, float *__restrict__ dst, const float *__restrict__ mask_src, uint8_t *__restrict__ amax) {
+    typedef SplitTile<LGW, MT> T;
+    constexpr int W = T::W, POS = T::POS, WT = W + 2;
+    const RoundParams p = rp[blockIdx.z];
+    if (u >= p.m) return;
+    extern __shared__ __attribute__((aligned(16))) bf8 sm[];
+    bf8 *const As = sm;                 // [3][2][POS]
+    bf8 *const Bs = sm + 6 * POS;       // [3][9][2][32]
+    __shared__ __attribute__((aligned(16))) float bs[32];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int dc0 = 32 * (int)blockIdx.x;
+    const int HW = g.H * W;
+    const int y0 = (int)blockIdx.y % g.rblocks * g.R, s0 = (int)blockIdx.y / g.rblocks * g.NS;   // row; sample of the mini-batch
+    const int ns = min(g.NS, B - s0);   // samples that exist
+    const int64_t sample0 = (int64_t)blockIdx.z * B + s0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(src) + sample0 * g.SC * HW, 0, 4 * g.SC * HW * ns, kBufferFlags);
+
+    // ---- staging: what this thread moves ----------------------------------------------------
+    // source: four pixels of one tile row, 8 channels (an octet of the chunk's two).  Threads in the
+    // order (four quarters of a row, octet, row, rest of the row): with POS odd the 16 lanes that
+    // write to LDS together then meet 16 different places.
+    constexpr int XL = W / 4 < 4 ? W / 4 : 4;
+    const int rowsT = g.R + 2, rows = g.NS * rowsT;
+    const int ao = (tid / XL) & 1, at = tid / (2 * XL), atr = at % rows, axq = tid % XL + XL * (at / rows);
+    const int as = atr / rowsT, ay = atr - as * rowsT - 1;
+    const int alds = axq < W / 4 ? ao * POS + atr * WT + 1 + 4 * axq : -1;
+    // (samples beyond the last lie beyond the buffer)
+    const uint32_t aoff = alds >= 0 && (unsigned)(y0 + ay) < (unsigned)g.H
+                              ? (uint32_t)(4 * ((as * g.SC + 8 * ao) * HW + (y0 + ay) * W + 4 * axq)) : kNowhere;
+    // weights: split and in order already
+    constexpr int WP = 6 * 9 * 32, WTURNS = (WP + 255) / 256;
+    const gu4_ptr wsrc = (gu4_ptr)(wsplit + blockIdx.z * wstride + (int64_t)blockIdx.x * WP);
+    const int wchunk = WP * (int)gridDim.x;
+    const int astep = 4 * HW;                    // bytes per source channel
+    f4 av[8];
+    u4 wv[WTURNS];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            av[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)aoff, (c0 + c) * astep, 0));
+        const gu4_ptr w = wsrc + (c0 >> 4) * wchunk;
+#pragma unroll
+        for (int i = 0; i < WTURNS; ++i) wv[i] = w[min(tid + 256 * i, WP - 1)];
+    };
+    auto stash = [&]() {
+        if (alds >= 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x[8] = {av[0][e], av[1][e], av[2][e], av[3][e], av[4][e], av[5][e], av[6][e], av[7][e]};
+                const Split8 s = split8(x);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) As[q * 2 * POS + alds + e] = s.p[q];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < WTURNS; ++i)
+            if (256 * (i + 1) <= WP || tid + 256 * i < WP) Bs[tid + 256 * i] = __builtin_bit_cast(bf8, wv[i]);
+    };
+    if (!BWD && tid < 32) bs[tid] = dc0 + tid < g.DC ? as_global((const float *)p.W)[g.b_off + dc0 + tid] : 0.f;
+    // the halo columns stay zero
+    for (int e = tid; e < 6 * rows * 2; e += 256) {
+        const int side = e & 1, r = (e >> 1) % rows, po = (e >> 1) / rows;
+        bf8 z;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.f;
+        As[po * POS + r * WT + side * (W + 1)] = z;
+    }
+
+    // ---- the wave's pixel tiles ---------------------------------------------------------------
+    int abase[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int px = 32 * (MT * wave + m) + li;
+        const int s = px >> g.lgRW, r = px & ((1 << g.lgRW) - 1);
+        abase[m] = lh * POS + (s * rowsT + (r >> LGW)) * WT + (r & (W - 1));
+    }
+    const int bbase = lh * 32 + li;
+    f16v main[MT], corr[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) main[m][r] = corr[m][r] = 0.f;
+
+    // ---- epilogue: lane has pixel li of the tile, register r channel dc0 + 8 (r / 4) + 4 lh + r % 4:
+    // every access is 128 contiguous bytes of a channel (with the channels over the lanes, 16 bytes
+    // each, the requests to L2 took longer than the products)
+    auto value = [&](int m, int r, float bias) {
+        float v = split_sum(main[m][r], corr[m][r]);
+        if (!BWD) v += bias;
+        if (!BWD && g.relu && !(v > 0.f)) v = 0.f;
+        return v;
+    };
+    auto store = [&]() {
+        if (!BWD && g.pool) {
+            constexpr int LGPW = LGW - 1;
+            const int PHW = (g.H / 2) << LGPW;
+            const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(dst + sample0 * g.DC * PHW, 0, 4 * g.DC * PHW * ns, kBufferFlags);
+            const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(amax + sample0 * g.DC * PHW, 0, g.DC * PHW * ns, kBufferFlags);
+            const bool odd = li & 1, low = LGW == 4 ? (li & 16) != 0 : (li & 8) != 0;   // column, row of the window
+#pragma unroll
+            for (int m = 0; m < MT; m += (LGW == 5 ? 2 : 1)) {
+                // the four lanes of a window (two, where its rows are in two tiles) look after a channel each
+                const int px = 32 * (MT * wave + m) + li, s = px >> g.lgRW, q = px & ((1 << g.lgRW) - 1);
+                const int y = y0 + (q >> LGW), x = q & (W - 1);
+                const int ch = dc0 + 4 * lh + (odd ? 1 : 0) + (LGW != 5 && low ? 2 : 0);
+                const uint32_t o = y < g.H ? (uint32_t)((s * g.DC + ch) * PHW + ((y >> 1) << LGPW) + (x >> 1)) : kNowhere / 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (dc0 + 8 * i >= g.DC) break;
+                    const f4 bias = *reinterpret_cast<const f4 *>(&bs[8 * i + 4 * lh]);
+                    // [channel pair][row of the window, where that is a tile] -> left and right value of the own channel
+                    float left[2][2], right[2][2];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+#pragma unroll
+                        for (int t = 0; t < (LGW == 5 ? 2 : 1); ++t) {
+                            const int mm = m + t < MT ? m + t : MT - 1;
+                            const float v0 = value(mm, 4 * i + 2 * c, bias[2 * c]), v1 = value(mm, 4 * i + 2 * c + 1, bias[2 * c + 1]);
+                            const float own = odd ? v1 : v0, other = dpp_mov<0xB1>(odd ? v0 : v1);
+                            left[c][t] = odd ? other : own;
+                            right[c][t] = odd ? own : other;
+                        }
+#pragma unroll
+                    for (int c = 0; c < (LGW == 5 ? 2 : 1); ++c) {
+                        float k[4];
+                        if (LGW == 5) {
+                            k[0] = left[c][0]; k[1] = right[c][0]; k[2] = left[c][1]; k[3] = right[c][1];
+                        } else if (LGW == 4) {
+                            const auto l = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, left[0][0]), __builtin_bit_cast(int, left[1][0]), false, false);
+                            const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, right[0][0]), __builtin_bit_cast(int, right[1][0]), false, false);
+                            k[0] = __builtin_bit_cast(float, (int)l[0]); k[2] = __builtin_bit_cast(float, (int)l[1]);
+                            k[1] = __builtin_bit_cast(float, (int)r[0]); k[3] = __builtin_bit_cast(float, (int)r[1]);
+                        } else {
+                            const float lo = low ? left[1][0] : left[0][0], lx = dpp_mov<0x128>(low ? left[0][0] : left[1][0]);
+                            const float ro = low ? right[1][0] : right[0][0], rx = dpp_mov<0x128>(low ? right[0][0] : right[1][0]);
+                            k[0] = low ? lx : lo; k[2] = low ? lo : lx;
+                            k[1] = low ? rx : ro; k[3] = low ? ro : rx;
+                        }
+                        float best = k[0];
+                        int which = 0;
+#pragma unroll
+                        for (int j = 1; j < 4; ++j)   // row-major: the first maximum wins
+                            if (k[j] > best) { best = k[j]; which = j; }
+                        const int so = (8 * i + 2 * c) * PHW;
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, best), rd, (int)(4 * o), 4 * so, 0);
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)which, ra, (int)o, so, 0);
+                    }
+                }
+            }
+            return;
+        }
+        const int bytes = 4 * g.DC * HW * ns;
+        const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(dst + sample0 * g.DC * HW, 0, bytes, kBufferFlags);
+        const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(BWD && mask_src ? mask_src : dst) + sample0 * g.DC * HW, 0, bytes, kBufferFlags);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int px = 32 * (MT * wave + m) + li, s = px >> g.lgRW, q = px & ((1 << g.lgRW) - 1);
+            const int y = y0 + (q >> LGW);
+            const uint32_t o = y < g.H ? 4u * (uint32_t)((s * g.DC + dc0 + 4 * lh) * HW + y0 * W + q) : kNowhere;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (dc0 + 8 * i >= g.DC) break;
+                float k[4];
+                f4 bias = {0.f, 0.f, 0.f, 0.f};
+                if (BWD && mask_src) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        k[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, (int)o, 4 * (8 * i + e) * HW, 0));
+                }
+                if (!BWD) bias = *reinterpret_cast<const f4 *>(&bs[8 * i + 4 * lh]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = value(m, 4 * i + e, bias[e]);
+                    if (BWD && mask_src && !(k[e] > 0.f)) v = 0.f;
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rd, (int)o, 4 * (8 * i + e) * HW, 0);
+                }
+            }
+        }
+    };
+
+    // (the next chunk is on its way while the products run; a workgroup that went on to further tiles
+    // and fetched those ahead as well was no faster: 42.4 ms a job against 40.1)
+    fetch(0);
+    for (int c0 = 0; c0 < g.SC; c0 += 16) {
+        __syncthreads();
+        stash();
+        __syncthreads();
+        if (c0 + 16 < g.SC) fetch(c0 + 16);
+        __builtin_amdgcn_sched_barrier(0);
+        bf8 a[2][MT][3], b[2][3];
+        auto operands = [&](int tap, int set) {
+            const int off = (tap / 3) * WT + tap % 3;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                b[set][q] = Bs[bbase + (q * 9 + tap) * 64];
+#pragma unroll
+                for (int m = 0; m < MT; ++m) a[set][m][q] = As[abase[m] + q * 2 * POS + off];
+            }
+        };
+        operands(0, 0);
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            if (tap + 1 < 9) operands(tap + 1, (tap + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);   // the next tap's operands are on their way before the products
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) split_mfma(i, b[tap & 1], a[tap & 1][m], main[m], corr[m]);
+        }
+    }
+    store();
+}
+
+// ---- the weights of a recursion, split ------------------------------------------------------
+// A layer's weights in one direction are pieces of 16 source and 32 destination channels, each as the
+// LDS holds it: [part][tap][octet][32][8], [chunk of source channels][block of destination channels].
+// Splitting them in the convolution's own staging, once per workgroup, took 132 of its 819 vector
+// instructions and wrote LDS with up to nine lanes to a bank.
+constexpr int kSplitPiece = 6 * 9 * 32 * 16;   // bytes
+constexpr int kSplitJobs = 32;   // 16 layers, both directions
+struct SplitJob {
+    char *dst;
+    int64_t w_off;
+    int ic, oc, bwd, nblk, piece0;
+};
+struct SplitJobs {
+    SplitJob j[kSplitJobs];
+    int n;
+};
+
+__global__ void __launch_bounds__(192)
+k_split_weights(const RoundParams *__restrict__ rp, int u, SplitJobs jobs, int64_t stride) {
+    const RoundParams p = rp[blockIdx.z];
+    if (u >= p.m) return;
+    int ji = 0;
+    while (ji + 1 < jobs.n && (int)blockIdx.x >= jobs.j[ji + 1].piece0) ++ji;
+    const SplitJob j = jobs.j[ji];
+    const int piece = (int)blockIdx.x - j.piece0, c0 = 16 * (piece / j.nblk), d0 = 32 * (piece % j.nblk);
+    const gcf_ptr W = as_global((const float *)p.W) + j.w_off;
+    u4 *dst = reinterpret_cast<u4 *>(j.dst + blockIdx.z * stride * 16) + (int64_t)piece * (kSplitPiece / 16);
+    const int lim = j.bwd ? j.ic : j.oc;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int t = (int)threadIdx.x + 192 * i;            // (tap, octet, destination channel)
+        const int tap = t >> 6, o = (t >> 5) & 1, d = d0 + (t & 31), c = c0 + 8 * o;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            x[e] = d >= lim ? 0.f : j.bwd ? W[((int64_t)(c + e) * j.ic + d) * 9 + 8 - tap] : W[((int64_t)d * j.ic + c + e) * 9 + tap];
+        const Split8 s = split8(x);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dst[q * 576 + t] = __builtin_bit_cast(u4, s.p[q]);
+    }
+}
+
+// both maps are the same size: 3 x 3, padding 1; MT: pixel tiles per wave
+bool split_dir(const LayerGeom &L, bool bwd, int MT, SplitDir *d) {
+    if (L.type != 0 || L.k != 3 || L.pad != 1 || L.ic % 16 != 0 || L.oc % 16 != 0) return false;
+    const int W = L.iw, PX = 128 * MT;
+    if (W != 8 && W != 16 && W != 32) return false;
+    d->ic = L.ic; d->oc = L.oc; d->relu = L.relu; d->pool = 0;
+    d->SC = bwd ? L.oc : L.ic; d->DC = bwd ? L.ic : L.oc;
+    d->H = L.ih;
+    d->w_off = L.w_off; d->b_off = L.b_off;
+    if (L.ih == W && L.ih * W < PX) {          // several samples per workgroup
+        d->R = L.ih; d->NS = PX / (L.ih * W); d->rblocks = 1;
+    } else {
+        d->R = PX / W; d->NS = 1; d->rblocks = (L.ih + d->R - 1) / d->R;
+    }
+    d->lgRW = 0;
+    while (1 << d->lgRW < d->R * W) ++d->lgRW;
+    // 32-bit byte offsets
+    return (int64_t)L.in_size * d->NS < (int64_t)1 << 28 && (int64_t)L.out_size * d->NS < (int64_t)1 << 28 &&
+           (int64_t)L.oc * L.ic * 9 < (int64_t)1 << 28;
+}
+
+template <int LGW, int MT, bool BWD>
+hipError_t split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, int B, const SplitDir &d, const u4 *w,
+                        int64_t wstride, const float *src, float *dst, const float *mask_src, uint8_t *amax) {
+    constexpr int lds = SplitTile<LGW, MT>::LDS;
+    if (lds > 64 * 1024) {
+        int dev = 0, done = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        static PerDevice allowed;
+        e = allowed.get(dev, &done, [](int *v) {
+            *v = 1;
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_split<LGW, MT, BWD>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        });
+        if (e != hipSuccess) return e;
+    }
+    k_conv_split<LGW, MT, BWD><<<grid, 256, lds, s>>>(dp, u, B, d, w, wstride, src, dst, mask_src, amax);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd) {
+    SplitDir d;
+    return split_dir(L, bwd, 2, &d) ? (size_t)(d.SC / 16) * ((d.DC + 31) / 32) * kSplitPiece : 0;
+}
+
+// Where this form is the faster one, time here / with kernels_conv_mfma.hip, forward | backward-data,
+// by the workgroups' worth of tiles of 256 pixels x 32 destination channels:
+//                     96            128           192           512           768 and more
+//   32 x 32 px  1.00 | 1.07                  0.70 | 0.85   0.71 | 0.71   0.75 | 0.83 (3,072: 0.81 | 1.05)
+//   16 x 16     1.02 | 1.07   1.01 | 1.06   0.72 | 0.73   0.62 | 0.74   0.74 | 0.84
+//   8 x 8       0.71 | 0.73   0.72 | 0.73   0.50 | 0.54   0.44 | 0.47
+// (8 x 8 images fill half a workgroup there.)  Below that a launch is a chain of trips through
+// memory, one for each chunk of channels, on either.  16 destination channels fill half a
+// tile: 0.9 to 1.4 everywhere.
+static bool conv_split_pays(const LayerGeom &L, bool bwd, int B, int nact) {
+    SplitDir d;
+    if (!split_dir(L, bwd, 2, &d) || d.DC < 32) return false;
+    const int64_t wgs = (int64_t)d.rblocks * ((B + d.NS - 1) / d.NS) * ((d.DC + 31) / 32) * nact;
+    return wgs >= (L.iw == 8 ? 96 : 192);
+}
+
+bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, const SplitWeights &sw) {
+    return sw.base && sw.off[l][bwd] >= 0 && conv_split_pays(lay[l], bwd, B, nact);
+}
+
+hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
+                                const SplitWeights &sw) {
+    SplitJobs jobs;
+    jobs.n = 0;
+    int pieces = 0;
+    for (int l = 0; l < L; ++l)
+        for (int bwd = 0; bwd < 2; ++bwd) {
+            if (!conv_split_used(lay, l, bwd, B, nact, sw)) continue;
+            SplitJob &j = jobs.j[jobs.n++];
+            j.bwd = bwd;
+            j.ic = lay[l].ic; j.oc = lay[l].oc;
+            j.w_off = lay[l].w_off;
+            j.dst = sw.base + sw.off[l][bwd];
+            j.piece0 = pieces;
+            j.nblk = ((bwd ? lay[l].ic : lay[l].oc) + 31) / 32;
+            pieces += (bwd ? lay[l].oc : lay[l].ic) / 16 * j.nblk;
+        }
+    if (pieces == 0) return hipSuccess;
+    k_split_weights<<<dim3((unsigned)pieces, 1, (unsigned)nact), 192, 0, s>>>(dp, u, jobs, sw.stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
+                             const LayerGeom &L, bool bwd, const SplitWeights &sw, int64_t off, const float *src, float *dst,
+                             const float *mask_src, uint8_t *amax) {
+    SplitDir d;
+    const u4 *w = reinterpret_cast<const u4 *>(sw.base + off);
+    const int MT = 2;
+    if (!split_dir(L, bwd, MT, &d)) return hipErrorInvalidValue;
+    d.pool = amax != nullptr;
+    const dim3 grid((unsigned)((d.DC + 31) / 32), (unsigned)(d.rblocks * ((B + d.NS - 1) / d.NS)), (unsigned)nact);
+    const int fam = bwd ? F_CONV_BWD_DATA : F_CONV_FWD;
+    const bool timed = prof && prof->on[fam];
+    if (timed) prof->before(fam, s);
+    hipError_t e = hipErrorInvalidValue;
+#define AET_SPLIT(lgw, mt) \
+    if (L.iw == 1 << lgw && MT == mt) e = bwd ? split_launch<lgw, mt, true>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax) \
+                                              : split_launch<lgw, mt, false>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax);
+    AET_SPLIT(3, 2) AET_SPLIT(4, 2) AET_SPLIT(5, 2)
+#undef AET_SPLIT
+    if (timed) prof->after(fam, s);
+    return e;
+}
+
+}  // namespace aet

@@ -661,14 +661,23 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         AET_TIMED(F_GATHER, k_gather<<<grid, 256, 0, s>>>(dp, u, B, D, sc.act[0], sc.labels));
         AET_RETURN_IF(hipGetLastError());
     }
+    if (sc.split.base && !sc.plain) AET_RETURN_IF(launch_split_weights(s, dp, nact, u, lay, L, B, sc.split));
+    auto split = [&](int l, bool bwd) {
+        return !sc.plain && conv_split_used(lay, l, bwd, B, nact, sc.split);
+    };
     // the last layer, forward to update, in one launch
     const bool head = !sc.plain && L > 1 && dense_head_pays(lay[L - 1], B, nact);
     const int LF = head ? L - 1 : L;
     for (int l = 0; l < LF; ++l) {
         const LayerGeom &g = lay[l];
         if (g.type == 0 && !sc.plain && l + 1 < L && lay[l + 1].type == 1 && conv_pool_fused(g, lay[l + 1])) {
-            AET_RETURN_IF(launch_conv_mfma(s, prof, dp, nact, u, B, g, false, sc.act[l], sc.act[l + 2], nullptr, sc.amax[l + 1]));
+            if (split(l, false))
+                AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, false, sc.split, sc.split.off[l][0], sc.act[l], sc.act[l + 2], nullptr, sc.amax[l + 1]));
+            else
+                AET_RETURN_IF(launch_conv_mfma(s, prof, dp, nact, u, B, g, false, sc.act[l], sc.act[l + 2], nullptr, sc.amax[l + 1]));
             ++l;   // the pooling layer
+        } else if (g.type == 0 && split(l, false)) {
+            AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, false, sc.split, sc.split.off[l][0], sc.act[l], sc.act[l + 1], nullptr, nullptr));
         } else if (g.type == 0) {
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 0, sc.act[l], nullptr,
                                         sc.act[l + 1], nullptr, !sc.plain));
@@ -707,7 +716,9 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
             if (l > 0 && !sc.plain && !conv_wgrad_direct_ok(g))
                 AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad[l], later, &taken));
             if (taken) continue;
-            if (l > 0)
+            if (l > 0 && split(l, true))
+                AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], sc.del[l + 1], sc.del[l], mask, nullptr));
+            else if (l > 0)
                 AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 1, sc.del[l + 1], nullptr,
                                             sc.del[l], mask, !sc.plain));
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 2, sc.act[l], sc.del[l + 1],

@@ -1,0 +1,110 @@
+"""Convolutions whose fp32 values are split in three bf16 parts: parity with the CPU oracle where the
+tiling can go wrong, precision against 64 bits, values that are not finite.  Run with  -m gpu  on
+an MI355X."""
+import re
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _conv(cout):
+    return W.Layer(W.CONV, cout, 3, 1, 1)
+
+
+def _maps(n, batch, shape, layers, rounds=2):
+    """A model on maps of the given (channels, rows, columns)."""
+    wl = W.config4(n_clients=n, n_per=70, hw=8, width=4, fc=8, batch=batch, rounds=rounds, a=0, b=batch)
+    wl.model = W.Model(*shape, layers + [W.Layer(W.DENSE, 10)], batch)
+    wl.X = [W._rng(3, c).standard_normal((70, wl.model.in_size()), dtype=np.float32) for c in range(n)]
+    wl.w0 = W.init_weights(wl.model, 5)
+    return wl
+
+
+# enough samples that each launch has the workgroups' worth of tiles from which this form is taken
+CASES = {
+    # 32 x 32 (pooled), 16 x 16 (both, pooled), two channel blocks
+    "cnn32": lambda: W.config4(n_clients=4, n_per=70, batch=50, fc=16, rounds=1, a=0, b=50),
+    # 8 x 8: four samples per workgroup, the last with two; 16 source channels: one chunk
+    "cnn16_b50": lambda: W.config4(n_clients=8, n_per=70, hw=16, width=16, fc=16, batch=50, rounds=2, a=0, b=50),
+    # 48 channels: a block of destination channels half full, three chunks
+    "cnn16_48": lambda: W.config4(n_clients=5, n_per=70, hw=16, width=24, fc=16, batch=41, rounds=2, a=0, b=41),
+    # 12 x 32: the second row block half empty; not pooled; the first layer has no backward-data
+    "rows_12_of_32": lambda: _maps(2, 48, (16, 12, 32), [_conv(32), _conv(32), W.Layer(W.POOL)]),
+    # 6 x 16: fewer rows than a workgroup has
+    "rows_6_of_16": lambda: _maps(4, 60, (32, 6, 16), [_conv(32), _conv(32)]),
+    # 10 x 8: rows of 8 that are no square map
+    "rows_10_of_8": lambda: _maps(4, 60, (16, 10, 8), [_conv(32), _conv(48), W.Layer(W.POOL)]),
+}
+
+
+def _smallest_workspace(monkeypatch, make):
+    """A context without room for what is optional: its convolutions stay on the fp32 unit."""
+    from paper_2112_13935_amd.binding import AetError
+    from paper_2112_13935_amd.runner import Run
+    run = Run(make())
+    lib = run.lib.lib
+    run.close()
+    size = [256]
+    with monkeypatch.context() as m:
+        m.setattr(lib, "aet_workspace_bytes", lambda *a: size[0])
+        with pytest.raises(AetError) as err:
+            Run(make())
+        size[0] = int(re.search(r"(\d+) needed", str(err.value)).group(1))
+        return Run(make())
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_parity(oracle_libs, name):
+    from oracle import Oracle
+    from paper_2112_13935_amd.runner import Run
+    from parity import lockstep
+    wl = CASES[name]()
+    run, orc = Run(wl), Oracle(wl, "f64")
+    lockstep(wl, run, orc)
+    run.close()
+
+
+@pytest.mark.parametrize("n,batch,shape", [(2, 50, (16, 32, 32)), (4, 50, (32, 16, 16)), (8, 50, (64, 8, 8))])
+def test_no_further_from_64_bits_than_the_fp32_unit(oracle_libs, monkeypatch, n, batch, shape):
+    """U of one recursion of two convolutions without ReLU or pooling (no decisions that rounding could
+    turn): the split products round less often (see split_bf16.h), so their error is the smaller one."""
+    from oracle import Oracle
+    from paper_2112_13935_amd.runner import Run
+
+    def make():
+        return _maps(n, batch, shape, [W.Layer(W.CONV, 32, 3, 1, 0), W.Layer(W.CONV, 64, 3, 1, 0)], rounds=1)
+    orc = Oracle(make(), "f64")
+    orc.run_round()
+    err = []
+    for run in (Run(make()), _smallest_workspace(monkeypatch, make)):
+        run.run_round()
+        d = [run.lib.aet_get_U(c, 0) - orc.get_U(c, 0) for c in range(orc.n)]
+        err.append(np.sqrt(sum((x ** 2).sum() for x in d) / sum((orc.get_U(c, 0) ** 2).sum() for c in range(orc.n))))
+        run.close()
+    print(f"{shape}: split {err[0]:.2e}, fp32 unit {err[1]:.2e}")
+    assert err[0] != err[1], "the split form was not taken"
+    assert err[0] < err[1]
+
+
+def test_infinities_stay_where_they_were(monkeypatch):
+    """One infinite pixel in one client's rows: the same entries of its model are finite, infinite and
+    NaN as with the products on the fp32 unit."""
+    from paper_2112_13935_amd.runner import Run
+
+    def make():
+        wl = CASES["cnn32"]()
+        wl.X[1] = wl.X[1].copy()
+        wl.X[1][:, 700] = np.inf
+        return wl
+    out = []
+    for run in (Run(make()), _smallest_workspace(monkeypatch, make)):
+        run.run_round()
+        out.append(np.stack([run.lib.aet_get_U(c, 0) for c in range(run.n)]))
+        run.close()
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(out[0]), kind(out[1]))
+    assert np.isfinite(out[0][0]).all() and not np.isfinite(out[0][1]).all()
