@@ -151,6 +151,11 @@ hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, 
 hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                              const LayerGeom &L, bool bwd, const SplitWeights &sw, int64_t off, const float *src, float *dst,
                              const float *mask_src, uint8_t *amax);
+// backward-weight: slices (partial results) per client, at most cap over all; 0: no such form.  KP, OCP: columns
+// and rows of a partial result
+int conv_wgrad_split_slices(const LayerGeom &L, int B, int nact, int cap);
+hipError_t launch_conv_wgrad_split(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L, int S, int KP,
+                                   int OCP, const float *in, const float *dout, float *partial);
 // amax != NULL (forward only): dst is the output of the 2 x 2 pooling layer behind it, amax its winners
 bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool);
 bool conv_wgrad_mfma_supported(const LayerGeom &L, int B);

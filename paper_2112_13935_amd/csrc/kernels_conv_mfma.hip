@@ -1182,6 +1182,16 @@ hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundPara
                                   float *partial, FinishList *later) {
     WgradGeom g;
     if (!wgrad_geom(L, B, nact, &g)) return hipErrorInvalidValue;
+    const int slices = conv_wgrad_split_slices(L, B, nact, wgrad_target(L));
+    if (slices > 0) {
+        g.S = slices;
+        const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
+        if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
+        hipError_t e = launch_conv_wgrad_split(s, dp, nact, u, B, L, slices, 16 * g.NTT, 16 * g.MTT, in, dout, partial);
+        if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, g, partial, later);
+        if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
+        return e;
+    }
     const size_t lds = wgrad_lds_bytes(g);
     const int mt = wgrad_mt(g), ntw = wgrad_ntw(g), wm = wgrad_wm(g);
     dim3 none(1, 1, 1);

@@ -280,6 +280,197 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
     store();
 }
 
+// ---- backward-weight ----------------------------------------------------------------------------
+// g[oc][ci][ky][kx] = sum over samples and pixels of dout[oc][y][x] in[ci][y+ky-1][x+kx-1]
+// M = 32 output channels, N = 32 input channels for each of the nine taps, K = pixels in steps of 16 (a
+// lane's eight elements are neighbours in a row).  A workgroup accumulates its slice of the client's
+// pixels for one (oc, ci) block and writes one partial result, in the layout and for the finish
+// kernel of kernels_conv_mfma.hip.  Its six waves are the three filter rows, twice: the two halves
+// take turns at the steps and are added at the end.  The three taps of a filter row read the same
+// pixels, shifted: the shifted operands are put together from aligned ones, not read.
+//
+// What bounds it: as above the clock under the power limit, then the staging between two
+// barriers, which only the compute unit's second workgroup covers (no registers are left to fetch the
+// next tile ahead: 96 accumulators of 168).  64 -> 64 channels at 16 x 16, 32 clients x 64 samples: 378
+// -> 260 us; 32 -> 32 at 32 x 32: 389 -> 278 us.
+struct SplitWgrad {
+    int IC, OC, H;
+    int items;           // tiles of R rows per sample
+    int units, U, S;     // 32-pixel units of a client, per slice; slices
+    int KP, OCP;         // the partial result's columns and rows
+    int cblocks;         // blocks of 32 input channels
+};
+
+template <int LGW>
+struct SplitWgradTile {
+    static constexpr int W = 1 << LGW, R = W == 32 ? 4 : 8, PX = R * W;
+    static constexpr int UNITS = PX / 32;                       // of a tile
+    static constexpr int RS = W + 8, ROWST = R + 2;             // a row: 8 elements of zeros (x = -1 is the last of them), the pixels
+    // 16-byte pieces of a channel, one part; the zeros behind the last row; odd, so that 16 lanes of
+    // an operand read meet 16 different places
+    static constexpr int IN = (ROWST * RS + 8) / 8 | 1, DO = PX / 8 | 1;
+    static constexpr int LDS = 3 * 32 * (IN + DO) * 16;
+    static constexpr int OUT = 32 * 288 * 4;                    // the partial result takes the tiles' place
+    static_assert(OUT <= LDS || W == 8, "room for the result");
+    static constexpr int BYTES = LDS > OUT ? LDS : OUT;
+};
+
+constexpr int kWgThreads = 384;
+
+template <int LGW>
+__global__ void __launch_bounds__(kWgThreads, 3)
+k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad g, const float *__restrict__ in,
+                   const float *__restrict__ dout, float *__restrict__ partial) {
+    typedef SplitWgradTile<LGW> T;
+    constexpr int W = T::W, R = T::R, IN = T::IN, DO = T::DO, W8 = W / 8;
+    if (u >= rp[blockIdx.z].m) return;
+    extern __shared__ __attribute__((aligned(16))) bf8 sm[];
+    bf8 *const Is = sm;                   // [3][32][IN]
+    bf8 *const Ds = sm + 3 * 32 * IN;     // [3][32][DO]
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ky = wave % 3, half = wave / 3;
+    const int oc0 = 32 * ((int)blockIdx.y / g.cblocks), ci0 = 32 * ((int)blockIdx.y % g.cblocks);
+    const int HW = g.H * W;
+
+    // zeros around the rows: never written again
+    for (int e = tid; e < 3 * 32 * (T::ROWST + 1); e += kWgThreads) {
+        bf8 z;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.f;
+        Is[e / (T::ROWST + 1) * IN + e % (T::ROWST + 1) * (T::RS / 8)] = z;
+    }
+    // staging: octets of pixels, [channel][row][octet]
+    constexpr int ITASKS = 32 * T::ROWST * W8, ITURNS = (ITASKS + kWgThreads - 1) / kWgThreads;
+    constexpr int DTASKS = 32 * R * W8, DTURNS = (DTASKS + kWgThreads - 1) / kWgThreads;
+    float bsum[DTURNS];
+#pragma unroll
+    for (int i = 0; i < DTURNS; ++i) bsum[i] = 0.f;
+    f4 iv[ITURNS][2], dv[DTURNS][2];
+    auto fetch = [&](int it) {
+        const int b = it / g.items, y0 = (it - b * g.items) * R;
+        const int64_t sample = (int64_t)blockIdx.z * B + b;
+        const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(in) + (sample * g.IC + ci0) * HW, 0, 4 * (g.IC - ci0) * HW, kBufferFlags);
+        const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(dout) + (sample * g.OC + oc0) * HW, 0, 4 * (g.OC - oc0) * HW, kBufferFlags);
+#pragma unroll
+        for (int i = 0; i < ITURNS; ++i) {
+            const int t = tid + kWgThreads * i, x8 = t % W8, row = t / W8 % T::ROWST, c = t / (W8 * T::ROWST);
+            const int y = y0 + row - 1;
+            const bool ok = t < ITASKS && (unsigned)y < (unsigned)g.H;
+            const uint32_t off = ok ? 4u * (uint32_t)(c * HW + y * W + 8 * x8) : kNowhere;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) iv[i][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ri, (int)off, 16 * q, 0));
+        }
+#pragma unroll
+        for (int i = 0; i < DTURNS; ++i) {
+            const int t = tid + kWgThreads * i, o = t % (R * W8), c = t / (R * W8);
+            const uint32_t off = t < DTASKS ? 4u * (uint32_t)(c * HW + y0 * W + 8 * o) : kNowhere;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) dv[i][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)off, 16 * q, 0));
+        }
+    };
+    // count: the pixels of the tile that are this slice's own, in octets (for the bias)
+    auto stash = [&](int o_lo, int o_hi) {
+#pragma unroll
+        for (int i = 0; i < ITURNS; ++i) {
+            const int t = tid + kWgThreads * i, x8 = t % W8, row = t / W8 % T::ROWST, c = t / (W8 * T::ROWST);
+            if (t < ITASKS) {
+                const float x[8] = {iv[i][0][0], iv[i][0][1], iv[i][0][2], iv[i][0][3], iv[i][1][0], iv[i][1][1], iv[i][1][2], iv[i][1][3]};
+                const Split8 s = split8(x);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) Is[(q * 32 + c) * IN + row * (T::RS / 8) + 1 + x8] = s.p[q];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < DTURNS; ++i) {
+            const int t = tid + kWgThreads * i, o = t % (R * W8), c = t / (R * W8);
+            if (t < DTASKS) {
+                const float x[8] = {dv[i][0][0], dv[i][0][1], dv[i][0][2], dv[i][0][3], dv[i][1][0], dv[i][1][1], dv[i][1][2], dv[i][1][3]};
+                const Split8 s = split8(x);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) Ds[(q * 32 + c) * DO + o] = s.p[q];
+                if (o >= o_lo && o < o_hi) bsum[i] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            }
+        }
+    };
+
+    f16v main[3], corr[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) main[k][r] = corr[k][r] = 0.f;
+
+    const int u0 = (int)blockIdx.x * g.U, u1 = min(u0 + g.U, g.units);
+    const uint32_t *const Iw = reinterpret_cast<const uint32_t *>(Is);
+    for (int it = u0 / T::UNITS; it * T::UNITS < u1; ++it) {
+        fetch(it);
+        const int lo = max(u0 - it * T::UNITS, 0), hi = min(u1 - it * T::UNITS, T::UNITS);
+        __syncthreads();   // the products of the previous tile are done with the tiles
+        stash(4 * lo, 4 * hi);
+        __syncthreads();
+        for (int un = lo; un < hi; ++un) {
+            const int o = 4 * un + 2 * half + lh;      // the lane's octet of the tile
+            const int row = o / W8 + ky, x8 = o % W8;
+            bf8 a[3], b[3][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                a[q] = Ds[(q * 32 + li) * DO + o];
+                const int at = (q * 32 + li) * IN + row * (T::RS / 8) + 1 + x8;
+                const u4 c = __builtin_bit_cast(u4, Is[at]);
+                const uint32_t l = Iw[4 * at - 1], r = Iw[4 * at + 4];
+                const uint32_t m1 = __builtin_amdgcn_alignbit(c[1], c[0], 16), m2 = __builtin_amdgcn_alignbit(c[2], c[1], 16),
+                               m3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
+                b[0][q] = __builtin_bit_cast(bf8, u4{(uint32_t)__builtin_amdgcn_alignbit(c[0], l, 16), m1, m2, m3});
+                b[1][q] = __builtin_bit_cast(bf8, c);
+                b[2][q] = __builtin_bit_cast(bf8, u4{m1, m2, m3, (uint32_t)__builtin_amdgcn_alignbit(r, c[3], 16)});
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) split_mfma(i, a, b[k], main[k], corr[k]);
+        }
+    }
+
+    // ---- partial[client][slice][oc][k], k = ci * 9 + tap: the halves are added in LDS ----------------
+    float *const out = reinterpret_cast<float *>(sm);     // [32][288]
+    const gf_ptr pg = as_global(partial) + ((int64_t)blockIdx.z * g.S + blockIdx.x) * g.OCP * g.KP;
+    if (ci0 == 0) {   // the bias column: the threads of a channel are neighbours in a row of 16 lanes (of 8)
+#pragma unroll
+        for (int i = 0; i < DTURNS; ++i) {
+            float v = bsum[i];
+            v += dpp_mov<0xB1>(v);
+            v += dpp_mov<0x4E>(v);
+            v += dpp_mov<0x141>(v);
+            if (R * W8 == 16) v += dpp_mov<0x140>(v);
+            const int t = tid + kWgThreads * i, c = t / (R * W8);
+            if (t < DTASKS && t % (R * W8) == 0 && oc0 + c < g.OC) pg[(int64_t)(oc0 + c) * g.KP + 9 * g.IC] = v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 1; h >= 0; --h) {
+        if (half == h) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float *p = out + (8 * (r / 4) + 4 * lh + r % 4) * 288 + li * 9 + 3 * ky + k;
+                    const float v = split_sum(main[k][r], corr[k][r]);
+                    *p = h == 1 ? v : v + *p;
+                }
+        }
+        __syncthreads();
+    }
+    const int cols4 = min(32, g.IC - ci0) * 9 / 4, rows = min(32, g.OC - oc0);   // IC is a multiple of 16
+    for (int e = tid; e < rows * cols4; e += kWgThreads) {
+        const int r = e / cols4, c = e - r * cols4;
+        *reinterpret_cast<f4 __attribute__((address_space(1))) *>(pg + (int64_t)(oc0 + r) * g.KP + 9 * ci0 + 4 * c) =
+            *reinterpret_cast<const f4 *>(out + r * 288 + 4 * c);
+    }
+}
+
 // ---- the weights of a recursion, split ------------------------------------------------------
 // A layer's weights in one direction are pieces of 16 source and 32 destination channels, each as the
 // LDS holds it: [part][tap][octet][32][8], [chunk of source channels][block of destination channels].
@@ -342,6 +533,8 @@ bool split_dir(const LayerGeom &L, bool bwd, int MT, SplitDir *d) {
     return (int64_t)L.in_size * d->NS < (int64_t)1 << 28 && (int64_t)L.out_size * d->NS < (int64_t)1 << 28 &&
            (int64_t)L.oc * L.ic * 9 < (int64_t)1 << 28;
 }
+
+constexpr int kSplitResident = 512;   // workgroups of a launch that are resident together: two per compute unit
 
 template <int LGW, int MT, bool BWD>
 hipError_t split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, int B, const SplitDir &d, const u4 *w,
@@ -432,6 +625,64 @@ hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *d
 #undef AET_SPLIT
     if (timed) prof->after(fam, s);
     return e;
+}
+
+// ---- backward-weight -----------------------------------------------------------------------------
+template <int LGW>
+static hipError_t wgrad_split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, int B, const SplitWgrad &g,
+                                     const float *in, const float *dout, float *partial) {
+    constexpr int lds = SplitWgradTile<LGW>::BYTES;
+    if (lds > 64 * 1024) {
+        int dev = 0, done = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        static PerDevice allowed;
+        e = allowed.get(dev, &done, [](int *v) {
+            *v = 1;
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_wgrad_split<LGW>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        });
+        if (e != hipSuccess) return e;
+    }
+    k_conv_wgrad_split<LGW><<<grid, kWgThreads, lds, s>>>(dp, u, B, g, in, dout, partial);
+    return hipGetLastError();
+}
+
+// Where it is the faster form, time here / with kernels_conv_mfma.hip, finish included:
+//   more than one block of 32 x 32 channels: 0.54 .. 0.91 at every size
+//   one block, by its pixels / 256   up to 32       48 .. 128      192           512 and more
+//     32 -> 32 channels              0.64 .. 1.08   0.96 .. 1.14   0.83 .. 0.98   0.67 .. 0.88
+//     16 -> 32                       0.71 .. 1.12   0.96 .. 1.25   0.94 .. 0.97   0.81 .. 0.82
+//     16 -> 16                       0.97 .. 1.13   1.02 .. 1.34   1.07 .. 1.15   1.01 .. 1.16
+// (CNN on 32 x 32, 32 clients, 4 rounds: 42.6 -> 37.0 ms.)
+int conv_wgrad_split_slices(const LayerGeom &L, int B, int nact, int cap) {
+    if (L.type != 0 || L.k != 3 || L.pad != 1 || L.ic % 16 != 0 || L.oc % 16 != 0) return 0;
+    const int W = L.iw, R = W == 32 ? 4 : 8;
+    if ((W != 8 && W != 16 && W != 32) || L.ih % R != 0) return 0;
+    if (L.in_size >= (int64_t)1 << 28 || L.out_size >= (int64_t)1 << 28) return 0;   // 32-bit byte offsets
+    const int pairs = ((L.oc + 31) / 32) * ((L.ic + 31) / 32), units = B * L.ih * W / 32;
+    if (pairs == 1 && (L.ic * L.oc < 512 || (int64_t)units * nact < 8 * 192)) return 0;
+    int S = kSplitResident / (nact * pairs);
+    if (S * nact > cap) S = cap / nact;
+    if (S < 1) S = 1;
+    const int U = (units + S - 1) / S;
+    return (units + U - 1) / U;   // the fewest slices with the same longest share
+}
+
+hipError_t launch_conv_wgrad_split(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L, int S, int KP,
+                                   int OCP, const float *in, const float *dout, float *partial) {
+    SplitWgrad g;
+    g.IC = L.ic; g.OC = L.oc; g.H = L.ih;
+    const int W = L.iw, R = W == 32 ? 4 : 8;
+    g.items = L.ih / R;
+    g.units = B * L.ih * W / 32;
+    g.U = (g.units + S - 1) / S;
+    g.S = S;
+    g.KP = KP; g.OCP = OCP;
+    g.cblocks = (L.ic + 31) / 32;
+    const dim3 grid((unsigned)S, (unsigned)((L.oc + 31) / 32 * g.cblocks), (unsigned)nact);
+    if (W == 8) return wgrad_split_launch<3>(s, grid, dp, u, B, g, in, dout, partial);
+    if (W == 16) return wgrad_split_launch<4>(s, grid, dp, u, B, g, in, dout, partial);
+    return wgrad_split_launch<5>(s, grid, dp, u, B, g, in, dout, partial);
 }
 
 }  // namespace aet

@@ -33,10 +33,14 @@ CASES = {
     # 48 channels: a block of destination channels half full, three chunks
     "cnn16_48": lambda: W.config4(n_clients=5, n_per=70, hw=16, width=24, fc=16, batch=41, rounds=2, a=0, b=41),
     # 12 x 32: the second row block half empty; not pooled; the first layer has no backward-data
-    "rows_12_of_32": lambda: _maps(2, 48, (16, 12, 32), [_conv(32), _conv(32), W.Layer(W.POOL)]),
+    "rows_12_of_32": lambda: _maps(3, 48, (16, 12, 32), [_conv(32), _conv(32), W.Layer(W.POOL)]),
     # 6 x 16: fewer rows than a workgroup has
     "rows_6_of_16": lambda: _maps(4, 60, (32, 6, 16), [_conv(32), _conv(32)]),
     # 10 x 8: rows of 8 that are no square map
+    # 16 x 8 and few pixels: only backward-weight takes this form, one and three samples a client
+    "rows_16_of_8": lambda: _maps(4, 60, (32, 16, 8), [_conv(64), _conv(48), W.Layer(W.POOL)]),
+    "one_sample": lambda: _maps(2, 1, (32, 8, 8), [_conv(64), _conv(64)]),
+    "three_samples": lambda: _maps(1, 3, (48, 16, 16), [_conv(64), _conv(64)]),
     "rows_10_of_8": lambda: _maps(4, 60, (16, 10, 8), [_conv(32), _conv(48), W.Layer(W.POOL)]),
 }
 
