@@ -147,7 +147,8 @@ bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, con
 // the weights of this recursion for every layer and direction that is used
 hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
                                 const SplitWeights &sw);
-// off: of the layer's weights in this direction, in sw
+// off: of the layer's weights in this direction, in sw.  amax: forward, as for launch_conv_mfma; backward-
+// data, not NULL: src is the gradient at the outputs of the 2 x 2 pooling layer behind, amax its winners
 hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                              const LayerGeom &L, bool bwd, const SplitWeights &sw, int64_t off, const float *src, float *dst,
                              const float *mask_src, uint8_t *amax);
@@ -155,7 +156,7 @@ hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *d
 // and rows of a partial result
 int conv_wgrad_split_slices(const LayerGeom &L, int B, int nact, int cap);
 hipError_t launch_conv_wgrad_split(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L, int S, int KP,
-                                   int OCP, const float *in, const float *dout, float *partial);
+                                   int OCP, const float *in, const float *dout, const uint8_t *amax, float *partial);
 // amax != NULL (forward only): dst is the output of the 2 x 2 pooling layer behind it, amax its winners
 bool conv_pool_fused(const LayerGeom &L, const LayerGeom &pool);
 bool conv_wgrad_mfma_supported(const LayerGeom &L, int B);
@@ -169,7 +170,11 @@ hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundPa
                                     const FinishList &later);
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial, FinishList *later);
+                                  float *partial, FinishList *later, const uint8_t *amax = nullptr);
+// whether the two backward kernels of a convolution both take the gradient of the 2 x 2 pooling layer behind it
+// (backward-data: where it runs in the split form) and put their own together from it and the winners; amax
+// then goes to launch_conv_wgrad_mfma
+bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact);
 // backward-data and backward-weight of a layer in one launch where both are small
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                                 const LayerGeom &L, const float *dout, float *din, const float *mask_src,

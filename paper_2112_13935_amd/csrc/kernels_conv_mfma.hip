@@ -1142,44 +1142,65 @@ hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundPa
 // most one workgroup per compute unit and the slices get as many again, so that all of both are
 // resident together; beyond that each fills the GPU by itself.  3 x 3 layers of up to 32
 // channels on both sides (the instantiations that exist).
+namespace {
+struct PairPlan {
+    ConvDir d;
+    WgradGeom w;
+    int nd, dx;
+    size_t lds;
+    void (*kernel)(const RoundParams *, int, int, ConvDir, int, int, WgradGeom, const float *, float *, const float *,
+                   const float *, float *);
+};
+}  // namespace
+
+static bool pair_plan(const LayerGeom &L, int B, int nact, PairPlan *p) {
+    ConvDir &d = p->d;
+    WgradGeom &w = p->w;
+    if (L.k != 3 || !conv_mfma_supported(L, true) || !conv_wgrad_mfma_supported(L, B)) return false;
+    if (!conv_dir(L, true, &d, 2) || !wgrad_geom(L, B, nact, &w)) return false;
+    const int cus = device_cus();
+    p->dx = (d.DC + 16 * d.NT - 1) / (16 * d.NT) * ((d.DH + d.R - 1) / d.R);
+    if ((int64_t)p->dx * B * nact > cus) return false;
+    const int mt = wgrad_mt(w), ntw = wgrad_ntw(w);
+    if (d.CCH != kCch || (!d.vec && d.npos != 1) || wgrad_wm(w) != 1 || mt > 2) return false;
+    wgrad_slices(L, B, nact, cus, &w);
+    p->nd = p->dx * B * nact;
+    const size_t la = conv_lds_bytes(d, 3), lb = wgrad_lds_bytes(w);
+    p->lds = la > lb ? la : lb;
+    p->kernel = nullptr;
+#define AET_PAIR(nt, m, n)                                                                              \
+    if (d.NT == nt && mt == m && ntw == n)                                                              \
+        p->kernel = d.vec ? (w.vec ? k_conv_bwd_pair<nt, true, m, n, true> : nullptr)                   \
+                          : (w.vec ? k_conv_bwd_pair<nt, false, m, n, true> : k_conv_bwd_pair<nt, false, m, n, false>);
+    AET_PAIR(1, 1, 2) AET_PAIR(1, 2, 2) AET_PAIR(1, 1, 5) AET_PAIR(1, 2, 5) AET_PAIR(2, 1, 5) AET_PAIR(2, 2, 5)
+#undef AET_PAIR
+    return p->kernel != nullptr;
+}
+
+bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact) {
+    PairPlan p;
+    return 2 * pool.oh == L.oh && 2 * pool.ow == L.ow && pool.oc == L.oc && conv_wgrad_mfma_supported(L, B) &&
+           conv_wgrad_split_slices(L, B, nact, wgrad_target(L)) > 0 && !pair_plan(L, B, nact, &p);
+}
+
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                                 const LayerGeom &L, const float *dout, float *din, const float *mask_src,
                                 const float *in, float *partial, FinishList *later, bool *taken) {
-    *taken = false;
-    ConvDir d;
-    WgradGeom w;
-    if (L.k != 3 || !conv_mfma_supported(L, true) || !conv_wgrad_mfma_supported(L, B)) return hipSuccess;
-    if (!conv_dir(L, true, &d, 2) || !wgrad_geom(L, B, nact, &w)) return hipSuccess;
-    const int cus = device_cus();
-    const int dx = (d.DC + 16 * d.NT - 1) / (16 * d.NT) * ((d.DH + d.R - 1) / d.R);
-    if ((int64_t)dx * B * nact > cus) return hipSuccess;
-    const int mt = wgrad_mt(w), ntw = wgrad_ntw(w);
-    if (d.CCH != kCch || (!d.vec && d.npos != 1) || wgrad_wm(w) != 1 || mt > 2) return hipSuccess;
-    wgrad_slices(L, B, nact, cus, &w);
-    const int nd = dx * B * nact;
-    const size_t la = conv_lds_bytes(d, 3), lb = wgrad_lds_bytes(w), lds = la > lb ? la : lb;
-    void (*kernel)(const RoundParams *, int, int, ConvDir, int, int, WgradGeom, const float *, float *, const float *,
-                   const float *, float *) = nullptr;
-#define AET_PAIR(nt, m, n)                                                                              \
-    if (d.NT == nt && mt == m && ntw == n)                                                              \
-        kernel = d.vec ? (w.vec ? k_conv_bwd_pair<nt, true, m, n, true> : nullptr)                      \
-                       : (w.vec ? k_conv_bwd_pair<nt, false, m, n, true> : k_conv_bwd_pair<nt, false, m, n, false>);
-    AET_PAIR(1, 1, 2) AET_PAIR(1, 2, 2) AET_PAIR(1, 1, 5) AET_PAIR(1, 2, 5) AET_PAIR(2, 1, 5) AET_PAIR(2, 2, 5)
-#undef AET_PAIR
-    if (!kernel) return hipSuccess;
-    *taken = true;
+    PairPlan p;
+    *taken = pair_plan(L, B, nact, &p);
+    if (!*taken) return hipSuccess;
     const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
     if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
-    kernel<<<(unsigned)(nd + w.S * nact), 256, lds, s>>>(dp, u, B, d, nd, dx, w, dout, din, mask_src, in, partial);
+    p.kernel<<<(unsigned)(p.nd + p.w.S * nact), 256, p.lds, s>>>(dp, u, B, p.d, p.nd, p.dx, p.w, dout, din, mask_src, in, partial);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, w, partial, later);
+    if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, p.w, partial, later);
     if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
     return e;
 }
 
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial, FinishList *later) {
+                                  float *partial, FinishList *later, const uint8_t *amax) {
     WgradGeom g;
     if (!wgrad_geom(L, B, nact, &g)) return hipErrorInvalidValue;
     const int slices = conv_wgrad_split_slices(L, B, nact, wgrad_target(L));
@@ -1187,11 +1208,12 @@ hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundPara
         g.S = slices;
         const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
         if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
-        hipError_t e = launch_conv_wgrad_split(s, dp, nact, u, B, L, slices, 16 * g.NTT, 16 * g.MTT, in, dout, partial);
+        hipError_t e = launch_conv_wgrad_split(s, dp, nact, u, B, L, slices, 16 * g.NTT, 16 * g.MTT, in, dout, amax, partial);
         if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, g, partial, later);
         if (timed) prof->after(F_CONV_BWD_WEIGHT, s);
         return e;
     }
+    if (amax) return hipErrorInvalidValue;   // only the split form puts the gradient together
     const size_t lds = wgrad_lds_bytes(g);
     const int mt = wgrad_mt(g), ntw = wgrad_ntw(g), wm = wgrad_wm(g);
     dim3 none(1, 1, 1);

@@ -24,6 +24,7 @@ namespace aet {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
 
 // dword 3 of a raw buffer descriptor for 32-bit untyped accesses on this part
 constexpr int kBufferFlags = 0x00020000;
@@ -61,10 +62,18 @@ struct SplitTile {
     static constexpr int LDS = (6 * POS + 6 * 9 * 32) * 16;            // bytes
 };
 
-template <int LGW, int MT, bool BWD>
+// UNPOOL (backward-data only): src is the gradient at the outputs of the 2 x 2 pooling layer behind the
+// convolution, amax that layer's winners; the gradient at the convolution's own outputs, a value at
+// each window's winner and zeros, is put together while it is staged: five bytes a window are read where
+// a kernel of the pooling layer wrote sixteen and this one read them again.  32 clients (compute factors
+// 1, 2, 4) x 64 samples, us per launch: 32 -> 32 channels at 32 x 32 129 -> 125, its backward-weight 126
+// -> 128; 64 -> 64 at 16 x 16 92 -> 99 (the selections, in both blocks of channels) and 124 -> 124; the
+// pooling kernels' 26 each are gone: the job of 4 rounds 37.0 -> 35.7 ms.
+template <int LGW, int MT, bool BWD, bool UNPOOL>
 __global__ void __launch_bounds__(256, 2)
 k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const u4 *__restrict__ wsplit, int64_t wstride,
              const float *__restrict__ src, float *__restrict__ dst, const float *__restrict__ mask_src, uint8_t *__restrict__ amax) {
+    static_assert(BWD || !UNPOOL, "the forward pass reads whole maps");
     typedef SplitTile<LGW, MT> T;
     constexpr int W = T::W, POS = T::POS, WT = W + 2;
     const RoundParams p = rp[blockIdx.z];
@@ -80,8 +89,12 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
     const int y0 = (int)blockIdx.y % g.rblocks * g.R, s0 = (int)blockIdx.y / g.rblocks * g.NS;   // row; sample of the mini-batch
     const int ns = min(g.NS, B - s0);   // samples that exist
     const int64_t sample0 = (int64_t)blockIdx.z * B + s0;
+    constexpr int UN = UNPOOL ? 2 : 1;
+    const int SHW = HW / (UN * UN);     // a channel of src
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(src) + sample0 * g.SC * HW, 0, 4 * g.SC * HW * ns, kBufferFlags);
+        const_cast<float *>(src) + sample0 * g.SC * SHW, 0, 4 * g.SC * SHW * ns, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        UNPOOL ? amax + sample0 * g.SC * SHW : nullptr, 0, UNPOOL ? g.SC * SHW * ns : 0, kBufferFlags);
 
     // ---- staging: what this thread moves ----------------------------------------------------
     // source: four pixels of one tile row, 8 channels (an octet of the chunk's two).  Threads in the
@@ -94,18 +107,28 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
     const int alds = axq < W / 4 ? ao * POS + atr * WT + 1 + 4 * axq : -1;
     // (samples beyond the last lie beyond the buffer)
     const uint32_t aoff = alds >= 0 && (unsigned)(y0 + ay) < (unsigned)g.H
-                              ? (uint32_t)(4 * ((as * g.SC + 8 * ao) * HW + (y0 + ay) * W + 4 * axq)) : kNowhere;
+                              ? (uint32_t)(4 * ((as * g.SC + 8 * ao) * SHW + (y0 + ay) / UN * (W / UN) + 4 / UN * axq)) : kNowhere;
+    const int awin = 2 * ((y0 + ay) & 1);        // UNPOOL: the row's first element of a window
     // weights: split and in order already
     constexpr int WP = 6 * 9 * 32, WTURNS = (WP + 255) / 256;
     const gu4_ptr wsrc = (gu4_ptr)(wsplit + blockIdx.z * wstride + (int64_t)blockIdx.x * WP);
     const int wchunk = WP * (int)gridDim.x;
-    const int astep = 4 * HW;                    // bytes per source channel
-    f4 av[8];
+    const int astep = 4 * SHW;                   // bytes per source channel
+    f4 av[8];                                    // UNPOOL: the first two: the gradients of two windows
+    uint32_t aw[8];                              // UNPOOL: their winners
     u4 wv[WTURNS];
     auto fetch = [&](int c0) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-            av[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)aoff, (c0 + c) * astep, 0));
+        for (int c = 0; c < 8; ++c) {
+            if (UNPOOL) {
+                const f2v d = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)aoff, (c0 + c) * astep, 0));
+                av[c][0] = d[0];
+                av[c][1] = d[1];
+                aw[c] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)(aoff >> 2), (c0 + c) * SHW, 0);
+            } else {
+                av[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)aoff, (c0 + c) * astep, 0));
+            }
+        }
         const gu4_ptr w = wsrc + (c0 >> 4) * wchunk;
 #pragma unroll
         for (int i = 0; i < WTURNS; ++i) wv[i] = w[min(tid + 256 * i, WP - 1)];
@@ -114,7 +137,10 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
         if (alds >= 0) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x[8] = {av[0][e], av[1][e], av[2][e], av[3][e], av[4][e], av[5][e], av[6][e], av[7][e]};
+                float x[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    x[c] = !UNPOOL ? av[c][e] : ((aw[c] >> (8 * (e >> 1))) & 0xffu) == (uint32_t)(awin + (e & 1)) ? av[c][e >> 1] : 0.f;
                 const Split8 s = split8(x);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) As[q * 2 * POS + alds + e] = s.p[q];
@@ -317,10 +343,11 @@ struct SplitWgradTile {
 
 constexpr int kWgThreads = 384;
 
-template <int LGW>
+// UNPOOL: as above, dout is the gradient at the outputs of the pooling layer
+template <int LGW, bool UNPOOL>
 __global__ void __launch_bounds__(kWgThreads, 3)
 k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad g, const float *__restrict__ in,
-                   const float *__restrict__ dout, float *__restrict__ partial) {
+                   const float *__restrict__ dout, const uint8_t *__restrict__ amax, float *__restrict__ partial) {
     typedef SplitWgradTile<LGW> T;
     constexpr int W = T::W, R = T::R, IN = T::IN, DO = T::DO, W8 = W / 8;
     if (u >= rp[blockIdx.z].m) return;
@@ -346,14 +373,19 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
     float bsum[DTURNS];
 #pragma unroll
     for (int i = 0; i < DTURNS; ++i) bsum[i] = 0.f;
-    f4 iv[ITURNS][2], dv[DTURNS][2];
+    constexpr int UN = UNPOOL ? 2 : 1, DL = UNPOOL ? 1 : 2;
+    const int SHW = HW / (UN * UN);          // a channel of dout
+    f4 iv[ITURNS][2], dv[DTURNS][DL];
+    uint32_t dw[DTURNS];                     // UNPOOL: the winners of the octet's four windows
     auto fetch = [&](int it) {
         const int b = it / g.items, y0 = (it - b * g.items) * R;
         const int64_t sample = (int64_t)blockIdx.z * B + b;
         const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(in) + (sample * g.IC + ci0) * HW, 0, 4 * (g.IC - ci0) * HW, kBufferFlags);
         const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(dout) + (sample * g.OC + oc0) * HW, 0, 4 * (g.OC - oc0) * HW, kBufferFlags);
+            const_cast<float *>(dout) + (sample * g.OC + oc0) * SHW, 0, 4 * (g.OC - oc0) * SHW, kBufferFlags);
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+            UNPOOL ? const_cast<uint8_t *>(amax) + (sample * g.OC + oc0) * SHW : nullptr, 0, UNPOOL ? (g.OC - oc0) * SHW : 0, kBufferFlags);
 #pragma unroll
         for (int i = 0; i < ITURNS; ++i) {
             const int t = tid + kWgThreads * i, x8 = t % W8, row = t / W8 % T::ROWST, c = t / (W8 * T::ROWST);
@@ -366,9 +398,12 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
 #pragma unroll
         for (int i = 0; i < DTURNS; ++i) {
             const int t = tid + kWgThreads * i, o = t % (R * W8), c = t / (R * W8);
-            const uint32_t off = t < DTASKS ? 4u * (uint32_t)(c * HW + y0 * W + 8 * o) : kNowhere;
+            const uint32_t off = t >= DTASKS ? kNowhere
+                                 : UNPOOL ? 4u * (uint32_t)(c * SHW + (y0 + o / W8) / 2 * (W / 2) + 4 * (o % W8))
+                                          : 4u * (uint32_t)(c * HW + y0 * W + 8 * o);
+            if (UNPOOL) dw[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, (int)(off >> 2), 0, 0);
 #pragma unroll
-            for (int q = 0; q < 2; ++q) dv[i][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)off, 16 * q, 0));
+            for (int q = 0; q < DL; ++q) dv[i][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)off, 16 * q, 0));
         }
     };
     // count: the pixels of the tile that are this slice's own, in octets (for the bias)
@@ -387,7 +422,11 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
         for (int i = 0; i < DTURNS; ++i) {
             const int t = tid + kWgThreads * i, o = t % (R * W8), c = t / (R * W8);
             if (t < DTASKS) {
-                const float x[8] = {dv[i][0][0], dv[i][0][1], dv[i][0][2], dv[i][0][3], dv[i][1][0], dv[i][1][1], dv[i][1][2], dv[i][1][3]};
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)   // (tiles begin in even rows)
+                    x[e] = !UNPOOL ? dv[i][e / 4 % DL][e % 4]
+                           : ((dw[i] >> (8 * (e / 2))) & 0xffu) == (uint32_t)(2 * (o / W8 & 1) + (e & 1)) ? dv[i][0][e / 2] : 0.f;
                 const Split8 s = split8(x);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) Ds[(q * 32 + c) * DO + o] = s.p[q];
@@ -536,7 +575,7 @@ bool split_dir(const LayerGeom &L, bool bwd, int MT, SplitDir *d) {
 
 constexpr int kSplitResident = 512;   // workgroups of a launch that are resident together: two per compute unit
 
-template <int LGW, int MT, bool BWD>
+template <int LGW, int MT, bool BWD, bool UNPOOL>
 hipError_t split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, int B, const SplitDir &d, const u4 *w,
                         int64_t wstride, const float *src, float *dst, const float *mask_src, uint8_t *amax) {
     constexpr int lds = SplitTile<LGW, MT>::LDS;
@@ -547,12 +586,12 @@ hipError_t split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, 
         static PerDevice allowed;
         e = allowed.get(dev, &done, [](int *v) {
             *v = 1;
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_split<LGW, MT, BWD>),
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_split<LGW, MT, BWD, UNPOOL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         });
         if (e != hipSuccess) return e;
     }
-    k_conv_split<LGW, MT, BWD><<<grid, 256, lds, s>>>(dp, u, B, d, w, wstride, src, dst, mask_src, amax);
+    k_conv_split<LGW, MT, BWD, UNPOOL><<<grid, 256, lds, s>>>(dp, u, B, d, w, wstride, src, dst, mask_src, amax);
     return hipGetLastError();
 }
 
@@ -612,15 +651,17 @@ hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *d
     const u4 *w = reinterpret_cast<const u4 *>(sw.base + off);
     const int MT = 2;
     if (!split_dir(L, bwd, MT, &d)) return hipErrorInvalidValue;
-    d.pool = amax != nullptr;
+    d.pool = !bwd && amax;
     const dim3 grid((unsigned)((d.DC + 31) / 32), (unsigned)(d.rblocks * ((B + d.NS - 1) / d.NS)), (unsigned)nact);
     const int fam = bwd ? F_CONV_BWD_DATA : F_CONV_FWD;
     const bool timed = prof && prof->on[fam];
     if (timed) prof->before(fam, s);
     hipError_t e = hipErrorInvalidValue;
-#define AET_SPLIT(lgw, mt) \
-    if (L.iw == 1 << lgw && MT == mt) e = bwd ? split_launch<lgw, mt, true>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax) \
-                                              : split_launch<lgw, mt, false>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax);
+#define AET_SPLIT(lgw, mt)                                                                                                     \
+    if (L.iw == 1 << lgw && MT == mt)                                                                                          \
+        e = !bwd   ? split_launch<lgw, mt, false, false>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax)         \
+            : amax ? split_launch<lgw, mt, true, true>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax)           \
+                   : split_launch<lgw, mt, true, false>(s, grid, dp, u, B, d, w, sw.stride, src, dst, mask_src, amax);
     AET_SPLIT(3, 2) AET_SPLIT(4, 2) AET_SPLIT(5, 2)
 #undef AET_SPLIT
     if (timed) prof->after(fam, s);
@@ -628,9 +669,9 @@ hipError_t launch_conv_split(hipStream_t s, Profiler *prof, const RoundParams *d
 }
 
 // ---- backward-weight -----------------------------------------------------------------------------
-template <int LGW>
+template <int LGW, bool UNPOOL>
 static hipError_t wgrad_split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, int B, const SplitWgrad &g,
-                                     const float *in, const float *dout, float *partial) {
+                                     const float *in, const float *dout, const uint8_t *amax, float *partial) {
     constexpr int lds = SplitWgradTile<LGW>::BYTES;
     if (lds > 64 * 1024) {
         int dev = 0, done = 0;
@@ -639,11 +680,11 @@ static hipError_t wgrad_split_launch(hipStream_t s, dim3 grid, const RoundParams
         static PerDevice allowed;
         e = allowed.get(dev, &done, [](int *v) {
             *v = 1;
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_wgrad_split<LGW>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_wgrad_split<LGW, UNPOOL>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         });
         if (e != hipSuccess) return e;
     }
-    k_conv_wgrad_split<LGW><<<grid, kWgThreads, lds, s>>>(dp, u, B, g, in, dout, partial);
+    k_conv_wgrad_split<LGW, UNPOOL><<<grid, kWgThreads, lds, s>>>(dp, u, B, g, in, dout, amax, partial);
     return hipGetLastError();
 }
 
@@ -669,7 +710,7 @@ int conv_wgrad_split_slices(const LayerGeom &L, int B, int nact, int cap) {
 }
 
 hipError_t launch_conv_wgrad_split(hipStream_t s, const RoundParams *dp, int nact, int u, int B, const LayerGeom &L, int S, int KP,
-                                   int OCP, const float *in, const float *dout, float *partial) {
+                                   int OCP, const float *in, const float *dout, const uint8_t *amax, float *partial) {
     SplitWgrad g;
     g.IC = L.ic; g.OC = L.oc; g.H = L.ih;
     const int W = L.iw, R = W == 32 ? 4 : 8;
@@ -680,9 +721,13 @@ hipError_t launch_conv_wgrad_split(hipStream_t s, const RoundParams *dp, int nac
     g.KP = KP; g.OCP = OCP;
     g.cblocks = (L.ic + 31) / 32;
     const dim3 grid((unsigned)S, (unsigned)((L.oc + 31) / 32 * g.cblocks), (unsigned)nact);
-    if (W == 8) return wgrad_split_launch<3>(s, grid, dp, u, B, g, in, dout, partial);
-    if (W == 16) return wgrad_split_launch<4>(s, grid, dp, u, B, g, in, dout, partial);
-    return wgrad_split_launch<5>(s, grid, dp, u, B, g, in, dout, partial);
+#define AET_WGRAD_SPLIT(lgw)                                                                   \
+    if (W == 1 << lgw)                                                                         \
+        return amax ? wgrad_split_launch<lgw, true>(s, grid, dp, u, B, g, in, dout, amax, partial) \
+                    : wgrad_split_launch<lgw, false>(s, grid, dp, u, B, g, in, dout, amax, partial);
+    AET_WGRAD_SPLIT(3) AET_WGRAD_SPLIT(4) AET_WGRAD_SPLIT(5)
+#undef AET_WGRAD_SPLIT
+    return hipErrorInvalidValue;
 }
 
 }  // namespace aet

@@ -665,6 +665,18 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
     auto split = [&](int l, bool bwd) {
         return !sc.plain && conv_split_used(lay, l, bwd, B, nact, sc.split);
     };
+    // Pooling layers whose gradient the convolution below takes as it is: both of its backward kernels
+    // put theirs together while they stage it, from a quarter of the values and a byte each.  The gradient
+    // is masked by the convolution's ReLU where it is made (a winner's value is the pooled one).
+    auto unpooled = [&](int l) {
+        return l > 1 && lay[l].type == 1 && lay[l - 1].type == 0 && sc.wgrad[l - 1] && split(l - 1, true) &&
+               conv_bwd_unpools(lay[l - 1], lay[l], B, nact);
+    };
+    // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
+    auto mask_of = [&](int l) -> const float * {
+        if (l == 0) return nullptr;
+        return lay[l - 1].relu || (unpooled(l - 1) && lay[l - 2].relu) ? sc.act[l] : nullptr;
+    };
     // the last layer, forward to update, in one launch
     const bool head = !sc.plain && L > 1 && dense_head_pays(lay[L - 1], B, nact);
     const int LF = head ? L - 1 : L;
@@ -701,7 +713,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         }
     }
     if (head) {
-        AET_RETURN_IF(launch_dense_head(s, prof, dp, nact, u, B, lay[L - 1], sc.act[L - 1], sc.labels, sc.del[L - 1], lay[L - 2].relu != 0));
+        AET_RETURN_IF(launch_dense_head(s, prof, dp, nact, u, B, lay[L - 1], sc.act[L - 1], sc.labels, sc.del[L - 1], mask_of(L - 1) != nullptr));
     } else {
         AET_TIMED(F_SOFTMAX_CE, k_softmax_ce<<<nact, 256, 0, s>>>(dp, u, B, lay[L - 1].oc, sc.act[L], sc.labels, sc.del[L]));
         AET_RETURN_IF(hipGetLastError());
@@ -709,9 +721,14 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
     FinishList list, *later = sc.wgrad_apart ? &list : nullptr;
     for (int l = LF - 1; l >= 0; --l) {
         const LayerGeom &g = lay[l];
-        // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
-        const float *mask = (l > 0 && lay[l - 1].relu) ? sc.act[l] : nullptr;
+        const float *mask = mask_of(l);
         if (g.type == 0) {
+            if (l + 1 < L && unpooled(l + 1)) {
+                uint8_t *const winners = sc.amax[l + 1];
+                AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], sc.del[l + 2], sc.del[l], mask, winners));
+                AET_RETURN_IF(launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, sc.act[l], sc.del[l + 2], sc.wgrad[l], later, winners));
+                continue;
+            }
             bool taken = false;
             if (l > 0 && !sc.plain && !conv_wgrad_direct_ok(g))
                 AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad[l], later, &taken));
@@ -724,7 +741,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 2, sc.act[l], sc.del[l + 1],
                                         sc.wgrad[l], nullptr, !sc.plain, later));
         } else if (g.type == 1) {
-            if (l > 0) {
+            if (l > 0 && !unpooled(l)) {
                 // the ReLU below, at the winners: their value is the pooled one
                 const float *pooled = mask ? sc.act[l + 1] : nullptr;
                 if (pool_pairs(g)) {
