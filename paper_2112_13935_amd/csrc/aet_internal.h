@@ -171,13 +171,12 @@ hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundPa
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
                                   float *partial, FinishList *later, const uint8_t *amax = nullptr);
-// whether the two backward kernels of a convolution both take the gradient of the 2 x 2 pooling layer behind it
-// (backward-data: where it runs in the split form) and put their own together from it and the winners; amax
-// then goes to launch_conv_wgrad_mfma
-bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact);
-// backward-data and backward-weight of a layer in one launch where both are small
+// whether the backward kernels of a convolution take the gradient of the 2 x 2 pooling layer behind it and put
+// their own together from it and the winners, amax (split: backward-data runs in the split form)
+bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact, bool split);
+// backward-data and backward-weight of a layer in one launch where both are small; amax as above
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
-                                const LayerGeom &L, const float *dout, float *din, const float *mask_src,
+                                const LayerGeom &L, const float *dout, uint8_t *amax, float *din, const float *mask_src,
                                 const float *in, float *partial, FinishList *later, bool *taken);
 // dense layers on the matrix cores (kernels_dense_mfma.hip); mode 0 fwd, 1 bwd-data, 2 bwd-weight
 hipError_t launch_dense_mfma(hipStream_t s, Profiler *prof, int mode, const RoundParams *dp, int nact,

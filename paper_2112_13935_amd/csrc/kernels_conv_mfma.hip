@@ -27,9 +27,15 @@
 namespace aet {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f4 mfma16x16x4(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// the gradient at element `at` of window h of several: d at the window's winner (a byte each), else zero
+__device__ __forceinline__ float unpool(float d, uint32_t winners, int h, int at) {
+    return ((winners >> (8 * h)) & 0xffu) == (uint32_t)at ? d : 0.f;
 }
 
 // dword 3 of a raw buffer descriptor for 32-bit untyped accesses on this part
@@ -81,11 +87,15 @@ struct ConvDir {
 // leave the GPU half empty anyway (what they wait for is one trip through memory per chunk; the
 // registers would cost a full launch a resident workgroup).  6 clients, 16 x 16 half-width CNN: 4.81 ->
 // 4.69 ms.
+// UNPOOL (backward-data, VEC): src is the gradient at the outputs of the 2 x 2 pooling layer behind the
+// convolution and amax that layer's winners; a group of four pixels is two windows, whose gradients go
+// to the winners' places on the way to LDS.
 // (bx, by, bz): row and channel block, sample, client.
-template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC, bool PRE>
+template <int KS, bool BWD, int CCH, int NT, int NPOS, bool VEC, bool PRE, bool UNPOOL = false>
 __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, const ConvDir &g, const float *__restrict__ src,
                                                float *__restrict__ dst, const float *__restrict__ mask_src,
                                                uint8_t *__restrict__ amax, int bx, int by, int bz, float *smem) {
+    static_assert(!UNPOOL || (BWD && VEC), "whole groups of four pixels");
     constexpr int KSQ = KS * KS;
     constexpr int KCHR = CCH * KSQ;          // K elements per chunk
     constexpr int KCH = (KCHR + 3) / 4 * 4;  // ... rounded up to whole contraction steps (zero weights)
@@ -100,8 +110,11 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     const int64_t sample = (int64_t)bz * B + by;
     // range-checked buffers: the sample's source planes and the layer's weights; an offset
     // beyond them (kNowhere, or a channel beyond the last) reads zero without touching memory
+    const int64_t src_size = UNPOOL ? g.src_size / 4 : g.src_size;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(src) + sample * g.src_size, 0, (int)(4 * g.src_size), kBufferFlags);
+        const_cast<float *>(src) + sample * src_size, 0, (int)(4 * src_size), kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rwin = __builtin_amdgcn_make_buffer_rsrc(
+        UNPOOL ? amax + sample * src_size : nullptr, 0, UNPOOL ? (int)src_size : 0, kBufferFlags);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         p.W + g.w_off, 0, 4 * g.ic * g.oc * KS * KS, kBufferFlags);
     auto bload = [](__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
@@ -152,7 +165,8 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     // up to 3 positions of the source tile and walks the chunk's channels, and to one K
     // element of the weight chunk and walks the destination channels; what lies outside asks
     // the range-checked buffers for an offset beyond their end and comes back as zero.
-    const uint32_t shw = 4u * (uint32_t)(g.SH * g.SW);   // bytes per source channel
+    constexpr int UN = UNPOOL ? 2 : 1;
+    const uint32_t shw = 4u * (uint32_t)(g.SH / UN * (g.SW / UN));   // bytes per source channel
     uint32_t soff[NPOS];
     bool sok[NPOS];
 #pragma unroll
@@ -210,7 +224,7 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     constexpr int NBT = (CCH + NGB - 1) / NGB;
     uint32_t voff[kTurnsS];
     bool vst[kTurnsS];
-    int vlds = 0, vstep = 0, fcol[4], gl[4];
+    int vlds = 0, vstep = 0, vwin = 0, fcol[4], gl[4];   // vwin: UNPOOL: the row's first element of a window
     int fq = 0, fd0 = 0, gq = 0, gcg = 0;
     if constexpr (VEC) {
         const int sw4 = g.SW >> 2;
@@ -222,8 +236,9 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
             const int c = vcg + g.sgrp * j;
             vst[j] = vcg < g.sgrp && c < CCH;
             voff[j] = (vst[j] && (unsigned)vsy < (unsigned)g.SH)
-                          ? 4u * (uint32_t)(vsy * g.SW + 4 * vxq) + (uint32_t)c * shw : kNowhere;
+                          ? 4u * (uint32_t)(vsy / UN * (g.SW / UN) + 4 / UN * vxq) + (uint32_t)c * shw : kNowhere;
         }
+        vwin = 2 * (vsy & 1);
         vlds = vcg * PL + vty * g.SWP + g.P + 4 * vxq;
         vstep = g.sgrp * PL;
         fq = tid % QF; fd0 = tid / QF;
@@ -250,12 +265,23 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
     // stored to LDS: one memory round trip per chunk.
     constexpr int NWL = (nd + WG_ - 1) / WG_;            // forward: destination channels per thread
     constexpr int NWV = BWD ? NPB * CCH : NWL;
+    uint32_t svw[UNPOOL ? kTurnsS : 1];                  // UNPOOL: the winners of two windows
     f4 sv4[VEC ? kTurnsS : 1], wv4[VEC ? (BWD ? NBT : NWF) : 1];
     float sv[VEC ? 1 : NPOS][VEC ? 1 : CCH], wv[VEC ? 1 : NWV];
     auto fetch = [&](int c0) {
         if constexpr (VEC) {
 #pragma unroll
-            for (int j = 0; j < kTurnsS; ++j) sv4[j] = bload4(rs, voff[j] + (uint32_t)c0 * shw);
+            for (int j = 0; j < kTurnsS; ++j) {
+                const uint32_t off = voff[j] + (uint32_t)c0 * shw;
+                if constexpr (UNPOOL) {
+                    const f2 d = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0));
+                    sv4[j][0] = d[0];
+                    sv4[j][1] = d[1];
+                    svw[j] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rwin, (int)(off >> 2), 0, 0);
+                } else {
+                    sv4[j] = bload4(rs, off);
+                }
+            }
             if (BWD) {
 #pragma unroll
                 for (int j = 0; j < NBT; ++j) {
@@ -305,7 +331,8 @@ __device__ __forceinline__ void conv_mfma_body(const RoundParams &p, int B, cons
             for (int j = 0; j < kTurnsS; ++j)
                 if (vst[j]) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) Ssm[vlds + j * vstep + e] = sv4[j][e];
+                    for (int e = 0; e < 4; ++e)
+                        Ssm[vlds + j * vstep + e] = UNPOOL ? unpool(sv4[j][e >> 1], svw[UNPOOL ? j : 0], e >> 1, vwin + (e & 1)) : sv4[j][e];
                 }
             if (BWD) {
 #pragma unroll
@@ -643,11 +670,14 @@ constexpr int kPreD = 16;   // the same for the d(output) tile
 // Staging: a thread is tied to one position of the tile (row, column) and walks the channels,
 // so the loop has no index arithmetic and no branches; the next work item's elements are
 // fetched into registers before the products of the current one start and go to LDS after them.
+// UNPOOL (VEC): dout and amax as src and amax above.
 // (sl, bz): slice, client.
-template <int KS, int MT, int NTW, int WM, bool VEC>
+template <int KS, int MT, int NTW, int WM, bool VEC, bool UNPOOL = false>
 __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const float *__restrict__ in,
-                                                const float *__restrict__ dout, float *__restrict__ partial,
-                                                int sl, int bz, float *smem) {
+                                                const float *__restrict__ dout, const uint8_t *__restrict__ amax,
+                                                float *__restrict__ partial, int sl, int bz, float *smem) {
+    static_assert(!UNPOOL || VEC, "whole groups of four pixels");
+    constexpr int UN = UNPOOL ? 2 : 1;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int m0 = WM == 1 ? 0 : (wave >> 1);   // first M tile of the wave, stride WM
     const int n0 = WM == 1 ? wave : (wave & 1);  // first N tile of the wave, stride NS
@@ -709,7 +739,8 @@ __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const
     const int drow = VEC ? g.OW >> 2 : g.OWP;
     const int dr = dpos / drow, dx = dpos - dr * drow;
     const bool dxok = dgrp < gd && (VEC || dx < g.OW);
-    const uint32_t ihw = (uint32_t)(g.IH * g.IW), ohw = (uint32_t)(g.OH * g.OW);
+    const uint32_t ihw = (uint32_t)(g.IH * g.IW), ohw = (uint32_t)(g.OH / UN * (g.OW / UN));
+    const int64_t dout_size = UNPOOL ? g.out_size / 4 : g.out_size;
     const uint32_t icstep = 4u * (uint32_t)gin * ihw, dcstep = 4u * (uint32_t)gd * ohw;   // bytes per turn
     const int isbase = VEC ? igrp * plane + ity * g.SWP + g.pad + 4 * itx
                            : (igrp < gin ? igrp * plane + ipos : (CP + 2) * plane + ipos);
@@ -724,6 +755,8 @@ __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const
     constexpr int PI = VEC ? kPreIn4 : kPreIn, PD = VEC ? kPreD4 : kPreD;
     typedef typename std::conditional<VEC, f4, float>::type stage_t;
     stage_t pin[PI], pd[PD];
+    uint32_t pdw[UNPOOL ? PD : 1];   // UNPOOL: the winners of two windows
+    int win = 0;                     // ... and the row's first element of a window
     const int items = B * g.items_per_sample;
     auto bload = [](__amdgpu_buffer_rsrc_t r, uint32_t off) -> stage_t {
         if constexpr (VEC) return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
@@ -736,7 +769,9 @@ __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const
         const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(in) + sample * g.in_size, 0, (int)(4 * g.in_size), kBufferFlags);
         const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(dout) + sample * g.out_size, 0, (int)(4 * g.out_size), kBufferFlags);
+            const_cast<float *>(dout) + sample * dout_size, 0, (int)(4 * dout_size), kBufferFlags);
+        const __amdgpu_buffer_rsrc_t rwin = __builtin_amdgcn_make_buffer_rsrc(
+            UNPOOL ? const_cast<uint8_t *>(amax) + sample * dout_size : nullptr, 0, UNPOOL ? (int)dout_size : 0, kBufferFlags);
         const int sy = y0 + ity - g.pad;
         const bool iok = ixok && (unsigned)sy < (unsigned)g.IH;
         const int sx = VEC ? 4 * itx : itx - g.pad;
@@ -745,10 +780,21 @@ __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const
         for (int q = 0; q < PI; ++q)
             if (q < nq_in) pin[q] = bload(rin, ivo + (uint32_t)q * icstep);
         const bool dok = dxok && y0 + dr < g.OH;
-        const uint32_t dvo = dok ? 4u * ((uint32_t)dgrp * ohw + (uint32_t)((y0 + dr) * g.OW + (VEC ? 4 * dx : dx))) : kNowhere;
+        const uint32_t dvo = dok ? 4u * ((uint32_t)dgrp * ohw + (uint32_t)((y0 + dr) / UN * (g.OW / UN) + (VEC ? 4 / UN * dx : dx))) : kNowhere;
+        win = 2 * ((y0 + dr) & 1);
 #pragma unroll
         for (int q = 0; q < PD; ++q)
-            if (q < nq_d) pd[q] = bload(rd, dvo + (uint32_t)q * dcstep);
+            if (q < nq_d) {
+                const uint32_t off = dvo + (uint32_t)q * dcstep;
+                if constexpr (UNPOOL) {
+                    const f2 d = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(rd, (int)off, 0, 0));
+                    pd[q][0] = d[0];
+                    pd[q][1] = d[1];
+                    pdw[q] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rwin, (int)(off >> 2), 0, 0);
+                } else {
+                    pd[q] = bload(rd, off);
+                }
+            }
     };
     auto stash = [&]() {   // the fetched tiles go to LDS
         if constexpr (VEC) {
@@ -763,7 +809,15 @@ __device__ __forceinline__ void conv_wgrad_body(int B, const WgradGeom &g, const
             if (dgrp < gd) {
 #pragma unroll
                 for (int q = 0; q < PD; ++q)
-                    if (q < nq_d) *reinterpret_cast<f4 *>(Dsm + dsbase + q * dsstep) = pd[q];
+                    if (q < nq_d) {
+                        f4 v = pd[q];
+                        if constexpr (UNPOOL) {
+                            const uint32_t w = pdw[q];
+                            v = f4{unpool(pd[q][0], w, 0, win), unpool(pd[q][0], w, 0, win + 1),
+                                   unpool(pd[q][1], w, 1, win), unpool(pd[q][1], w, 1, win + 1)};
+                        }
+                        *reinterpret_cast<f4 *>(Dsm + dsbase + q * dsstep) = v;
+                    }
             }
         } else {
 #pragma unroll
@@ -850,7 +904,7 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
                   float *__restrict__ partial) {
     if (u >= rp[blockIdx.z].m) return;
     extern __shared__ float smem[];
-    conv_wgrad_body<KS, MT, NTW, WM, VEC>(B, g, in, dout, partial, blockIdx.x, blockIdx.z, smem);
+    conv_wgrad_body<KS, MT, NTW, WM, VEC>(B, g, in, dout, nullptr, partial, blockIdx.x, blockIdx.z, smem);
 }
 
 // Backward-data and backward-weight of one layer in one launch, for launches too small to fill
@@ -858,23 +912,24 @@ k_conv_wgrad_mfma(const RoundParams *__restrict__ rp, int u, int B, WgradGeom g,
 // by the finish kernel).  Workgroups 0 .. nd-1 are backward-data blocks, the rest slices.
 // What bounds such launches is their latency (a few dependent trips through memory each, half of
 // the compute units idle), not work: 6 clients, 16 x 16 half-width CNN, 45 recursions: 6.30 ->
-// 5.82 ms; 3 clients, 12 x 12, 27 recursions: 3.28 -> 2.93 ms.
-template <int NT, bool VECD, int MT, int NTW, bool VECW>
+// 5.82 ms; 3 clients, 12 x 12, 27 recursions: 3.28 -> 2.93 ms.  UNPOOL: one launch less again for each
+// pooling layer, 14.0 -> 13.6 and 10.3 -> 9.8 us for these: 6 clients as above 6.32 -> 6.02 ms.
+template <int NT, bool VECD, int MT, int NTW, bool VECW, bool UNPOOL = false>
 __global__ void __launch_bounds__(256)
 k_conv_bwd_pair(const RoundParams *__restrict__ rp, int u, int B, ConvDir d, int nd, int dx, WgradGeom w,
-                const float *__restrict__ dout, float *__restrict__ din, const float *__restrict__ mask_src,
-                const float *__restrict__ in, float *__restrict__ partial) {
+                const float *__restrict__ dout, uint8_t *__restrict__ amax, float *__restrict__ din,
+                const float *__restrict__ mask_src, const float *__restrict__ in, float *__restrict__ partial) {
     extern __shared__ float smem[];
     const int id = blockIdx.x;
     if (id < nd) {
         const int bx = id % dx, r = id / dx, by = r % B, bz = r / B;
         const RoundParams p = rp[bz];
         if (u >= p.m) return;
-        conv_mfma_body<3, true, kCch, NT, 1, VECD, true>(p, B, d, dout, din, mask_src, nullptr, bx, by, bz, smem);
+        conv_mfma_body<3, true, kCch, NT, 1, VECD, true, UNPOOL>(p, B, d, dout, din, mask_src, UNPOOL ? amax : nullptr, bx, by, bz, smem);
     } else {
         const int sl = (id - nd) % w.S, bz = (id - nd) / w.S;
         if (u >= rp[bz].m) return;
-        conv_wgrad_body<3, MT, NTW, 1, VECW>(B, w, in, dout, partial, sl, bz, smem);
+        conv_wgrad_body<3, MT, NTW, 1, VECW, UNPOOL>(B, w, in, dout, amax, partial, sl, bz, smem);
     }
 }
 
@@ -1148,12 +1203,12 @@ struct PairPlan {
     WgradGeom w;
     int nd, dx;
     size_t lds;
-    void (*kernel)(const RoundParams *, int, int, ConvDir, int, int, WgradGeom, const float *, float *, const float *,
+    void (*kernel)(const RoundParams *, int, int, ConvDir, int, int, WgradGeom, const float *, uint8_t *, float *, const float *,
                    const float *, float *);
 };
 }  // namespace
 
-static bool pair_plan(const LayerGeom &L, int B, int nact, PairPlan *p) {
+static bool pair_plan(const LayerGeom &L, int B, int nact, bool unpool, PairPlan *p) {
     ConvDir &d = p->d;
     WgradGeom &w = p->w;
     if (L.k != 3 || !conv_mfma_supported(L, true) || !conv_wgrad_mfma_supported(L, B)) return false;
@@ -1170,28 +1225,30 @@ static bool pair_plan(const LayerGeom &L, int B, int nact, PairPlan *p) {
     p->kernel = nullptr;
 #define AET_PAIR(nt, m, n)                                                                              \
     if (d.NT == nt && mt == m && ntw == n)                                                              \
-        p->kernel = d.vec ? (w.vec ? k_conv_bwd_pair<nt, true, m, n, true> : nullptr)                   \
-                          : (w.vec ? k_conv_bwd_pair<nt, false, m, n, true> : k_conv_bwd_pair<nt, false, m, n, false>);
+        p->kernel = unpool  ? (d.vec && w.vec ? k_conv_bwd_pair<nt, true, m, n, true, true> : nullptr)  \
+                    : d.vec ? (w.vec ? k_conv_bwd_pair<nt, true, m, n, true> : nullptr)                 \
+                            : (w.vec ? k_conv_bwd_pair<nt, false, m, n, true> : k_conv_bwd_pair<nt, false, m, n, false>);
     AET_PAIR(1, 1, 2) AET_PAIR(1, 2, 2) AET_PAIR(1, 1, 5) AET_PAIR(1, 2, 5) AET_PAIR(2, 1, 5) AET_PAIR(2, 2, 5)
 #undef AET_PAIR
     return p->kernel != nullptr;
 }
 
-bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact) {
+bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact, bool split) {
     PairPlan p;
-    return 2 * pool.oh == L.oh && 2 * pool.ow == L.ow && pool.oc == L.oc && conv_wgrad_mfma_supported(L, B) &&
-           conv_wgrad_split_slices(L, B, nact, wgrad_target(L)) > 0 && !pair_plan(L, B, nact, &p);
+    if (2 * pool.oh != L.oh || 2 * pool.ow != L.ow || pool.oc != L.oc || !conv_wgrad_mfma_supported(L, B)) return false;
+    if (pair_plan(L, B, nact, false, &p)) return p.d.vec && p.w.vec;
+    return split && conv_wgrad_split_slices(L, B, nact, wgrad_target(L)) > 0;
 }
 
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
-                                const LayerGeom &L, const float *dout, float *din, const float *mask_src,
+                                const LayerGeom &L, const float *dout, uint8_t *amax, float *din, const float *mask_src,
                                 const float *in, float *partial, FinishList *later, bool *taken) {
     PairPlan p;
-    *taken = pair_plan(L, B, nact, &p);
+    *taken = pair_plan(L, B, nact, amax != nullptr, &p);
     if (!*taken) return hipSuccess;
     const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];
     if (timed) prof->before(F_CONV_BWD_WEIGHT, s);
-    p.kernel<<<(unsigned)(p.nd + p.w.S * nact), 256, p.lds, s>>>(dp, u, B, p.d, p.nd, p.dx, p.w, dout, din, mask_src, in, partial);
+    p.kernel<<<(unsigned)(p.nd + p.w.S * nact), 256, p.lds, s>>>(dp, u, B, p.d, p.nd, p.dx, p.w, dout, amax, din, mask_src, in, partial);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = wgrad_finish(s, dp, nact, u, B, L, p.w, partial, later);
     if (timed) prof->after(F_CONV_BWD_WEIGHT, s);

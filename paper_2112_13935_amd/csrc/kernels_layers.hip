@@ -668,10 +668,13 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
     // Pooling layers whose gradient the convolution below takes as it is: both of its backward kernels
     // put theirs together while they stage it, from a quarter of the values and a byte each.  The gradient
     // is masked by the convolution's ReLU where it is made (a winner's value is the pooled one).
-    auto unpooled = [&](int l) {
-        return l > 1 && lay[l].type == 1 && lay[l - 1].type == 0 && sc.wgrad[l - 1] && split(l - 1, true) &&
-               conv_bwd_unpools(lay[l - 1], lay[l], B, nact);
-    };
+    uint32_t unpooled_layers = 0;
+    if (!sc.plain)
+        for (int l = 2; l < L; ++l)
+            if (lay[l].type == 1 && lay[l - 1].type == 0 && sc.wgrad[l - 1] && !conv_wgrad_direct_ok(lay[l - 1]) &&
+                conv_bwd_unpools(lay[l - 1], lay[l], B, nact, split(l - 1, true)))
+                unpooled_layers |= 1u << l;
+    auto unpooled = [&](int l) { return (unpooled_layers >> l & 1) != 0; };
     // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
     auto mask_of = [&](int l) -> const float * {
         if (l == 0) return nullptr;
@@ -723,16 +726,17 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         const LayerGeom &g = lay[l];
         const float *mask = mask_of(l);
         if (g.type == 0) {
-            if (l + 1 < L && unpooled(l + 1)) {
-                uint8_t *const winners = sc.amax[l + 1];
-                AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], sc.del[l + 2], sc.del[l], mask, winners));
-                AET_RETURN_IF(launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, sc.act[l], sc.del[l + 2], sc.wgrad[l], later, winners));
-                continue;
-            }
+            uint8_t *const winners = l + 1 < L && unpooled(l + 1) ? sc.amax[l + 1] : nullptr;
+            const float *const dout = winners ? sc.del[l + 2] : sc.del[l + 1];
             bool taken = false;
             if (l > 0 && !sc.plain && !conv_wgrad_direct_ok(g))
-                AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, sc.del[l + 1], sc.del[l], mask, sc.act[l], sc.wgrad[l], later, &taken));
+                AET_RETURN_IF(launch_conv_bwd_pair(s, prof, dp, nact, u, B, g, dout, winners, sc.del[l], mask, sc.act[l], sc.wgrad[l], later, &taken));
             if (taken) continue;
+            if (winners) {
+                AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], dout, sc.del[l], mask, winners));
+                AET_RETURN_IF(launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, sc.act[l], dout, sc.wgrad[l], later, winners));
+                continue;
+            }
             if (l > 0 && split(l, true))
                 AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], sc.del[l + 1], sc.del[l], mask, nullptr));
             else if (l > 0)

@@ -23,6 +23,11 @@ CASES = {
     "two_pools": lambda: _maps(4, 50, (16, 16, 16), [_conv(32), _conv(64), POOL, POOL]),
     # a hidden dense layer behind
     "dense": lambda: _maps(4, 50, (16, 16, 16), [_conv(32), _conv(64), POOL, W.Layer(W.DENSE, 64, relu=1)]),
+    # small launches, both backward kernels in one: 16 and 32 channels, 16 x 16 and 8 x 8
+    "pair": lambda: _maps(2, 7, (8, 16, 16), [_conv(16), _conv(16), POOL, _conv(32), _conv(32), POOL]),
+    # rows that end inside a block of them, 24 channels, no ReLU
+    "pair_10x12": lambda: _maps(3, 5, (8, 10, 12), [_conv(16), W.Layer(W.CONV, 24, 3, 1, 0), POOL]),
+    "pair_6x20": lambda: _maps(1, 1, (8, 6, 20), [_conv(32), _conv(32), POOL]),
 }
 
 
