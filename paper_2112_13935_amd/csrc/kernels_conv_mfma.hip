@@ -1192,11 +1192,10 @@ hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundPa
     return hipGetLastError();
 }
 
-// Both backward kernels of a layer in one launch (and the finish).  *taken = false: nothing was
-// launched, the caller runs them one after the other.  The rule: the backward-data blocks take at
-// most one workgroup per compute unit and the slices get as many again, so that all of both are
-// resident together; beyond that each fills the GPU by itself.  3 x 3 layers of up to 32
-// channels on both sides (the instantiations that exist).
+// Which layers run both backward kernels in one launch: the backward-data blocks take at most one
+// workgroup per compute unit and the slices get as many again, so that all of both are resident
+// together; beyond that each fills the GPU by itself.  3 x 3 layers of up to 32 channels on both sides
+// (the instantiations that exist).  unpool: dout is the gradient of the pooling layer behind.
 namespace {
 struct PairPlan {
     ConvDir d;
@@ -1233,13 +1232,19 @@ static bool pair_plan(const LayerGeom &L, int B, int nact, bool unpool, PairPlan
     return p->kernel != nullptr;
 }
 
+// With whole groups of four pixels only: what the paired kernel stages otherwise are single elements,
+// and each would need a second load for its winner.  The separate fp32 kernels (launches between the
+// paired and the split ones) keep the pooling kernel in front of them.
 bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact, bool split) {
+    if (L.ic % 16 != 0 || L.oc % 8 != 0 || L.ow % 4 != 0) return false;   // what both forms ask for, before more work is done
     PairPlan p;
     if (2 * pool.oh != L.oh || 2 * pool.ow != L.ow || pool.oc != L.oc || !conv_wgrad_mfma_supported(L, B)) return false;
     if (pair_plan(L, B, nact, false, &p)) return p.d.vec && p.w.vec;
     return split && conv_wgrad_split_slices(L, B, nact, wgrad_target(L)) > 0;
 }
 
+// Both backward kernels of a layer in one launch (and the finish).  *taken = false: nothing was
+// launched, the caller runs them one after the other.
 hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, int B,
                                 const LayerGeom &L, const float *dout, uint8_t *amax, float *din, const float *mask_src,
                                 const float *in, float *partial, FinishList *later, bool *taken) {

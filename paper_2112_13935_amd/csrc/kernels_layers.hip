@@ -671,8 +671,8 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
     uint32_t unpooled_layers = 0;
     if (!sc.plain)
         for (int l = 2; l < L; ++l)
-            if (lay[l].type == 1 && lay[l - 1].type == 0 && sc.wgrad[l - 1] && !conv_wgrad_direct_ok(lay[l - 1]) &&
-                conv_bwd_unpools(lay[l - 1], lay[l], B, nact, split(l - 1, true)))
+            if (lay[l].type == 1 && lay[l - 1].type == 0 && sc.wgrad[l - 1] &&
+                conv_bwd_unpools(lay[l - 1], lay[l], B, nact, split(l - 1, true)) && !conv_wgrad_direct_ok(lay[l - 1]))
                 unpooled_layers |= 1u << l;
     auto unpooled = [&](int l) { return (unpooled_layers >> l & 1) != 0; };
     // the gradient handed to act[l] is masked by the ReLU of the layer that produced it
