@@ -15,6 +15,8 @@
 // moves 0.87 GB in 0.27 ms).  Unlike the fp32 matrix instructions these leave the vector ALU free
 // for the splitting.  CNN on 32 x 32, 32 clients, 4 rounds: forward and backward-data together 24
 // -> 16 ms, the job 48.9 -> 40.1.
+#include <type_traits>
+
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "split_bf16.h"
@@ -133,18 +135,24 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
 #pragma unroll
         for (int i = 0; i < WTURNS; ++i) wv[i] = w[min(tid + 256 * i, WP - 1)];
     };
+    auto stash_source = [&](auto clamp, uint32_t &seen) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float x[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                x[c] = !UNPOOL ? av[c][e] : ((aw[c] >> (8 * (e >> 1))) & 0xffu) == (uint32_t)(awin + (e & 1)) ? av[c][e >> 1] : 0.f;
+            const Split8 s = split8<decltype(clamp)::value>(x);
+            split_watch(seen, s);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) As[q * 2 * POS + alds + e] = s.p[q];
+        }
+    };
     auto stash = [&]() {
         if (alds >= 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float x[8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    x[c] = !UNPOOL ? av[c][e] : ((aw[c] >> (8 * (e >> 1))) & 0xffu) == (uint32_t)(awin + (e & 1)) ? av[c][e >> 1] : 0.f;
-                const Split8 s = split8(x);
-#pragma unroll
-                for (int q = 0; q < 3; ++q) As[q * 2 * POS + alds + e] = s.p[q];
-            }
+            uint32_t seen = 0;
+            stash_source(std::false_type(), seen);
+            if (split_over(seen)) stash_source(std::true_type(), seen);
         }
 #pragma unroll
         for (int i = 0; i < WTURNS; ++i)
@@ -407,13 +415,14 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
         }
     };
     // count: the pixels of the tile that are this slice's own, in octets (for the bias)
-    auto stash = [&](int o_lo, int o_hi) {
+    auto stash_tiles = [&](auto clamp, uint32_t &seen, int o_lo, int o_hi) {
 #pragma unroll
         for (int i = 0; i < ITURNS; ++i) {
             const int t = tid + kWgThreads * i, x8 = t % W8, row = t / W8 % T::ROWST, c = t / (W8 * T::ROWST);
             if (t < ITASKS) {
                 const float x[8] = {iv[i][0][0], iv[i][0][1], iv[i][0][2], iv[i][0][3], iv[i][1][0], iv[i][1][1], iv[i][1][2], iv[i][1][3]};
-                const Split8 s = split8(x);
+                const Split8 s = split8<decltype(clamp)::value>(x);
+                split_watch(seen, s);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) Is[(q * 32 + c) * IN + row * (T::RS / 8) + 1 + x8] = s.p[q];
             }
@@ -427,12 +436,18 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
                 for (int e = 0; e < 8; ++e)   // (tiles begin in even rows)
                     x[e] = !UNPOOL ? dv[i][e / 4 % DL][e % 4]
                            : ((dw[i] >> (8 * (e / 2))) & 0xffu) == (uint32_t)(2 * (o / W8 & 1) + (e & 1)) ? dv[i][0][e / 2] : 0.f;
-                const Split8 s = split8(x);
+                const Split8 s = split8<decltype(clamp)::value>(x);
+                split_watch(seen, s);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) Ds[(q * 32 + c) * DO + o] = s.p[q];
-                if (o >= o_lo && o < o_hi) bsum[i] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+                if (!decltype(clamp)::value && o >= o_lo && o < o_hi) bsum[i] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
             }
         }
+    };
+    auto stash = [&](int o_lo, int o_hi) {
+        uint32_t seen = 0;
+        stash_tiles(std::false_type(), seen, o_lo, o_hi);
+        if (split_over(seen)) stash_tiles(std::true_type(), seen, o_lo, o_hi);
     };
 
     f16v main[3], corr[3];
@@ -546,7 +561,7 @@ k_split_weights(const RoundParams *__restrict__ rp, int u, SplitJobs jobs, int64
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             x[e] = d >= lim ? 0.f : j.bwd ? W[((int64_t)(c + e) * j.ic + d) * 9 + 8 - tap] : W[((int64_t)d * j.ic + c + e) * 9 + tap];
-        const Split8 s = split8(x);
+        const Split8 s = split8<true>(x);
 #pragma unroll
         for (int q = 0; q < 3; ++q) dst[q * 576 + t] = __builtin_bit_cast(u4, s.p[q]);
     }

@@ -36,11 +36,11 @@ CASES = {
     "rows_12_of_32": lambda: _maps(3, 48, (16, 12, 32), [_conv(32), _conv(32), W.Layer(W.POOL)]),
     # 6 x 16: fewer rows than a workgroup has
     "rows_6_of_16": lambda: _maps(4, 60, (32, 6, 16), [_conv(32), _conv(32)]),
-    # 10 x 8: rows of 8 that are no square map
     # 16 x 8 and few pixels: only backward-weight takes this form, one and three samples a client
     "rows_16_of_8": lambda: _maps(4, 60, (32, 16, 8), [_conv(64), _conv(48), W.Layer(W.POOL)]),
     "one_sample": lambda: _maps(2, 1, (32, 8, 8), [_conv(64), _conv(64)]),
     "three_samples": lambda: _maps(1, 3, (48, 16, 16), [_conv(64), _conv(64)]),
+    # 10 x 8: rows of 8 that are no square map
     "rows_10_of_8": lambda: _maps(4, 60, (16, 10, 8), [_conv(32), _conv(48), W.Layer(W.POOL)]),
 }
 
@@ -112,3 +112,53 @@ def test_infinities_stay_where_they_were(monkeypatch):
     for kind in (np.isnan, np.isposinf, np.isneginf):
         assert np.array_equal(kind(out[0]), kind(out[1]))
     assert np.isfinite(out[0][0]).all() and not np.isfinite(out[0][1]).all()
+
+
+def _one_layer(scale_w, scale_dense):
+    """One convolution without ReLU; its weights and the dense layer's scaled."""
+    wl = _maps(4, 50, (16, 16, 16), [W.Layer(W.CONV, 32, 3, 1, 0)], rounds=1)
+    s = wl.model.param_slices()
+    wl.w0[s[0][0]:s[0][0] + s[0][1]] *= np.float32(scale_w)
+    wl.w0[s[1][0]:s[1][0] + s[1][1]] *= np.float32(scale_dense)
+    return wl
+
+
+def _largest_pixel():
+    """Rows with a pixel near the largest fp32 value: its outputs are about 1e7, its gradients 1e29."""
+    wl = _one_layer(1e-30, 1e-7)
+    for x in wl.X:
+        x[:, 700] = 3.4e38
+    return wl
+
+
+def _largest_weight():
+    wl = _one_layer(1.0, 1e-9)
+    for x in wl.X:
+        x *= np.float32(1e-30)
+    wl.w0[1234] = -3.4e38
+    return wl
+
+
+@pytest.mark.parametrize("make", [_largest_pixel, _largest_weight])
+def test_largest_finite_values(oracle_libs, make):
+    """Finite values beyond the largest finite bf16 value (3.390e38) keep their finite products.  Bound:
+    rounding of fp32 sums, 1e-5 of the tensor's norm; tensors that are below fp32's normal range (the
+    weights' gradient where the weight is the large factor) are not compared."""
+    from oracle import Oracle
+    from paper_2112_13935_amd.runner import Run
+    wl = make()
+    run, orc = Run(wl), Oracle(make(), "f64")
+    orc.run_round()
+    run.run_round()
+    for c in range(run.n):
+        got, want = run.lib.aet_get_U(c, 0).astype(np.float64), orc.get_U(c, 0)
+        compared = 0
+        for s in [x for x in wl.model.param_slices() if x is not None]:
+            for at, n in ((s[0], s[1]), (s[2], s[3])):
+                g, w = got[at:at + n], want[at:at + n]
+                if np.abs(w).max() < 1e-30:
+                    continue
+                assert np.linalg.norm(g - w) <= 1e-5 * np.linalg.norm(w), (c, at, np.isfinite(g).all())
+                compared += 1
+        assert compared >= 2
+    run.close()
