@@ -17,4 +17,15 @@ inline int resident_clusters(int capacity, int xcds, int cluster_size) {
     return xcds * ((capacity / xcds) / cluster_size);
 }
 
+// Words that stay in an XCD's L2 are seen by that XCD alone (cluster_post.h): a line of memory that
+// holds them must not hold words of a cluster that may run on another one.  So each client's records
+// take whole lines.
+constexpr int kLineWords = 16;   // 64-bit words of a 128-byte line
+constexpr int whole_lines(int words) { return (words + kLineWords - 1) / kLineWords * kLineWords; }
+
+// Records of one client of mini-batch softmax, in words: [step parity][workgroup][sample][12 classes]
+constexpr int softmax_batch_record_words(int workgroups, int batch) {
+    return workgroups > 1 ? whole_lines(2 * workgroups * batch * 12) : 0;
+}
+
 }  // namespace aet

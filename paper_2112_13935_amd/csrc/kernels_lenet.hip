@@ -84,6 +84,7 @@ constexpr int kXDw = 26 * 512 + 128; // one workgroup's dense gradients, as its 
                                      // the biases (32 + 32 + 16) and the loss sum
 constexpr int kXSet = kXB3s + 8 * kXDw;
 constexpr int kXWords2 = 2 * kXB3 + 2 * kXSet;
+static_assert(kXWords % kLineWords == 0 && kXWords2 % kLineWords == 0, "whole lines");
 
 struct LenetDims {
     int H0, P1, H2, P2, F0, lgF0;    // input side, sides after pool 1 / conv 2 / pool 2, F0 = 16 P2^2 = 2^lgF0

@@ -57,7 +57,9 @@ constexpr int kMlpThreads = 64 * kMlpWaves;
 constexpr int kMlpMaxTPW = 7;        // K tiles (of 16) per wave  => D <= 16*8*7 = 896
 constexpr int kMlpMaxG = 16;         // workgroups per client
 constexpr int kMlpRec = 512;         // 64-bit words per exchange record (B*C <= 512)
+static_assert(kMlpRec % kLineWords == 0, "whole lines");
 constexpr int kMlpPair = 512;        // 64-bit words per pair record (B*16 <= 512)
+static_assert(kMlpPair % kLineWords == 0, "whole lines");
 constexpr int kMlpHalfTPW = 4;       // K tiles per wave when two workgroups share the columns
 constexpr int kSpinLimit = 1 << 22;  // bounded wait of the exchange poll
 

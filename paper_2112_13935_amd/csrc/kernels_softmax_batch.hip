@@ -48,6 +48,7 @@ constexpr int kSbThreads = 64 * kSbWaves;
 constexpr int kSbClasses = 10;         // the forward part sums two samples' classes as 20 values
 constexpr int kSbQ = 3;                // groups of four class rows
 constexpr int kSbC = 4 * kSbQ;         // class slots
+static_assert(kSbC == 12, "softmax_batch_record_words");
 static_assert(2 * kSbClasses == 20 && kSbClasses <= kSbC, "five registers of four sums hold two samples' classes");
 constexpr int kSbMaxHF = 6;            // workgroups of a cluster, at most
 constexpr int kSbMaxD = kSbMaxHF * kSbThreads;
@@ -347,8 +348,7 @@ __global__ void k_sb_zero(u64 *p, size_t n) {
 
 // exchange record of one client: [step parity][workgroup][sample][class slot]
 int rec_words(int D, int B) {
-    const int hf = (D + kSbThreads - 1) / kSbThreads;
-    return hf > 1 ? 2 * hf * B * kSbC : 0;
+    return softmax_batch_record_words((D + kSbThreads - 1) / kSbThreads, B);
 }
 // the records of all clients, then the workgroups' places [client][kSbMaxHF]; the error flag follows
 size_t all_words(int n_clients, int D, int B) {

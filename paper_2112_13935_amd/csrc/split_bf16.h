@@ -35,7 +35,7 @@ struct Split8 {
 // is not finite, or would round to infinity, is NaN: split_watch collects the third parts of what a thread
 // stages and split_over says, the same for the wave, whether there may be such values (or of 2^17 and
 // more: the parts' exponents are or-ed together); they are then staged again.  CNN 32 x 32, 32 clients, 4
-// rounds: 34.65 ms, 34.73 so; with a test of each eight values before they are split 1.5 % more, with one of
+// rounds: 34.73 ms, 34.78 so; with a test of each eight values before they are split 1.5 % more, with one of
 // all that a thread stages, which waits for all its loads, 3 to 4 %.
 template <bool CLAMP>
 __device__ __forceinline__ Split8 split8(const float (&x)[8]) {

@@ -1,5 +1,5 @@
 """Clusters per launch (csrc/cluster_plan.h): every workgroup of a launch has a place on its own
-XCD.  The header is plain host code; a small C++ program prints its answers and the launch is
+XCD, and no two clients' records share a line of memory.  The header is plain host code; a small C++ program prints its answers and the launch is
 laid out here the way the round kernels number their workgroups."""
 import os
 import subprocess
@@ -17,7 +17,8 @@ def plan(tmp_path_factory):
     with open(src, "w") as f:
         f.write('#include "cluster_plan.h"\n#include <cstdio>\nint main() {\n'
                 "    int c, x, s;\n"
-                '    while (scanf("%d %d %d", &c, &x, &s) == 3) printf("%d\\n", aet::resident_clusters(c, x, s));\n}\n')
+                '    while (scanf("%d %d %d", &c, &x, &s) == 3)\n'
+                '        printf("%d\\n", c ? aet::resident_clusters(c, x, s) : aet::softmax_batch_record_words(x, s));\n}\n')
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", exe, src], check=True)
 
     def ask(rows):
@@ -51,6 +52,27 @@ def test_every_workgroup_of_a_launch_has_a_place(plan, cus, xcds):
 
 def test_a_cluster_larger_than_an_xcd_has_no_place(plan):
     assert plan([(256, 8, 33)]) == [0]
+
+
+def test_no_two_clients_share_a_line(plan):
+    """A line is 16 words; a client's records are two sets of 12 words per sample and workgroup."""
+    rows = [(0, hf, b) for hf in range(1, 7) for b in range(2, 65)]
+    for (_, hf, b), words in zip(rows, plan(rows)):
+        assert words % 16 == 0
+        assert words == 0 if hf == 1 else 24 * hf * b <= words < 24 * hf * b + 16
+
+
+def test_records_of_mini_batch_softmax_are_laid_out_so():
+    """Workspace of n clients whose records are 3 * 5 * 24 = 360 words without the rounding, 368 with it: beside
+    them a client has its model, its displacement, the layers' values and its place in the lists."""
+    import ctypes
+    import workloads as W
+    from paper_2112_13935_amd.binding import load_library, model_desc
+    lib = load_library()
+    sizes = [lib.aet_workspace_bytes(ctypes.byref(model_desc(W.softmax_model(1100, 10, b))), 512, 1, 1) for b in (5, 6)]
+    # per sample of 512 clients: input row, logits and their gradient, label, and the records' share
+    rest = 512 * (4 * (1100 + 10 + 10) + 4)
+    assert sizes[1] - sizes[0] == rest + 512 * 8 * (432 - 368)
 
 
 @pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet"])

@@ -22,6 +22,7 @@ CASES = {
     "lenet": lambda: W.config3(n_clients=3, n_per=60, rounds=3),
     "lenet_two_clusters": lambda: W.config3(n_clients=3, n_per=60, batch=20, rounds=3, a=20, b=20),
     "softmax_cluster_of_six": lambda: _softmax(3, 3072, 20),
+    "softmax_cluster_of_three_b5": lambda: _softmax(11, 1100, 5),   # records that end inside a line
     "softmax_cluster_of_two": lambda: _softmax(90, 600, 8),
     "softmax_alone": lambda: _softmax(3, 40, 8),
 }
