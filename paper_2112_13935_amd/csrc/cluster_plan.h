@@ -28,4 +28,9 @@ constexpr int softmax_batch_record_words(int workgroups, int batch) {
     return workgroups > 1 ? whole_lines(2 * workgroups * batch * 12) : 0;
 }
 
+// How many times a workgroup polls for a peer's word before it gives up: 2.2 s with polls of the XCD's L2
+// (0.26 us), twice that with polls that go through memory.  (A count and not the clock, which goes on while
+// the queue is preempted, and which cost the LeNet round with two clusters a client 1.3 %.)
+constexpr int kWaitPolls = 1 << 23;
+
 }  // namespace aet

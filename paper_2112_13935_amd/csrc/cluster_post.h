@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cluster_plan.h"
+
 namespace aet {
 
 constexpr int kClusterMax = 32;   // workgroups of a cluster, at most
@@ -28,24 +30,31 @@ __device__ __forceinline__ void cluster_announce(unsigned long long *places, int
         __hip_atomic_store(places + me, ((unsigned long long)tag << 32) | (unsigned)xcc_id(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Do all n workgroups of the cluster run on one XCD?  Every wave asks for itself.  The wait is
-// bounded: on expiry (or once another workgroup's has expired) *dead is set and the answer is no.
-__device__ __forceinline__ bool cluster_on_one_xcd(const unsigned long long *places, int n, uint32_t tag,
-                                                   int spin_limit, int *errflag, bool *dead) {
+// The bounded wait of a poll loop: gave_up() after every poll in vain.  Once this or another workgroup's
+// wait has expired the error flag is set and the answer is yes.
+struct BoundedWait {
+    int polls = 0;
+    __device__ __forceinline__ bool gave_up(int *errflag) {
+        if ((++polls & 255) != 0) return false;
+        if (polls < kWaitPolls && __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return false;
+        __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+};
+
+// Do all n workgroups of the cluster run on one XCD?  Every wave asks for itself.  Where the wait
+// expires *dead is set and the answer is no.
+__device__ __forceinline__ bool cluster_on_one_xcd(const unsigned long long *places, int n, uint32_t tag, int *errflag, bool *dead) {
     if (!places) return false;
     const int lane = threadIdx.x & 63;
     unsigned long long v = 0;
-    int spins = 0;
+    BoundedWait wait;
     for (;;) {
         v = __hip_atomic_load(places + min(lane, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__all((uint32_t)(v >> 32) == tag)) break;
         if (*dead) return false;
         __builtin_amdgcn_s_sleep(1);
-        if ((++spins & 255) == 0 &&
-            (spins >= spin_limit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
-            __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *dead = true;
-        }
+        if (wait.gave_up(errflag)) *dead = true;
     }
     return __all((int)(uint32_t)v == xcc_id());
 }

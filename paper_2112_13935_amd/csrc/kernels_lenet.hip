@@ -67,7 +67,6 @@ constexpr int kS1 = 124, kS2 = 88;   // LDS row strides of arrays with 120 / 84 
 constexpr int kWS = 164;              // LDS row stride of the conv-2 filters (150 used; 4 mod 32: the rows of 8 channels cover all banks)
 constexpr int kDP = 32 * 17;         // floats of one wave's slice of partial dense outputs
 constexpr int kConvP = 2572;         // parameters of the two filter banks (150 + 6 + 2400 + 16)
-constexpr int kLnSpin = 1 << 22;     // bounded wait of the exchange poll
 
 // exchange records of one client, in 64-bit words
 constexpr int kXA1 = 0;              // [16][256]      pooled output of conv 2
@@ -125,7 +124,7 @@ __device__ __forceinline__ void xpost(u64 *p, const Waiter &w, float v) { cluste
 // the current step.  Words that are not needed still point at valid memory.
 template <int N>
 __device__ __forceinline__ void xfetch(const u64 *(&p)[N], const bool (&need)[N], float (&out)[N], Waiter &w) {
-    int spins = 0;
+    BoundedWait wait;
     for (;;) {
         u64 v[N];
 #pragma unroll
@@ -139,12 +138,7 @@ __device__ __forceinline__ void xfetch(const u64 *(&p)[N], const bool (&need)[N]
             return;
         }
         __builtin_amdgcn_s_sleep(1);
-        if ((++spins & 255) == 0) {
-            if (spins >= kLnSpin || __hip_atomic_load(w.errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                __hip_atomic_store(w.errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                w.dead = true;
-            }
-        }
+        if (wait.gave_up(w.errflag)) w.dead = true;
     }
 }
 
@@ -308,7 +302,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     if (p.m > 0) {
         load_rows(0, xr, labr);
         store_rows(xr, labr);
-        wt.one_xcd = cluster_on_one_xcd(places, kLnG * S, tag0, kLnSpin, errflag, &wt.dead);
+        wt.one_xcd = cluster_on_one_xcd(places, kLnG * S, tag0, errflag, &wt.dead);
     }
     __syncthreads();
 

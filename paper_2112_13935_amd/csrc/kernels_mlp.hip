@@ -61,7 +61,6 @@ static_assert(kMlpRec % kLineWords == 0, "whole lines");
 constexpr int kMlpPair = 512;        // 64-bit words per pair record (B*16 <= 512)
 static_assert(kMlpPair % kLineWords == 0, "whole lines");
 constexpr int kMlpHalfTPW = 4;       // K tiles per wave when two workgroups share the columns
-constexpr int kSpinLimit = 1 << 22;  // bounded wait of the exchange poll
 
 // Hides a value from the optimiser so that addresses derived from it are computed where
 // they are used instead of being kept in registers across the whole recursion loop.
@@ -276,7 +275,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     // pair records [client][unit group][step parity][half][B * 16]
     unsigned long long *prec_base = prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair;
     bool dead = false;  // the poll expired: keep going, the host will see the flag
-    const bool one_xcd = cluster_on_one_xcd(places, G * HF, tag0, kSpinLimit, errflag, &dead);
+    const bool one_xcd = cluster_on_one_xcd(places, G * HF, tag0, errflag, &dead);
     __syncthreads();
 
     auto park_rows = [&]() {
@@ -347,17 +346,12 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             next_rows();
             const unsigned long long *theirs = pr + (1 - hf) * kMlpPair + min(i, B * 16 - 1);
             unsigned long long v = 0;
-            int spins = 0;
+            BoundedWait wait;
             for (;;) {
                 v = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (__all((uint32_t)(v >> 32) == tag) || dead) break;
                 __builtin_amdgcn_s_sleep(1);
-                if ((++spins & 255) == 0) {
-                    if (spins >= kSpinLimit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                        __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        dead = true;
-                    }
-                }
+                if (wait.gave_up(errflag)) dead = true;
             }
             if (i < B * 16) {
                 const float other = __uint_as_float((uint32_t)v);
@@ -414,7 +408,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             const int b = tid >> 4, o = tid & 15;
             const bool mine = b < B && o < C;
             float z = 0.f;
-            int spins = 0;
+            BoundedWait wait;
             if (mine) {
                 const unsigned long long *src = rec + b * C + o;
                 constexpr int GC = 8;  // records fetched per batch of loads
@@ -447,12 +441,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                     }
                     if (ok || dead) break;
                     if (!one_xcd) __builtin_amdgcn_s_sleep(2);
-                    if ((++spins & 255) == 0) {
-                        if (spins >= kSpinLimit || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                            __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            dead = true;
-                        }
-                    }
+                    if (wait.gave_up(errflag)) dead = true;
                 }
             }
             if (b < B) {

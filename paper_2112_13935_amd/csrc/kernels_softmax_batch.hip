@@ -54,7 +54,6 @@ constexpr int kSbMaxHF = 6;            // workgroups of a cluster, at most
 constexpr int kSbMaxD = kSbMaxHF * kSbThreads;
 constexpr int kSbMaxB = 64;
 constexpr int kSbPS = 13;              // LDS stride of a sample's partial logits
-constexpr int kSbSpin = 1 << 22;       // bounded wait of the exchange poll
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
@@ -158,7 +157,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
 #pragma unroll
         for (int j = 0; j < NC; ++j) load_col(j);
         if (wave == 0 && lane < BC) labs[lane] = labn;
-        if (HF > 1) one_xcd = cluster_on_one_xcd(places, HF, tag0, kSbSpin, errflag, &dead);
+        if (HF > 1) one_xcd = cluster_on_one_xcd(places, HF, tag0, errflag, &dead);
     }
     for (int u = 0; u < p.m; ++u) {
         int lio = li;   // compared where it is needed: 16 masks kept in scalar registers would spill
@@ -226,7 +225,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                 const int i = tid + T * e, b = i >> 4, o = i & 15;
                 if (b < Br && o < C) {
                     const u64 *src = rec + (int64_t)b * kSbC + o;
-                    int spins = 0;
+                    BoundedWait wait;
                     float sum;
                     for (;;) {
                         u64 v[6];
@@ -243,12 +242,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                             }
                         if (ok || dead) break;
                         __builtin_amdgcn_s_sleep(1);
-                        if ((++spins & 255) == 0) {
-                            if (spins >= kSbSpin || __hip_atomic_load(errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                                __hip_atomic_store(errflag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                dead = true;
-                            }
-                        }
+                        if (wait.gave_up(errflag)) dead = true;
                     }
                     z[e] = sum;
                 }
