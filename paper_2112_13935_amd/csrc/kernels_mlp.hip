@@ -43,6 +43,8 @@
 // working workgroups on an XCD than it holds (cluster_plan.h; 1 per compute unit with this
 // LDS footprint).  The poll is bounded: on expiry an error flag is raised and every workgroup
 // still runs to the end, so the grid always drains.
+#include <type_traits>
+
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "cluster_plan.h"
@@ -185,7 +187,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     float *b2s = Ub1s + 16;
     float *Ub2s = b2s + 16;
     float *lossb = Ub2s + 16;         // [B]
-    float *lossacc = lossb + B;       // [16], entry 0: the round's loss sum
+    float *lossacc = lossb + B;       // [16], entry 0: the round's loss sum; 1: not zero: the cluster spans XCDs
     int *labs = reinterpret_cast<int *>(lossacc + 16);  // [B]
     float *Xs = reinterpret_cast<float *>(labs + B); // [B][ld]
 
@@ -275,8 +277,10 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     // pair records [client][unit group][step parity][half][B * 16]
     unsigned long long *prec_base = prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair;
     bool dead = false;  // the poll expired: keep going, the host will see the flag
-    const bool one_xcd = cluster_on_one_xcd(places, G * HF, tag0, errflag, &dead);
+    // the same answer in all waves (one whose wait expired says no): there are barriers that hang on it
+    if (!cluster_on_one_xcd(places, G * HF, tag0, errflag, &dead)) lossacc[1] = 1.f;
     __syncthreads();
+    const bool one_xcd = __builtin_amdgcn_readfirstlane(lossacc[1] == 0.f);
 
     auto park_rows = [&]() {
 #pragma unroll
@@ -286,273 +290,301 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                 if (FULL || tt < nt)
                     *reinterpret_cast<f4 *>(Xs + (16 * bt + li) * ld + col0 + 16 * tt + 4 * lg) = xreg[bt][tt];
     };
-    for (int u = 0; u < p.m; ++u) {
-        // ---- z1 partial sums on the matrix cores ----------------------------------------
-        {
-            f4 acc[NBT];
+    auto recursions = [&](const auto same) {   // same: whether the words stay in the L2 of one XCD
+        for (int u = 0; u < p.m; ++u) {
+            // ---- z1 partial sums on the matrix cores ----------------------------------------
+            {
+                f4 acc[NBT];
 #pragma unroll
-            for (int bt = 0; bt < NBT; ++bt) acc[bt] = f4{0.f, 0.f, 0.f, 0.f};
-            // the A operand comes straight from the registers the rows were loaded into
-            // (all TPW slots, free of branches: an empty slot holds zeros on both sides; skipping
-            // it measured slower here, while the backward product below gains from skipping)
+                for (int bt = 0; bt < NBT; ++bt) acc[bt] = f4{0.f, 0.f, 0.f, 0.f};
+                // the A operand comes straight from the registers the rows were loaded into
+                // (all TPW slots, free of branches: an empty slot holds zeros on both sides; skipping
+                // it measured slower here, while the backward product below gains from skipping)
 #pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
+                for (int tt = 0; tt < TPW; ++tt) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+                    for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int bt = 0; bt < NBT; ++bt) acc[bt] = mfma16(xreg[bt][tt][r], W1r[tt][r], acc[bt]);
+                        for (int bt = 0; bt < NBT; ++bt) acc[bt] = mfma16(xreg[bt][tt][r], W1r[tt][r], acc[bt]);
+                }
+                // the backward product needs the rows transposed: park them in LDS (this wave's
+                // columns only, so no barrier; the writes drain while the logits are exchanged).
+                // With two workgroups per unit group they are parked between the post and the
+                // poll of the pair exchange instead.
+                if constexpr (HF == 1) park_rows();
+#pragma unroll
+                for (int bt = 0; bt < NBT; ++bt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        red[(wave * B + 16 * bt + 4 * lg + r) * 16 + li] = acc[bt][r];
             }
-            // the backward product needs the rows transposed: park them in LDS (this wave's
-            // columns only, so no barrier; the writes drain while the logits are exchanged).
-            // With two workgroups per unit group they are parked between the post and the
-            // poll of the pair exchange instead.
-            if constexpr (HF == 1) park_rows();
+            __syncthreads();
+            // the rows the next recursion samples (Algorithm 2, sampling step; a counter
+            // hash, so they are known ahead); with two workgroups per unit group the hash is
+            // computed while the pair exchange is in flight
+            uint32_t rowv = 0;
+            const bool more = u + 1 < p.m;
+            auto next_rows = [&]() {
+                if (more && lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)(u + 1) * Br + min(lane, Br - 1)), p.n_samples);
+            };
+            // ---- h = relu(z1 + b1) ----------------------------------------------------------
+            const uint32_t tag = tag0 + (uint32_t)u;
+            if constexpr (HF == 1) {
+                for (int i = tid; i < B * 16; i += kMlpThreads) {
+                    float s = b1s[i & 15];
 #pragma unroll
-            for (int bt = 0; bt < NBT; ++bt)
+                    for (int w = 0; w < kMlpWaves; ++w) s += red[w * B * 16 + i];
+                    hs[i] = s > 0.f ? s : 0.f;
+                }
+            } else {
+                // the own half's sums go to the pair record, the other half's come from there;
+                // both halves add them in the same order (half 0 + half 1), so both get the same h
+                unsigned long long *pr = prec_base + (int64_t)(u & 1) * 2 * kMlpPair;
+                const int i = tid;   // B * 16 <= 512 elements, one per thread
+                float own = 0.f;
+                if (i < B * 16) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    red[(wave * B + 16 * bt + 4 * lg + r) * 16 + li] = acc[bt][r];
-        }
-        __syncthreads();
-        // the rows the next recursion samples (Algorithm 2, sampling step; a counter
-        // hash, so they are known ahead); with two workgroups per unit group the hash is
-        // computed while the pair exchange is in flight
-        uint32_t rowv = 0;
-        const bool more = u + 1 < p.m;
-        auto next_rows = [&]() {
-            if (more && lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)(u + 1) * Br + min(lane, Br - 1)), p.n_samples);
-        };
-        // ---- h = relu(z1 + b1) ----------------------------------------------------------
-        const uint32_t tag = tag0 + (uint32_t)u;
-        if constexpr (HF == 1) {
-            for (int i = tid; i < B * 16; i += kMlpThreads) {
-                float s = b1s[i & 15];
-#pragma unroll
-                for (int w = 0; w < kMlpWaves; ++w) s += red[w * B * 16 + i];
-                hs[i] = s > 0.f ? s : 0.f;
-            }
-        } else {
-            // the own half's sums go to the pair record, the other half's come from there;
-            // both halves add them in the same order (half 0 + half 1), so both get the same h
-            unsigned long long *pr = prec_base + (int64_t)(u & 1) * 2 * kMlpPair;
-            const int i = tid;   // B * 16 <= 512 elements, one per thread
-            float own = 0.f;
-            if (i < B * 16) {
-#pragma unroll
-                for (int w = 0; w < kMlpWaves; ++w) own += red[w * B * 16 + i];
-                cluster_post(pr + hf * kMlpPair + i, tag, own, one_xcd);
-            }
-            park_rows();
-            next_rows();
-            const unsigned long long *theirs = pr + (1 - hf) * kMlpPair + min(i, B * 16 - 1);
-            unsigned long long v = 0;
-            BoundedWait wait;
-            for (;;) {
-                v = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (__all((uint32_t)(v >> 32) == tag) || dead) break;
-                __builtin_amdgcn_s_sleep(1);
-                if (wait.gave_up(errflag)) dead = true;
-            }
-            if (i < B * 16) {
-                const float other = __uint_as_float((uint32_t)v);
-                const float s = b1s[i & 15] + (hf == 0 ? own + other : other + own);
-                hs[i] = s > 0.f ? s : 0.f;
-            }
-        }
-        __syncthreads();
-        // ---- partial logits of the own 16 units -> tagged exchange record ---------------
-        unsigned long long *rec = rec_base + (int64_t)(u & 1) * kMlpMaxG * kMlpRec;
-        if (wave < NBT && hf == 0) {
-            const int bt = wave;
-            f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                acc = mfma16(hs[(16 * bt + li) * 16 + 4 * s + lg], W2s[li * 16 + 4 * s + lg], acc);
-            if (li < C) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int b = 16 * bt + 4 * lg + r;
-                    cluster_post(rec + (int64_t)g * kMlpRec + b * C + li, tag, acc[r], one_xcd);
+                    for (int w = 0; w < kMlpWaves; ++w) own += red[w * B * 16 + i];
+                    cluster_post(pr + hf * kMlpPair + i, tag, own, same);
+                }
+                park_rows();
+                next_rows();
+                const unsigned long long *theirs = pr + (1 - hf) * kMlpPair + min(i, B * 16 - 1);
+                unsigned long long v = 0;
+                BoundedWait wait;
+                for (;;) {
+                    v = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (__all((uint32_t)(v >> 32) == tag) || dead) break;
+                    __builtin_amdgcn_s_sleep(1);
+                    if (wait.gave_up(errflag)) dead = true;
+                }
+                if (i < B * 16) {
+                    const float other = __uint_as_float((uint32_t)v);
+                    const float s = b1s[i & 15] + (hf == 0 ? own + other : other + own);
+                    hs[i] = s > 0.f ? s : 0.f;
                 }
             }
-        }
-        // ---- prefetch the rows of the NEXT recursion into registers ----------------------
-        // (Algorithm 2, sampling step; the indices are a counter hash, so they are
-        // known ahead of time).  Loads of one wave return in order, so nothing is issued
-        // before the exchange poll.
-        int labn = 0;
-        // the rows' indices and the labels now; the row loads themselves are issued a few at
-        // a time between the first tiles of the backward product, so that a wave that has to
-        // wait for room in the memory pipeline leaves the matrix core to the SIMD's other
-        // wave.  They go into the registers the forward product has finished with.
-        gcf_ptr myrow[NBT];
-        auto prefetch_rows = [&]() {
-            if (!more) return;
-            if constexpr (HF == 1) next_rows();
-            if (wave == 0 && lane < B) labn = yg[rowv];
+            __syncthreads();
+            // ---- partial logits of the own 16 units -> tagged exchange record ---------------
+            unsigned long long *rec = rec_base + (int64_t)(u & 1) * kMlpMaxG * kMlpRec;
+            if (wave < NBT && hf == 0) {
+                const int bt = wave;
+                f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int bt = 0; bt < NBT; ++bt) myrow[bt] = lane_src + (int64_t)__shfl(rowv, 16 * bt + li) * D;
-        };
-        constexpr int PFT = TPW > 4 ? 4 : TPW;   // tiles of the backward product that carry loads
-        auto prefetch_load = [&](int i) {        // i = tt * NBT + bt: in the order the forward product uses them
-            if (!more) return;
-            xreg[i % NBT][i / NBT] = load_piece(myrow[i % NBT], i / NBT);
-        };
-        // ---- logits, softmax, d logits: thread (b, o) = (tid / 16, tid % 16) ------------
-        // Every thread with o < C polls the G tagged words of its own element (b, o): an exchange
-        // is then one trip.  (While the words went through memory such polls slowed the peers'
-        // stores down, and one wave watched one word per record before anybody fetched; with the
-        // words in the XCD's L2 the watch costs more than it saves: 16 clients, 784 -> 128, 50
-        // rounds 7.61 ms with it, 7.47 without; through memory, and watched, 8.77.)
-        {
-            const int b = tid >> 4, o = tid & 15;
-            const bool mine = b < B && o < C;
-            float z = 0.f;
-            BoundedWait wait;
-            if (mine) {
-                const unsigned long long *src = rec + b * C + o;
-                constexpr int GC = 8;  // records fetched per batch of loads
-                for (;;) {
-                    bool ok = true;
-                    z = b2s[o];
-                    if (G <= GC) {   // one batch; records beyond the last stand for it
-                        unsigned long long v[GC];
+                for (int s = 0; s < 4; ++s)
+                    acc = mfma16(hs[(16 * bt + li) * 16 + 4 * s + lg], W2s[li * 16 + 4 * s + lg], acc);
+                if (li < C) {
 #pragma unroll
-                        for (int gg = 0; gg < GC; ++gg)
-                            v[gg] = __hip_atomic_load(src + min(gg, G - 1) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int r = 0; r < 4; ++r) {
+                        const int b = 16 * bt + 4 * lg + r;
+                        cluster_post(rec + (int64_t)g * kMlpRec + b * C + li, tag, acc[r], same);
+                    }
+                }
+            }
+            // ---- prefetch the rows of the NEXT recursion into registers ----------------------
+            // (Algorithm 2, sampling step; the indices are a counter hash, so they are
+            // known ahead of time).  Loads of one wave return in order, so nothing is issued
+            // before the exchange poll.
+            int labn = 0;
+            // the rows' indices and the labels now; the row loads themselves are issued a few at
+            // a time between the first tiles of the backward product, so that a wave that has to
+            // wait for room in the memory pipeline leaves the matrix core to the SIMD's other
+            // wave.  They go into the registers the forward product has finished with.
+            gcf_ptr myrow[NBT];
+            auto prefetch_rows = [&]() {
+                if (!more) return;
+                if constexpr (HF == 1) next_rows();
+                if (wave == 0 && lane < B) labn = yg[rowv];
 #pragma unroll
-                        for (int gg = 0; gg < GC; ++gg) {
-                            ok = ok && (uint32_t)(v[gg] >> 32) == tag;
-                            if (gg < G) z += __uint_as_float((uint32_t)v[gg]);
+                for (int bt = 0; bt < NBT; ++bt) myrow[bt] = lane_src + (int64_t)__shfl(rowv, 16 * bt + li) * D;
+            };
+            constexpr int PFT = TPW > 4 ? 4 : TPW;   // tiles of the backward product that carry loads
+            auto prefetch_load = [&](int i) {        // i = tt * NBT + bt: in the order the forward product uses them
+                if (!more) return;
+                xreg[i % NBT][i / NBT] = load_piece(myrow[i % NBT], i / NBT);
+            };
+            // ---- logits, softmax, d logits: thread (b, o) = (tid / 16, tid % 16) ------------
+            // Every thread with o < C polls the G tagged words of its own element (b, o): with the
+            // words in the XCD's L2 an exchange is then one trip.  Polls through memory slow the peers'
+            // stores down (they meet in the same memory channels): there, while the peers are still
+            // computing, only wave 0 looks, and only at one word per record and batch tile (the last one
+            // its owner stores).  The element tags are still checked, and the fetch repeated if one is
+            // stale.  (A separate flag word per poster, stored after the logits, overtakes them on the
+            // way.)  16 clients, 784 -> 128, 50 rounds: in L2 7.61 ms with the watch, 7.47 without;
+            // through memory 8.9 and 12.1.
+            {
+                const int b = tid >> 4, o = tid & 15;
+                const bool mine = b < B && o < C;
+                float z = 0.f;
+                BoundedWait wait;
+                if (!same) {
+                    if (wave == 0) {
+                        // lane -> (record, batch tile); the word of sample 16*bt+15, class C-1
+                        const int gg = lane % G, bt = lane / G;
+                        const unsigned long long *w = rec + (int64_t)gg * kMlpRec + (16 * min(bt, NBT - 1) + 15) * C + (C - 1);
+                        for (;;) {
+                            bool ok = true;
+                            if (bt < NBT) ok = (uint32_t)(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == tag;
+                            if (__all(ok) || dead) break;
+                            __builtin_amdgcn_s_sleep(2);
+                            if (wait.gave_up(errflag)) dead = true;
                         }
-                    } else {
-                        for (int g0 = 0; g0 < G; g0 += GC) {
+                    }
+                    __syncthreads();
+                }
+                if (mine) {
+                    const unsigned long long *src = rec + b * C + o;
+                    constexpr int GC = 8;  // records fetched per batch of loads
+                    for (;;) {
+                        bool ok = true;
+                        z = b2s[o];
+                        if (G <= GC) {   // one batch; records beyond the last stand for it
                             unsigned long long v[GC];
 #pragma unroll
                             for (int gg = 0; gg < GC; ++gg)
-                                if (g0 + gg < G) v[gg] = __hip_atomic_load(src + (g0 + gg) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                v[gg] = __hip_atomic_load(src + min(gg, G - 1) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                            for (int gg = 0; gg < GC; ++gg)
-                                if (g0 + gg < G) {
-                                    ok = ok && (uint32_t)(v[gg] >> 32) == tag;
-                                    z += __uint_as_float((uint32_t)v[gg]);
-                                }
+                            for (int gg = 0; gg < GC; ++gg) {
+                                ok = ok && (uint32_t)(v[gg] >> 32) == tag;
+                                if (gg < G) z += __uint_as_float((uint32_t)v[gg]);
+                            }
+                        } else {
+                            for (int g0 = 0; g0 < G; g0 += GC) {
+                                unsigned long long v[GC];
+#pragma unroll
+                                for (int gg = 0; gg < GC; ++gg)
+                                    if (g0 + gg < G) v[gg] = __hip_atomic_load(src + (g0 + gg) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                                for (int gg = 0; gg < GC; ++gg)
+                                    if (g0 + gg < G) {
+                                        ok = ok && (uint32_t)(v[gg] >> 32) == tag;
+                                        z += __uint_as_float((uint32_t)v[gg]);
+                                    }
+                            }
+                        }
+                        if (ok || dead) break;
+                        if (!same) __builtin_amdgcn_s_sleep(2);
+                        if (wait.gave_up(errflag)) dead = true;
+                    }
+                }
+                if (b < B) {
+                    const float zmax = row16_max(o < C ? z : -3.0e38f);
+                    // PAD: expf and logf as in the layer engine, where these models run otherwise
+                    const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
+                    const float ex = o < C ? exp_of(z - zmax) : 0.f;
+                    const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
+                    const int lab = labs[b];
+                    if (o == lab) lossb[b] = lse - z;
+                    zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+                }
+            }
+            __syncthreads();
+            // ---- small products on the matrix cores -----------------------------------------
+            prefetch_rows();
+            f4 dW2acc = {0.f, 0.f, 0.f, 0.f};
+            if (wave < NBT) {
+                // dh = (dz W2) * 1[h > 0] for samples 16*wave .. 16*wave+15
+                const int bt = wave;
+                f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc = mfma16(zs[(16 * bt + li) * 16 + 4 * s + lg], W2s[(4 * s + lg) * 16 + li], acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = (16 * bt + 4 * lg + r) * 16 + li;
+                    dhs[i] = hs[i] > 0.f ? acc[r] : 0.f;
+                }
+            } else if (wave == 2) {
+                // dW2[o][j] = sum_b dz[b][o] h[b][j]; applied after the barrier (W2 is still read)
+#pragma unroll
+                for (int s = 0; s < 4 * NBT; ++s)
+                    dW2acc = mfma16(zs[(4 * s + lg) * 16 + li], hs[(4 * s + lg) * 16 + li], dW2acc);
+            } else if (wave == 3) {
+                // second-layer bias: column sums of dz
+                const float s = col_sum16<B>(zs, lane) * invB;
+                if (lane < C) {
+                    b2s[lane] -= p.eta * s;
+                    Ub2s[lane] += s;
+                }
+            } else if (wave == 4) {
+                // the recursion's mean loss
+                const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
+                if (lane == 0) lossacc[0] += s * invB;
+            }
+            __syncthreads();
+            // ---- second layer and first-layer bias: w <- w - eta g, U <- U + g ---------------
+            if (wave == 2) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = (4 * lg + r) * 16 + li;  // (o, j)
+                    const float gv = dW2acc[r] * invB;
+                    W2s[i] -= p.eta * gv;
+                    U2s[i] += gv;
+                }
+            } else if (wave == 3) {
+                // first-layer bias: column sums of dh
+                const float s = col_sum16<B>(dhs, lane) * invB;
+                if (lane < 16) {
+                    b1s[lane] -= p.eta * s;
+                    Ub1s[lane] += s;
+                }
+            }
+            // ---- first layer: dW1^T = X^T dh on the matrix cores, update in registers -------
+            {
+                // contraction step s of lane group lg takes sample 16*(s/4) + (s%4) + 4*lg: with
+                // rows 4*lg apart the four lane groups read LDS banks 16 apart (ld = 4 mod 32)
+                float dhb[4 * NBT];
+#pragma unroll
+                for (int s = 0; s < 4 * NBT; ++s) dhb[s] = dhs[(16 * (s >> 2) + (s & 3) + 4 * lg) * 16 + li];
+                float xb[2][4 * NBT];
+                const float *xcol = Xs + opaque(4 * lg * ld + col0 + li);
+                if (FULL || nt > 0) {
+#pragma unroll
+                    for (int s = 0; s < 4 * NBT; ++s) xb[0][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld];
+                }
+                const float eb = p.eta * invB;
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) {
+                    if (tt + 1 < TPW && (FULL || tt + 1 < nt)) {
+#pragma unroll
+                        for (int s = 0; s < 4 * NBT; ++s) xb[(tt + 1) & 1][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld + 16 * (tt + 1)];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // the next tile's operands are on their way before the products
+                    if (FULL || tt < nt) {
+                        // two independent accumulation chains per tile
+                        // (the first product of each chain takes the constant zero as its addend)
+                        f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], f4{0.f, 0.f, 0.f, 0.f});
+                        f4 acc1 = mfma16(xb[tt & 1][1], dhb[1], f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                        for (int s = 2; s < 4 * NBT; s += 2) {
+                            acc0 = mfma16(xb[tt & 1][s], dhb[s], acc0);
+                            acc1 = mfma16(xb[tt & 1][s + 1], dhb[s + 1], acc1);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float gsum = acc0[r] + acc1[r];
+                            W1r[tt][r] -= eb * gsum;
+                            U1r[tt][r] += invB * gsum;
                         }
                     }
-                    if (ok || dead) break;
-                    if (!one_xcd) __builtin_amdgcn_s_sleep(2);
-                    if (wait.gave_up(errflag)) dead = true;
+                    // this tile's share of the next recursion's row loads
+#pragma unroll
+                    for (int i = tt * NI / PFT; i < (tt + 1) * NI / PFT && i < NI; ++i) prefetch_load(i);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if (b < B) {
-                const float zmax = row16_max(o < C ? z : -3.0e38f);
-                // PAD: expf and logf as in the layer engine, where these models run otherwise
-                const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
-                const float ex = o < C ? exp_of(z - zmax) : 0.f;
-                const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
-                const int lab = labs[b];
-                if (o == lab) lossb[b] = lse - z;
-                zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
-            }
+            // ---- the next recursion's labels ----------------------------------------------------
+            if (more && wave == 0 && lane < B) labs[lane] = labn;
         }
-        __syncthreads();
-        // ---- small products on the matrix cores -----------------------------------------
-        prefetch_rows();
-        f4 dW2acc = {0.f, 0.f, 0.f, 0.f};
-        if (wave < NBT) {
-            // dh = (dz W2) * 1[h > 0] for samples 16*wave .. 16*wave+15
-            const int bt = wave;
-            f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                acc = mfma16(zs[(16 * bt + li) * 16 + 4 * s + lg], W2s[(4 * s + lg) * 16 + li], acc);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (16 * bt + 4 * lg + r) * 16 + li;
-                dhs[i] = hs[i] > 0.f ? acc[r] : 0.f;
-            }
-        } else if (wave == 2) {
-            // dW2[o][j] = sum_b dz[b][o] h[b][j]; applied after the barrier (W2 is still read)
-#pragma unroll
-            for (int s = 0; s < 4 * NBT; ++s)
-                dW2acc = mfma16(zs[(4 * s + lg) * 16 + li], hs[(4 * s + lg) * 16 + li], dW2acc);
-        } else if (wave == 3) {
-            // second-layer bias: column sums of dz
-            const float s = col_sum16<B>(zs, lane) * invB;
-            if (lane < C) {
-                b2s[lane] -= p.eta * s;
-                Ub2s[lane] += s;
-            }
-        } else if (wave == 4) {
-            // the recursion's mean loss
-            const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
-            if (lane == 0) lossacc[0] += s * invB;
-        }
-        __syncthreads();
-        // ---- second layer and first-layer bias: w <- w - eta g, U <- U + g ---------------
-        if (wave == 2) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (4 * lg + r) * 16 + li;  // (o, j)
-                const float gv = dW2acc[r] * invB;
-                W2s[i] -= p.eta * gv;
-                U2s[i] += gv;
-            }
-        } else if (wave == 3) {
-            // first-layer bias: column sums of dh
-            const float s = col_sum16<B>(dhs, lane) * invB;
-            if (lane < 16) {
-                b1s[lane] -= p.eta * s;
-                Ub1s[lane] += s;
-            }
-        }
-        // ---- first layer: dW1^T = X^T dh on the matrix cores, update in registers -------
-        {
-            // contraction step s of lane group lg takes sample 16*(s/4) + (s%4) + 4*lg: with
-            // rows 4*lg apart the four lane groups read LDS banks 16 apart (ld = 4 mod 32)
-            float dhb[4 * NBT];
-#pragma unroll
-            for (int s = 0; s < 4 * NBT; ++s) dhb[s] = dhs[(16 * (s >> 2) + (s & 3) + 4 * lg) * 16 + li];
-            float xb[2][4 * NBT];
-            const float *xcol = Xs + opaque(4 * lg * ld + col0 + li);
-            if (FULL || nt > 0) {
-#pragma unroll
-                for (int s = 0; s < 4 * NBT; ++s) xb[0][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld];
-            }
-            const float eb = p.eta * invB;
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
-                if (tt + 1 < TPW && (FULL || tt + 1 < nt)) {
-#pragma unroll
-                    for (int s = 0; s < 4 * NBT; ++s) xb[(tt + 1) & 1][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld + 16 * (tt + 1)];
-                }
-                __builtin_amdgcn_sched_barrier(0);   // the next tile's operands are on their way before the products
-                if (FULL || tt < nt) {
-                    // two independent accumulation chains per tile
-                    // (the first product of each chain takes the constant zero as its addend)
-                    f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], f4{0.f, 0.f, 0.f, 0.f});
-                    f4 acc1 = mfma16(xb[tt & 1][1], dhb[1], f4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-                    for (int s = 2; s < 4 * NBT; s += 2) {
-                        acc0 = mfma16(xb[tt & 1][s], dhb[s], acc0);
-                        acc1 = mfma16(xb[tt & 1][s + 1], dhb[s + 1], acc1);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float gsum = acc0[r] + acc1[r];
-                        W1r[tt][r] -= eb * gsum;
-                        U1r[tt][r] += invB * gsum;
-                    }
-                }
-                // this tile's share of the next recursion's row loads
-#pragma unroll
-                for (int i = tt * NI / PFT; i < (tt + 1) * NI / PFT && i < NI; ++i) prefetch_load(i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // ---- the next recursion's labels ----------------------------------------------------
-        if (more && wave == 0 && lane < B) labs[lane] = labn;
-    }
+    };
+    // Written out for either answer, or with a test in one loop where two would not fit the registers
+    // (two batch tiles with seven column tiles: 260 to 350 bytes spilled).  No test and no watch / one
+    // loop with them / two loops, words in L2, ms: 16 clients, 784 -> 128, B = 32, 50 rounds 7.46, 7.57,
+    // 7.29; 20 rounds: 100 clients, 60 -> 64 3.05, -, 2.91; 48, 784 -> 128 4.05, 3.91, 4.76; 40, 896 -> 256
+    // 7.25, 7.08, 10.3; B = 16: 40, 896 -> 256 4.93, -, 4.84; 48, 784 -> 128 2.53, 2.61, 2.57.
+    if (NBT * TPW > 2 * kMlpHalfTPW) recursions(one_xcd);
+    else if (one_xcd) recursions(std::true_type());
+    else recursions(std::false_type());
 
     // ---- end of round: the replica and the message payload go to HBM ---------------------
 #pragma unroll
