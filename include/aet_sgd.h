@@ -319,6 +319,16 @@ aet_status aet_reset(aet_ctx *ctx);
  * defaults.  It also changes what aet_workspace_bytes returns. */
 void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers);
 
+/* Test hooks, process-wide; aet_test_variants(0) restores the defaults.
+ * AET_TEST_XCDS_DIFFER  rounds launched until the next call: the first workgroup of each client names
+ *                       another XCD than its own, so that the client's workgroups find that they do not
+ *                       share one.
+ * aet_test_one_xcd_clients: clients whose workgroups found, in the last round that asked, that they share an
+ * XCD (0 for models whose rounds do not run in clusters); synchronises. */
+#define AET_TEST_XCDS_DIFFER 1u
+void aet_test_variants(uint32_t variants);
+aet_status aet_test_one_xcd_clients(aet_ctx *ctx, int32_t *count);
+
 /* Optional kernel timing for measurement harnesses.  The library's kernels are grouped
  * in families (aet_profile_family_name gives each family's kernel name); while a family
  * is enabled, every launch of it is bracketed by a pair of HIP events recorded on the

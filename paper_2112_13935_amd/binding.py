@@ -25,6 +25,7 @@ EXPORTS = [
     "aet_profile_family_name", "aet_profile_enable", "aet_profile_read", "aet_run_ticks",
     "aet_topology_workspace_bytes", "aet_set_topology", "aet_receive", "aet_set_setup",
     "aet_set_weights", "aet_init_static", "aet_test_select_kernels",
+    "aet_test_variants", "aet_test_one_xcd_clients",
 ]
 
 
@@ -135,6 +136,10 @@ def load_library():
     lib.aet_profile_read.argtypes = [vp, i32, C.POINTER(i64), C.POINTER(C.c_double), i32]
     lib.aet_test_select_kernels.restype = None
     lib.aet_test_select_kernels.argtypes = [i32, i32]
+    lib.aet_test_variants.restype = None
+    lib.aet_test_variants.argtypes = [C.c_uint32]
+    lib.aet_test_one_xcd_clients.restype = C.c_int
+    lib.aet_test_one_xcd_clients.argtypes = [vp, C.POINTER(i32)]
     lib.aet_destroy.restype = None
     lib.aet_destroy.argtypes = [vp]
     _LIB = lib
@@ -327,6 +332,11 @@ class AetSgd:
 
     def aet_reset(self):
         self._check(self.lib.aet_reset(self.ctx))
+
+    def aet_test_one_xcd_clients(self) -> int:
+        count = C.c_int32()
+        self._check(self.lib.aet_test_one_xcd_clients(self.ctx, C.byref(count)))
+        return count.value
 
     def aet_profile_enable(self, family: int, on: bool):
         self._check(self.lib.aet_profile_enable(self.ctx, family, 1 if on else 0))

@@ -15,6 +15,7 @@
 #include "../../include/aet_sgd.h"
 #include "aet_device.h"
 #include "aet_internal.h"
+#include "cluster_plan.h"
 #include "cluster_turns.h"
 
 using namespace aet;
@@ -389,6 +390,7 @@ const std::vector<int64_t> &setup_shares(aet_ctx *ctx, int64_t i, int64_t a, int
 }  // namespace
 
 bool aet::g_posts_to_memory = false;
+int aet::g_xcd_skew = 0;
 
 extern "C" {
 
@@ -397,6 +399,8 @@ void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers) {
     g_posts_to_memory = force_layer_engine == 2;
     g_plain_layers = plain_layers != 0;
 }
+
+void aet_test_variants(uint32_t variants) { g_xcd_skew = (variants & AET_TEST_XCDS_DIFFER) ? 1 : 0; }
 
 int64_t aet_n_params(const aet_model_desc *model) {
     LayerGeom lay[AET_MAX_LAYERS];
@@ -882,14 +886,38 @@ aet_status aet_receive(aet_ctx *ctx, float scale, int32_t *n_applied, int32_t *a
     return AET_OK;
 }
 
+// The error flag of the rounds in clusters, NULL where the rounds are none.  The places of the clients'
+// workgroups are the words in front of it.
+static const int *cluster_flag(aet_ctx *ctx) {
+    char *fused = ctx->ws + ctx->lo.fused;
+    switch (ctx->engine) {
+        case ENGINE_MLP: return mlp_error_flag_ptr(fused, ctx->n, ctx->B);
+        case ENGINE_LENET: return lenet_error_flag_ptr(fused, ctx->n, ctx->B);
+        case ENGINE_SOFTMAX_BATCH: return softmax_batch_error_flag_ptr(fused, ctx->n, (int)ctx->lay[0].in_size, ctx->B);
+        default: return nullptr;
+    }
+}
+
+aet_status aet_test_one_xcd_clients(aet_ctx *ctx, int32_t *count) {
+    if (!ctx) return AET_EINVAL;
+    if (!count) return fail(ctx, AET_EINVAL, "NULL argument");
+    if (ctx->dead) return fail(ctx, AET_ESTATE, "context is unusable after a HIP error");
+    *count = 0;
+    const int *flag = cluster_flag(ctx);
+    if (!flag || ctx->epoch == 0 || (ctx->engine == ENGINE_SOFTMAX_BATCH && !softmax_batch_in_clusters((int)ctx->lay[0].in_size))) return AET_OK;
+    std::vector<uint64_t> places((size_t)ctx->n * kPlaces);
+    AET_HIP(ctx, hipMemcpyAsync(places.data(), reinterpret_cast<const uint64_t *>(flag) - places.size(), places.size() * 8,
+                                hipMemcpyDeviceToHost, ctx->stream));
+    AET_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    for (int c = 0; c < ctx->n; ++c) *count += places[(size_t)c * kPlaces + kPlaces - 1] == 1;
+    return AET_OK;
+}
+
 // After a synchronisation: did a fused kernel give up waiting for its cluster peers?
 static aet_status check_device_flag(aet_ctx *ctx) {
-    if (ctx->engine != ENGINE_MLP && ctx->engine != ENGINE_LENET && ctx->engine != ENGINE_SOFTMAX_BATCH) return AET_OK;
+    const int *dflag = cluster_flag(ctx);
+    if (!dflag) return AET_OK;
     int flag = 0;
-    char *fused = ctx->ws + ctx->lo.fused;
-    const int *dflag = ctx->engine == ENGINE_MLP     ? mlp_error_flag_ptr(fused, ctx->n, ctx->B)
-                       : ctx->engine == ENGINE_LENET ? lenet_error_flag_ptr(fused, ctx->n, ctx->B)
-                                                     : softmax_batch_error_flag_ptr(fused, ctx->n, (int)ctx->lay[0].in_size, ctx->B);
     AET_HIP(ctx, hipMemcpyAsync(&flag, dflag, 4, hipMemcpyDeviceToHost, ctx->stream));
     AET_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (flag) {

@@ -31,6 +31,8 @@ inline bool stream_is_capturing(hipStream_t s) {
 
 // Test hook: the exchange words of clusters always go through memory (see cluster_post.h).
 extern bool g_posts_to_memory;
+// Test hook: the first workgroup of a cluster names an XCD that is not its own.
+extern int g_xcd_skew;
 
 // Resolved geometry of one layer (activations are C,H,W per sample).
 struct LayerGeom {

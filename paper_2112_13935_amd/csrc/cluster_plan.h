@@ -28,6 +28,10 @@ constexpr int softmax_batch_record_words(int workgroups, int batch) {
     return workgroups > 1 ? whole_lines(2 * workgroups * batch * 12) : 0;
 }
 
+// Words of a client's workgroups about where they run: one each, and the last for their answer
+constexpr int kClusterMax = 32;   // workgroups of a cluster, at most
+constexpr int kPlaces = whole_lines(kClusterMax + 1);
+
 // How many times a workgroup polls for a peer's word before it gives up: 2.2 s with polls of the XCD's L2
 // (0.26 us), twice that with polls that go through memory.  (A count and not the clock, which goes on while
 // the queue is preempted, and which cost the LeNet round with two clusters a client 1.3 %.)

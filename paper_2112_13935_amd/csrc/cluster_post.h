@@ -9,6 +9,11 @@
 // sees the latter.  So the workgroups of a cluster first tell each other which XCD they run on
 // (agent scope, once per launch, while the replica is loaded), and only where it is one and the
 // same do the words stay in its L2.
+//
+// The memory model promises none of this: a store of workgroup scope may stay invisible to other
+// workgroups.  It holds for this part (gfx950: one L2 per XCD, the L1 written through), which is the only
+// one this library is built for.  Were it not so, no word would be taken for another one (each carries its
+// step's tag): the bounded waits would expire and the error flag would say so.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -17,17 +22,16 @@
 
 namespace aet {
 
-constexpr int kClusterMax = 32;   // workgroups of a cluster, at most
-
 __device__ __forceinline__ int xcc_id() {   // hardware register 20, bits 0 .. 3
     return (int)__builtin_amdgcn_s_getreg(20 | (3 << 11));
 }
 
-// places: one word per workgroup of the cluster (NULL: words always go to memory); tag: not in
-// any word of an earlier launch
-__device__ __forceinline__ void cluster_announce(unsigned long long *places, int me, uint32_t tag) {
+// places: one word per workgroup of the cluster and one for the answer, the last of kPlaces (NULL: words
+// always go to memory); tag: not in any word of an earlier launch; skew: added to the first workgroup's answer (a test's: 0 otherwise)
+__device__ __forceinline__ void cluster_announce(unsigned long long *places, int me, uint32_t tag, int skew) {
     if (places && threadIdx.x == 0)
-        __hip_atomic_store(places + me, ((unsigned long long)tag << 32) | (unsigned)xcc_id(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(places + me, ((unsigned long long)tag << 32) | (unsigned)(xcc_id() + (me == 0 ? skew : 0)),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The bounded wait of a poll loop: gave_up() after every poll in vain.  Once this or another workgroup's
@@ -43,8 +47,8 @@ struct BoundedWait {
 };
 
 // Do all n workgroups of the cluster run on one XCD?  Every wave asks for itself.  Where the wait
-// expires *dead is set and the answer is no.
-__device__ __forceinline__ bool cluster_on_one_xcd(const unsigned long long *places, int n, uint32_t tag, int *errflag, bool *dead) {
+// expires *dead is set and the answer is no.  The first workgroup's is left behind for a test to read.
+__device__ __forceinline__ bool cluster_on_one_xcd(unsigned long long *places, int me, int n, uint32_t tag, int *errflag, bool *dead) {
     if (!places) return false;
     const int lane = threadIdx.x & 63;
     unsigned long long v = 0;
@@ -56,7 +60,9 @@ __device__ __forceinline__ bool cluster_on_one_xcd(const unsigned long long *pla
         __builtin_amdgcn_s_sleep(1);
         if (wait.gave_up(errflag)) *dead = true;
     }
-    return __all((int)(uint32_t)v == xcc_id());
+    const bool yes = __all((int)(uint32_t)v == xcc_id());
+    if (me == 0 && threadIdx.x == 0) __hip_atomic_store(places + kPlaces - 1, yes ? 1ull : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return yes;
 }
 
 // one_xcd: what cluster_on_one_xcd said (the same for all lanes)

@@ -180,7 +180,7 @@ __device__ __forceinline__ float relu_pool(const float (&acc)[4], int &which) {
 template <bool G28, int S, bool PAD>
 __global__ void __launch_bounds__(kLnThreads, 1)
 k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, const LenetDims d, int Brun,
-              u64 *__restrict__ xrec, u64 *__restrict__ places, uint32_t tag0, int *__restrict__ errflag) {
+              u64 *__restrict__ xrec, u64 *__restrict__ places, int skew, uint32_t tag0, int *__restrict__ errflag) {
     // consecutive workgroup ids go round the 8 XCDs: the four workgroups of a client get ids
     // that land on the same XCD and exchange through its L2
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -188,8 +188,8 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     const int g = S == 1 ? gs : gs % kLnG, sub = S == 1 ? 0 : gs / kLnG;   // workgroup of the cluster, cluster (samples 16 sub ..)
     const int Br = PAD ? Brun : kLnB * S;       // samples of the mini-batch
     if (a >= nhere) return;
-    if (places) places += (int64_t)(rec0 + a) * (kLnG * S);
-    cluster_announce(places, gs, tag0);
+    if (places) places += (int64_t)(rec0 + a) * kPlaces;
+    cluster_announce(places, gs, tag0, skew);
     const RoundParams p = rp[a];
     const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
@@ -302,7 +302,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     if (p.m > 0) {
         load_rows(0, xr, labr);
         store_rows(xr, labr);
-        wt.one_xcd = cluster_on_one_xcd(places, kLnG * S, tag0, errflag, &wt.dead);
+        wt.one_xcd = cluster_on_one_xcd(places, gs, kLnG * S, tag0, errflag, &wt.dead);
     }
     __syncthreads();
 
@@ -1592,16 +1592,17 @@ size_t lenet_lds_bytes(const LenetDims &d) {
 }
 
 // the instantiations: 28 x 28 or any geometry; one or two clusters; exact or padded
-typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, u64 *, uint32_t, int *);
+typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, u64 *, int, uint32_t, int *);
 LenetKernel lenet_kernel(bool g28, int S, bool pad) {
     if (S == 2) return g28 ? k_lenet_round<true, 2, true> : k_lenet_round<false, 2, true>;
     if (pad) return g28 ? k_lenet_round<true, 1, true> : k_lenet_round<false, 1, true>;
     return g28 ? k_lenet_round<true, 1, false> : k_lenet_round<false, 1, false>;
 }
+static_assert(2 * kLnG <= kClusterMax, "a place for every workgroup");
 int lenet_clusters(int B) { return B > kLnB ? 2 : 1; }
 size_t lenet_rec_words(int n_clients, int B) { return (size_t)n_clients * (lenet_clusters(B) == 1 ? kXWords : kXWords2); }
-// the records of all clients, then their workgroups' places
-size_t lenet_words(int n_clients, int B) { return lenet_rec_words(n_clients, B) + (size_t)n_clients * kLnG * lenet_clusters(B); }
+// the records of all clients, then their workgroups' places [client][kPlaces]
+size_t lenet_words(int n_clients, int B) { return lenet_rec_words(n_clients, B) + (size_t)n_clients * kPlaces; }
 
 }  // namespace
 
@@ -1692,7 +1693,7 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
         const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * kLnG * S);
         if (prof && prof->on[F_LENET_ROUND]) prof->before(F_LENET_ROUND, s);
-        kernel<<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, B, xrec, places, tag0, errflag);
+        kernel<<<grid, kLnThreads, lds, s>>>(dp + a0, here, a0, Wg, d, B, xrec, places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_LENET_ROUND]) prof->after(F_LENET_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

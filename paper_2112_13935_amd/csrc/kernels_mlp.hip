@@ -135,7 +135,7 @@ template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
 __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             int D, int H, int C, int G, int Brun, unsigned long long *__restrict__ xrec,
-            unsigned long long *__restrict__ prec, unsigned long long *__restrict__ places,
+            unsigned long long *__restrict__ prec, unsigned long long *__restrict__ places, int skew,
             uint32_t tag0, int *__restrict__ errflag) {
     constexpr int B = 16 * NBT;
     const int Br = PAD ? Brun : B;   // samples of the mini-batch
@@ -146,8 +146,8 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     const int a = xcd + 8 * (slot / (G * HF));  // index into this launch's records
     const int g = (slot % (G * HF)) / HF, hf = slot % HF;
     if (a >= nhere) return;
-    if (places) places += (int64_t)(rec0 + a) * kClusterMax;
-    cluster_announce(places, g * HF + hf, tag0);
+    if (places) places += (int64_t)(rec0 + a) * kPlaces;
+    cluster_announce(places, g * HF + hf, tag0, skew);
     const RoundParams p = pack.p[a];
     const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
@@ -278,7 +278,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     unsigned long long *prec_base = prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair;
     bool dead = false;  // the poll expired: keep going, the host will see the flag
     // the same answer in all waves (one whose wait expired says no): there are barriers that hang on it
-    if (!cluster_on_one_xcd(places, G * HF, tag0, errflag, &dead)) lossacc[1] = 1.f;
+    if (!cluster_on_one_xcd(places, g * HF + hf, G * HF, tag0, errflag, &dead)) lossacc[1] = 1.f;
     __syncthreads();
     const bool one_xcd = __builtin_amdgcn_readfirstlane(lossacc[1] == 0.f);
 
@@ -669,10 +669,10 @@ bool mlp_padded_pays(int D, int H, int n_clients) {
 }
 
 // exchange records [client][2][kMlpMaxG][kMlpRec] 64-bit words, the pair records
-// [client][kMlpMaxG][2][2][kMlpPair], the workgroups' places [client][kClusterMax], then the error flag
+// [client][kMlpMaxG][2][2][kMlpPair], the workgroups' places [client][kPlaces], then the error flag
 static size_t mlp_rec_words(int n_clients) { return (size_t)n_clients * 2 * kMlpMaxG * kMlpRec; }
 static size_t mlp_pair_words(int n_clients) { return (size_t)n_clients * kMlpMaxG * 4 * kMlpPair; }
-static size_t mlp_all_words(int n_clients) { return mlp_rec_words(n_clients) + mlp_pair_words(n_clients) + (size_t)n_clients * kClusterMax; }
+static size_t mlp_all_words(int n_clients) { return mlp_rec_words(n_clients) + mlp_pair_words(n_clients) + (size_t)n_clients * kPlaces; }
 static_assert(2 * kMlpMaxG <= kClusterMax, "a place for every workgroup");
 
 size_t mlp_round_scratch_bytes(int n_clients, int B) {
@@ -745,7 +745,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -51,6 +51,7 @@ constexpr int kSbC = 4 * kSbQ;         // class slots
 static_assert(kSbC == 12, "softmax_batch_record_words");
 static_assert(2 * kSbClasses == 20 && kSbClasses <= kSbC, "five registers of four sums hold two samples' classes");
 constexpr int kSbMaxHF = 6;            // workgroups of a cluster, at most
+static_assert(kSbMaxHF <= kClusterMax, "a place for every workgroup");
 constexpr int kSbMaxD = kSbMaxHF * kSbThreads;
 constexpr int kSbMaxB = 64;
 constexpr int kSbPS = 13;              // LDS stride of a sample's partial logits
@@ -81,7 +82,7 @@ __device__ __forceinline__ float fold16(float a, float b) {
 template <int NC, int BC>
 __global__ void __launch_bounds__(kSbThreads, 1)
 k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, int D, int C,
-                      int HF, int Br, int rec_words, u64 *__restrict__ xrec, u64 *__restrict__ places, uint32_t tag0, int *__restrict__ errflag) {
+                      int HF, int Br, int rec_words, u64 *__restrict__ xrec, u64 *__restrict__ places, int skew, uint32_t tag0, int *__restrict__ errflag) {
     constexpr int Q = kSbQ, T = kSbThreads, NW = kSbWaves;
     constexpr int GS = BC < 32 ? BC : 32;   // samples whose logits are collected before a store
     constexpr int DZ = BC + 4;              // LDS stride of a class row of dz^T
@@ -90,8 +91,8 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int a = xcd + 8 * (slot / HF), h = slot % HF;
     if (a >= nhere) return;
-    if (places) places += (int64_t)(rec0 + a) * kSbMaxHF;
-    if (HF > 1) cluster_announce(places, h, tag0);
+    if (places) places += (int64_t)(rec0 + a) * kPlaces;
+    if (HF > 1) cluster_announce(places, h, tag0, skew);
     const RoundParams p = rp[a];
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
@@ -157,7 +158,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
 #pragma unroll
         for (int j = 0; j < NC; ++j) load_col(j);
         if (wave == 0 && lane < BC) labs[lane] = labn;
-        if (HF > 1) one_xcd = cluster_on_one_xcd(places, HF, tag0, errflag, &dead);
+        if (HF > 1) one_xcd = cluster_on_one_xcd(places, h, HF, tag0, errflag, &dead);
     }
     for (int u = 0; u < p.m; ++u) {
         int lio = li;   // compared where it is needed: 16 masks kept in scalar registers would spill
@@ -344,10 +345,10 @@ __global__ void k_sb_zero(u64 *p, size_t n) {
 int rec_words(int D, int B) {
     return softmax_batch_record_words((D + kSbThreads - 1) / kSbThreads, B);
 }
-// the records of all clients, then the workgroups' places [client][kSbMaxHF]; the error flag follows
+// the records of all clients, then the workgroups' places [client][kPlaces]; the error flag follows
 size_t all_words(int n_clients, int D, int B) {
     const int words = rec_words(D, B);
-    return words > 0 ? (size_t)n_clients * (words + kSbMaxHF) : 0;
+    return words > 0 ? (size_t)n_clients * (words + kPlaces) : 0;
 }
 
 }  // namespace
@@ -386,7 +387,7 @@ static hipError_t sb_launch(hipStream_t s, Profiler *prof, const RoundParams *dp
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
         const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * HF);
         if (prof && prof->on[F_SOFTMAX_ROUND]) prof->before(F_SOFTMAX_ROUND, s);
-        k_softmax_batch_round<NC, BC><<<grid, kSbThreads, 0, s>>>(dp + a0, here, a0, Wg, D, C, HF, B, words, xrec, places, tag0, errflag);
+        k_softmax_batch_round<NC, BC><<<grid, kSbThreads, 0, s>>>(dp + a0, here, a0, Wg, D, C, HF, B, words, xrec, places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_SOFTMAX_ROUND]) prof->after(F_SOFTMAX_ROUND, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

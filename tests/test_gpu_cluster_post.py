@@ -1,5 +1,6 @@
-"""The words that the workgroups of a client exchange stay in their XCD's L2 or go through memory;
-either way the same words arrive, so the models have the same bits.  Run with  -m gpu  on an MI355X."""
+"""The words that the workgroups of a client exchange stay in their XCD's L2 or go through memory, as the
+workgroups find that they share an XCD or not; either way the same words arrive, so the models have the
+same bits.  Run with  -m gpu  on an MI355X."""
 import numpy as np
 import pytest
 
@@ -22,26 +23,39 @@ CASES = {
     "lenet": lambda: W.config3(n_clients=3, n_per=60, rounds=3),
     "lenet_two_clusters": lambda: W.config3(n_clients=3, n_per=60, batch=20, rounds=3, a=20, b=20),
     "softmax_cluster_of_six": lambda: _softmax(3, 3072, 20),
-    "softmax_cluster_of_three_b5": lambda: _softmax(11, 1100, 5),   # records that end inside a line
-    "softmax_cluster_of_two": lambda: _softmax(90, 600, 8),
+    "softmax_cluster_of_three_b17": lambda: _softmax(11, 1100, 17),   # records that end inside a line
+    "softmax_cluster_of_two": lambda: _softmax(90, 600, 20),
+    "softmax_alone_three_columns": lambda: _softmax(90, 600, 8),
     "softmax_alone": lambda: _softmax(3, 40, 8),
 }
 
 
-@pytest.mark.parametrize("name", sorted(CASES))
-def test_same_words_through_memory(name):
+def _rounds(name, mode, variants):
+    """The model after all rounds, how many clients had their words in one L2 at the end, and all clients."""
     from paper_2112_13935_amd import load_library
     from paper_2112_13935_amd.runner import Run
     lib = load_library()
-    out = []
-    for mode in (0, 2):
-        lib.aet_test_select_kernels(mode, 0)
-        try:
-            run = Run(CASES[name]())
-            run.run_all()
-            out.append(run.lib.aet_get_weights(-1))
-            run.close()
-        finally:
-            lib.aet_test_select_kernels(0, 0)
-    assert np.isfinite(out[0]).all()
-    assert np.array_equal(out[0], out[1])
+    lib.aet_test_select_kernels(mode, 0)
+    lib.aet_test_variants(variants)
+    try:
+        run = Run(CASES[name]())
+        run.run_all()
+        out = run.lib.aet_get_weights(-1), run.lib.aet_test_one_xcd_clients(), run.n
+        run.close()
+    finally:
+        lib.aet_test_select_kernels(0, 0)
+        lib.aet_test_variants(0)
+    return out
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_same_words_through_memory(name):
+    """In L2, through memory without asking, and through memory because one workgroup of each client
+    names another XCD."""
+    model, shared, clients = _rounds(name, 0, 0)
+    assert shared == (0 if name.startswith("softmax_alone") else clients)
+    assert np.isfinite(model).all()
+    for mode, variants in ((2, 0), (0, 1)):
+        other, shared, _ = _rounds(name, mode, variants)
+        assert shared == 0
+        assert np.array_equal(model, other)
