@@ -320,12 +320,15 @@ aet_status aet_reset(aet_ctx *ctx);
 void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers);
 
 /* Test hooks, process-wide; aet_test_variants(0) restores the defaults.
- * AET_TEST_XCDS_DIFFER  rounds launched until the next call: the first workgroup of each client names
- *                       another XCD than its own, so that the client's workgroups find that they do not
- *                       share one.
+ * AET_TEST_XCDS_DIFFER        rounds launched until the next call: the first workgroup of each client names
+ *                             another XCD than its own, so that the client's workgroups find that they
+ *                             do not share one.
+ * AET_TEST_FP32_CONVOLUTIONS  contexts created until the next call: no convolution's products on the bf16
+ *                             matrix cores.
  * aet_test_one_xcd_clients: clients whose workgroups found, in the last round that asked, that they share an
  * XCD (0 for models whose rounds do not run in clusters); synchronises. */
 #define AET_TEST_XCDS_DIFFER 1u
+#define AET_TEST_FP32_CONVOLUTIONS 2u
 void aet_test_variants(uint32_t variants);
 aet_status aet_test_one_xcd_clients(aet_ctx *ctx, int32_t *count);
 

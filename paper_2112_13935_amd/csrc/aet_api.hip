@@ -157,6 +157,7 @@ enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENE
 
 // aet_test_select_kernels: which kernel set contexts created from now on use
 int g_force_layer_engine = 0, g_plain_layers = 0;
+bool g_fp32_convolutions = false;   // aet_test_variants: of contexts created from now on
 
 // Padded forms of the fused rounds (widths or mini-batches that do not fill their tiles) go to
 // the layer engine beyond this many clients for their memory: the exchange records take 0.4 MB
@@ -218,7 +219,7 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     int64_t sp = 0;
     for (int l = 0; l < L; ++l)
         for (int bwd = 0; bwd < 2; ++bwd) {
-            const size_t bytes = split && eng == ENGINE_LAYERS && lay[l].type == AET_CONV && (l > 0 || !bwd) ? conv_split_weight_bytes(lay[l], bwd) : 0;
+            const size_t bytes = split && !g_fp32_convolutions && eng == ENGINE_LAYERS && lay[l].type == AET_CONV && (l > 0 || !bwd) ? conv_split_weight_bytes(lay[l], bwd) : 0;
             lo->split_off[l][bwd] = bytes ? sp : -1;
             sp += (int64_t)bytes;
         }
@@ -400,7 +401,10 @@ void aet_test_select_kernels(int32_t force_layer_engine, int32_t plain_layers) {
     g_plain_layers = plain_layers != 0;
 }
 
-void aet_test_variants(uint32_t variants) { g_xcd_skew = (variants & AET_TEST_XCDS_DIFFER) ? 1 : 0; }
+void aet_test_variants(uint32_t variants) {
+    g_xcd_skew = (variants & AET_TEST_XCDS_DIFFER) ? 1 : 0;
+    g_fp32_convolutions = (variants & AET_TEST_FP32_CONVOLUTIONS) != 0;
+}
 
 int64_t aet_n_params(const aet_model_desc *model) {
     LayerGeom lay[AET_MAX_LAYERS];
@@ -503,6 +507,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     for (int l = 0; l < ctx->L; ++l) ctx->sc.wgrad[l] = reinterpret_cast<float *>(ctx->ws + ctx->lo.wgrad[l]);
     ctx->sc.wgrad_apart = ctx->lo.wgrad_apart;
     ctx->sc.plain = g_plain_layers != 0;
+    ctx->sc.fp32_convolutions = g_fp32_convolutions;
     ctx->sc.split.base = ctx->lo.split_stride > 0 ? ctx->ws + ctx->lo.split : nullptr;
     ctx->sc.split.stride = ctx->lo.split_stride;
     for (int l = 0; l < ctx->L; ++l)

@@ -88,6 +88,7 @@ struct LayerScratch {
     bool wgrad_apart;   // ... each layer's in a place of its own (else all in the same)
     SplitWeights split;
     bool plain;         // use the plain (non matrix-core) layer kernels
+    bool fp32_convolutions;   // no split ones
 };
 
 // Kernel families, for the optional per-launch timing with HIP events.
@@ -172,7 +173,7 @@ hipError_t launch_conv_wgrad_finish(hipStream_t s, Profiler *prof, const RoundPa
                                     const FinishList &later);
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial, FinishList *later, const uint8_t *amax = nullptr);
+                                  float *partial, FinishList *later, bool split_ok, const uint8_t *amax = nullptr);
 // whether the backward kernels of a convolution take the gradient of the 2 x 2 pooling layer behind it and put
 // their own together from it and the winners, amax (split: backward-data runs in the split form)
 bool conv_bwd_unpools(const LayerGeom &L, const LayerGeom &pool, int B, int nact, bool split);

@@ -1262,10 +1262,10 @@ hipError_t launch_conv_bwd_pair(hipStream_t s, Profiler *prof, const RoundParams
 
 hipError_t launch_conv_wgrad_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                   int B, const LayerGeom &L, const float *in, const float *dout,
-                                  float *partial, FinishList *later, const uint8_t *amax) {
+                                  float *partial, FinishList *later, bool split_ok, const uint8_t *amax) {
     WgradGeom g;
     if (!wgrad_geom(L, B, nact, &g)) return hipErrorInvalidValue;
-    const int slices = conv_wgrad_split_slices(L, B, nact, wgrad_target(L));
+    const int slices = split_ok ? conv_wgrad_split_slices(L, B, nact, wgrad_target(L)) : 0;
     if (slices > 0) {
         g.S = slices;
         const bool timed = prof && prof->on[F_CONV_BWD_WEIGHT];

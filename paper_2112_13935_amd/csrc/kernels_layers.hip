@@ -636,13 +636,13 @@ static hipError_t launch_conv_wgrad_direct(hipStream_t s, Profiler *prof, const 
 
 static hipError_t conv_dispatch(int ks, hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u,
                                 int B, const LayerGeom &g, int which, const float *a,
-                                const float *b, float *c, const float *mask, bool mfma, FinishList *later = nullptr) {
+                                const float *b, float *c, const float *mask, bool mfma, FinishList *later = nullptr, bool split_ok = true) {
     if (which < 2 && mfma && conv_mfma_supported(g, which == 1))
         return launch_conv_mfma(s, prof, dp, nact, u, B, g, which == 1, a, c, mask);
     if (which == 2 && mfma && conv_wgrad_direct_ok(g))
         return launch_conv_wgrad_direct(s, prof, dp, nact, u, B, g, a, b);
     if (which == 2 && mfma && c && conv_wgrad_mfma_supported(g, B))
-        return launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, a, b, c, later);
+        return launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, a, b, c, later, split_ok);
     switch (ks) {
         case 1: return conv_step<1>(s, prof, dp, nact, u, B, g, which, a, b, c, mask);
         case 2: return conv_step<2>(s, prof, dp, nact, u, B, g, which, a, b, c, mask);
@@ -734,7 +734,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
             if (taken) continue;
             if (winners) {
                 AET_RETURN_IF(launch_conv_split(s, prof, dp, nact, u, B, g, true, sc.split, sc.split.off[l][1], dout, sc.del[l], mask, winners));
-                AET_RETURN_IF(launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, sc.act[l], dout, sc.wgrad[l], later, winners));
+                AET_RETURN_IF(launch_conv_wgrad_mfma(s, prof, dp, nact, u, B, g, sc.act[l], dout, sc.wgrad[l], later, true, winners));
                 continue;
             }
             if (l > 0 && split(l, true))
@@ -743,7 +743,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
                 AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 1, sc.del[l + 1], nullptr,
                                             sc.del[l], mask, !sc.plain));
             AET_RETURN_IF(conv_dispatch(g.k, s, prof, dp, nact, u, B, g, 2, sc.act[l], sc.del[l + 1],
-                                        sc.wgrad[l], nullptr, !sc.plain, later));
+                                        sc.wgrad[l], nullptr, !sc.plain, later, !sc.fp32_convolutions));
         } else if (g.type == 1) {
             if (l > 0 && !unpooled(l)) {
                 // the ReLU below, at the winners: their value is the pooled one

@@ -45,8 +45,20 @@ CASES = {
 }
 
 
+def _on_the_fp32_unit(make):
+    """A context none of whose convolutions, in either direction or for the weights, takes this form."""
+    from paper_2112_13935_amd import load_library
+    from paper_2112_13935_amd.runner import Run
+    lib = load_library()
+    lib.aet_test_variants(2)
+    try:
+        return Run(make())
+    finally:
+        lib.aet_test_variants(0)
+
+
 def _smallest_workspace(monkeypatch, make):
-    """A context without room for what is optional: its convolutions stay on the fp32 unit."""
+    """A context without room for what is optional: forward and backward-data stay on the fp32 unit."""
     from paper_2112_13935_amd.binding import AetError
     from paper_2112_13935_amd.runner import Run
     run = Run(make())
@@ -72,29 +84,44 @@ def test_parity(oracle_libs, name):
     run.close()
 
 
+def test_parity_in_the_smallest_workspace(oracle_libs, monkeypatch):
+    from oracle import Oracle
+    from parity import lockstep
+    wl = CASES["cnn32"]()
+    run, orc = _smallest_workspace(monkeypatch, CASES["cnn32"]), Oracle(wl, "f64")
+    lockstep(wl, run, orc)
+    run.close()
+
+
 @pytest.mark.parametrize("n,batch,shape", [(2, 50, (16, 32, 32)), (4, 50, (32, 16, 16)), (8, 50, (64, 8, 8))])
-def test_no_further_from_64_bits_than_the_fp32_unit(oracle_libs, monkeypatch, n, batch, shape):
-    """U of one recursion of two convolutions without ReLU or pooling (no decisions that rounding could
-    turn): the split products round less often (see split_bf16.h), so their error is the smaller one."""
+@pytest.mark.parametrize("layers", [1, 2])
+def test_no_further_from_64_bits_than_the_fp32_unit(oracle_libs, n, batch, shape, layers):
+    """U of one recursion of convolutions without ReLU or pooling (no decisions that rounding could
+    turn): the split products round less often (see split_bf16.h), so the error of each convolution's
+    weights is the smaller one.  With one convolution its weights' gradient is a backward-weight product
+    of the input rows themselves, with two the first one's went through backward-data as well."""
     from oracle import Oracle
     from paper_2112_13935_amd.runner import Run
 
     def make():
-        return _maps(n, batch, shape, [W.Layer(W.CONV, 32, 3, 1, 0), W.Layer(W.CONV, 64, 3, 1, 0)], rounds=1)
+        return _maps(n, batch, shape, [W.Layer(W.CONV, 32 * (i + 1), 3, 1, 0) for i in range(layers)], rounds=1)
     orc = Oracle(make(), "f64")
     orc.run_round()
-    err = []
-    for run in (Run(make()), _smallest_workspace(monkeypatch, make)):
+    us = []
+    for run in (Run(make()), _on_the_fp32_unit(make)):
         run.run_round()
-        d = [run.lib.aet_get_U(c, 0) - orc.get_U(c, 0) for c in range(orc.n)]
-        err.append(np.sqrt(sum((x ** 2).sum() for x in d) / sum((orc.get_U(c, 0) ** 2).sum() for c in range(orc.n))))
+        us.append([run.lib.aet_get_U(c, 0).astype(np.float64) for c in range(orc.n)])
         run.close()
-    print(f"{shape}: split {err[0]:.2e}, fp32 unit {err[1]:.2e}")
-    assert err[0] != err[1], "the split form was not taken"
-    assert err[0] < err[1]
+    ref = [orc.get_U(c, 0) for c in range(orc.n)]
+    for l, s in enumerate(run.wl.model.param_slices()):
+        at = slice(s[0], s[0] + s[1])
+        err = [np.sqrt(sum(((x[at] - r[at]) ** 2).sum() for x, r in zip(u, ref)) / sum((r[at] ** 2).sum() for r in ref)) for u in us]
+        print(f"{shape}, layer {l} of {layers + 1}: split {err[0]:.2e}, fp32 unit {err[1]:.2e}")
+        if l < layers:
+            assert err[0] < err[1], l
 
 
-def test_infinities_stay_where_they_were(monkeypatch):
+def test_infinities_stay_where_they_were():
     """One infinite pixel in one client's rows: the same entries of its model are finite, infinite and
     NaN as with the products on the fp32 unit."""
     from paper_2112_13935_amd.runner import Run
@@ -105,7 +132,7 @@ def test_infinities_stay_where_they_were(monkeypatch):
         wl.X[1][:, 700] = np.inf
         return wl
     out = []
-    for run in (Run(make()), _smallest_workspace(monkeypatch, make)):
+    for run in (Run(make()), _on_the_fp32_unit(make)):
         run.run_round()
         out.append(np.stack([run.lib.aet_get_U(c, 0) for c in range(run.n)]))
         run.close()
