@@ -219,7 +219,8 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     int64_t sp = 0;
     for (int l = 0; l < L; ++l)
         for (int bwd = 0; bwd < 2; ++bwd) {
-            const size_t bytes = split && !g_fp32_convolutions && eng == ENGINE_LAYERS && lay[l].type == AET_CONV && (l > 0 || !bwd) ? conv_split_weight_bytes(lay[l], bwd) : 0;
+            const bool room = split && !g_fp32_convolutions && !g_plain_layers && eng == ENGINE_LAYERS;
+            const size_t bytes = room && lay[l].type == AET_CONV && (l > 0 || !bwd) ? conv_split_weight_bytes(lay[l], bwd, B, n) : 0;
             lo->split_off[l][bwd] = bytes ? sp : -1;
             sp += (int64_t)bytes;
         }

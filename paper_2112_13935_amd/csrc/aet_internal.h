@@ -145,7 +145,8 @@ hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp
                             const LayerGeom &L, bool bwd, const float *src, float *dst,
                             const float *mask_src, uint8_t *amax = nullptr);
 // the same on the bf16 matrix cores (kernels_conv_split.hip), where that is faster
-size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd);   // 0: no such form
+// bytes per client that it wants for the layer's weights; 0: never used with so many clients
+size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd, int B, int n_clients);
 bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, const SplitWeights &sw);
 // the weights of this recursion for every layer and direction that is used
 hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,

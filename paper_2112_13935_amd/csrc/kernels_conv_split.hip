@@ -612,18 +612,15 @@ hipError_t split_launch(hipStream_t s, dim3 grid, const RoundParams *dp, int u, 
 
 }  // namespace
 
-size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd) {
-    SplitDir d;
-    return split_dir(L, bwd, 2, &d) ? (size_t)(d.SC / 16) * ((d.DC + 31) / 32) * kSplitPiece : 0;
-}
-
 // Where this form is the faster one, time here / with kernels_conv_mfma.hip, forward | backward-data,
 // by the workgroups' worth of tiles of 256 pixels x 32 destination channels:
 //                     96            128           192           512           768 and more
-//   32 x 32 px  1.00 | 1.07                  0.70 | 0.85   0.71 | 0.71   0.75 | 0.83 (3,072: 0.81 | 1.05)
+//   32 x 32 px  1.00 | 1.07                  0.70 | 0.85   0.71 | 0.71   0.75 | 0.83
 //   16 x 16     1.02 | 1.07   1.01 | 1.06   0.72 | 0.73   0.62 | 0.74   0.74 | 0.84
 //   8 x 8       0.71 | 0.73   0.72 | 0.73   0.50 | 0.54   0.44 | 0.47
-// (8 x 8 images fill half a workgroup there.)  Below that a launch is a chain of trips through
+// (8 x 8 images fill half a workgroup there; 32 x 32 and 32 channels, 1,536 | 3,072 | 8,192 workgroups'
+// worth: forward 0.66, 0.63, 0.62, backward-data 0.69, 0.77, 0.77, and 0.57, 0.53, 0.62 where it takes the
+// pooled gradient, with the pooling kernel's time on the other side.)  Below that a launch is a chain of trips through
 // memory, one for each chunk of channels, on either.  16 destination channels fill half a
 // tile: 0.9 to 1.4 everywhere.
 static bool conv_split_pays(const LayerGeom &L, bool bwd, int B, int nact) {
@@ -631,6 +628,12 @@ static bool conv_split_pays(const LayerGeom &L, bool bwd, int B, int nact) {
     if (!split_dir(L, bwd, 2, &d) || d.DC < 32) return false;
     const int64_t wgs = (int64_t)d.rblocks * ((B + d.NS - 1) / d.NS) * ((d.DC + 31) / 32) * nact;
     return wgs >= (L.iw == 8 ? 96 : 192);
+}
+
+// (the rule is taken by the more clients, the more often)
+size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd, int B, int n_clients) {
+    SplitDir d;
+    return conv_split_pays(L, bwd, B, n_clients) && split_dir(L, bwd, 2, &d) ? (size_t)(d.SC / 16) * ((d.DC + 31) / 32) * kSplitPiece : 0;
 }
 
 bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, const SplitWeights &sw) {

@@ -48,3 +48,31 @@ def test_model_validation_runs_on_the_host():
     assert lib.aet_workspace_bytes(ctypes.byref(bad), 4, 1, 1) == 0
     ok = model_desc(W.softmax_model(8, 3))
     assert lib.aet_workspace_bytes(ctypes.byref(ok), 0, 1, 1) == 0
+
+
+def test_room_for_split_weights_only_where_they_are_used():
+    """The workspace of a model with convolutions, with and without the form that wants its weights as bf16
+    parts (27,648 bytes for 16 source and 32 destination channels and a client)."""
+    import workloads as W
+    from paper_2112_13935_amd.binding import load_library, model_desc
+    lib = load_library()
+
+    def room(model, clients, plain=0):
+        sizes = []
+        for variant in (0, 2):
+            lib.aet_test_select_kernels(0, plain)
+            lib.aet_test_variants(variant)
+            try:
+                sizes.append(lib.aet_workspace_bytes(ctypes.byref(model_desc(model)), clients, 1, 10))
+            finally:
+                lib.aet_test_select_kernels(0, 0)
+                lib.aet_test_variants(0)
+        return sizes[0] - sizes[1]
+
+    # forward and backward-data of 32 -> 32, 32 -> 64 and 64 -> 64 channels (the first layer has three)
+    assert room(W.cnn32_model(64), 32) == 32 * 27648 * (2 + 2 + 4 + 4 + 8 + 8)
+    assert room(W.cnn32_model(64), 32, plain=1) == 0
+    # backward-data of 16 -> 32 channels has 16 destination channels, 16 -> 16 both ways: not used
+    assert room(W.cnn32_model(64, hw=16, width=16), 32) == 32 * 27648 * (1 + 2 + 2)
+    # too few tiles with every client at work
+    assert room(W.cnn32_model(16, hw=16, width=16, fc=64), 6) == 0
