@@ -368,6 +368,8 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
     const int oc0 = 32 * ((int)blockIdx.y / g.cblocks), ci0 = 32 * ((int)blockIdx.y % g.cblocks);
     const int HW = g.H * W;
 
+    __shared__ bool again;
+    if (tid == 0) again = false;
     // zeros around the rows: never written again
     for (int e = tid; e < 3 * 32 * (T::ROWST + 1); e += kWgThreads) {
         bf8 z;
@@ -379,8 +381,6 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
     constexpr int ITASKS = 32 * T::ROWST * W8, ITURNS = (ITASKS + kWgThreads - 1) / kWgThreads;
     constexpr int DTASKS = 32 * R * W8, DTURNS = (DTASKS + kWgThreads - 1) / kWgThreads;
     float bsum[DTURNS];
-#pragma unroll
-    for (int i = 0; i < DTURNS; ++i) bsum[i] = 0.f;
     constexpr int UN = UNPOOL ? 2 : 1, DL = UNPOOL ? 1 : 2;
     const int SHW = HW / (UN * UN);          // a channel of dout
     f4 iv[ITURNS][2], dv[DTURNS][DL];
@@ -414,15 +414,18 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
             for (int q = 0; q < DL; ++q) dv[i][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)off, 16 * q, 0));
         }
     };
-    // count: the pixels of the tile that are this slice's own, in octets (for the bias)
-    auto stash_tiles = [&](auto clamp, uint32_t &seen, int o_lo, int o_hi) {
+    // A value whose first part became infinite makes the corrections NaN: then all again, with the first parts
+    // kept finite.  (A watch in the staging as above costs this kernel 1 to 2 %, this 0.5 %.)
+    bool clamp = false;
+    // o_lo, o_hi: the pixels of the tile that are this slice's own, in octets (for the bias)
+    auto stash = [&](int o_lo, int o_hi) {
 #pragma unroll
         for (int i = 0; i < ITURNS; ++i) {
             const int t = tid + kWgThreads * i, x8 = t % W8, row = t / W8 % T::ROWST, c = t / (W8 * T::ROWST);
             if (t < ITASKS) {
                 const float x[8] = {iv[i][0][0], iv[i][0][1], iv[i][0][2], iv[i][0][3], iv[i][1][0], iv[i][1][1], iv[i][1][2], iv[i][1][3]};
-                const Split8 s = split8<decltype(clamp)::value>(x);
-                split_watch(seen, s);
+                Split8 s = split8<false>(x);
+                if (__builtin_expect(clamp, 0)) s = split8<true>(x);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) Is[(q * 32 + c) * IN + row * (T::RS / 8) + 1 + x8] = s.p[q];
             }
@@ -436,55 +439,62 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
                 for (int e = 0; e < 8; ++e)   // (tiles begin in even rows)
                     x[e] = !UNPOOL ? dv[i][e / 4 % DL][e % 4]
                            : ((dw[i] >> (8 * (e / 2))) & 0xffu) == (uint32_t)(2 * (o / W8 & 1) + (e & 1)) ? dv[i][0][e / 2] : 0.f;
-                const Split8 s = split8<decltype(clamp)::value>(x);
-                split_watch(seen, s);
+                Split8 s = split8<false>(x);
+                if (__builtin_expect(clamp, 0)) s = split8<true>(x);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) Ds[(q * 32 + c) * DO + o] = s.p[q];
-                if (!decltype(clamp)::value && o >= o_lo && o < o_hi) bsum[i] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+                if (o >= o_lo && o < o_hi) bsum[i] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
             }
         }
-    };
-    auto stash = [&](int o_lo, int o_hi) {
-        uint32_t seen = 0;
-        stash_tiles(std::false_type(), seen, o_lo, o_hi);
-        if (split_over(seen)) stash_tiles(std::true_type(), seen, o_lo, o_hi);
     };
 
     f16v main[3], corr[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) main[k][r] = corr[k][r] = 0.f;
-
     const int u0 = (int)blockIdx.x * g.U, u1 = min(u0 + g.U, g.units);
     const uint32_t *const Iw = reinterpret_cast<const uint32_t *>(Is);
-    for (int it = u0 / T::UNITS; it * T::UNITS < u1; ++it) {
-        fetch(it);
-        const int lo = max(u0 - it * T::UNITS, 0), hi = min(u1 - it * T::UNITS, T::UNITS);
-        __syncthreads();   // the products of the previous tile are done with the tiles
-        stash(4 * lo, 4 * hi);
-        __syncthreads();
-        for (int un = lo; un < hi; ++un) {
-            const int o = 4 * un + 2 * half + lh;      // the lane's octet of the tile
-            const int row = o / W8 + ky, x8 = o % W8;
-            bf8 a[3], b[3][3];
+    for (;;) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                a[q] = Ds[(q * 32 + li) * DO + o];
-                const int at = (q * 32 + li) * IN + row * (T::RS / 8) + 1 + x8;
-                const u4 c = __builtin_bit_cast(u4, Is[at]);
-                const uint32_t l = Iw[4 * at - 1], r = Iw[4 * at + 4];
-                const uint32_t m1 = __builtin_amdgcn_alignbit(c[1], c[0], 16), m2 = __builtin_amdgcn_alignbit(c[2], c[1], 16),
-                               m3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
-                b[0][q] = __builtin_bit_cast(bf8, u4{(uint32_t)__builtin_amdgcn_alignbit(c[0], l, 16), m1, m2, m3});
-                b[1][q] = __builtin_bit_cast(bf8, c);
-                b[2][q] = __builtin_bit_cast(bf8, u4{m1, m2, m3, (uint32_t)__builtin_amdgcn_alignbit(r, c[3], 16)});
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) main[k][r] = corr[k][r] = 0.f;
+#pragma unroll
+        for (int i = 0; i < DTURNS; ++i) bsum[i] = 0.f;
+        for (int it = u0 / T::UNITS; it * T::UNITS < u1; ++it) {
+            fetch(it);
+            const int lo = max(u0 - it * T::UNITS, 0), hi = min(u1 - it * T::UNITS, T::UNITS);
+            __syncthreads();   // the products of the previous tile are done with the tiles
+            stash(4 * lo, 4 * hi);
+            __syncthreads();
+            for (int un = lo; un < hi; ++un) {
+                const int o = 4 * un + 2 * half + lh;      // the lane's octet of the tile
+                const int row = o / W8 + ky, x8 = o % W8;
+                bf8 a[3], b[3][3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    a[q] = Ds[(q * 32 + li) * DO + o];
+                    const int at = (q * 32 + li) * IN + row * (T::RS / 8) + 1 + x8;
+                    const u4 c = __builtin_bit_cast(u4, Is[at]);
+                    const uint32_t l = Iw[4 * at - 1], r = Iw[4 * at + 4];
+                    const uint32_t m1 = __builtin_amdgcn_alignbit(c[1], c[0], 16), m2 = __builtin_amdgcn_alignbit(c[2], c[1], 16),
+                                   m3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
+                    b[0][q] = __builtin_bit_cast(bf8, u4{(uint32_t)__builtin_amdgcn_alignbit(c[0], l, 16), m1, m2, m3});
+                    b[1][q] = __builtin_bit_cast(bf8, c);
+                    b[2][q] = __builtin_bit_cast(bf8, u4{m1, m2, m3, (uint32_t)__builtin_amdgcn_alignbit(r, c[3], 16)});
+                }
+#pragma unroll
+                for (int i = 0; i < 6; ++i)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) split_mfma(i, a, b[k], main[k], corr[k]);
             }
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) split_mfma(i, a, b[k], main[k], corr[k]);
         }
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += corr[k][r];
+        if (sum != sum) again = true;
+        __syncthreads();   // (the products are done with the tiles too)
+        if (clamp || !again) break;
+        clamp = true;
     }
 
     // ---- partial[client][slice][oc][k], k = ci * 9 + tap: the halves are added in LDS ----------------
@@ -502,7 +512,6 @@ k_conv_wgrad_split(const RoundParams *__restrict__ rp, int u, int B, SplitWgrad 
             if (t < DTASKS && t % (R * W8) == 0 && oc0 + c < g.OC) pg[(int64_t)(oc0 + c) * g.KP + 9 * g.IC] = v;
         }
     }
-    __syncthreads();
 #pragma unroll
     for (int h = 1; h >= 0; --h) {
         if (half == h) {
