@@ -87,6 +87,26 @@ def byte_models(model, recursions, client_rounds):
             "streaming": (16 * P + rows) * recursions}
 
 
+def kernel_sources(fam_name):
+    """The files of csrc/ that a fused round kernel is made from: its own and every header that it
+    includes, themselves or through another; None for the other families."""
+    import re
+    src = {"k_mlp_round": "kernels_mlp.hip", "k_softmax_round": "kernels_softmax.hip",
+           "k_lenet_round": "kernels_lenet.hip"}.get(fam_name)
+    if src is None:
+        return None
+    csrc = os.path.join(ROOT, "paper_2112_13935_amd", "csrc")
+    found, todo = set(), [src]
+    while todo:
+        f = todo.pop()
+        if f in found or not os.path.exists(os.path.join(csrc, f)):
+            continue
+        found.add(f)
+        with open(os.path.join(csrc, f)) as fh:
+            todo += re.findall(r'^#include "([^"]+)"', fh.read(), re.M)
+    return [os.path.join(csrc, f) for f in [src] + sorted(found - {src})]
+
+
 def counter_traffic(fam_name, workload):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter
     summary (FETCH_SIZE and WRITE_SIZE, each scaled by what the same counter reads for a
@@ -101,13 +121,12 @@ def counter_traffic(fam_name, workload):
         parts = line.strip().split(": ", 1)
         if len(parts) == 2 and line.startswith("    "):
             rec[parts[0]] = parts[1]
-    src = {"k_mlp_round": "kernels_mlp.hip", "k_softmax_round": "kernels_softmax.hip",
-           "k_lenet_round": "kernels_lenet.hip"}.get(fam_name)
-    if src is None or "source_sha256" not in rec:
+    files = kernel_sources(fam_name)
+    if files is None or "source_sha256" not in rec:
         return None
     h = hashlib.sha256()
-    for f in (src, "aet_device.h", "aet_internal.h"):
-        with open(os.path.join(ROOT, "paper_2112_13935_amd", "csrc", f), "rb") as fh:
+    for f in files:
+        with open(f, "rb") as fh:
             h.update(fh.read())
     if h.hexdigest() != rec["source_sha256"]:
         return None
