@@ -149,7 +149,7 @@ hipError_t launch_conv_mfma(hipStream_t s, Profiler *prof, const RoundParams *dp
 size_t conv_split_weight_bytes(const LayerGeom &L, bool bwd, int B, int n_clients);
 bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, const SplitWeights &sw);
 // the weights of this recursion for every layer and direction that is used
-hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
+hipError_t launch_split_weights(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
                                 const SplitWeights &sw);
 // off: of the layer's weights in this direction, in sw.  amax: forward, as for launch_conv_mfma; backward-
 // data, not NULL: src is the gradient at the outputs of the 2 x 2 pooling layer behind, amax its winners

@@ -649,7 +649,7 @@ bool conv_split_used(const LayerGeom *lay, int l, bool bwd, int B, int nact, con
     return sw.base && sw.off[l][bwd] >= 0 && conv_split_pays(lay[l], bwd, B, nact);
 }
 
-hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
+hipError_t launch_split_weights(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int u, const LayerGeom *lay, int L, int B,
                                 const SplitWeights &sw) {
     SplitJobs jobs;
     jobs.n = 0;
@@ -667,7 +667,10 @@ hipError_t launch_split_weights(hipStream_t s, const RoundParams *dp, int nact, 
             pieces += (bwd ? lay[l].oc : lay[l].ic) / 16 * j.nblk;
         }
     if (pieces == 0) return hipSuccess;
+    const bool timed = prof && prof->on[F_CONV_FWD];   // for both directions
+    if (timed) prof->before(F_CONV_FWD, s);
     k_split_weights<<<dim3((unsigned)pieces, 1, (unsigned)nact), 192, 0, s>>>(dp, u, jobs, sw.stride);
+    if (timed) prof->after(F_CONV_FWD, s);
     return hipGetLastError();
 }
 

@@ -661,7 +661,7 @@ hipError_t launch_layer_step(hipStream_t s, Profiler *prof, const RoundParams *d
         AET_TIMED(F_GATHER, k_gather<<<grid, 256, 0, s>>>(dp, u, B, D, sc.act[0], sc.labels));
         AET_RETURN_IF(hipGetLastError());
     }
-    if (sc.split.base && !sc.plain) AET_RETURN_IF(launch_split_weights(s, dp, nact, u, lay, L, B, sc.split));
+    if (sc.split.base && !sc.plain) AET_RETURN_IF(launch_split_weights(s, prof, dp, nact, u, lay, L, B, sc.split));
     auto split = [&](int l, bool bwd) {
         return !sc.plain && conv_split_used(lay, l, bwd, B, nact, sc.split);
     };

@@ -189,3 +189,16 @@ def test_largest_finite_values(oracle_libs, make):
                 compared += 1
         assert compared >= 2
     run.close()
+
+
+def test_splitting_of_the_weights_is_timed():
+    """Once a recursion for all layers, in the family of the forward convolutions."""
+    from paper_2112_13935_amd.runner import Run
+    launches = []
+    for run in (Run(CASES["cnn32"]()), _on_the_fp32_unit(CASES["cnn32"])):
+        fam = run.lib.profile_family_names().index("k_conv_fwd")
+        run.lib.aet_profile_enable(fam, True)
+        run.run_round()
+        launches.append(run.lib.aet_profile_read(fam)[0])
+        run.close()
+    assert launches == [5, 4]   # one recursion, four convolutions
