@@ -9,12 +9,13 @@
 // K = (tap, sc) in chunks of 16 source channels.  A workgroup owns 256 pixels (rows of one sample, or
 // several samples of 8 x 8) and 32 destination channels; each of its 4 waves owns two pixel tiles.
 //
-// What bounds it: the clock that the power limit leaves while the matrix cores run (1.6 GHz in a
-// loop of these launches; the products alone would take 126 us of the 204 of a 64 -> 64 layer, 32
-// clients x 64 samples of 16 x 16), then reading the maps (backward-data of 32 -> 32 channels at 32 x 32
-// moves 0.87 GB in 0.27 ms).  Unlike the fp32 matrix instructions these leave the vector ALU free
-// for the splitting.  CNN on 32 x 32, 32 clients, 4 rounds: forward and backward-data together 24
-// -> 16 ms, the job 48.9 -> 40.1.
+// What bounds it: in launches of all 32 clients of the CNN on 32 x 32 the matrix cores are busy 52 to 55 % of
+// the time in forward, 47 % in backward-data at 16 x 16 and 38 % at 32 x 32, where it moves 0.72 GB in about
+// 0.25 ms; the rest is the staging between two barriers and the LDS (9 reads of 16 bytes for 12 products, and
+// 17 % of a compute unit's cycles in bank conflicts on maps of 16).  The clock meanwhile is 2.1 GHz of 2.4: cards
+// differ by 5 % after what their power limit leaves.  Unlike the fp32 matrix instructions these leave the
+// vector ALU free for the splitting.  CNN on 32 x 32, 32 clients, 4 rounds: forward and backward-data
+// together 24 -> 16 ms, the job 48.9 -> 40.1.
 #include <type_traits>
 
 #include "aet_device.h"
@@ -323,9 +324,9 @@ k_conv_split(const RoundParams *__restrict__ rp, int u, int B, SplitDir g, const
 // take turns at the steps and are added at the end.  The three taps of a filter row read the same
 // pixels, shifted: the shifted operands are put together from aligned ones, not read.
 //
-// What bounds it: as above the clock under the power limit, then the staging between two
-// barriers, which only the compute unit's second workgroup covers (no registers are left to fetch the
-// next tile ahead: 96 accumulators of 168).  64 -> 64 channels at 16 x 16, 32 clients x 64 samples: 378
+// What bounds it: the staging between two barriers, which only the compute unit's second workgroup
+// covers (no registers are left to fetch the next tile ahead: 96 accumulators of 168): the matrix cores are
+// busy 36 to 38 % of the time in launches of all 32 clients.  64 -> 64 channels at 16 x 16, 32 clients x 64 samples: 378
 // -> 260 us; 32 -> 32 at 32 x 32: 389 -> 278 us.
 struct SplitWgrad {
     int IC, OC, H;
