@@ -153,7 +153,7 @@ bool resolve(const aet_model_desc *m, LayerGeom *lay, int64_t *P, std::string *w
 
 // which engine runs the local rounds of this model
 enum Engine { ENGINE_LAYERS = 0, ENGINE_MLP = 1, ENGINE_SOFTMAX = 2, ENGINE_LENET = 3,
-              ENGINE_SOFTMAX_BATCH = 4 };
+              ENGINE_SOFTMAX_BATCH = 4, ENGINE_CNN = 5 };
 
 // aet_test_select_kernels: which kernel set contexts created from now on use
 int g_force_layer_engine = 0, g_plain_layers = 0;
@@ -181,6 +181,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
     if (L == 1 && lay[0].type == AET_DENSE && padded_ok && softmax_batch_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX_BATCH;
     if (lenet_round_supported(lay, L, B) && (lenet_round_exact(B) || (padded && lenet_padded_pays(lay[0], B, n)))) return ENGINE_LENET;
+    if (padded_ok && cnn_round_pays(lay, L, B, n)) return ENGINE_CNN;
     return ENGINE_LAYERS;
 }
 
@@ -201,6 +202,7 @@ bool make_layout(const LayerGeom *lay, int L, int64_t P, int B, int n, int infli
     lo->labels = take((size_t)n * B * 4);
     // exchange records of the fused dense-ReLU-dense engine, only for models it runs
     lo->fused = take(eng == ENGINE_MLP ? mlp_round_scratch_bytes(n, B) : eng == ENGINE_LENET ? lenet_round_scratch_bytes(n, B)
+                     : eng == ENGINE_CNN ? cnn_round_scratch_bytes(lay, L, n, B)
                      : eng == ENGINE_SOFTMAX_BATCH ? softmax_batch_scratch_bytes(n, (int)lay[0].in_size, B) : 0);
     // partial sums of the convolutions' weight gradients: apart (so that one launch can finish all
     // layers), or in turns in the same place where the workspace is too small for that
@@ -527,7 +529,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         if (e == hipSuccess) e = ctx->ring_a.create((size_t)n_clients * max_inflight * sizeof(Arrival));
     }
     ctx->v_params.resize(n_clients);
-    const bool clusters = ctx->engine == ENGINE_MLP || ctx->engine == ENGINE_LENET ||
+    const bool clusters = ctx->engine == ENGINE_MLP || ctx->engine == ENGINE_LENET || ctx->engine == ENGINE_CNN ||
                           (ctx->engine == ENGINE_SOFTMAX_BATCH && softmax_batch_in_clusters((int)ctx->lay[0].in_size));
     if (clusters && !static_ws) {
         if (e == hipSuccess) e = hipGetDevice(&dev);
@@ -538,6 +540,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_LENET)
         e = lenet_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
+    if (e == hipSuccess && ctx->engine == ENGINE_CNN)
+        e = cnn_prepare(ctx->stream, ctx->lay, ctx->L, ctx->B, ctx->ws + ctx->lo.fused, n_clients);
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
         e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0
@@ -639,7 +643,7 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
         // dense-ReLU-dense engine takes them in its kernel arguments from plain host memory; the
         // other fused engines read them where they are, in the pinned ring (every workgroup
         // reads its own record once, at its start: no copy in the stream ahead of the kernel)
-        const bool direct = !ctx->static_ws && (ctx->engine == ENGINE_SOFTMAX || ctx->engine == ENGINE_LENET || ctx->engine == ENGINE_SOFTMAX_BATCH);
+        const bool direct = !ctx->static_ws && (ctx->engine == ENGINE_SOFTMAX || ctx->engine == ENGINE_LENET || ctx->engine == ENGINE_CNN || ctx->engine == ENGINE_SOFTMAX_BATCH);
         const bool ring = ctx->engine != ENGINE_MLP && !ctx->static_ws;
         void *slot = ctx->v_params.data();
         if (ring) AET_HIP(ctx, ctx->ring_p.acquire(&slot));
@@ -695,6 +699,11 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
             AET_HIP(ctx, ctx->clustered([&] {
                 return launch_lenet_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
                                           ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+            }));
+        } else if (ctx->engine == ENGINE_CNN) {
+            AET_HIP(ctx, ctx->clustered([&] {
+                return launch_cnn_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
+                                        ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
             }));
         } else {
             AET_HIP(ctx, launch_begin_round(ctx->stream, ctx->profp(), dp, nact, start, ctx->P));
@@ -899,6 +908,7 @@ static const int *cluster_flag(aet_ctx *ctx) {
     switch (ctx->engine) {
         case ENGINE_MLP: return mlp_error_flag_ptr(fused, ctx->n, ctx->B);
         case ENGINE_LENET: return lenet_error_flag_ptr(fused, ctx->n, ctx->B);
+        case ENGINE_CNN: return cnn_error_flag_ptr(fused, ctx->n);
         case ENGINE_SOFTMAX_BATCH: return softmax_batch_error_flag_ptr(fused, ctx->n, (int)ctx->lay[0].in_size, ctx->B);
         default: return nullptr;
     }

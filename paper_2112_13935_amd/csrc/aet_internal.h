@@ -95,7 +95,7 @@ struct LayerScratch {
 enum Family {
     F_BEGIN_ROUND = 0, F_GATHER, F_DENSE_FWD, F_DENSE_BWD_DATA, F_DENSE_BWD_WEIGHT, F_CONV_FWD,
     F_CONV_BWD_DATA, F_CONV_BWD_WEIGHT, F_POOL_FWD, F_POOL_BWD, F_SOFTMAX_CE, F_SERVER_REDUCE,
-    F_SOFTMAX_ROUND, F_MLP_ROUND, F_NEIGHBOUR_APPLY, F_LENET_ROUND, F_COUNT
+    F_SOFTMAX_ROUND, F_MLP_ROUND, F_NEIGHBOUR_APPLY, F_LENET_ROUND, F_CNN_ROUND, F_COUNT
 };
 const char *family_name(int fam);
 
@@ -229,5 +229,12 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
                               int n_clients, uint32_t *epoch);
 hipError_t lenet_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B);
 const int *lenet_error_flag_ptr(void *scratch, int n_clients, int B);
+// fused round of small convolutional networks (kernels_cnn.hip); dp: DEVICE array of round records
+bool cnn_round_pays(const LayerGeom *lay, int L, int B, int n_clients);   // supported, and faster than the layer engine
+size_t cnn_round_scratch_bytes(const LayerGeom *lay, int L, int n_clients, int B);
+hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m, const float *Wg,
+                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, uint32_t *epoch);
+hipError_t cnn_prepare(hipStream_t s, const LayerGeom *lay, int L, int B, void *scratch, int n_clients);   // once, ahead of the first launch
+const int *cnn_error_flag_ptr(void *scratch, int n_clients);
 
 }  // namespace aet
