@@ -17,11 +17,13 @@
 // latency and its epilogue, in a large one the fp32 matrix instructions (32 clocks each) take
 // as much again; the two barriers of the cluster and three trips through L2 (weights, dense layers,
 // gradients) are a quarter of a recursion.  The layer engine spends 13 - 15 launches on a recursion, each
-// a launch boundary and two to four dependent trips through memory.  16 x 16 half-width CNN, 6 clients,
-// mini-batch 16, 6 rounds: 5.53 -> 2.72 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch 5: 1.94 -> 0.88
-// ms.  Sixteen waves of 128 registers: eight of 256 took 10 - 30 % longer in the products, which wait for LDS.
-// One body for both directions of the convolutions and plans worked out by the host: with each form
-// written out the kernel had 84 KB of code, more than the instruction cache, and took 4.8 ms.
+// a launch boundary and two to four dependent trips through memory.  16 x 16 half-width CNN, 6 clients with
+// compute factors, mini-batch 16, 6 rounds: 5.42 -> 3.33 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch
+// 5, 6 rounds: 1.94 -> 0.86 ms.  Sixteen waves of 128 registers: eight of 256 took 10 - 30 % longer in the
+// products, which wait for LDS.  One body for both directions of the convolutions, and steps worked out by the
+// host: with each form written out the kernel had 84 KB of code, more than the instruction cache
+// holds, and took 1.7 times as long.  The update by whole waves, filters and dense layers side by side
+// and not one after the other: 14.5 -> 9.2 K clocks of a recursion's 138 K.
 //
 // Layout of a map in LDS: a plane per channel, rows of W + 1 floats of which the first is zero (left
 // edge of its row and right edge of the one before), a row of zeros above and below.  So every tap of a
@@ -88,7 +90,6 @@ struct CnnPlan {
     int w1, b1, w2, b2;                // offsets into the parameters
     int conv_params;                   // they come first
     int in_size, in_w, in_hw, in_src, in_pl;
-    unsigned div_cols1, div_cols2;
     int feat, hid, dhid, logit;        // LDS: inputs and gradients of the dense layers
     int wbuf, red;                     // LDS: staged weights, partial sums of split tiles
     int lds_floats;
@@ -387,20 +388,20 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
         }
         return at;
     };
-    // dense weights in columns of four units; the last column of a layer is its biases
-    const int cols1 = g.F0 + 1, cols2 = g.H + 1;
-    const int items1 = ((g.H + 3) >> 2) * cols1, items = items1 + ((g.C + 3) >> 2) * cols2;
+    // The parameters' owners, by the wave: 64 filter weights, or 64 columns of four units of a dense layer (the
+    // last column of a layer is its biases).  Wave w of workgroup g takes pieces 16 g + w, ...
+    const int conv_pieces = (Pc + 63) >> 6, cols1 = (g.F0 + 64) >> 6, cols2 = (g.H + 64) >> 6;
+    const int pieces1 = conv_pieces + ((g.H + 3) >> 2) * cols1, pieces = pieces1 + ((g.C + 3) >> 2) * cols2;
     struct Item { bool second; int u0, f, F, un, first, step; };   // first: of the units' weights, step from one to the next
-    auto dense_item = [&](int it) {
+    auto dense_item = [&](int piece) {
         Item o;
-        o.second = it >= items1;
-        const int r = o.second ? it - items1 : it;
-        const int q = (int)quotient((unsigned)r, o.second ? g.div_cols2 : g.div_cols1);
+        o.second = piece >= pieces1;
+        const int r = piece - (o.second ? pieces1 : conv_pieces), n = o.second ? cols2 : cols1, q = r / n;
         o.u0 = 4 * q;
-        o.f = r - q * (o.second ? cols2 : cols1);
+        o.f = 64 * (r - q * n) + lane;
         o.F = o.second ? g.H : g.F0;
-        o.un = min(4, (o.second ? g.C : g.H) - o.u0);
-        const bool bias = o.f == o.F;
+        o.un = o.f <= o.F ? min(4, (o.second ? g.C : g.H) - o.u0) : 0;   // 0: no such column
+        const bool bias = o.f >= o.F;
         o.first = bias ? (o.second ? g.b2 : g.b1) + o.u0 : (o.second ? g.w2 : g.w1) + o.u0 * o.F + o.f;
         o.step = bias ? 1 : o.F;
         return o;
@@ -408,17 +409,21 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
     // (the images' padding, channels and taps that do not exist, is zero)
     for (int e = me * kCnThreads + tid; e < g.rec; e += G * kCnThreads) put1(rs, 4 * e, 0, 0.f, one_xcd);
     cluster_barrier();
-    for (int i = me * kCnThreads + tid; i < Pc; i += G * kCnThreads) {
-        const float w = W0[i];
-        const i2 at = image_places(i);
-        put1(rs, at[0], 0, w, one_xcd);
-        put1(rs, at[1], 0, w, one_xcd);
-        if (Wg) put1(rw, 4 * i, 0, w, one_xcd);
-        U[i] = 0.f;
-        table[i] = at;
-    }
-    for (int it = me * kCnThreads + tid; it < items; it += G * kCnThreads) {
-        const Item o = dense_item(it);
+    for (int piece = me * kCnWaves + wave; piece < pieces; piece += G * kCnWaves) {
+        if (piece < conv_pieces) {
+            const int i = 64 * piece + lane;
+            if (i < Pc) {
+                const float w = W0[i];
+                const i2 at = image_places(i);
+                put1(rs, at[0], 0, w, one_xcd);
+                put1(rs, at[1], 0, w, one_xcd);
+                if (Wg) put1(rw, 4 * i, 0, w, one_xcd);
+                U[i] = 0.f;
+                table[i] = at;
+            }
+            continue;
+        }
+        const Item o = dense_item(piece);
         for (int j = 0; j < o.un; ++j) {
             const int i = o.first + j * o.step;
             if (Wg) put1(rw, 4 * i, 0, W0[i], one_xcd);
@@ -524,13 +529,11 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
                         put1(rs, 4 * f, rec + g.rec_d1, d, one_xcd);
                     }
                     __syncthreads();
-                    if (g.t_clear) clear_edges(lds, g.t_del, g.t_pl, g.t_planes, g.t_h, g.t_swp);
-                    // d(features), masked and put where the maxima came from
-#pragma unroll 1
-                    for (int f = tid; f < g.F0; f += kCnThreads) {
+                    // sum over units o0 .. o1 - 1 of gradient times weight
+                    auto features = [&](int f, int o0, int o1) {
                         float d = 0.f;
 #pragma unroll 1
-                        for (int o0 = 0; o0 < g.H; o0 += 32) {
+                        for (; o0 < o1; o0 += 32) {
                             float w[32];
 #pragma unroll
                             for (int j = 0; j < 32; ++j) w[j] = get1(rw, 4 * f, g.w1 + min(o0 + j, g.H - 1) * g.F0);
@@ -540,6 +543,22 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
                                 d += w[j] * dh[0] + w[j + 1] * dh[1] + (w[j + 2] * dh[2] + w[j + 3] * dh[3]);
                             }
                         }
+                        return d;
+                    };
+                    if (g.t_clear) clear_edges(lds, g.t_del, g.t_pl, g.t_planes, g.t_h, g.t_swp);
+                    // d(features), masked and put where the maxima came from.  Up to half as many features as
+                    // threads: two threads a feature, the first half of the units and the second
+                    const bool halves = 2 * g.F0 <= kCnThreads && g.H > 32;
+                    const int mid = halves ? (g.H / 2 + 31) & ~31 : g.H;
+                    if (halves) {
+                        const int f = tid - kCnThreads / 2;
+                        if (f >= 0 && f < g.F0) lds[g.red + f] = features(f, mid, g.H);
+                        else if (tid < g.F0) lds[g.red + g.F0 + tid] = features(tid, 0, mid);
+                        __syncthreads();
+                    }
+#pragma unroll 1
+                    for (int f = tid; f < g.F0; f += kCnThreads) {
+                        float d = halves ? lds[g.red + g.F0 + f] + lds[g.red + f] : features(f, 0, g.H);
                         const float a = lds[g.feat + f];
                         put1(rs, 4 * f, rec, a, one_xcd);
                         if (g.t_relu && !(a > 0.f)) d = 0.f;
@@ -680,51 +699,57 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
 
         // ---- this workgroup's share of the sums and of the update -----------------------------------------
 #pragma unroll 1
-        for (int i = me * kCnThreads + tid; i < Pc; i += G * kCnThreads) {
-            const float w = get1(rw, 4 * i, 0), uo = U[i];
-            const i2 at = table[i];
-            float sum = 0.f;
+        for (int piece = me * kCnWaves + wave; piece < pieces; piece += G * kCnWaves) {
+            if (piece < conv_pieces) {
+                const int i = min(64 * piece + lane, Pc - 1);
+                const float w = get1(rw, 4 * i, 0), uo = U[i];
+                const i2 at = table[i];
+                float sum = 0.f;
 #pragma unroll 1
-            for (int k0 = 0; k0 < g.A; k0 += kCnBatch) {
-                float v[kCnBatch];
+                for (int k0 = 0; k0 < g.A; k0 += kCnBatch) {
+                    float v[kCnBatch];
 #pragma unroll
-                for (int k = 0; k < kCnBatch; ++k) v[k] = get1(rs, 4 * i, g.part + min(k0 + k, g.A - 1) * g.partials);
+                    for (int k = 0; k < kCnBatch; ++k) v[k] = get1(rs, 4 * i, g.part + min(k0 + k, g.A - 1) * g.partials);
 #pragma unroll
-                for (int k = 0; k < kCnBatch; ++k)
-                    if (k0 + k < g.A) sum += v[k];
+                    for (int k = 0; k < kCnBatch; ++k)
+                        if (k0 + k < g.A) sum += v[k];
+                }
+                if (64 * piece + lane < Pc) {
+                    const float gr = sum * invB, wn = w - p.eta * gr;
+                    put1(rw, 4 * i, 0, wn, one_xcd);
+                    put1(rs, at[0], 0, wn, one_xcd);
+                    put1(rs, at[1], 0, wn, one_xcd);
+                    U[i] = uo + gr;
+                }
+                continue;
             }
-            const float gr = sum * invB, wn = w - p.eta * gr;
-            put1(rw, 4 * i, 0, wn, one_xcd);
-            put1(rs, at[0], 0, wn, one_xcd);
-            put1(rs, at[1], 0, wn, one_xcd);
-            U[i] = uo + gr;
-        }
-#pragma unroll 1
-        for (int it = me * kCnThreads + tid; it < items; it += G * kCnThreads) {
-            const Item o = dense_item(it);
-            const bool bias = o.f == o.F;
-            const int in = 4 * ((o.second ? g.rec_h : 0) + min(o.f, o.F - 1)), out = 4 * ((o.second ? g.rec_d2 : g.rec_d1) + o.u0);
+            const Item o = dense_item(piece);
+            const bool bias = o.f >= o.F;
+            const int in = 4 * ((o.second ? g.rec_h : 0) + min(o.f, o.F - 1)), out = (o.second ? g.rec_d2 : g.rec_d1) + o.u0;
             float w[4], uo[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int i = o.first + min(j, o.un - 1) * o.step;
-                w[j] = get1(rw, 4 * i, 0);
-                uo[j] = U[i];
+                const int i = o.first + max(min(j, o.un - 1), 0) * o.step;
+                w[j] = get1(rw, o.un > 0 ? 4 * i : kNowhere, 0);
+                uo[j] = U[o.un > 0 ? i : 0];
             }
             f4 sum = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-            for (int b0 = 0; b0 < B; b0 += kCnBatch / 2) {
-                float a[kCnBatch / 2];
-                f4 d[kCnBatch / 2];
+            for (int b0 = 0; b0 < B; b0 += kCnBatch) {
+                // the units' gradients are the same for all lanes: lane k brings sample b0 + k's
+                const f4 d = get4(rs, 4 * min(b0 + (lane & (kCnBatch - 1)), B - 1) * g.records, g.rec + out);
+                float a[kCnBatch];
 #pragma unroll
-                for (int k = 0; k < kCnBatch / 2; ++k) {
-                    const int base = g.rec + min(b0 + k, B - 1) * g.records;
-                    a[k] = get1(rs, in, base);
-                    d[k] = get4(rs, out, base);
+                for (int k = 0; k < kCnBatch; ++k) a[k] = get1(rs, in, g.rec + min(b0 + k, B - 1) * g.records);
+#pragma unroll
+                for (int k = 0; k < kCnBatch; ++k) {
+                    const float x = b0 + k >= B ? 0.f : bias ? 1.f : a[k];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float dj = d[j];   // (a bit cast of the element itself takes the first one's bits)
+                        sum[j] += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dj), k)) * x;
+                    }
                 }
-#pragma unroll
-                for (int k = 0; k < kCnBatch / 2; ++k)
-                    if (b0 + k < B) sum += d[k] * (bias ? 1.f : a[k]);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -825,8 +850,6 @@ bool cnn_plan(const LayerGeom *lay, int L, int B, int n_clients, CnnPlan *g) {
     const int per_xcd = (n_clients + 7) / 8, room_for = kClusterMax / (per_xcd < kClusterMax ? per_xcd : kClusterMax);
     const int wanted = ((int)(d2.b_off + d2.oc) + 2047) / 2048, helped = wanted < room_for ? wanted : room_for;
     g->G = helped > g->A ? helped : g->A;
-    g->div_cols1 = reciprocal(g->F0 + 1);
-    g->div_cols2 = reciprocal(g->H + 1);
     g->in_size = (int)lay[0].in_size;
     if (g->in_size > kCnRow * kCnThreads) return false;
     // LDS: the input planes of every convolution, what goes to the dense layers, winners
