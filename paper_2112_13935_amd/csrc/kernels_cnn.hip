@@ -200,10 +200,8 @@ __device__ __forceinline__ void taps(f4 &acc, const float *lds, int a, int pl4, 
 #pragma unroll 1
     for (int i = 2; i <= n; i += 2) {
         load(y);
-        __builtin_amdgcn_sched_barrier(0);
         products(x);
         if (i < n) load(x);
-        __builtin_amdgcn_sched_barrier(0);
         products(y);
     }
     if (n & 1) products(x);
@@ -234,14 +232,12 @@ __device__ __forceinline__ void pixels(f4 &acc, const float *lds, int a, int b, 
     for (;;) {
         load(y[0]);
         load(y[1]);
-        __builtin_amdgcn_sched_barrier(0);
         products(x[0]);
         if (n > 1) products(x[1]);
         n -= 2;
         if (n <= 0) break;
         load(x[0]);
         load(x[1]);
-        __builtin_amdgcn_sched_barrier(0);
         products(y[0]);
         if (n > 1) products(y[1]);
         n -= 2;
