@@ -499,7 +499,7 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const
                     __syncthreads();
                     if (wave == 0) {
                         const bool real = lane < g.C;
-                        const float z = real ? lds[g.logit + lane] : -3.0e38f;
+                        const float z = real ? lds[g.logit + lane] : -INFINITY;   // (a finite value could be above the logits)
                         const float zmax = all_max(z);
                         const float lse = zmax + logf(all_sum(real ? expf(z - zmax) : 0.f));
                         const float dz = real ? expf(z - lse) - (lane == lab ? 1.f : 0.f) : 0.f;

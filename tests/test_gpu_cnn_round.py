@@ -140,6 +140,35 @@ def test_layer_engine_where_this_round_took_over(oracle_libs):
     run.close()
 
 
+@pytest.mark.parametrize("biases", [
+    [-3.2e38] * 10,                              # every logit below -3e38: ten equal ones
+    [-np.inf] + [0.0] * 9,                       # a class that is ruled out
+    [-np.inf] * 4 + [-3.3e38] * 5 + [-np.inf],   # and no other one near zero
+], ids=["lowest", "ruled_out", "both"])
+def test_logits_near_the_lowest_value(biases):
+    """Logits that are finite, or -inf for some classes, have a softmax: U is what the layer engine gives, and
+    finite.  (The labels are classes of finite logits.)"""
+    from paper_2112_13935_amd import load_library
+    from paper_2112_13935_amd.runner import Run
+    out = []
+    for layers in (1, 0):
+        wl = _cnn(2, 8, 5, 12, 4, rounds=1)
+        wl.w0[-10:] = biases
+        real = np.flatnonzero(np.isfinite(biases))
+        wl.y = [real[y % real.size].astype(np.int32) for y in wl.y]
+        load_library().aet_test_select_kernels(layers, 0)
+        try:
+            run = Run(wl)
+        finally:
+            load_library().aet_test_select_kernels(0, 0)
+        run.run_round()
+        out.append(np.stack([run.lib.aet_get_U(c, 0) for c in range(wl.n_clients)]).astype(np.float64))
+        run.close()
+    assert np.isfinite(out[0]).all() and np.isfinite(out[1]).all()
+    # (sums in another order, as below)
+    assert np.linalg.norm(out[1] - out[0]) <= 1e-5 * np.linalg.norm(out[0])
+
+
 def test_small_workspace_takes_the_layer_engine(monkeypatch):
     """Its images and records are an option: without room for them the call is still accepted."""
     import re
