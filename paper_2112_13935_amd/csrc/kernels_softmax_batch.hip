@@ -84,6 +84,12 @@ __device__ __forceinline__ float fold16(float a, float b) {
     return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
 }
 
+// What the wave's lanes wrote to LDS is there for all of them afterwards, and what they read before may be
+// written again.  No instruction: a wave's LDS accesses are carried out in order, this keeps the compiler's.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+}
+
 typedef f4 __attribute__((aligned(4))) f4_any;   // four floats at any place
 typedef const f4_any __attribute__((address_space(1))) *gcf4_ptr;
 typedef f4_any __attribute__((address_space(1))) *gf4_ptr;
@@ -317,6 +323,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                     for (int t = 0; t < MT; ++t)
                         if (BC % 16 == 0 || li < BC) *reinterpret_cast<f4 *>(turn + n * BC * 16 + (16 * t + li) * 16 + 4 * lg) = x[t][j0 + n];
                 }
+                wave_lds_order();
                 if (!DB && u + 1 < p.m) {
 #pragma unroll
                     for (int n = 0; n < NX; ++n) load_block(x, j0 + n);
@@ -340,6 +347,7 @@ k_softmax_batch_round(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                     else U[ULDS ? 0 : j] += G[n] * invB;
                 }
             }
+            wave_lds_order();   // the next block, or the next recursion's logits, go to the same place
             __builtin_amdgcn_sched_barrier(0);   // (registers: the loop does not spill)
         }
     };
