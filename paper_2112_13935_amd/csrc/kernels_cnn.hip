@@ -1048,20 +1048,34 @@ size_t cnn_head_bytes(int n_clients) { return cnn_plan_at(n_clients) + (sizeof(C
 }  // namespace
 
 // A turn is what one launch does with one sample per workgroup.  Time here / in the layer engine, per
-// recursion, for clients x mini-batch (8 x 8 maps and 16 channels | 8 x 8, 32 | 12 x 12, 24 | 16 x 16, 16):
-//   one turn    1 x 1   0.54 0.76 0.68 0.75    4 x 5   0.52 0.67 0.59 0.67    16 x 16  0.44 0.60 0.47 0.51    8 x 32  0.46 0.57 0.49 0.52
-//   two turns   1 x 64  0.83 1.28 1.12 1.08    4 x 64  0.76 1.03 0.87 0.89    8 x 64   0.55 0.75 0.62 0.67   32 x 16  0.61 0.80 0.63 0.69
-//   four turns  16 x 64 0.77 0.98 0.73 0.95   32 x 32  0.89 1.02 0.77 1.06
-// So one turn always pays, two pay for small layers or where they are filled, beyond that it depends on
-// the layers and the layer engine keeps what it had.
+// recursion, for clients x mini-batch (8 x 8 maps and 16 channels | 8 x 8, 32 | 12 x 12, 24 | 16 x 16, 16 | seven
+// layers of 16 on 8 x 8 | 32 x 32, 4; hidden layers of 64 and 30 units):
+//   one turn    1 x 1   0.47 0.70 0.65 0.70 0.64 0.82    4 x 5   0.45 0.61 0.56 0.64 0.58 0.71    16 x 16  0.38 0.51 0.43 0.46 0.49 0.41
+//   two turns   1 x 33  0.80 1.25 1.06 1.13 1.03 1.04    4 x 64  0.70 0.97 0.82 0.83 0.89 0.68     5 x 64  0.50 0.76 0.68 0.66 0.64 0.62
+//               6 x 64  0.49 0.75 0.65 0.63 0.64 0.58   12 x 32  0.52 0.77 0.67 0.66 0.67 0.66   24 x 16  0.55 0.76 0.65 0.68 0.70 0.63
+// So one turn pays, two pay for small convolutions or with many samples, beyond that the layer engine keeps what it had.
+//
+// That is without the dense layers' part: every workgroup reads the first one's weights twice per sample, 0.155 us
+// per thousand, where the layer engine reads them once for many samples.  Features x units that it has time for
+// come with the convolutions (launches of the layer engine) and, a little, with all clients' parameters.  One
+// convolution on 8 x 8 maps, 1 x 1 and 8 x 32: 65 K weights 0.63 - 0.92 and 0.54 - 0.87, 131 K 0.83 - 0.92 and 0.72 - 0.75,
+// 262 K 1.13 - 1.31 and 0.95 - 1.03, 4 M 7.4 and 2.6.  And a client's only workgroup makes the whole update, 0.85 us per thousand
+// parameters: two launches of 300 clients, mini-batch 1: 8 x 8, 16 channels (25 K) 0.75, 12 x 12, 24 (65 K) 1.15, 8 x 8, 32 (72 K) 1.31.
+// Of 3,243 random networks (1 - 7 convolutions of 3 - 64 channels, maps of 4 x 4 to 32 x 32, 8 - 1,024 units, 1 - 500
+// clients, mini-batch 1 - 64) of up to two turns the dense limits turn 128 away, of which half had lost (up to 4.1);
+// of those that are taken, ten take longer than the layer engine by more than 2 %, 1.17 at most (median 0.41, with two turns 0.56).
 bool cnn_round_pays(const LayerGeom *lay, int L, int B, int n_clients) {
     CnnPlan g;
     if (!cnn_plan(lay, L, B, n_clients, &g)) return false;
-    const int per_launch = 8 * (kClusterMax / g.G), turns = (n_clients + per_launch - 1) / per_launch * ((B + g.A - 1) / g.A);
+    const int per_launch = 8 * (kClusterMax / g.G), launches = (n_clients + per_launch - 1) / per_launch;
+    const int turns = launches * ((B + g.A - 1) / g.A);
     int64_t macs = 0;
     for (int l = 0; l < L; ++l)
         if (lay[l].type == 0) macs += lay[l].out_size * lay[l].ic * 9;
-    return turns == 1 || (turns == 2 && (macs <= 1000000 || (int64_t)n_clients * B >= 384));
+    const int64_t params = g.b2 + g.C, dense = (int64_t)turns * g.F0 * g.H, clients = n_clients;
+    if (turns == 1) return dense <= 200000 * g.nconv + clients * params / 200;
+    if (g.G == 1 && params > 16000 * g.nconv) return false;
+    return turns == 2 && dense <= 130000 * g.nconv + clients * params / 200 && (macs <= 1000000 || clients * B >= 384);
 }
 
 size_t cnn_round_scratch_bytes(const LayerGeom *lay, int L, int n_clients, int B) {

@@ -124,6 +124,23 @@ def test_where_it_is_the_faster_engine(n, hw, width, batch, launches):
     assert _launches(Run(_cnn(n, hw, width, 16, batch, 1))) == launches
 
 
+@pytest.mark.parametrize("n,channels,units,batch,launches", [
+    (1, 8, 384, 1, 1), (1, 8, 400, 1, 0), (8, 16, 196, 32, 1), (8, 16, 256, 32, 0), (1, 64, 48, 8, 1), (1, 64, 1024, 8, 0),
+    (4, 8, 120, 64, 1), (4, 8, 192, 64, 0),
+])
+def test_wide_dense_layers_keep_the_layer_engine(n, channels, units, batch, launches):
+    """One convolution on 8 x 8 maps: every workgroup goes through the hidden layer's weights twice per sample."""
+    from paper_2112_13935_amd.runner import Run
+    assert _launches(Run(_net(n, batch, (3, 8, 8), [_conv(channels), _dense(units)], 1))) == launches
+
+
+@pytest.mark.parametrize("width,launches", [(16, 2), (32, 0)])
+def test_lone_workgroups_with_many_parameters_keep_the_layer_engine(width, launches):
+    """More clients than compute units, mini-batch 1: one workgroup makes a client's whole update."""
+    from paper_2112_13935_amd.runner import Run
+    assert _launches(Run(_cnn(257, 8, width, 64, 1, 1))) == launches
+
+
 def test_layer_engine_where_this_round_took_over(oracle_libs):
     """A shape whose split convolutions end inside their tiles, which without asking runs fused."""
     from oracle import Oracle
