@@ -312,23 +312,35 @@ struct aet_ctx {
     // a context whose rounds run in clusters: its place among those of its GPU
     struct Turn : ClusterTurns<hipStream_t>::Member {
         ClusterTurns<hipStream_t> *among = nullptr;
-        hipEvent_t ev = nullptr;   // none in a context on the library's own workspace
+        ClusterTurns<hipStream_t>::Need need;
+        hipEvent_t ev = nullptr, mark = nullptr;   // none in a context on the library's own workspace; mark: only of launches that go beside others
     };
     Turn turn;
-    // The cluster launch, behind those that other contexts made on other streams.  (Under capture
-    // there is no order to other streams: a replay beside other cluster launches is the caller's
-    // to prevent.)
+    // The cluster launch, beside those that other contexts made on other streams or behind them.  (Under
+    // capture there is no order to other streams: a replay beside other cluster launches is the
+    // caller's to prevent.)
     template <class Launch>
-    hipError_t clustered(Launch launch) {
-        if (!turn.among) return launch();
-        const bool captured = stream_is_capturing(stream);
-        return turn.among->take(&turn, [&](ClusterTurns<hipStream_t>::Member *m) -> hipError_t {
-            if (captured || stream_is_capturing(m->stream)) return hipSuccess;
+    hipError_t clustered(const ClusterTurns<hipStream_t>::Need &need, Launch launch) {
+        using Member = ClusterTurns<hipStream_t>::Member;
+        if (!turn.among || stream_is_capturing(stream)) return launch(need.most);
+        const auto done = [](hipError_t e) {
+            if (e == hipErrorNotReady) (void)hipGetLastError();   // an answer, not an error of the launch that follows
+            return e == hipSuccess;
+        };
+        const auto idle = [&](Member *m) { return !stream_is_capturing(m->stream) && done(hipStreamQuery(m->stream)); };
+        const auto mark = [](Member *m) { return static_cast<Turn *>(m)->mark ? hipEventRecord(static_cast<Turn *>(m)->mark, m->stream) : hipSuccess; };
+        const auto passed = [&](Member *m) { return static_cast<Turn *>(m)->mark && done(hipEventQuery(static_cast<Turn *>(m)->mark)); };
+        return turn.among->take(&turn, need, idle, mark, passed, [&](Member *m) -> hipError_t {
+            if (stream_is_capturing(m->stream)) return hipSuccess;
             // only one context of a GPU has no event, so one of the two has
             const hipEvent_t own = static_cast<Turn *>(m)->ev, ev = own ? own : turn.ev;
             const hipError_t e = hipEventRecord(ev, m->stream);
             return e != hipSuccess ? e : hipStreamWaitEvent(stream, ev, 0);
         }, launch);
+    }
+    template <class Launch>
+    hipError_t clustered(Launch launch) {
+        return clustered(ClusterTurns<hipStream_t>::Need(), [&](int) { return launch(); });
     }
     std::string err;
     Profiler prof;
@@ -535,6 +547,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess && (dev < 0 || dev >= kMaxDevices)) e = hipErrorInvalidDevice;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->turn.ev, hipEventDisableTiming);
+        if (e == hipSuccess && ctx->engine == ENGINE_CNN) e = hipEventCreateWithFlags(&ctx->turn.mark, hipEventDisableTiming);
     }
     if (e == hipSuccess && ctx->engine == ENGINE_MLP)
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
@@ -542,6 +555,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         e = lenet_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
     if (e == hipSuccess && ctx->engine == ENGINE_CNN)
         e = cnn_prepare(ctx->stream, ctx->lay, ctx->L, ctx->B, ctx->ws + ctx->lo.fused, n_clients);
+    if (e == hipSuccess && ctx->engine == ENGINE_CNN)
+        e = cnn_cluster_need(ctx->lay, ctx->L, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.clusters, &ctx->turn.need.least, &ctx->turn.need.most);
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
         e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0
@@ -701,9 +716,9 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
                                           ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
             }));
         } else if (ctx->engine == ENGINE_CNN) {
-            AET_HIP(ctx, ctx->clustered([&] {
+            AET_HIP(ctx, ctx->clustered(ctx->turn.need, [&](int size) {
                 return launch_cnn_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
-                                        ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+                                        ctx->ws + ctx->lo.fused, ctx->n, size, &ctx->epoch);
             }));
         } else {
             AET_HIP(ctx, launch_begin_round(ctx->stream, ctx->profp(), dp, nact, start, ctx->P));
@@ -1104,6 +1119,7 @@ void aet_destroy(aet_ctx *ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->turn.among) ctx->turn.among->leave(&ctx->turn);
     if (ctx->turn.ev) (void)hipEventDestroy(ctx->turn.ev);
+    if (ctx->turn.mark) (void)hipEventDestroy(ctx->turn.mark);
     if (ctx->static_ws && ctx->device >= 0 && g_scratch_owner[ctx->device] == ctx) g_scratch_owner[ctx->device] = nullptr;
     ctx->ring_p.destroy();
     ctx->ring_a.destroy();

@@ -85,7 +85,7 @@ struct CnnPlan {
     CnnStep step[kCnSteps];
     int nsteps, turn;                  // steps; the first on the way down
     int first, first_floats;           // the first chunk of weights
-    int B, G, A;                       // mini-batch, workgroups of a cluster, those of them that take samples
+    int B, G, A;                       // mini-batch; workgroups of a cluster, at most, and those of them that take samples
     int F0, H, C, relu_h;              // dense: F0 -> H -> C
     int w1, b1, w2, b2;                // offsets into the parameters
     int conv_params;                   // they come first
@@ -279,12 +279,11 @@ __device__ __forceinline__ void clear_edges(float *lds, int base, int pl, int pl
 }
 
 __global__ void __launch_bounds__(kCnThreads, 1)
-k_cnn_round(const RoundParams *__restrict__ rp, int nact, const float *Wg, const CnnPlan *plan, float *scratch, u64 *words,
+k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, const float *Wg, const CnnPlan *plan, float *scratch, u64 *words,
             u64 *places, int skew, uint32_t tag0, int *errflag) {
     const ConstantPlan &g = *(const ConstantPlan *)plan;   // read with scalar loads
     extern __shared__ __attribute__((aligned(16))) float lds[];
     uint8_t *const lds8 = reinterpret_cast<uint8_t *>(lds);
-    const int G = g.G;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int who = (slot / G) * 8 + xcd, me = slot % G;   // client of the launch, workgroup of its cluster
     if (who >= nact) return;
@@ -1096,11 +1095,26 @@ const int *cnn_error_flag_ptr(void *scratch, int n_clients) {
     return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + cnn_words(n_clients));
 }
 
-hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m, const float *Wg,
-                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, uint32_t *epoch) {
-    if (nact <= 0) return hipSuccess;
+hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, int *cus, int *clusters, int *least, int *most) {
     CnnPlan g;
     if (!cnn_plan(lay, L, B, n_clients, &g)) return hipErrorInvalidValue;
+    int dev = 0, all = 0, xcds = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&all, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = device_xcds(&xcds);
+    if (e != hipSuccess) return e;
+    *cus = all / xcds;
+    *clusters = (n_clients + xcds - 1) / xcds;
+    *least = g.A;
+    *most = g.G;
+    return hipSuccess;
+}
+
+hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m, const float *Wg,
+                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, int size, uint32_t *epoch) {
+    if (nact <= 0) return hipSuccess;
+    CnnPlan g;
+    if (!cnn_plan(lay, L, B, n_clients, &g) || size < g.A || size > g.G) return hipErrorInvalidValue;
     const size_t lds = (size_t)g.lds_floats * 4;
     int dev = 0, cus = 0, per_cu = 0, sized = 0, xcds = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1114,7 +1128,7 @@ hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cnn_round, kCnThreads, lds);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
-    const int per_launch = resident_clusters(cus * per_cu, xcds, g.G);
+    const int per_launch = resident_clusters(cus * per_cu, xcds, size);
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     u64 *words = static_cast<u64 *>(scratch), *all_places = words + (size_t)n_clients * whole_lines(kClusterMax);
     u64 *places = g_posts_to_memory ? nullptr : all_places;
@@ -1136,9 +1150,9 @@ hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp
     *epoch += need;
     for (int a0 = 0; a0 < nact; a0 += per_launch) {
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
-        const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * g.G);
+        const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * size);
         if (prof && prof->on[F_CNN_ROUND]) prof->before(F_CNN_ROUND, s);
-        k_cnn_round<<<grid, kCnThreads, lds, s>>>(dp + a0, here, Wg, plan, data, words, places, g_xcd_skew, tag0, errflag);
+        k_cnn_round<<<grid, kCnThreads, lds, s>>>(dp + a0, here, size, Wg, plan, data, words, places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_CNN_ROUND]) prof->after(F_CNN_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

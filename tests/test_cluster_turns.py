@@ -1,9 +1,12 @@
 """Cluster launches of several contexts on one GPU (csrc/cluster_turns.h): never two in flight on
-different streams, and no event where a context is alone or the others are idle.  The header is
+different streams, or as many as the compute units hold where a launch says what it needs, and no event where a context
+is alone or the others are idle.  The header is
 plain host code; a C++ program drives it with streams that only keep what they are ordered
 behind."""
 import os
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -79,10 +82,132 @@ int main() {
 """
 
 
-def test_cluster_launches_are_ordered_across_streams(tmp_path):
+# Contexts whose launches may go beside others.  A stream is a row of launches; each knows those that are done before it
+# starts, and the GPU gets on at random.
+SHARED = r"""
+#include "cluster_turns.h"
+#include <cstdio>
+#include <map>
+#include <random>
+#include <set>
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s (line %d)\n", #x, __LINE__); return 1; } } while (0)
+using Turns = aet::ClusterTurns<int>;
+constexpr int kCus = 32;
+struct Launch { int stream, held; };
+struct Gpu {
+    std::vector<Launch> all;
+    std::map<int, std::vector<int>> row;        // stream -> its launches
+    std::map<int, std::set<int>> behind;        // stream -> launches its next one is ordered behind
+    std::set<int> done;
+    std::map<Turns::Member *, size_t> mark;     // launches of the stream ahead of the latest mark
+    int events = 0;
+    bool finish(int l) {                        // if all before it are done
+        for (int k : row[all[l].stream]) if (k < l && !done.count(k)) return false;
+        return done.insert(l).second;
+    }
+};
+int main() {
+    for (int seed = 1; seed <= 60; ++seed) {
+        std::mt19937 rng(seed);
+        Turns turns;
+        Gpu gpu;
+        const int N = 2 + (int)(rng() % 5);
+        std::vector<Turns::Member> m(N);
+        std::vector<Turns::Need> need(N);
+        for (int i = 0; i < N; ++i) {
+            m[i].stream = (int)(rng() % 5);
+            if (rng() % 4) {
+                need[i].cus = kCus;
+                need[i].clusters = 1 + (int)(rng() % 4);
+                need[i].least = 1 + (int)(rng() % (seed % 2 ? 16 : 4));
+                need[i].most = need[i].least + (int)(rng() % 17);
+            }
+            turns.join(&m[i]);
+        }
+        bool bad = false;
+        for (int step = 0; step < 300; ++step) {
+            if (!gpu.all.empty()) for (int k = (int)(rng() % (1 + seed % 4)); k > 0; --k) gpu.finish((int)(rng() % gpu.all.size()));
+            if (rng() % 40 == 0 && seed % 4) for (size_t l = 0; l < gpu.all.size(); ++l) gpu.finish((int)l);
+            const int i = (int)(rng() % N), s = m[i].stream;
+            const bool whole = need[i].least == Turns::kAll || need[i].clusters * need[i].least > kCus;
+            turns.take(&m[i], need[i],
+                [&](Turns::Member *o) { for (int l : gpu.row[o->stream]) if (!gpu.done.count(l)) return false; return true; },
+                [&](Turns::Member *o) { gpu.mark[o] = gpu.row[o->stream].size(); return 0; },
+                [&](Turns::Member *o) {
+                    const auto &r = gpu.row[o->stream];
+                    for (size_t k = 0; k < gpu.mark[o]; ++k) if (!gpu.done.count(r[k])) return false;
+                    return true;
+                },
+                [&](Turns::Member *o) {
+                    ++gpu.events;
+                    auto &b = gpu.behind[s];
+                    b.insert(gpu.row[o->stream].begin(), gpu.row[o->stream].end());
+                    const auto theirs = gpu.behind[o->stream];
+                    b.insert(theirs.begin(), theirs.end());
+                    return 0;
+                },
+                [&](int size) {
+                    const int held = whole ? kCus : std::min(kCus, size * need[i].clusters);
+                    if (!whole) bad = bad || size < need[i].least || size > need[i].most;
+                    // the most that other streams may have running beside it
+                    int sum = 0;
+                    for (const auto &r : gpu.row) {
+                        int most = 0;
+                        if (r.first != s)
+                            for (int l : r.second) if (!gpu.done.count(l) && !gpu.behind[s].count(l)) most = std::max(most, gpu.all[l].held);
+                        sum += most;
+                    }
+                    bad = bad || (sum && sum + held > kCus);
+                    gpu.row[s].push_back((int)gpu.all.size());
+                    gpu.all.push_back({s, held});
+                    return 0;
+                });
+            CHECK(!bad);
+            for (auto &x : m) CHECK(x.runs.size() <= 4);
+        }
+        turns.leave(&m[0]);
+        for (int i = 1; i < N; ++i) for (auto &o : m[i].orders) CHECK(o.of != &m[0]);
+    }
+    // two of 1 to 25 workgroups each: the first is alone, then both have a half, without events in between
+    Turns turns;
+    Turns::Member a, b;
+    a.stream = 1; b.stream = 2;
+    turns.join(&a); turns.join(&b);
+    Turns::Need need{kCus, 1, 1, 25};
+    std::vector<int> sizes;
+    int events = 0;
+    bool idle_now = false;
+    auto go = [&](Turns::Member *me) {
+        turns.take(me, need, [&](Turns::Member *) { return idle_now; }, [](Turns::Member *) { return 0; }, [](Turns::Member *) { return true; },
+                   [&](Turns::Member *) { ++events; return 0; }, [&](int size) { sizes.push_back(size); return 0; });
+    };
+    for (int k = 0; k < 4; ++k) { go(&a); go(&b); }
+    CHECK((sizes == std::vector<int>{25, 7, 16, 16, 16, 16, 16, 16}) && events == 0);
+    // the other one is done: all there is again
+    idle_now = true;
+    sizes.clear();
+    for (int k = 0; k < 2; ++k) go(&a);
+    CHECK(sizes.back() == 25 && events == 0);
+    // no room beside it: behind it, once, and so that its next launch fits
+    need = Turns::Need{kCus, 1, 12, 25};
+    idle_now = false;
+    sizes.clear();
+    for (int k = 0; k < 3; ++k) { go(&b); go(&a); }
+    CHECK((sizes == std::vector<int>{16, 16, 16, 16, 16, 16}) && events == 1);
+    // what cannot share takes turns
+    need = Turns::Need{kCus, 1, 20, 25};
+    for (int k = 0; k < 3; ++k) { go(&b); go(&a); }
+    CHECK(sizes.back() == 20 && events == 7);
+    std::puts("ok");
+}
+"""
+
+
+@pytest.mark.parametrize("program", ["PROGRAM", "SHARED"])
+def test_cluster_launches_are_ordered_across_streams(tmp_path, program):
     src, exe = str(tmp_path / "p.cpp"), str(tmp_path / "p")
     with open(src, "w") as f:
-        f.write(PROGRAM)
+        f.write(globals()[program])
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", "-fsanitize=thread", "-I",
                     os.path.join(ROOT, "paper_2112_13935_amd", "csrc"), "-o", exe, src], check=True)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=120)
@@ -94,3 +219,4 @@ def test_every_cluster_launch_takes_its_turn():
     for launch in ("launch_mlp_round(", "launch_softmax_batch_round(", "launch_lenet_round("):
         at = text.index(launch)
         assert "ctx->clustered([&] {" in text[at - 120:at], launch
+    assert "ctx->clustered(ctx->turn.need, [&](int size) {" in text[text.index("launch_cnn_round(") - 120:text.index("launch_cnn_round(")]

@@ -18,6 +18,10 @@ def softmax_batch(n, d, batch):
     return wl
 
 
+def cnn(n, hw, width, fc, batch, rounds=6):
+    return W.config4(n_clients=n, n_per=60, hw=hw, width=width, fc=fc, batch=batch, rounds=rounds, a=batch, b=2 * batch)
+
+
 MIXES = {
     # clusters of 32 workgroups: one of them fills an XCD
     "two padded MLPs": lambda: [W.config2(n_clients=3, n_total=180, d=784, hidden=250, batch=20, rounds=6, a=20, b=40) for _ in range(2)],
@@ -26,6 +30,11 @@ MIXES = {
     "four engines": lambda: [W.config2(n_clients=5, n_total=300, d=784, hidden=100, batch=20, rounds=6, a=20, b=40),
                              W.config3(n_clients=9, n_per=40, hw=16, batch=20, rounds=4, a=20, b=40),
                              softmax_batch(20, 3072, 50), softmax_batch(9, 400, 20)],
+    # clusters of 5 workgroups, of 1 to 25, of 16 and of 32: beside each other where there is room
+    "small CNNs": lambda: [cnn(3, 12, 6, 18, 5), cnn(8, 16, 16, 64, 1), cnn(2, 8, 16, 64, 16), cnn(1, 16, 16, 64, 32)],
+    "four alike": lambda: [cnn(6, 8, 16, 64, 8, 12) for _ in range(4)],
+    "small CNNs and an MLP": lambda: [cnn(3, 12, 6, 18, 5), cnn(9, 8, 8, 32, 4),
+                                      W.config2(n_clients=8, n_total=480, d=784, hidden=256, batch=16, rounds=6, a=16, b=32)],
 }
 
 
