@@ -12,8 +12,11 @@
 //
 // The memory model promises none of this: a store of workgroup scope may stay invisible to other
 // workgroups.  It holds for this part (gfx950: one L2 per XCD, the L1 written through), which is the only
-// one this library is built for.  Were it not so, no word would be taken for another one (each carries its
-// step's tag): the bounded waits would expire and the error flag would say so.
+// one this library is built for.  Were it not so, no tagged word would be taken for another one: the
+// bounded waits would expire and the error flag would say so.  Not every client of this header is that safe:
+// k_cnn_round also leaves plain words in the L2 (weights, records, partial gradients; put1), and only the barrier
+// behind them is tagged.  They are ordered ahead of it by s_waitcnt vmcnt(0), a store being acknowledged by the
+// L2, and read past the L1; were they not visible then, a peer would go on with old values and nothing would say so.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

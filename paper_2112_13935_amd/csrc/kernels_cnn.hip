@@ -111,6 +111,8 @@ typedef const CnnPlan __attribute__((address_space(4))) ConstantPlan;
 __device__ __forceinline__ unsigned quotient(unsigned n, unsigned div) { return div ? __umulhi(n, div) : n; }
 
 // ---- words that other workgroups of the cluster write or read --------------------------------------
+// They carry no tag: what makes them visible is the cluster's barrier, which waits until the L2 (or, where the cluster
+// is on several XCDs, memory) has acknowledged the workgroup's stores before it posts its tagged word.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float *p, int floats) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, 4 * floats, kBufferFlags);
 }
