@@ -33,12 +33,11 @@
 // All workgroups of a cluster must be resident together: the launcher never puts more on an
 // XCD than it has compute units (cluster_plan.h).  The wait is bounded and raises an error flag
 // instead of hanging (every workgroup still runs to the end).
-#include <type_traits>
-
 #include "aet_device.h"
 #include "aet_internal.h"
 #include "cluster_plan.h"
 #include "cluster_post.h"
+#include "softmax_batch_form.h"
 
 namespace aet {
 
@@ -49,6 +48,7 @@ typedef unsigned long long u64;
 
 constexpr int kSbWaves = 8;
 constexpr int kSbThreads = 64 * kSbWaves;
+static_assert(kSbThreads == kSbRun && kSbWaves == 8, "softmax_batch_form");
 constexpr int kSbClasses = 10;         // the forward part sums two samples' classes as 20 values
 constexpr int kSbC = 12;               // class slots of an exchange record
 static_assert(kSbClasses <= kSbC && kSbC == 12, "softmax_batch_record_words");
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(kSbThreads, 1)
 k_softmax_batch_lanes(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, int D, int C,
                       int HF, int Br, int rec_words, u64 *__restrict__ xrec, u64 *__restrict__ places, int skew, uint32_t tag0, int *__restrict__ errflag) {
     constexpr int Q = kSbQ, T = kSbThreads, NW = kSbWaves;
-    constexpr int GS = BC < 32 ? BC : 32;   // samples whose logits are collected before a store
+    static_assert(BC <= 32, "the samples' logits are collected before one store");
     constexpr int DZ = BC + 4;              // LDS stride of a class row of dz^T
     constexpr int NE = (BC * 16 + T - 1) / T;   // (sample, class) elements per thread
     // the workgroups of a client get ids that land on one XCD
@@ -495,15 +495,14 @@ k_softmax_batch_lanes(const RoundParams *__restrict__ rp, int nhere, int rec0, c
         int lio = li;   // compared where it is needed: 16 masks kept in scalar registers would spill
         asm volatile("" : "+v"(lio));
         // ---- partial logits of the own columns -------------------------------------------------
-#pragma unroll
-        for (int b0 = 0; b0 < BC; b0 += GS) {
+        {
             float res[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < GS / 2; ++c) {
+            for (int c = 0; c < BC / 2; ++c) {
                 float s[2 * kSbClasses];
 #pragma unroll
                 for (int i = 0; i < 2 * kSbClasses; ++i) {
-                    const int o = i % kSbClasses, b = b0 + 2 * c + i / kSbClasses;
+                    const int o = i % kSbClasses, b = 2 * c + i / kSbClasses;
                     s[i] = W[0][o >> 2][o & 3] * x[b][0];
 #pragma unroll
                     for (int j = 1; j < NC; ++j) s[i] += W[j][o >> 2][o & 3] * x[b][j];
@@ -526,12 +525,12 @@ k_softmax_batch_lanes(const RoundParams *__restrict__ rp, int nhere, int rec0, c
                 for (int kk = 0; kk < 5; ++kk) res[kk] = lio == c ? t[kk] : res[kk];
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (li < GS / 2) {
+            if (li < BC / 2) {
                 const int row = lane >> 4, o0 = ((row & 1) << 1) | (row >> 1);
 #pragma unroll
                 for (int kk = 0; kk < 5; ++kk) {
                     const int i = 4 * kk + o0, second = i >= kSbClasses ? 1 : 0;
-                    part[wave][(b0 + 2 * li + second) * kSbLanePS + i - kSbClasses * second] = res[kk];
+                    part[wave][(2 * li + second) * kSbLanePS + i - kSbClasses * second] = res[kk];
                 }
             }
         }
@@ -747,46 +746,29 @@ hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const Round
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
-    // How many runs of 512 columns a workgroup takes at most: more workgroups per client have fewer blocks
-    // each, fewer need no exchange and take more clients per launch.  Microseconds per recursion, with m tiles of 16
-    // samples: 1 + 1.2 m for what does not depend on the columns, 0.5 for an exchange, 0.16 m per block and
-    // wave.  (One workgroup per compute unit is sure to be resident.)
-    const int m = B > 32 ? 4 : B > 16 ? 2 : 1;
-    int best = 0;
-    double least = 0;
-    int resident[4] = {};
-    for (int nc = 1; nc <= (m == 4 ? 2 : 3); ++nc) {
-        const int hf = (D + nc * kSbThreads - 1) / (nc * kSbThreads);
-        resident[nc] = resident_clusters(cus, xcds, hf);
-        const int launches = (nact + resident[nc] - 1) / resident[nc];
-        const int blocks = (((D + 15) / 16 + hf - 1) / hf + kSbWaves - 1) / kSbWaves;
-        const double cost = launches * (1.0 + 1.2 * m + (hf > 1 ? 0.5 : 0.0) + 0.16 * m * blocks);
-        if (best == 0 || cost < least) best = nc, least = cost;
+    const SoftmaxBatchForm f = softmax_batch_form(D, B, nact, cus, xcds);
+    const auto launch = [&](auto kernel) {
+        return sb_launch(kernel, s, prof, dp, nact, f.resident, Wg, D, C, B, f.workgroups, n_clients, scratch, tag0);
+    };
+    if (f.lanes) return launch(f.runs == 1 ? k_softmax_batch_lanes<1, 8> : f.samples == 8 ? k_softmax_batch_lanes<3, 8> : k_softmax_batch_lanes<3, 16>);
+    // (what has fewer than four columns has one run of them)
+#define AET_SB(nc, bc) return launch(f.columns == D_FULL ? k_softmax_batch_round<nc, bc, D_FULL> : k_softmax_batch_round<nc, bc, D_ANY>)
+#define AET_SB_ONE(bc) return launch(f.columns == D_FULL ? k_softmax_batch_round<1, bc, D_FULL> : f.columns == D_ANY ? k_softmax_batch_round<1, bc, D_ANY> : k_softmax_batch_round<1, bc, D_TINY>)
+    switch (f.samples + f.runs) {
+        case 8 + 1: AET_SB_ONE(8);
+        case 8 + 2: AET_SB(2, 8);
+        case 16 + 1: AET_SB_ONE(16);
+        case 16 + 2: AET_SB(2, 16);
+        case 16 + 3: AET_SB(3, 16);
+        case 32 + 1: AET_SB_ONE(32);
+        case 32 + 2: AET_SB(2, 32);
+        case 32 + 3: AET_SB(3, 32);
+        case 64 + 1: AET_SB_ONE(64);
+        case 64 + 2: AET_SB(2, 64);
     }
-    // Mini-batches that fill no more than half of a tile's rows have no use for the matrix cores in the largest
-    // form, nor where a compute unit gets several clients in turn (the lane form leaves registers for two at
-    // once); nor have those of up to 16 whose rows, at odd addresses, come in twice as many pieces as 16-byte loads.
-    // Here / there: mini-batch 8, 400 clients x 1,100 columns 1.31, 192 x 3,072 1.10, 400 x 500 1.14 (100 x 1,100
-    // 0.94); 16, 192 x 3,071 1.09 (192 x 3,072 0.83).
-    const bool odd = D % 4 != 0;
-    if ((best == 3 && (B <= 8 || (B <= 16 && odd))) || (B <= 8 && (nact > cus ? D > 256 : best == 2 && odd && D > 2 * kSbThreads))) {
-        const int wide = D > kSbThreads ? 3 : 1, hf = (D + wide * kSbThreads - 1) / (wide * kSbThreads);
-        const auto kernel = wide == 1 ? k_softmax_batch_lanes<1, 8> : B <= 8 ? k_softmax_batch_lanes<3, 8> : k_softmax_batch_lanes<3, 16>;
-        return sb_launch(kernel, s, prof, dp, nact, resident_clusters(cus, xcds, hf), Wg, D, C, B, hf, n_clients, scratch, tag0);
-    }
-    const int hf = (D + best * kSbThreads - 1) / (best * kSbThreads);
-    const bool full = D == hf * kSbThreads * best;
-#define AET_SB_KERNEL(nc, bc)                                                                     \
-    sb_launch(full ? k_softmax_batch_round<nc, bc, D_FULL> : D >= 4 || nc > 1 ? k_softmax_batch_round<nc, bc, D_ANY> \
-                                                             : k_softmax_batch_round<1, bc, D_TINY>,             \
-              s, prof, dp, nact, resident[best], Wg, D, C, B, hf, n_clients, scratch, tag0)
-#define AET_SB(bc) return best == 1 ? AET_SB_KERNEL(1, bc) : best == 2 ? AET_SB_KERNEL(2, bc) : AET_SB_KERNEL(3, bc)
-    if (B <= 8) AET_SB(8);
-    if (B <= 16) AET_SB(16);
-    if (B <= 32) AET_SB(32);
-    return best == 1 ? AET_SB_KERNEL(1, 64) : AET_SB_KERNEL(2, 64);
-#undef AET_SB_KERNEL
+    return hipErrorInvalidValue;
 #undef AET_SB
+#undef AET_SB_ONE
 }
 
 }  // namespace aet

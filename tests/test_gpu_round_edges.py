@@ -72,19 +72,19 @@ def test_dense_layers_on_the_layer_engine(gpu, oracle_libs, layer_engine, n, d, 
 
 @pytest.mark.parametrize("n,d,batch", [
     (1, 3, 2),           # the smallest: three columns, two samples
-    (3, 512, 8),         # one column per thread, full; mini-batch at its bound
+    (3, 512, 8),         # one run of columns, full; mini-batch at its bound
     (2, 513, 33),        # one column beyond, one sample beyond 32: a cluster of two
-    (3, 1537, 16),       # three columns per thread, one column in the second workgroup
+    (3, 1537, 16),       # one column in the fourth workgroup
     (2, 3072, 64),       # widest and largest: a cluster of six
-    (130, 1600, 20),     # more workgroups (4 x 130) than are resident: three columns per thread
-    (300, 700, 50),      # a cluster of two that takes three launches
+    (130, 1600, 20),     # more workgroups (4 x 130) than are resident: two runs of columns each
+    (300, 700, 50),      # two runs in one workgroup, two launches
     (2, 500, 13),        # one workgroup per client, mini-batches up to 16 and up to 32
     (3, 400, 20),
-    (3, 3000, 29),       # clusters of six, one column per thread
-    (2, 1540, 7),        # three columns per thread, mini-batches up to 8
-    (40, 3072, 20),      # as many clusters of six as the XCDs hold: one column per thread
-    (41, 3072, 20),      # one client more: three columns per thread, clusters of two
-    (43, 3072, 50),      # clusters of six for 40 clients, then for three
+    (3, 3000, 29),       # clusters of six, one run each
+    (2, 1540, 7),        # clusters of four, mini-batches up to 8
+    (40, 3072, 20),      # as many clusters of six as the XCDs hold: one run each
+    (41, 3072, 20),      # one client more: two runs, clusters of three
+    (43, 3072, 50),      # the same with room for 64 samples
 ])
 def test_softmax_mini_batches(gpu, oracle_libs, n, d, batch):
     _lockstep(gpu, _mini_batch_softmax(n, d, batch))
