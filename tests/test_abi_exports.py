@@ -60,7 +60,7 @@ def test_room_for_split_weights_only_where_they_are_used():
     def room(model, clients, plain=0):
         sizes = []
         for variant in (0, 2):
-            lib.aet_test_select_kernels(0, plain)
+            lib.aet_test_select_kernels(1, plain)   # the layer engine, also for the models that do not run on it by default
             lib.aet_test_variants(variant)
             try:
                 sizes.append(lib.aet_workspace_bytes(ctypes.byref(model_desc(model)), clients, 1, 10))

@@ -25,6 +25,8 @@ CASES = {
     "one round": lambda: W.config2(n_clients=4, n_total=200, d=600, hidden=40, batch=20, rounds=1, a=0, b=80),
     "LeNet 16 x 16, mini-batch 16": lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=16, rounds=2, a=16, b=32),
     "LeNet 16 x 16, mini-batch 20": lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=20, rounds=2, a=20, b=40),
+    "small CNN": lambda: W.config4(n_clients=2, n_per=40, hw=8, width=6, fc=20, batch=4, rounds=2, a=4, b=8),
+    # made with that engine asked for
     "layer engine": lambda: W.config4(n_clients=2, n_per=40, hw=8, width=6, fc=20, batch=4, rounds=2, a=4, b=8),
 }
 
@@ -38,17 +40,23 @@ def job(wl, lib):
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_every_replay_is_the_job_on_the_present_data(name):
     import torch
+    from paper_2112_13935_amd import load_library
     from paper_2112_13935_amd.binding import AetSgd
     from paper_2112_13935_amd.runner import Run, upload
     wl = CASES[name]()
     wl.compute_factor = wl.is_straggler = None
     wl.delay_min = wl.delay_max = 0
     X, y = upload(wl)
-    eager = Run(wl, shards=(X, y))
     stream = torch.cuda.Stream()
-    torch.cuda.synchronize()
+    load_library().aet_test_select_kernels(1 if name == "layer engine" else 0, 0)
+    try:
+        eager = Run(wl, shards=(X, y))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            lib = AetSgd(wl.model, X, y, wl.w0, wl.seed, max_inflight=1, max_rounds=wl.rounds, stream=stream, static_workspace=True)
+    finally:
+        load_library().aet_test_select_kernels(0, 0)
     with torch.cuda.stream(stream):
-        lib = AetSgd(wl.model, X, y, wl.w0, wl.seed, max_inflight=1, max_rounds=wl.rounds, stream=stream, static_workspace=True)
         warm = job(wl, lib).clone()      # eager work of this context ahead of the recording
         stream.synchronize()
         graph = torch.cuda.CUDAGraph()

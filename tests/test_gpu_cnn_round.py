@@ -141,7 +141,7 @@ def test_lone_workgroups_with_many_parameters_keep_the_layer_engine(width, launc
     assert _launches(Run(_cnn(257, 8, width, 64, 1, 1))) == launches
 
 
-def test_layer_engine_where_this_round_took_over(oracle_libs):
+def test_layer_engine_where_the_fused_round_took_over(oracle_libs):
     """A shape whose split convolutions end inside their tiles, which without asking runs fused."""
     from oracle import Oracle
     from paper_2112_13935_amd import load_library

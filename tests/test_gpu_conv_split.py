@@ -11,6 +11,15 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def layer_engine():
+    """These are kernels of the layer engine; some of the models run in one launch per round by default."""
+    from paper_2112_13935_amd import load_library
+    load_library().aet_test_select_kernels(1, 0)
+    yield
+    load_library().aet_test_select_kernels(0, 0)
+
+
 def _conv(cout):
     return W.Layer(W.CONV, cout, 3, 1, 1)
 

@@ -324,6 +324,35 @@ def test_config4_reduced_free_running_8_rounds(gpu, oracle_libs):
     run.close()
 
 
+@pytest.fixture
+def layer_engine():
+    """Contexts of one test on the layer engine; the default choice comes back afterwards."""
+    from paper_2112_13935_amd import load_library
+    load_library().aet_test_select_kernels(1, 0)
+    yield
+    load_library().aet_test_select_kernels(0, 0)
+
+
+@pytest.mark.parametrize("name", ["cnn8_factors", "cnn12_six_channels"])
+def test_small_cnns_on_the_layer_engine(gpu, oracle_libs, layer_engine, name):
+    """Models that by default run in one launch per round."""
+    from parity import lockstep
+    wl = small_cases()[name]
+    run, orc = _both(gpu, wl)
+    report(name + ", layer engine", lockstep(wl, run, orc))
+    run.close()
+
+
+@pytest.mark.timeout(900)
+def test_config4_reduced_20_rounds_on_the_layer_engine(gpu, oracle_libs, layer_engine):
+    from parity import lockstep
+    wl = W.config4(n_clients=6, n_per=300, hw=16, width=16, fc=64, batch=16, rounds=20, a=16, b=32)
+    run, orc = _both(gpu, wl)
+    report("config 4 reduced, layer engine (6 clients, 20 rounds, common start per tick)",
+           lockstep(wl, run, orc, resync=True))
+    run.close()
+
+
 @pytest.mark.timeout(900)
 def test_config5_full_clients_20_rounds(gpu, oracle_libs):
     """All 1,024 clients and 3,072 features, the 20 rounds the tolerance is defined on

@@ -124,7 +124,7 @@ def test_lenet_on_the_layer_engine(gpu, oracle_libs, layer_engine, hw, batch):
     (2, 8, 4, 40, 80),     # more samples than the unrolled tiles, still one launch
     (2, 8, 4, 300, 64),    # too wide for it: forward, softmax, backward as launches of their own
 ])
-def test_cnn_last_layer_and_rows(gpu, oracle_libs, n, hw, width, fc, batch):
+def test_cnn_last_layer_and_rows(gpu, oracle_libs, layer_engine, n, hw, width, fc, batch):
     _lockstep(gpu, W.config4(n_clients=n, n_per=90, hw=hw, width=width, fc=fc, batch=batch, rounds=2, a=batch, b=batch))
 
 
@@ -134,7 +134,7 @@ def test_cnn_last_layer_and_rows(gpu, oracle_libs, n, hw, width, fc, batch):
     (6, 16, 16, 16),     # as many backward-data blocks as a launch of both may have
     (7, 16, 16, 32),     # more: one launch each
 ])
-def test_conv_backward_in_one_launch(gpu, oracle_libs, n, hw, width, batch):
+def test_conv_backward_in_one_launch(gpu, oracle_libs, layer_engine, n, hw, width, batch):
     _lockstep(gpu, W.config4(n_clients=n, n_per=50, hw=hw, width=width, fc=20, batch=batch, rounds=2, a=0, b=batch))
 
 
