@@ -322,7 +322,7 @@ struct aet_ctx {
     template <class Launch>
     hipError_t clustered(const ClusterTurns<hipStream_t>::Need &need, Launch launch) {
         using Member = ClusterTurns<hipStream_t>::Member;
-        if (!turn.among || stream_is_capturing(stream)) return launch(need.most);
+        if (!turn.among || stream_is_capturing(stream)) return launch({need.most, -1});
         const auto done = [](hipError_t e) {
             if (e == hipErrorNotReady) (void)hipGetLastError();   // an answer, not an error of the launch that follows
             return e == hipSuccess;
@@ -340,7 +340,7 @@ struct aet_ctx {
     }
     template <class Launch>
     hipError_t clustered(Launch launch) {
-        return clustered(ClusterTurns<hipStream_t>::Need(), [&](int) { return launch(); });
+        return clustered(ClusterTurns<hipStream_t>::Need(), [&](const ClusterTurns<hipStream_t>::Place &) { return launch(); });
     }
     std::string err;
     Profiler prof;
@@ -556,7 +556,8 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     if (e == hipSuccess && ctx->engine == ENGINE_CNN)
         e = cnn_prepare(ctx->stream, ctx->lay, ctx->L, ctx->B, ctx->ws + ctx->lo.fused, n_clients);
     if (e == hipSuccess && ctx->engine == ENGINE_CNN)
-        e = cnn_cluster_need(ctx->lay, ctx->L, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.clusters, &ctx->turn.need.least, &ctx->turn.need.most);
+        e = cnn_cluster_need(ctx->lay, ctx->L, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.least, &ctx->turn.need.most);
+    ctx->turn.need.clients = n_clients;
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
         e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0
@@ -716,9 +717,9 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
                                           ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
             }));
         } else if (ctx->engine == ENGINE_CNN) {
-            AET_HIP(ctx, ctx->clustered(ctx->turn.need, [&](int size) {
+            AET_HIP(ctx, ctx->clustered(ctx->turn.need, [&](const ClusterTurns<hipStream_t>::Place &place) {
                 return launch_cnn_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, ctx->lay, ctx->L, ctx->B,
-                                        ctx->ws + ctx->lo.fused, ctx->n, size, &ctx->epoch);
+                                        ctx->ws + ctx->lo.fused, ctx->n, place.size, place.first, &ctx->epoch);
             }));
         } else {
             AET_HIP(ctx, launch_begin_round(ctx->stream, ctx->profp(), dp, nact, start, ctx->P));

@@ -233,9 +233,10 @@ const int *lenet_error_flag_ptr(void *scratch, int n_clients, int B);
 bool cnn_round_pays(const LayerGeom *lay, int L, int B, int n_clients);   // supported, and faster than the layer engine
 size_t cnn_round_scratch_bytes(const LayerGeom *lay, int L, int n_clients, int B);
 hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m, const float *Wg,
-                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, int size, uint32_t *epoch);
-// Compute units of an XCD, clusters there, workgroups of a cluster: the fewest (the ones that take samples) and as many as help
-hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, int *cus, int *clusters, int *least, int *most);
+                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, int size, int first, uint32_t *epoch);
+// Compute units of an XCD (0: there are not eight, or they are not to be shared), workgroups of a cluster: the fewest (the
+// ones that take samples) and as many as help
+hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, int *cus, int *least, int *most);
 hipError_t cnn_prepare(hipStream_t s, const LayerGeom *lay, int L, int B, void *scratch, int n_clients);   // once, ahead of the first launch
 const int *cnn_error_flag_ptr(void *scratch, int n_clients);
 

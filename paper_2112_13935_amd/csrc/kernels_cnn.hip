@@ -12,18 +12,20 @@
 //          workgroups of the cluster in equal shares, in a fixed order (workgroups, samples ascending).
 // Two barriers of the cluster separate the two (tagged words, as in the other fused rounds).
 //
-// What bounds it: the chain of one sample, about a dozen steps (a layer each way) with a barrier of the
-// workgroup between them.  A step of a small layer is some 4,000 clocks of scalar and address work, LDS
+// What bounds it: the chain of one sample, a step for each layer each way (eight for four convolutions) with a barrier of
+// the workgroup between them.  A step of a small layer is some 4,000 clocks of scalar and address work, LDS
 // latency and its epilogue, in a large one the fp32 matrix instructions (32 clocks each) take
 // as much again; the two barriers of the cluster and three trips through L2 (weights, dense layers,
-// gradients) are a quarter of a recursion.  The layer engine spends 13 - 15 launches on a recursion, each
-// a launch boundary and two to four dependent trips through memory.  16 x 16 half-width CNN, 6 clients with
-// compute factors, mini-batch 16, 6 rounds: 5.42 -> 3.33 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch
+// gradients) are a quarter of a recursion.  Of its 130 K clocks (16 x 16 half-width CNN, mini-batch 16): forward 33 K,
+// backward-data 37 K, filter gradients 26 K, dense layers and softmax 19 K, update and barriers 13 K.  The layer
+// engine spends 13 - 15 launches on a recursion, each a launch boundary and two to four dependent trips through memory.
+// 6 clients of that CNN with compute factors, 6 rounds: 5.93 -> 3.65 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch
 // 5, 6 rounds: 1.94 -> 0.86 ms.  Sixteen waves of 128 registers: eight of 256 took 10 - 30 % longer in the
 // products, which wait for LDS.  One body for both directions of the convolutions, and steps worked out by the
 // host: with each form written out the kernel had 84 KB of code, more than the instruction cache
 // holds, and took 1.7 times as long.  The update by whole waves, filters and dense layers side by side
-// and not one after the other: 14.5 -> 9.2 K clocks of a recursion's 138 K.
+// and not one after the other: 14.5 -> 9.2 K clocks.  Workgroups without samples of their own help with the update (one
+// sample per recursion: 105 -> 59 us); how many there are is the launch's to say, and no sum depends on it.
 //
 // Layout of a map in LDS: a plane per channel, rows of W + 1 floats of which the first is zero (left
 // edge of its row and right edge of the one before), a row of zeros above and below.  So every tap of a
@@ -281,12 +283,14 @@ __device__ __forceinline__ void clear_edges(float *lds, int base, int pl, int pl
 }
 
 __global__ void __launch_bounds__(kCnThreads, 1)
-k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, const float *Wg, const CnnPlan *plan, float *scratch, u64 *words,
-            u64 *places, int skew, uint32_t tag0, int *errflag) {
+k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, int first, const float *Wg, const CnnPlan *plan, float *scratch, u64 *words,
+            u64 *places, u64 *claims, int skew, uint32_t tag0, int *errflag) {
     const ConstantPlan &g = *(const ConstantPlan *)plan;   // read with scalar loads
     extern __shared__ __attribute__((aligned(16))) float lds[];
     uint8_t *const lds8 = reinterpret_cast<uint8_t *>(lds);
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    // Workgroups with ids equal modulo 8 share an XCD; which one begins differs from queue to queue.  Where the launch has
+    // to know (others are beside it), client 0 is on XCD `first` and the workgroup asks where it is.
+    const int xcd = (first < 0 ? (int)blockIdx.x : xcc_id() - first) & 7, slot = blockIdx.x >> 3;
     const int who = (slot / G) * 8 + xcd, me = slot % G;   // client of the launch, workgroup of its cluster
     if (who >= nact) return;
     const RoundParams p = rp[who];
@@ -294,7 +298,20 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, const float *Wg
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     bool dead = false;
     u64 *const place = places ? places + (size_t)p.client * kPlaces : nullptr;
-    cluster_announce(place, me, tag0, skew);
+    if (first < 0) {
+        cluster_announce(place, me, tag0, skew);
+    } else {
+        // the same word, and a claim: a second workgroup in this place, should the ids not go round the XCDs, goes
+        if (tid == 0) {
+            const u64 word = ((u64)tag0 << 32) | (unsigned)(xcc_id() + (me == 0 ? skew : 0));
+            const u64 was = __hip_atomic_exchange(claims + (size_t)p.client * kPlaces + me, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lds[0] = (uint32_t)(was >> 32) == tag0 ? 1.f : 0.f;
+        }
+        __syncthreads();
+        const bool taken = lds[0] != 0.f;
+        __syncthreads();
+        if (taken) return;
+    }
 
     float *const mine = scratch + (size_t)p.client * g.client_floats;   // the client's scratch memory
     const gf_ptr U = as_global(p.U);
@@ -1097,7 +1114,7 @@ const int *cnn_error_flag_ptr(void *scratch, int n_clients) {
     return reinterpret_cast<const int *>(static_cast<u64 *>(scratch) + cnn_words(n_clients));
 }
 
-hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, int *cus, int *clusters, int *least, int *most) {
+hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, int *cus, int *least, int *most) {
     CnnPlan g;
     if (!cnn_plan(lay, L, B, n_clients, &g)) return hipErrorInvalidValue;
     int dev = 0, all = 0, xcds = 0;
@@ -1105,18 +1122,17 @@ hipError_t cnn_cluster_need(const LayerGeom *lay, int L, int B, int n_clients, i
     if (e == hipSuccess) e = hipDeviceGetAttribute(&all, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
-    *cus = all / xcds;
-    *clusters = (n_clients + xcds - 1) / xcds;
+    *cus = xcds == 8 ? all / xcds : 0;
     *least = g.A;
     *most = g.G;
     return hipSuccess;
 }
 
 hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp, int nact, int max_m, const float *Wg,
-                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, int size, uint32_t *epoch) {
+                            const LayerGeom *lay, int L, int B, void *scratch, int n_clients, int size, int first, uint32_t *epoch) {
     if (nact <= 0) return hipSuccess;
     CnnPlan g;
-    if (!cnn_plan(lay, L, B, n_clients, &g) || size < g.A || size > g.G) return hipErrorInvalidValue;
+    if (!cnn_plan(lay, L, B, n_clients, &g) || size < g.A || size > g.G || first > 7) return hipErrorInvalidValue;
     const size_t lds = (size_t)g.lds_floats * 4;
     int dev = 0, cus = 0, per_cu = 0, sized = 0, xcds = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1154,7 +1170,7 @@ hipError_t launch_cnn_round(hipStream_t s, Profiler *prof, const RoundParams *dp
         const int here = nact - a0 < per_launch ? nact - a0 : per_launch;
         const unsigned grid = (unsigned)(8 * ((here + 7) / 8) * size);
         if (prof && prof->on[F_CNN_ROUND]) prof->before(F_CNN_ROUND, s);
-        k_cnn_round<<<grid, kCnThreads, lds, s>>>(dp + a0, here, size, Wg, plan, data, words, places, g_xcd_skew, tag0, errflag);
+        k_cnn_round<<<grid, kCnThreads, lds, s>>>(dp + a0, here, size, first, Wg, plan, data, words, places, all_places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_CNN_ROUND]) prof->after(F_CNN_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -93,21 +93,22 @@ SHARED = r"""
 #define CHECK(x) do { if (!(x)) { std::printf("failed: %s (line %d)\n", #x, __LINE__); return 1; } } while (0)
 using Turns = aet::ClusterTurns<int>;
 constexpr int kCus = 32;
-struct Launch { int stream, held; };
+using Held = Turns::Held;
+struct Launch { int stream; Held held; };
 struct Gpu {
     std::vector<Launch> all;
     std::map<int, std::vector<int>> row;        // stream -> its launches
     std::map<int, std::set<int>> behind;        // stream -> launches its next one is ordered behind
     std::set<int> done;
     std::map<Turns::Member *, size_t> mark;     // launches of the stream ahead of the latest mark
-    int events = 0;
     bool finish(int l) {                        // if all before it are done
         for (int k : row[all[l].stream]) if (k < l && !done.count(k)) return false;
         return done.insert(l).second;
     }
 };
 int main() {
-    for (int seed = 1; seed <= 60; ++seed) {
+    int beside = 0;
+    for (int seed = 1; seed <= 80; ++seed) {
         std::mt19937 rng(seed);
         Turns turns;
         Gpu gpu;
@@ -118,9 +119,9 @@ int main() {
             m[i].stream = (int)(rng() % 5);
             if (rng() % 4) {
                 need[i].cus = kCus;
-                need[i].clusters = 1 + (int)(rng() % 4);
+                need[i].clients = 1 + (int)(rng() % (seed % 3 ? 8 : 30));
                 need[i].least = 1 + (int)(rng() % (seed % 2 ? 16 : 4));
-                need[i].most = need[i].least + (int)(rng() % 17);
+                need[i].most = std::max(need[i].least, kCus / ((need[i].clients + 7) / 8) - (int)(rng() % 4));
             }
             turns.join(&m[i]);
         }
@@ -128,8 +129,8 @@ int main() {
         for (int step = 0; step < 300; ++step) {
             if (!gpu.all.empty()) for (int k = (int)(rng() % (1 + seed % 4)); k > 0; --k) gpu.finish((int)(rng() % gpu.all.size()));
             if (rng() % 40 == 0 && seed % 4) for (size_t l = 0; l < gpu.all.size(); ++l) gpu.finish((int)l);
-            const int i = (int)(rng() % N), s = m[i].stream;
-            const bool whole = need[i].least == Turns::kAll || need[i].clusters * need[i].least > kCus;
+            const int i = (int)(rng() % N), s = m[i].stream, there = (need[i].clients + 7) / 8;
+            const bool whole = need[i].cus == 0 || there * need[i].least > kCus;
             turns.take(&m[i], need[i],
                 [&](Turns::Member *o) { for (int l : gpu.row[o->stream]) if (!gpu.done.count(l)) return false; return true; },
                 [&](Turns::Member *o) { gpu.mark[o] = gpu.row[o->stream].size(); return 0; },
@@ -139,25 +140,33 @@ int main() {
                     return true;
                 },
                 [&](Turns::Member *o) {
-                    ++gpu.events;
                     auto &b = gpu.behind[s];
                     b.insert(gpu.row[o->stream].begin(), gpu.row[o->stream].end());
                     const auto theirs = gpu.behind[o->stream];
                     b.insert(theirs.begin(), theirs.end());
                     return 0;
                 },
-                [&](int size) {
-                    const int held = whole ? kCus : std::min(kCus, size * need[i].clusters);
-                    if (!whole) bad = bad || size < need[i].least || size > need[i].most;
+                [&](const Turns::Place &p) {
+                    Held held{};
+                    if (whole) held.fill(kCus);
+                    else if (p.first < 0) held.fill(std::min(kCus, there * p.size));   // wherever it begins
+                    else for (int c = 0; c < need[i].clients; ++c) held[(p.first + c) % 8] += p.size;
+                    if (!whole) bad = bad || p.size < need[i].least || p.size > need[i].most || p.first > 7;
                     // the most that other streams may have running beside it
-                    int sum = 0;
+                    Held sum{};
                     for (const auto &r : gpu.row) {
-                        int most = 0;
+                        Held most{};
                         if (r.first != s)
-                            for (int l : r.second) if (!gpu.done.count(l) && !gpu.behind[s].count(l)) most = std::max(most, gpu.all[l].held);
-                        sum += most;
+                            for (int l : r.second) if (!gpu.done.count(l) && !gpu.behind[s].count(l))
+                                for (int x = 0; x < 8; ++x) most[x] = std::max(most[x], gpu.all[l].held[x]);
+                        for (int x = 0; x < 8; ++x) sum[x] += most[x];
                     }
-                    bad = bad || (sum && sum + held > kCus);
+                    bool any = false;
+                    for (int x = 0; x < 8; ++x) {
+                        bad = bad || (sum[x] && held[x] && sum[x] + held[x] > kCus);
+                        any = any || sum[x];
+                    }
+                    beside += any;
                     gpu.row[s].push_back((int)gpu.all.size());
                     gpu.all.push_back({s, held});
                     return 0;
@@ -168,36 +177,59 @@ int main() {
         turns.leave(&m[0]);
         for (int i = 1; i < N; ++i) for (auto &o : m[i].orders) CHECK(o.of != &m[0]);
     }
-    // two of 1 to 25 workgroups each: the first is alone, then both have a half, without events in between
-    Turns turns;
-    Turns::Member a, b;
-    a.stream = 1; b.stream = 2;
-    turns.join(&a); turns.join(&b);
-    Turns::Need need{kCus, 1, 1, 25};
-    std::vector<int> sizes;
+    CHECK(beside > 1000);
+    std::vector<Turns::Place> places;
     int events = 0;
     bool idle_now = false;
-    auto go = [&](Turns::Member *me) {
+    auto go = [&](Turns &turns, Turns::Member *me, const Turns::Need &need) {
         turns.take(me, need, [&](Turns::Member *) { return idle_now; }, [](Turns::Member *) { return 0; }, [](Turns::Member *) { return true; },
-                   [&](Turns::Member *) { ++events; return 0; }, [&](int size) { sizes.push_back(size); return 0; });
+                   [&](Turns::Member *) { ++events; return 0; }, [&](const Turns::Place &p) { places.push_back(p); return 0; });
     };
-    for (int k = 0; k < 4; ++k) { go(&a); go(&b); }
-    CHECK((sizes == std::vector<int>{25, 7, 16, 16, 16, 16, 16, 16}) && events == 0);
-    // the other one is done: all there is again
-    idle_now = true;
-    sizes.clear();
-    for (int k = 0; k < 2; ++k) go(&a);
-    CHECK(sizes.back() == 25 && events == 0);
-    // no room beside it: behind it, once, and so that its next launch fits
-    need = Turns::Need{kCus, 1, 12, 25};
-    idle_now = false;
-    sizes.clear();
-    for (int k = 0; k < 3; ++k) { go(&b); go(&a); }
-    CHECK((sizes == std::vector<int>{16, 16, 16, 16, 16, 16}) && events == 1);
-    // what cannot share takes turns
-    need = Turns::Need{kCus, 1, 20, 25};
-    for (int k = 0; k < 3; ++k) { go(&b); go(&a); }
-    CHECK(sizes.back() == 20 && events == 7);
+    auto sizes = [&] { std::vector<int> v; for (auto &p : places) v.push_back(p.size); places.clear(); return v; };
+    using V = std::vector<int>;
+    {   // two on all XCDs, of 1 to 25 workgroups a cluster: the first is alone, then both have a half, without events in between
+        Turns turns;
+        Turns::Member a, b;
+        a.stream = 1; b.stream = 2;
+        turns.join(&a); turns.join(&b);
+        Turns::Need need{kCus, 8, 1, 25};
+        for (int k = 0; k < 4; ++k) { go(turns, &a, need); go(turns, &b, need); }
+        CHECK((sizes() == V{25, 7, 16, 16, 16, 16, 16, 16}) && events == 0);
+        // the other one is done: all there is again
+        idle_now = true;
+        for (int k = 0; k < 3; ++k) go(turns, &a, need);
+        CHECK((sizes() == V{16, 25, 25}) && events == 0);
+        // no room beside it: behind it, once, and so that its next launch fits
+        need.least = 12;
+        idle_now = false;
+        for (int k = 0; k < 3; ++k) { go(turns, &b, need); go(turns, &a, need); }
+        CHECK((sizes() == V{16, 16, 16, 16, 16, 16}) && events == 1);
+        // what cannot share takes turns
+        need.least = 20;
+        for (int k = 0; k < 3; ++k) { go(turns, &b, need); go(turns, &a, need); }
+        CHECK(sizes().back() == 20 && events == 7);
+    }
+    {   // one client each: an XCD each
+        Turns turns;
+        Turns::Member m[8];
+        for (int i = 0; i < 8; ++i) { m[i].stream = i; turns.join(&m[i]); }
+        events = 0;
+        for (int k = 0; k < 3; ++k) for (auto &x : m) go(turns, &x, {kCus, 1, 32, 32});
+        std::set<int> firsts;
+        for (size_t k = 0; k < places.size(); ++k) {
+            CHECK(places[k].size == 32 && places[k].first == places[k % 8].first);
+            firsts.insert(places[k].first);
+        }
+        CHECK(firsts.size() == 8 && *firsts.begin() == 0 && events == 0);
+    }
+    {   // alone: wherever the queue begins
+        Turns turns;
+        Turns::Member a;
+        turns.join(&a);
+        places.clear();
+        go(turns, &a, {kCus, 3, 5, 25});
+        CHECK(places[0].first == -1 && places[0].size == 25);
+    }
     std::puts("ok");
 }
 """
@@ -219,4 +251,4 @@ def test_every_cluster_launch_takes_its_turn():
     for launch in ("launch_mlp_round(", "launch_softmax_batch_round(", "launch_lenet_round("):
         at = text.index(launch)
         assert "ctx->clustered([&] {" in text[at - 120:at], launch
-    assert "ctx->clustered(ctx->turn.need, [&](int size) {" in text[text.index("launch_cnn_round(") - 120:text.index("launch_cnn_round(")]
+    assert "ctx->clustered(ctx->turn.need, [&](const ClusterTurns<hipStream_t>::Place &place) {" in text[text.index("launch_cnn_round(") - 120:text.index("launch_cnn_round(")]

@@ -33,9 +33,60 @@ MIXES = {
     # clusters of 5 workgroups, of 1 to 25, of 16 and of 32: beside each other where there is room
     "small CNNs": lambda: [cnn(3, 12, 6, 18, 5), cnn(8, 16, 16, 64, 1), cnn(2, 8, 16, 64, 16), cnn(1, 16, 16, 64, 32)],
     "four alike": lambda: [cnn(6, 8, 16, 64, 8, 12) for _ in range(4)],
+    # an XCD each
+    "single clients": lambda: [cnn(1, 16, 16, 64, 32) for _ in range(3)] + [cnn(1, 8, 16, 64, 24), cnn(1, 12, 6, 18, 5)],
     "small CNNs and an MLP": lambda: [cnn(3, 12, 6, 18, 5), cnn(9, 8, 8, 32, 4),
                                       W.config2(n_clients=8, n_total=480, d=784, hidden=256, batch=16, rounds=6, a=16, b=32)],
 }
+
+
+@pytest.mark.parametrize("mode,variants", [(2, 0), (0, 1)])
+def test_contexts_beside_each_other_by_the_other_ways_of_exchange(mode, variants):
+    """Words through memory, without asking and because one workgroup of each client names another XCD, with the XCD of
+    the first client given: the bits of a context that is alone."""
+    import torch
+    from paper_2112_13935_amd import load_library
+    from paper_2112_13935_amd.binding import AetSgd
+    from paper_2112_13935_amd.runner import upload
+    lib = load_library()
+
+    def job(ctx, wl):
+        ctx.aet_reset()
+        ctx.aet_run_ticks(wl.a, wl.b, wl.rounds, wl.eta0, wl.beta, wl.power, wl.agg_scale)
+        return ctx.aet_get_weights_device(-1)
+    jobs = []
+    for n in (1, 3, 2):
+        wl = cnn(n, 8, 5, 12, 5)
+        X, y = upload(wl)
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            ctx = AetSgd(wl.model, X, y, wl.w0, wl.seed, max_inflight=1, max_rounds=wl.rounds, stream=stream)
+            alone = None if jobs else job(ctx, wl).clone()
+        torch.cuda.synchronize()
+        jobs.append((ctx, wl, stream, alone))
+    lib.aet_test_select_kernels(mode, 0)
+    lib.aet_test_variants(variants)
+    try:
+        out = []
+        for ctx, wl, stream, _ in jobs + jobs:
+            with torch.cuda.stream(stream):
+                out.append(job(ctx, wl))
+        torch.cuda.synchronize()
+        for ctx, *_, alone in jobs:   # (what the last round that asked found: the first context's was before)
+            assert ctx.aet_test_one_xcd_clients() == (1 if mode and alone is not None else 0)
+    finally:
+        lib.aet_test_select_kernels(0, 0)
+        lib.aet_test_variants(0)
+    assert torch.equal(out[0], jobs[0][3])
+    for a, b in zip(out[:3], out[3:]):
+        assert torch.equal(a, b) and torch.isfinite(a).all()
+    with torch.cuda.stream(jobs[0][2]):      # and as usual again
+        job(jobs[0][0], jobs[0][1])
+        assert jobs[0][0].aet_test_one_xcd_clients() == 1
+    for ctx, *_ in jobs:
+        ctx.aet_synchronize()
+        ctx.aet_destroy()
 
 
 @pytest.mark.parametrize("mix", sorted(MIXES))
