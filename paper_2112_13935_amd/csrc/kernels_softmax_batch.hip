@@ -747,8 +747,9 @@ hipError_t launch_softmax_batch_round(hipStream_t s, Profiler *prof, const Round
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
     const SoftmaxBatchForm f = softmax_batch_form(D, B, nact, cus, xcds);
+    const int resident = resident_clusters(cus, xcds, f.workgroups);
     const auto launch = [&](auto kernel) {
-        return sb_launch(kernel, s, prof, dp, nact, f.resident, Wg, D, C, B, f.workgroups, n_clients, scratch, tag0);
+        return sb_launch(kernel, s, prof, dp, nact, resident, Wg, D, C, B, f.workgroups, n_clients, scratch, tag0);
     };
     if (f.lanes) return launch(f.runs == 1 ? k_softmax_batch_lanes<1, 8> : f.samples == 8 ? k_softmax_batch_lanes<3, 8> : k_softmax_batch_lanes<3, 16>);
     // (what has fewer than four columns has one run of them)

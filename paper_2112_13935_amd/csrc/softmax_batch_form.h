@@ -13,7 +13,6 @@ struct SoftmaxBatchForm {
     int samples;      // room for samples
     int columns;      // tiles: 0 every wave has all its blocks and all columns of them exist, 1 four columns and more, 2 fewer
     int workgroups;   // of a cluster
-    int resident;     // clusters of a launch
 };
 
 // batch: 2 .. 64; clients: of the launch; cus: one workgroup per compute unit is sure to be resident
@@ -45,7 +44,6 @@ inline SoftmaxBatchForm softmax_batch_form(int D, int batch, int clients, int cu
     f.samples = batch <= 8 ? 8 : batch <= 16 ? 16 : batch <= 32 ? 32 : 64;
     f.workgroups = (D + best * kSbRun - 1) / (best * kSbRun);
     f.columns = lanes ? 0 : D == f.workgroups * kSbRun * best ? 0 : D >= 4 ? 1 : 2;
-    f.resident = resident_clusters(cus, xcds, f.workgroups);
     return f;
 }
 

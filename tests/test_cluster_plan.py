@@ -82,13 +82,13 @@ def test_a_wait_is_no_shorter_where_polls_are_cheap(plan):
     assert plan([(-1, 0, 0)])[0] * 0.26e-6 >= 2.15
 
 
-@pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet"])
+@pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet", "cnn"])
 def test_every_poll_of_a_peer_is_bounded_so(kernel):
     text = open(os.path.join(CSRC, f"kernels_{kernel}.hip")).read()
     assert "gave_up(" in text and "spins" not in text
 
 
-@pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet"])
+@pytest.mark.parametrize("kernel", ["softmax_batch", "mlp", "lenet", "cnn"])
 def test_the_launchers_take_their_clusters_from_the_plan(kernel):
     text = open(os.path.join(CSRC, f"kernels_{kernel}.hip")).read()
     assert "per_launch" in text and "resident_clusters(" in text

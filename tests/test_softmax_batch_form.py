@@ -19,7 +19,7 @@ PROGRAM = r"""
 static std::string form(int n, int D, int B, bool *fits) {
     const auto f = aet::softmax_batch_form(D, B, n, 256, 8);
     // the exchange records are made for a run of columns per workgroup
-    *fits = f.workgroups * f.runs * aet::kSbRun >= D && f.workgroups <= (D + aet::kSbRun - 1) / aet::kSbRun && f.samples >= B && f.resident >= 1;
+    *fits = f.workgroups * f.runs * aet::kSbRun >= D && f.workgroups <= (D + aet::kSbRun - 1) / aet::kSbRun && f.samples >= B;
     return std::string(f.lanes ? "lanes " : "tiles ") + std::to_string(f.runs) + "x" + std::to_string(f.samples) +
            (f.lanes ? "" : f.columns == 0 ? " full" : f.columns == 1 ? " any" : " tiny");
 }
