@@ -9,8 +9,8 @@
 //
 // Per recursion:
 //   - each of the 8 waves owns a contiguous eighth of the input columns: it has loaded its
-//     part of the B sampled rows into registers during the previous recursion, in the
-//     A-operand layout of the forward product;
+//     part of the B sampled rows into registers during the recursions before (two ahead
+//     where the registers hold two mini-batches), in the A-operand layout of the forward product;
 //   - z1 = X W1^T on the matrix cores (fp32 MFMA 16x16x4) straight from those registers,
 //     partial over the wave's columns, summed over the waves through LDS; h = relu(z1 + b1);
 //     the rows are then parked in LDS for the backward product (no workgroup barrier:
@@ -35,9 +35,19 @@
 //
 // Widths and mini-batches that do not fill the 16 x 16 tiles are padded: hidden units beyond H
 // have zero weights, samples beyond the mini-batch repeat its last row with d logits of zero
-// (never a row that was not drawn: it could hold a value that is not finite).  12 clients, 784 ->
-// 100 -> 10, mini-batch 20: 4.8 us per recursion here, 28.7 us as seven launches of the
-// layer-by-layer engine.
+// (never a row that was not drawn: it could hold a value that is not finite).
+//
+// What bounds it: the chain of one recursion, forward product - sum over the waves - (pair exchange) - logits -
+// exchange - softmax - d(hidden) - backward product, four workgroup barriers long; the two large products are a
+// third of it at 784 columns, a tenth at 60.  So the rows are on their way for a whole recursion, which row comes
+// next is worked out by one wave while others have the small products, exchanges take no address arithmetic, and the
+// operands of a small product that are there before its barrier are read ahead of it.  Per job, with the rows one
+// recursion ahead and pieces of odd rows in up to four loads, and now: 16 clients, 784 -> 128, B = 32, 50 rounds 7.28 ->
+// 6.73 ms; 12, 784 -> 100, B = 20 2.00 -> 1.83; 40, 523 -> 240, B = 32 0.75 -> 0.58; 16, 435 -> 34, B = 32 2.88 -> 1.76;
+// 4, 70 -> 239, B = 32 0.48 -> 0.35; 30, 30 -> 16, B = 4 0.66 -> 0.55.  Measured and dropped: everything between the two
+// large products in one wave for 16 samples, four values a lane, with two barriers instead of four: 7.68 ms (a
+// single wave issues an instruction every eight clocks or so, and there are four times as many); all row loads ahead of
+// the backward product: 7.55; two mini-batches ahead with seven tiles a wave: 40 clients, 896 -> 256 3.14 -> 3.47.
 //
 // All workgroups of a client must be resident together: the launcher never puts more
 // working workgroups on an XCD than it holds (cluster_plan.h; 1 per compute unit with this
@@ -53,16 +63,21 @@
 namespace aet {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // where rows begin at any float
+typedef int i2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMlpWaves = 8;         // waves per workgroup (2 per SIMD)
 constexpr int kMlpThreads = 64 * kMlpWaves;
 constexpr int kMlpMaxTPW = 7;        // K tiles (of 16) per wave  => D <= 16*8*7 = 896
 constexpr int kMlpMaxG = 16;         // workgroups per client
-constexpr int kMlpRec = 512;         // 64-bit words per exchange record (B*C <= 512)
+constexpr int kMlpRec = 512;         // 64-bit words per exchange record (B*16 <= 512)
 static_assert(kMlpRec % kLineWords == 0, "whole lines");
 constexpr int kMlpPair = 512;        // 64-bit words per pair record (B*16 <= 512)
 static_assert(kMlpPair % kLineWords == 0, "whole lines");
+constexpr int kRowsWave = 5;         // the wave that works out which rows come next
 constexpr int kMlpHalfTPW = 4;       // K tiles per wave when two workgroups share the columns
+constexpr int kBufferFlags = 0x00020000;   // dword 3 of a raw buffer descriptor for 32-bit untyped accesses
+constexpr int kAgent = 16;           // cache policy of agent scope: a load passes the L1 by, a store goes through to memory
 
 // Hides a value from the optimiser so that addresses derived from it are computed where
 // they are used instead of being kept in registers across the whole recursion loop.
@@ -71,9 +86,45 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
+// The same for a scalar: what follows from it is worked out by scalar instructions where it is used (kept across the loop
+// it would fill the scalar registers, and what is spilled comes back through vector ones).
+__device__ __forceinline__ int opaque_scalar(int x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+// A client's exchange words through a range-checked buffer: the lane's own byte offset never changes, what differs from
+// record to record is a scalar, so that a post or a poll takes no address arithmetic.  The scopes are cluster_post's.
+struct Words {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Words(unsigned long long *p, int n) : r(__builtin_amdgcn_make_buffer_rsrc(p, 0, 8 * n, kBufferFlags)) {}
+    // {value, tag}.  A poll loop needs look_again() in it: to the compiler this is a load like any other
+    __device__ __forceinline__ i2 get(int at, int base) const {
+        return __builtin_bit_cast(i2, __builtin_amdgcn_raw_buffer_load_b64(r, at, base, kAgent));
+    }
+    static __device__ __forceinline__ void look_again() { asm volatile("" ::: "memory"); }
+    __device__ __forceinline__ void post(int at, int base, uint32_t tag, const f4 &v, bool one_xcd) const {   // four neighbours
+        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+        const u4 a = {__float_as_uint(v[0]), tag, __float_as_uint(v[1]), tag}, b = {__float_as_uint(v[2]), tag, __float_as_uint(v[3]), tag};
+        if (one_xcd) {
+            __builtin_amdgcn_raw_buffer_store_b128(a, r, at, base, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(b, r, at + 16, base, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b128(a, r, at, base, kAgent);
+            __builtin_amdgcn_raw_buffer_store_b128(b, r, at + 16, base, kAgent);
+        }
+    }
+    __device__ __forceinline__ void post(int at, int base, uint32_t tag, float v, bool one_xcd) const {
+        typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+        const u2 word = {__float_as_uint(v), tag};
+        if (one_xcd) __builtin_amdgcn_raw_buffer_store_b64(word, r, at, base, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(word, r, at, base, kAgent);
+    }
+};
+
 // sum / max over the 16 lanes of one sample (lanes 16k .. 16k+15 of the wave), with the
 // data-parallel-primitive lane permutations inside a row: neighbours in a quad, the other
 // pair of the quad, the mirrored half row, the mirrored row
@@ -189,31 +240,44 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     float *lossb = Ub2s + 16;         // [B]
     float *lossacc = lossb + B;       // [16], entry 0: the round's loss sum; 1: not zero: the cluster spans XCDs
     int *labs = reinterpret_cast<int *>(lossacc + 16);  // [B]
-    float *Xs = reinterpret_cast<float *>(labs + B); // [B][ld]
+    uint32_t *rows = reinterpret_cast<uint32_t *>(labs + B); // [B]  the rows of recursion u + AHEAD
+    float *Xs = reinterpret_cast<float *>(rows + B); // [B][ld]
 
     const int64_t b1_off = (int64_t)H * D, w2_off = b1_off + H, b2_off = w2_off + (int64_t)C * H;
     const float invB = 1.0f / (float)Br;
 
     // The mini-batch travels global -> registers -> matrix core / LDS in the A-operand layout
     // of the forward product: lane (li, lg) holds, for batch tile bt and K tile tt, the four
-    // values x[16*bt + li][col0 + 16*tt + 4*lg .. +3] (one 16-byte load when FAST: D a
-    // multiple of 16, so every piece is inside the row and aligned).
+    // values x[16*bt + li][col0 + 16*tt + 4*lg .. +3], one 16-byte load.  Where D is no multiple of 16
+    // (not FAST) the last tile's pieces can reach beyond the row's end: such a piece is loaded as far
+    // back as that takes, and put right (tail_piece) when it is used, so that a load has no branches and
+    // nothing waits for it early.  (As up to four guarded 4-byte loads a piece: 40 clients, 523 -> 240, B = 32,
+    // 28.4 K clocks a recursion, 15.7 K of them in the step that issues the loads.)
+    const bool narrow = TPW == 2 && D < 4;        // a row is shorter than a piece: value by value
+    const int tail_tt = !FAST && !narrow && (D & 15) && nt > 0 && tbase + t0 + nt == KTall ? nt - 1 : -1;
+    const int tail_by = max(0, gcol0 + 16 * tail_tt + 4 * lg - (D - 4));   // columns back
     const gcf_ptr lane_src = Xg + gcol0 + 4 * lg;
     // rowp: the lane's piece of tile 0 of its row, lane_src + row * D
-    auto load_piece = [&](gcf_ptr rowp, int tt) -> f4 {
+    auto load_piece = [&](gcf_ptr rowp, int tt, int nt, int tail_tt) -> f4 {
         f4 x = {0.f, 0.f, 0.f, 0.f};
         if (FULL || tt < nt) {
             const gcf_ptr src = rowp + 16 * tt;
             if constexpr (FAST) {
                 x = *reinterpret_cast<const f4 __attribute__((address_space(1))) *>(src);
-            } else {
-                const int col = gcol0 + 16 * tt + 4 * lg;
+            } else if (narrow) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (col + r < D) x[r] = src[r];
+                for (int r = 0; r < 3; ++r)
+                    if (4 * lg + r < D) x[r] = src[r];
+            } else {
+                x = *reinterpret_cast<const f4u __attribute__((address_space(1))) *>(src - (tt == tail_tt ? tail_by : 0));
             }
         }
         return x;
+    };
+    auto tail_piece = [&](f4 &x) {
+        f4 t = tail_by & 1 ? f4{x[1], x[2], x[3], 0.f} : x;
+        t = tail_by & 2 ? f4{t[2], t[3], 0.f, 0.f} : t;
+        x = tail_by & ~3 ? f4{0.f, 0.f, 0.f, 0.f} : t;
     };
 
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL:
@@ -226,18 +290,9 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     f4 W1r[TPW], U1r[TPW];
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-        f4 w = {0.f, 0.f, 0.f, 0.f};
-        if (tt < nt && unit_ok) {
-            const float *src = Wg + (int64_t)unit * D + gcol0 + 16 * tt + 4 * lg;
-            if constexpr (FAST) {   // D a multiple of 16: the four values are one aligned piece
-                w = *reinterpret_cast<const f4 *>(src);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (gcol0 + 16 * tt + 4 * lg + r < D) w[r] = src[r];
-            }
-        }
-        W1r[tt] = w;
+        f4 w = load_piece(as_global(Wg) + (int64_t)unit * D + gcol0 + 4 * lg, tt, nt, tail_tt);
+        if (tt == tail_tt) tail_piece(w);
+        W1r[tt] = unit_ok ? w : f4{0.f, 0.f, 0.f, 0.f};
         U1r[tt] = f4{0.f, 0.f, 0.f, 0.f};
     }
     {
@@ -256,332 +311,362 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         }
     }
     __syncthreads();
-    // rows of recursion 0 into registers, labels into LDS
-    f4 xreg[NBT][TPW];
+    // Rows of the next recursions in registers, AHEAD sets that take turns (Algorithm 2, sampling step; the
+    // indices are a counter hash, so they are known ahead).  The loads of a recursion are issued in its backward product, the
+    // last step: with one set the next forward product, the first step, waits for them for 1 - 2 K clocks; with
+    // two they have a whole recursion.
+    constexpr int AHEAD = TPW <= kMlpHalfTPW ? 2 : 1;
+    f4 xreg[AHEAD][NBT][TPW];
+    int lab_next = 0, lab_ahead = 0;   // labels of recursions u + 1 and u + AHEAD (of the wave that sees to the rows)
+    auto rows_of = [&](int u) -> uint32_t {
+        return lane < B ? sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * Br + min(lane, Br - 1)), p.n_samples) : 0u;
+    };
 #pragma unroll
-    for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) xreg[bt][tt] = f4{0.f, 0.f, 0.f, 0.f};
-    if (p.m > 0) {
-        uint32_t rowv = 0;
-        if (lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + min(lane, Br - 1)), p.n_samples);
-        if (wave == 0 && lane < B) labs[lane] = yg[rowv];
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) {
-            const gcf_ptr rowp = lane_src + (int64_t)__shfl(rowv, 16 * bt + li) * D;
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) xreg[bt][tt] = load_piece(rowp, tt);
-        }
-    }
-    unsigned long long *rec_base = xrec + (int64_t)(rec0 + a) * 2 * kMlpMaxG * kMlpRec;
-    // pair records [client][unit group][step parity][half][B * 16]
-    unsigned long long *prec_base = prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair;
-    bool dead = false;  // the poll expired: keep going, the host will see the flag
-    // the same answer in all waves (one whose wait expired says no): there are barriers that hang on it
-    if (!cluster_on_one_xcd(places, g * HF + hf, G * HF, tag0, errflag, &dead)) lossacc[1] = 1.f;
-    __syncthreads();
-    const bool one_xcd = __builtin_amdgcn_readfirstlane(lossacc[1] == 0.f);
-
-    auto park_rows = [&]() {
+    for (int k = 0; k < AHEAD; ++k) {
 #pragma unroll
         for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
-            for (int tt = 0; tt < TPW; ++tt)
-                if (FULL || tt < nt)
-                    *reinterpret_cast<f4 *>(Xs + (16 * bt + li) * ld + col0 + 16 * tt + 4 * lg) = xreg[bt][tt];
-    };
-    auto recursions = [&](const auto same) {   // same: whether the words stay in the L2 of one XCD
-        for (int u = 0; u < p.m; ++u) {
-            // ---- z1 partial sums on the matrix cores ----------------------------------------
-            {
-                f4 acc[NBT];
-#pragma unroll
-                for (int bt = 0; bt < NBT; ++bt) acc[bt] = f4{0.f, 0.f, 0.f, 0.f};
-                // the A operand comes straight from the registers the rows were loaded into
-                // (all TPW slots, free of branches: an empty slot holds zeros on both sides; skipping
-                // it measured slower here, while the backward product below gains from skipping)
-#pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int bt = 0; bt < NBT; ++bt) acc[bt] = mfma16(xreg[bt][tt][r], W1r[tt][r], acc[bt]);
-                }
-                // the backward product needs the rows transposed: park them in LDS (this wave's
-                // columns only, so no barrier; the writes drain while the logits are exchanged).
-                // With two workgroups per unit group they are parked between the post and the
-                // poll of the pair exchange instead.
-                if constexpr (HF == 1) park_rows();
-#pragma unroll
-                for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        red[(wave * B + 16 * bt + 4 * lg + r) * 16 + li] = acc[bt][r];
+            for (int tt = 0; tt < TPW; ++tt) xreg[k][bt][tt] = f4{0.f, 0.f, 0.f, 0.f};
+        if (k < p.m) {
+            const uint32_t rowv = rows_of(k);
+            if (wave == kRowsWave && lane < B) {
+                const int lab = yg[rowv];
+                if (k == 0) labs[lane] = lab;
+                else lab_next = lab;
             }
-            __syncthreads();
-            // the rows the next recursion samples (Algorithm 2, sampling step; a counter
-            // hash, so they are known ahead); with two workgroups per unit group the hash is
-            // computed while the pair exchange is in flight
-            uint32_t rowv = 0;
-            const bool more = u + 1 < p.m;
-            auto next_rows = [&]() {
-                if (more && lane < B) rowv = sample_row(p.key, (uint64_t)(p.q0 + (int64_t)(u + 1) * Br + min(lane, Br - 1)), p.n_samples);
-            };
-            // ---- h = relu(z1 + b1) ----------------------------------------------------------
-            const uint32_t tag = tag0 + (uint32_t)u;
-            if constexpr (HF == 1) {
-                for (int i = tid; i < B * 16; i += kMlpThreads) {
-                    float s = b1s[i & 15];
 #pragma unroll
-                    for (int w = 0; w < kMlpWaves; ++w) s += red[w * B * 16 + i];
-                    hs[i] = s > 0.f ? s : 0.f;
-                }
-            } else {
-                // the own half's sums go to the pair record, the other half's come from there;
-                // both halves add them in the same order (half 0 + half 1), so both get the same h
-                unsigned long long *pr = prec_base + (int64_t)(u & 1) * 2 * kMlpPair;
-                const int i = tid;   // B * 16 <= 512 elements, one per thread
-                float own = 0.f;
-                if (i < B * 16) {
+            for (int bt = 0; bt < NBT; ++bt) {
+                const gcf_ptr rowp = lane_src + (int64_t)__shfl(rowv, 16 * bt + li) * D;
 #pragma unroll
-                    for (int w = 0; w < kMlpWaves; ++w) own += red[w * B * 16 + i];
-                    cluster_post(pr + hf * kMlpPair + i, tag, own, same);
+                for (int tt = 0; tt < TPW; ++tt) xreg[k][bt][tt] = load_piece(rowp, tt, nt, tail_tt);
+            }
+        }
+    }
+    // logit records [step parity][unit group][sample][class]
+    const Words rec(xrec + (int64_t)(rec0 + a) * 2 * kMlpMaxG * kMlpRec, 2 * kMlpMaxG * kMlpRec);
+    // pair records [client][unit group][step parity][half][B * 16]
+    const Words pair(prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair, 4 * kMlpPair);
+    int dead = 0;  // not 0: the poll expired: keep going, the host will see the flag (the same for the whole wave)
+    {
+        bool gone = false;
+        // the same answer in all waves (one whose wait expired says no): there are barriers that hang on it
+        if (!cluster_on_one_xcd(places, g * HF + hf, G * HF, tag0, errflag, &gone)) lossacc[1] = 1.f;
+        dead = __any(gone);
+    }
+    __syncthreads();
+    const bool one_xcd = __builtin_amdgcn_readfirstlane(lossacc[1] == 0.f);
+
+    // x: this recursion's rows; their registers take the rows of recursion u + AHEAD
+    auto recursion = [&](int u, f4 (&x)[NBT][TPW], const auto same) __attribute__((always_inline)) {   // same: whether the words stay in the L2 of one XCD
+        const int ntile = opaque_scalar(nt), tail = opaque_scalar(tail_tt);
+        auto park_rows = [&]() {
+#pragma unroll
+            for (int bt = 0; bt < NBT; ++bt)
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt)
+                    if (FULL || tt < ntile)
+                        *reinterpret_cast<f4 *>(Xs + (16 * bt + li) * ld + col0 + 16 * tt + 4 * lg) = x[bt][tt];
+        };
+        if constexpr (!FAST) {
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt)
+                if (tt == tail) {
+#pragma unroll
+                    for (int bt = 0; bt < NBT; ++bt) tail_piece(x[bt][tt]);
                 }
-                park_rows();
-                next_rows();
-                const unsigned long long *theirs = pr + (1 - hf) * kMlpPair + min(i, B * 16 - 1);
-                unsigned long long v = 0;
+        }
+        // ---- z1 partial sums on the matrix cores ----------------------------------------
+        {
+            f4 acc[NBT];
+#pragma unroll
+            for (int bt = 0; bt < NBT; ++bt) acc[bt] = f4{0.f, 0.f, 0.f, 0.f};
+            // The rows come straight from the registers they were loaded into; empty slots are
+            // skipped (us a job with the last slot skipped, and with every one: 16 clients, 784 -> 128 6,980
+            // and 6,950, multiplying zeros 7,110; 16, 435 -> 34 2,000 and 1,860, 2,080; 30, 30 -> 16 625 and 598, 624).
+            // Units are the product's rows and samples its columns here and in the two small products: a lane
+            // has four neighbouring units or classes of one sample, one 16-byte piece.
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt) {
+                if (!FULL && tt >= ntile) break;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int bt = 0; bt < NBT; ++bt) acc[bt] = mfma16(W1r[tt][r], x[bt][tt][r], acc[bt]);
+            }
+            // the backward product needs the rows transposed: park them in LDS (this wave's
+            // columns only, so no barrier; the writes drain while the logits are exchanged).
+            // With two workgroups per unit group they are parked between the post and the
+            // poll of the pair exchange instead.
+            if constexpr (HF == 1) park_rows();
+#pragma unroll
+            for (int bt = 0; bt < NBT; ++bt) *reinterpret_cast<f4 *>(red + (wave * B + 16 * bt + li) * 16 + 4 * lg) = acc[bt];
+        }
+        __syncthreads();
+        const bool more = u + AHEAD < p.m;
+        // ---- h = relu(z1 + b1) ----------------------------------------------------------
+        const uint32_t tag = tag0 + (uint32_t)u;
+        const int par = u & 1;
+        // (addresses are worked out here: kept across the loop they would fill the registers)
+        const int ln = opaque(lane), li = ln & 15, lg = ln >> 4, tid = 64 * wave + ln;
+        const int mt = 16 * wave + li;   // waves 0 .. NBT - 1: the lane's sample in the small products
+        // (threads beyond the B * 16 elements do the last one's sums and keep them to themselves)
+        const int i = min(tid, B * 16 - 1);
+        const bool mine_h = B * 16 >= kMlpThreads || tid < B * 16;
+        float part[kMlpWaves];
+#pragma unroll
+        for (int w = 0; w < kMlpWaves; ++w) part[w] = red[w * B * 16 + i];
+        const float bias1 = b1s[i & 15];
+        f4 w2 = {0.f, 0.f, 0.f, 0.f};   // class li, units 4 lg ..
+        if (wave < NBT) w2 = *reinterpret_cast<const f4 *>(W2s + 16 * li + 4 * lg);
+        __builtin_amdgcn_sched_barrier(0);   // all on their way before the first is added
+        if constexpr (HF == 1) {
+            float s = bias1;
+#pragma unroll
+            for (int w = 0; w < kMlpWaves; ++w) s += part[w];
+            if (mine_h) hs[i] = s > 0.f ? s : 0.f;
+        } else {
+            // the own half's sums go to the pair record, the other half's come from there;
+            // both halves add them in the same order (half 0 + half 1), so both get the same h
+            float own = 0.f;
+#pragma unroll
+            for (int w = 0; w < kMlpWaves; ++w) own += part[w];
+            const int base = 8 * par * 2 * kMlpPair;
+            if (mine_h) pair.post(8 * i, base + 8 * hf * kMlpPair, tag, own, same);
+            __builtin_amdgcn_sched_barrier(0);
+            park_rows();
+            i2 v;
+            BoundedWait wait;
+            for (;;) {
+                Words::look_again();
+                v = pair.get(8 * i, base + 8 * (1 - hf) * kMlpPair);
+                if (__all((uint32_t)v[1] == tag) || dead) break;
+                __builtin_amdgcn_s_sleep(1);
+                if (wait.gave_up(errflag)) dead = 1;
+            }
+            const int got = v[0];
+            const float other = __builtin_bit_cast(float, got);
+            const float s = bias1 + (hf == 0 ? own + other : other + own);
+            if (mine_h) hs[i] = s > 0.f ? s : 0.f;
+        }
+        __syncthreads();
+        // ---- partial logits of the own 16 units -> tagged exchange record ---------------
+        const int recpar = 8 * par * kMlpMaxG * kMlpRec;
+        f4 h = {0.f, 0.f, 0.f, 0.f};   // sample mt, units 4 lg ..
+        if (wave < NBT) {
+            h = *reinterpret_cast<const f4 *>(hs + 16 * mt + 4 * lg);
+            if (hf == 0) {
+                f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc = mfma16(w2[s], h[s], acc);
+                if (4 * lg < C) rec.post(8 * (16 * mt + 4 * lg), recpar + 8 * g * kMlpRec, tag, acc, same);
+            }
+        }
+        // ---- logits, softmax, d logits: thread (b, o) = (tid / 16, tid % 16) ------------
+        // Every thread polls the G tagged words of its own element (b, o): with the
+        // words in the XCD's L2 an exchange is then one trip.  Polls through memory slow the peers'
+        // stores down (they meet in the same memory channels): there, while the peers are still
+        // computing, only wave 0 looks, and only at one word per record and batch tile (the last one
+        // its owner stores).  The element tags are still checked, and the fetch repeated if one is
+        // stale.  (A separate flag word per poster, stored after the logits, overtakes them on the
+        // way.)  16 clients, 784 -> 128, 50 rounds: in L2 7.61 ms with the watch, 7.47 without;
+        // through memory 8.9 and 12.1.
+        if (!same) {
+            if (wave == 0) {
+                // lane -> (record, batch tile); the word of sample 16*bt+15, class C-1
+                const int gg = lane % G, bt = lane / G;
+                const int at = 8 * (gg * kMlpRec + (16 * min(bt, NBT - 1) + 15) * 16 + (C - 1));
                 BoundedWait wait;
                 for (;;) {
-                    v = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (__all((uint32_t)(v >> 32) == tag) || dead) break;
-                    __builtin_amdgcn_s_sleep(1);
-                    if (wait.gave_up(errflag)) dead = true;
-                }
-                if (i < B * 16) {
-                    const float other = __uint_as_float((uint32_t)v);
-                    const float s = b1s[i & 15] + (hf == 0 ? own + other : other + own);
-                    hs[i] = s > 0.f ? s : 0.f;
+                    Words::look_again();
+                    const bool ok = bt >= NBT || (uint32_t)rec.get(at, recpar)[1] == tag;
+                    if (__all(ok) || dead) break;
+                    __builtin_amdgcn_s_sleep(2);
+                    if (wait.gave_up(errflag)) dead = 1;
                 }
             }
             __syncthreads();
-            // ---- partial logits of the own 16 units -> tagged exchange record ---------------
-            unsigned long long *rec = rec_base + (int64_t)(u & 1) * kMlpMaxG * kMlpRec;
-            if (wave < NBT && hf == 0) {
-                const int bt = wave;
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
+        }
+        float w2t[4];   // unit li, classes 4 lg ..
+        if (wave < 4 * NBT) {
+            const int b = tid >> 4, o = tid & 15;
+            const int at = 8 * (16 * b + min(o, C - 1));
+            const float bias2 = b2s[o];
+            const int lab = labs[b];
+            if (wave < NBT) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc = mfma16(hs[(16 * bt + li) * 16 + 4 * s + lg], W2s[li * 16 + 4 * s + lg], acc);
-                if (li < C) {
+                for (int s = 0; s < 4; ++s) w2t[s] = W2s[(4 * lg + s) * 16 + li];
+            }
+            float z;
+            BoundedWait wait;
+            const int Gn = opaque_scalar(G);
+            // all records at once, as many as there are at most; those beyond the last stand for it
+            auto fetch = [&](auto most) __attribute__((always_inline)) {
+                constexpr int GC = decltype(most)::value;
+                i2 v[GC];
+                Words::look_again();
+#pragma unroll
+                for (int gg = 0; gg < GC; ++gg) v[gg] = rec.get(at, recpar + 8 * min(gg, Gn - 1) * kMlpRec);
+                __builtin_amdgcn_sched_barrier(0);
+                uint32_t stale = 0;
+                z = bias2;
+#pragma unroll
+                for (int gg = 0; gg < GC; ++gg) {
+                    const int bits = v[gg][0];
+                    stale |= (uint32_t)v[gg][1] ^ tag;
+                    if (gg < Gn) z += __builtin_bit_cast(float, bits);
+                }
+                return __all(stale == 0);
+            };
+            for (;;) {
+                if (Gn <= 4 ? fetch(std::integral_constant<int, 4>{}) : Gn <= 8 ? fetch(std::integral_constant<int, 8>{}) : fetch(std::integral_constant<int, kMlpMaxG>{})) break;
+                if (dead) break;
+                if (!same) __builtin_amdgcn_s_sleep(2);
+                if (wait.gave_up(errflag)) dead = 1;
+            }
+            const float zmax = row16_max(o < C ? z : -3.0e38f);
+            // PAD: expf and logf as in the layer engine, where these models run otherwise
+            const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
+            const float ex = o < C ? exp_of(z - zmax) : 0.f;
+            const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
+            if (o == lab) lossb[b] = lse - z;
+            zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+        }
+        __syncthreads();
+        // ---- small products on the matrix cores -----------------------------------------
+        f4 dW2acc = {0.f, 0.f, 0.f, 0.f};
+        if (wave < NBT) {
+            // dh = (dz W2) * 1[h > 0] for samples 16*wave .. 16*wave+15
+            const f4 dz = *reinterpret_cast<const f4 *>(zs + 16 * mt + 4 * lg);
+            f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = mfma16(w2t[s], dz[s], acc);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = h[r] > 0.f ? acc[r] : 0.f;
+            *reinterpret_cast<f4 *>(dhs + 16 * mt + 4 * lg) = acc;
+        } else if (wave == 2) {
+            // dW2[o][j] = sum_b dz[b][o] h[b][j]; applied after the barrier (W2 is still read)
+            float za[4 * NBT], hb[4 * NBT];
+#pragma unroll
+            for (int s = 0; s < 4 * NBT; ++s) {
+                za[s] = zs[(4 * s + lg) * 16 + li];
+                hb[s] = hs[(4 * s + lg) * 16 + li];
+            }
+#pragma unroll
+            for (int s = 0; s < 4 * NBT; ++s) dW2acc = mfma16(za[s], hb[s], dW2acc);
+        } else if (wave == 3) {
+            // second-layer bias: column sums of dz
+            const float s = col_sum16<B>(zs, lane) * invB;
+            if (lane < C) {
+                b2s[lane] -= p.eta * s;
+                Ub2s[lane] += s;
+            }
+        } else if (wave == 4) {
+            // the recursion's mean loss
+            const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
+            if (lane == 0) lossacc[0] += s * invB;
+        } else if (wave == kRowsWave && more) {
+            // the rows that recursion u + AHEAD samples, for all waves, and their labels
+            const uint32_t row = rows_of(u + AHEAD);
+            if (lane < B) {
+                rows[lane] = row;
+                lab_ahead = yg[row];
+            }
+        }
+        __syncthreads();
+        // The row loads are issued a few at a time between the first tiles of the backward product, so that a wave
+        // that has to wait for room in the memory pipeline leaves the matrix core to the SIMD's other
+        // wave.  They go into the registers the forward product has finished with.  (Loads of one wave return in
+        // order, so nothing is issued before the exchange polls.)
+        gcf_ptr myrow[NBT];
+        if (more) {
+#pragma unroll
+            for (int bt = 0; bt < NBT; ++bt) myrow[bt] = lane_src + (int64_t)rows[16 * bt + li] * D;
+        }
+        constexpr int PFT = TPW > 4 ? 4 : TPW;   // tiles of the backward product that carry loads
+        auto prefetch_load = [&](int j) {        // j = tt * NBT + bt: in the order the forward product uses them
+            // (beyond the last recursion zeros: the rows at work end here on every way, which frees their registers before)
+            f4 piece = {0.f, 0.f, 0.f, 0.f};
+            if (more) piece = load_piece(myrow[j % NBT], j / NBT, ntile, tail);
+            x[j % NBT][j / NBT] = piece;
+        };
+        // ---- second layer and first-layer bias: w <- w - eta g, U <- U + g ---------------
+        if (wave == 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int e = (4 * lg + r) * 16 + li;  // (o, j)
+                const float gv = dW2acc[r] * invB;
+                W2s[e] -= p.eta * gv;
+                U2s[e] += gv;
+            }
+        } else if (wave == 3) {
+            // first-layer bias: column sums of dh
+            const float s = col_sum16<B>(dhs, lane) * invB;
+            if (lane < 16) {
+                b1s[lane] -= p.eta * s;
+                Ub1s[lane] += s;
+            }
+        }
+        // ---- first layer: dW1^T = X^T dh on the matrix cores, update in registers -------
+        {
+            // contraction step s of lane group lg takes sample 16*(s/4) + (s%4) + 4*lg: with
+            // rows 4*lg apart the four lane groups read LDS banks 16 apart (ld = 4 mod 32)
+            float dhb[4 * NBT];
+#pragma unroll
+            for (int s = 0; s < 4 * NBT; ++s) dhb[s] = dhs[(16 * (s >> 2) + (s & 3) + 4 * lg) * 16 + li];
+            float xb[2][4 * NBT];
+            const float *xcol = Xs + opaque(4 * lg * ld + col0 + li);
+            if (FULL || ntile > 0) {
+#pragma unroll
+                for (int s = 0; s < 4 * NBT; ++s) xb[0][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld];
+            }
+            const float eb = p.eta * invB;
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt) {
+                if (tt + 1 < TPW && (FULL || tt + 1 < ntile)) {
+#pragma unroll
+                    for (int s = 0; s < 4 * NBT; ++s) xb[(tt + 1) & 1][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld + 16 * (tt + 1)];
+                }
+                __builtin_amdgcn_sched_barrier(0);   // the next tile's operands are on their way before the products
+                if (FULL || tt < ntile) {
+                    // two independent accumulation chains per tile
+                    // (the first product of each chain takes the constant zero as its addend)
+                    f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], f4{0.f, 0.f, 0.f, 0.f});
+                    f4 acc1 = mfma16(xb[tt & 1][1], dhb[1], f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int s = 2; s < 4 * NBT; s += 2) {
+                        acc0 = mfma16(xb[tt & 1][s], dhb[s], acc0);
+                        acc1 = mfma16(xb[tt & 1][s + 1], dhb[s + 1], acc1);
+                    }
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int b = 16 * bt + 4 * lg + r;
-                        cluster_post(rec + (int64_t)g * kMlpRec + b * C + li, tag, acc[r], same);
+                        const float gsum = acc0[r] + acc1[r];
+                        W1r[tt][r] -= eb * gsum;
+                        U1r[tt][r] += invB * gsum;
                     }
                 }
+                // this tile's share of the row loads
+#pragma unroll
+                for (int j = tt * NI / PFT; j < (tt + 1) * NI / PFT && j < NI; ++j) prefetch_load(j);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            // ---- prefetch the rows of the NEXT recursion into registers ----------------------
-            // (Algorithm 2, sampling step; the indices are a counter hash, so they are
-            // known ahead of time).  Loads of one wave return in order, so nothing is issued
-            // before the exchange poll.
-            int labn = 0;
-            // the rows' indices and the labels now; the row loads themselves are issued a few at
-            // a time between the first tiles of the backward product, so that a wave that has to
-            // wait for room in the memory pipeline leaves the matrix core to the SIMD's other
-            // wave.  They go into the registers the forward product has finished with.
-            gcf_ptr myrow[NBT];
-            auto prefetch_rows = [&]() {
-                if (!more) return;
-                if constexpr (HF == 1) next_rows();
-                if (wave == 0 && lane < B) labn = yg[rowv];
-#pragma unroll
-                for (int bt = 0; bt < NBT; ++bt) myrow[bt] = lane_src + (int64_t)__shfl(rowv, 16 * bt + li) * D;
-            };
-            constexpr int PFT = TPW > 4 ? 4 : TPW;   // tiles of the backward product that carry loads
-            auto prefetch_load = [&](int i) {        // i = tt * NBT + bt: in the order the forward product uses them
-                if (!more) return;
-                xreg[i % NBT][i / NBT] = load_piece(myrow[i % NBT], i / NBT);
-            };
-            // ---- logits, softmax, d logits: thread (b, o) = (tid / 16, tid % 16) ------------
-            // Every thread with o < C polls the G tagged words of its own element (b, o): with the
-            // words in the XCD's L2 an exchange is then one trip.  Polls through memory slow the peers'
-            // stores down (they meet in the same memory channels): there, while the peers are still
-            // computing, only wave 0 looks, and only at one word per record and batch tile (the last one
-            // its owner stores).  The element tags are still checked, and the fetch repeated if one is
-            // stale.  (A separate flag word per poster, stored after the logits, overtakes them on the
-            // way.)  16 clients, 784 -> 128, 50 rounds: in L2 7.61 ms with the watch, 7.47 without;
-            // through memory 8.9 and 12.1.
-            {
-                const int b = tid >> 4, o = tid & 15;
-                const bool mine = b < B && o < C;
-                float z = 0.f;
-                BoundedWait wait;
-                if (!same) {
-                    if (wave == 0) {
-                        // lane -> (record, batch tile); the word of sample 16*bt+15, class C-1
-                        const int gg = lane % G, bt = lane / G;
-                        const unsigned long long *w = rec + (int64_t)gg * kMlpRec + (16 * min(bt, NBT - 1) + 15) * C + (C - 1);
-                        for (;;) {
-                            bool ok = true;
-                            if (bt < NBT) ok = (uint32_t)(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == tag;
-                            if (__all(ok) || dead) break;
-                            __builtin_amdgcn_s_sleep(2);
-                            if (wait.gave_up(errflag)) dead = true;
-                        }
-                    }
-                    __syncthreads();
-                }
-                if (mine) {
-                    const unsigned long long *src = rec + b * C + o;
-                    constexpr int GC = 8;  // records fetched per batch of loads
-                    for (;;) {
-                        bool ok = true;
-                        z = b2s[o];
-                        if (G <= GC) {   // one batch; records beyond the last stand for it
-                            unsigned long long v[GC];
-#pragma unroll
-                            for (int gg = 0; gg < GC; ++gg)
-                                v[gg] = __hip_atomic_load(src + min(gg, G - 1) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                            for (int gg = 0; gg < GC; ++gg) {
-                                ok = ok && (uint32_t)(v[gg] >> 32) == tag;
-                                if (gg < G) z += __uint_as_float((uint32_t)v[gg]);
-                            }
-                        } else {
-                            for (int g0 = 0; g0 < G; g0 += GC) {
-                                unsigned long long v[GC];
-#pragma unroll
-                                for (int gg = 0; gg < GC; ++gg)
-                                    if (g0 + gg < G) v[gg] = __hip_atomic_load(src + (g0 + gg) * kMlpRec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                                for (int gg = 0; gg < GC; ++gg)
-                                    if (g0 + gg < G) {
-                                        ok = ok && (uint32_t)(v[gg] >> 32) == tag;
-                                        z += __uint_as_float((uint32_t)v[gg]);
-                                    }
-                            }
-                        }
-                        if (ok || dead) break;
-                        if (!same) __builtin_amdgcn_s_sleep(2);
-                        if (wait.gave_up(errflag)) dead = true;
-                    }
-                }
-                if (b < B) {
-                    const float zmax = row16_max(o < C ? z : -3.0e38f);
-                    // PAD: expf and logf as in the layer engine, where these models run otherwise
-                    const auto exp_of = [](float v) { return PAD ? expf(v) : __expf(v); };
-                    const float ex = o < C ? exp_of(z - zmax) : 0.f;
-                    const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
-                    const int lab = labs[b];
-                    if (o == lab) lossb[b] = lse - z;
-                    zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
-                }
+        }
+        // ---- the next recursion's labels ----------------------------------------------------
+        if (AHEAD == 1) lab_next = lab_ahead;
+        if (wave == kRowsWave && lane < B && u + 1 < p.m) labs[lane] = lab_next;
+        lab_next = lab_ahead;
+    };
+    auto recursions = [&](const auto same) __attribute__((always_inline)) {
+        for (int u = 0; u < p.m; ++u) {
+            recursion(u, xreg[0], same);
+            if constexpr (AHEAD == 2) {
+                if (++u == p.m) break;
+                recursion(u, xreg[1], same);
             }
-            __syncthreads();
-            // ---- small products on the matrix cores -----------------------------------------
-            prefetch_rows();
-            f4 dW2acc = {0.f, 0.f, 0.f, 0.f};
-            if (wave < NBT) {
-                // dh = (dz W2) * 1[h > 0] for samples 16*wave .. 16*wave+15
-                const int bt = wave;
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc = mfma16(zs[(16 * bt + li) * 16 + 4 * s + lg], W2s[(4 * s + lg) * 16 + li], acc);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = (16 * bt + 4 * lg + r) * 16 + li;
-                    dhs[i] = hs[i] > 0.f ? acc[r] : 0.f;
-                }
-            } else if (wave == 2) {
-                // dW2[o][j] = sum_b dz[b][o] h[b][j]; applied after the barrier (W2 is still read)
-#pragma unroll
-                for (int s = 0; s < 4 * NBT; ++s)
-                    dW2acc = mfma16(zs[(4 * s + lg) * 16 + li], hs[(4 * s + lg) * 16 + li], dW2acc);
-            } else if (wave == 3) {
-                // second-layer bias: column sums of dz
-                const float s = col_sum16<B>(zs, lane) * invB;
-                if (lane < C) {
-                    b2s[lane] -= p.eta * s;
-                    Ub2s[lane] += s;
-                }
-            } else if (wave == 4) {
-                // the recursion's mean loss
-                const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
-                if (lane == 0) lossacc[0] += s * invB;
-            }
-            __syncthreads();
-            // ---- second layer and first-layer bias: w <- w - eta g, U <- U + g ---------------
-            if (wave == 2) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = (4 * lg + r) * 16 + li;  // (o, j)
-                    const float gv = dW2acc[r] * invB;
-                    W2s[i] -= p.eta * gv;
-                    U2s[i] += gv;
-                }
-            } else if (wave == 3) {
-                // first-layer bias: column sums of dh
-                const float s = col_sum16<B>(dhs, lane) * invB;
-                if (lane < 16) {
-                    b1s[lane] -= p.eta * s;
-                    Ub1s[lane] += s;
-                }
-            }
-            // ---- first layer: dW1^T = X^T dh on the matrix cores, update in registers -------
-            {
-                // contraction step s of lane group lg takes sample 16*(s/4) + (s%4) + 4*lg: with
-                // rows 4*lg apart the four lane groups read LDS banks 16 apart (ld = 4 mod 32)
-                float dhb[4 * NBT];
-#pragma unroll
-                for (int s = 0; s < 4 * NBT; ++s) dhb[s] = dhs[(16 * (s >> 2) + (s & 3) + 4 * lg) * 16 + li];
-                float xb[2][4 * NBT];
-                const float *xcol = Xs + opaque(4 * lg * ld + col0 + li);
-                if (FULL || nt > 0) {
-#pragma unroll
-                    for (int s = 0; s < 4 * NBT; ++s) xb[0][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld];
-                }
-                const float eb = p.eta * invB;
-#pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
-                    if (tt + 1 < TPW && (FULL || tt + 1 < nt)) {
-#pragma unroll
-                        for (int s = 0; s < 4 * NBT; ++s) xb[(tt + 1) & 1][s] = xcol[(16 * (s >> 2) + (s & 3)) * ld + 16 * (tt + 1)];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // the next tile's operands are on their way before the products
-                    if (FULL || tt < nt) {
-                        // two independent accumulation chains per tile
-                        // (the first product of each chain takes the constant zero as its addend)
-                        f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], f4{0.f, 0.f, 0.f, 0.f});
-                        f4 acc1 = mfma16(xb[tt & 1][1], dhb[1], f4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-                        for (int s = 2; s < 4 * NBT; s += 2) {
-                            acc0 = mfma16(xb[tt & 1][s], dhb[s], acc0);
-                            acc1 = mfma16(xb[tt & 1][s + 1], dhb[s + 1], acc1);
-                        }
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float gsum = acc0[r] + acc1[r];
-                            W1r[tt][r] -= eb * gsum;
-                            U1r[tt][r] += invB * gsum;
-                        }
-                    }
-                    // this tile's share of the next recursion's row loads
-#pragma unroll
-                    for (int i = tt * NI / PFT; i < (tt + 1) * NI / PFT && i < NI; ++i) prefetch_load(i);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // ---- the next recursion's labels ----------------------------------------------------
-            if (more && wave == 0 && lane < B) labs[lane] = labn;
         }
     };
-    // Written out for either answer, or with a test in one loop where two would not fit the registers
-    // (two batch tiles with seven column tiles: 260 to 350 bytes spilled).  No test and no watch / one
-    // loop with them / two loops, words in L2, ms: 16 clients, 784 -> 128, B = 32, 50 rounds 7.46, 7.57,
-    // 7.29; 20 rounds: 100 clients, 60 -> 64 3.05, -, 2.91; 48, 784 -> 128 4.05, 3.91, 4.76; 40, 896 -> 256
-    // 7.25, 7.08, 10.3; B = 16: 40, 896 -> 256 4.93, -, 4.84; 48, 784 -> 128 2.53, 2.61, 2.57.
+    // Written out for either answer, or with a test in one loop where two are no faster.  One loop / two, words in L2, ms
+    // a job: 16 clients, 784 -> 128, B = 32 6.99 / 6.73; 13, 256 -> 128 0.516 / 0.501; 48, 784 -> 128, B = 16 2.06 / 2.03; 40, 896 -> 256,
+    // B = 32 (two batch tiles with seven column tiles) 3.14 / 3.29.
     if (NBT * TPW > 2 * kMlpHalfTPW) recursions(one_xcd);
     else if (one_xcd) recursions(std::true_type());
     else recursions(std::false_type());
@@ -635,7 +720,7 @@ static int mlp_tpw(int D) { return (D + 15) / 16 <= 2 * kMlpWaves ? 2 : kMlpMaxT
 
 static size_t mlp_lds_bytes_tpw(int tpw, int B) {
     const int ld = 16 * kMlpWaves * tpw + 4;
-    return sizeof(float) * ((size_t)B * ld + kMlpWaves * B * 16 + 3 * B * 16 + 512 + 64 + B + 16) + sizeof(int) * B;
+    return sizeof(float) * ((size_t)B * ld + kMlpWaves * B * 16 + 3 * B * 16 + 512 + 64 + B + 16) + sizeof(int) * 2 * B;
 }
 static size_t mlp_lds_bytes(int D, int B) { return mlp_lds_bytes_tpw(mlp_tpw(D), B); }
 
@@ -648,6 +733,7 @@ bool mlp_round_supported(int D, int H, int C, int B) {
 
 bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0; }
 
+// (The ratios are those of the form that had one mini-batch ahead; the present one is 1.05 to 1.6 times as fast.)
 // The layer engine's launches take all clients, these as many as are resident (at most kMlpPack)
 // and follow one another, so it catches up with many clients, the sooner the smaller the
 // model.  Time here / there per recursion at mini-batches of 1 to 31, launches in brackets:
