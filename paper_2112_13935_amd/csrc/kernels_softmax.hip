@@ -1,6 +1,6 @@
 // Fused local round for softmax regression (one dense layer D -> C, per-sample SGD, B = 1).
 //
-// One workgroup (8 waves) per client runs the client's whole round (Algorithm 2,
+// One workgroup (8 waves; fewer where a row has no columns for them) per client runs the client's whole round (Algorithm 2,
 // MainComputeNode: s_i recursions).  The replica w_c (C x D weights + C biases) and the
 // gradient sum U stay in registers for the round: thread t owns columns t, t+512, ... of
 // every class row.  Per recursion the only memory traffic is the sampled row (fetched three
@@ -19,7 +19,7 @@
 
 namespace aet {
 
-constexpr int kSmWaves = 8;
+constexpr int kSmWaves = 8;    // at most
 constexpr int kSmThreads = 64 * kSmWaves;
 constexpr int kSmDepth = 4;    // rows in registers: at work, just done with, and two on the way
 constexpr int kSmBlock = 48;   // recursions per block of row numbers; a multiple of kSmDepth
@@ -110,12 +110,12 @@ constexpr int kBufferFlags = 0x00020000;
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
-// NC columns per thread; EXACT: D == 512 * NC, no column guards.
-template <int NC, bool EXACT>
-__global__ void __launch_bounds__(kSmThreads, 1)
+// NW waves of NC columns per thread; EXACT: D == 64 * NW * NC, no column guards.
+template <int NC, bool EXACT, int NW>
+__global__ void __launch_bounds__(64 * NW, NC == 3 ? 4 : 1)
 k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
     constexpr int C = 10, Q = 3;   // classes, groups of four class rows
-    constexpr int NW = kSmWaves, T = kSmThreads, DEPTH = kSmDepth;
+    constexpr int T = 64 * NW, QW = (NW + 3) / 4, DEPTH = kSmDepth;
     const RoundParams p = rp[blockIdx.x];
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
@@ -124,7 +124,7 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
 
     // partial logits [parity][four waves][class]: a lane reads the eight waves' sums of its class
     // as two 16-byte pieces, the lanes of a row from neighbouring places
-    __shared__ __attribute__((aligned(16))) float zpart[2][NW / 4][16][4];
+    __shared__ __attribute__((aligned(16))) float zpart[2][QW][16][4];
 
     const gcf_ptr W0 = as_global(Wg ? Wg : p.W);
     f4v W[NC][Q], U[NC][Q];
@@ -183,7 +183,7 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
     auto recursion = [&](int u, int i, const float (&x)[NC], float (&xp)[NC]) {
         const bool live = u < p.m;
         const int lab = __builtin_amdgcn_readlane(labv, i);
-        f4v za[NW / 4];
+        f4v za[QW];
         if (live) {
             float(*zp)[16][4] = zpart[u & 1];
             float s[C];
@@ -203,7 +203,7 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
             }
             __syncthreads();
 #pragma unroll
-            for (int h = 0; h < NW / 4; ++h) za[h] = *reinterpret_cast<const f4v *>(zp[h][real ? cls : 0]);
+            for (int h = 0; h < QW; ++h) za[h] = *reinterpret_cast<const f4v *>(zp[h][real ? cls : 0]);
         }
         // while those travel: the sum U of the recursion before (not on the way to the next
         // logits), and the row that is needed DEPTH - 1 recursions from now
@@ -286,14 +286,32 @@ hipError_t launch_softmax_round(hipStream_t s, Profiler *prof, const RoundParams
     (void)C;
     const bool timed = prof && prof->on[F_SOFTMAX_ROUND];
     if (timed) prof->before(F_SOFTMAX_ROUND, s);
-    if (D <= kSmThreads)
-        k_softmax_round<1, false><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+    // As many waves as have columns, and as many columns a thread: a wave or a column without data adds zeros to the logits,
+    // in its place (so every form gives the widest one's bits), but takes part in every barrier, softmax and update.
+    // us a job of 20 rounds, eight waves / as many as have columns: 903 clients x 19 (12 rounds) 1,980 / 959; 5 x 60 1,281 / 945;
+    // 20 x 84 (11 rounds) 439 / 360; 346 x 114 2,219 / 1,492; 300 x 200 2,197 / 1,518.  Six columns a thread / as many as there
+    // are, 18 rounds: 5 x 1,500 956 / 740; 300 x 1,500 2,003 / 1,320; 1,000 x 1,500 4,063 / 2,635; 300 x 2,000 2,042 / 1,785;
+    // 300 x 2,400 2,075 / 1,960.  (Three columns fit 128 registers, so that a compute unit holds two clients.)
+    if (D <= 64)
+        k_softmax_round<1, false, 1><<<nact, 64, 0, s>>>(dp, Wg, D);
+    else if (D <= 128)
+        k_softmax_round<1, false, 2><<<nact, 128, 0, s>>>(dp, Wg, D);
+    else if (D <= 256)
+        k_softmax_round<1, false, 4><<<nact, 256, 0, s>>>(dp, Wg, D);
+    else if (D <= kSmThreads)
+        k_softmax_round<1, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
     else if (D <= 2 * kSmThreads)
-        k_softmax_round<2, false><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+        k_softmax_round<2, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+    else if (D <= 3 * kSmThreads)
+        k_softmax_round<3, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+    else if (D <= 4 * kSmThreads)
+        k_softmax_round<4, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+    else if (D <= 5 * kSmThreads)
+        k_softmax_round<5, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
     else if (D == 6 * kSmThreads)
-        k_softmax_round<6, true><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+        k_softmax_round<6, true, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
     else
-        k_softmax_round<6, false><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
+        k_softmax_round<6, false, kSmWaves><<<nact, kSmThreads, 0, s>>>(dp, Wg, D);
     if (timed) prof->after(F_SOFTMAX_ROUND, s);
     return hipGetLastError();
 }
