@@ -1,4 +1,4 @@
-// Fused local round for dense-ReLU-dense models (D -> H -> C, mini-batch up to 32).
+// Fused local round for dense-ReLU-dense models (D -> H -> C, mini-batch up to 64).
 //
 // One launch runs the whole round (Algorithm 2, MainComputeNode: all s_i/B recursions) of
 // every active client.  A client is handled by a cluster of G = ceil(H/16) workgroups; workgroup
@@ -35,7 +35,9 @@
 //
 // Widths and mini-batches that do not fill the 16 x 16 tiles are padded: hidden units beyond H
 // have zero weights, samples beyond the mini-batch repeat its last row with d logits of zero
-// (never a row that was not drawn: it could hold a value that is not finite).
+// (never a row that was not drawn: it could hold a value that is not finite).  Mini-batches of
+// 33 .. 64 are two steps of 32 samples, with one update: 4 clients, 784 -> 100, 64 samples 29 -> 12 us per recursion
+// (five launches of the layer-by-layer engine before).
 //
 // What bounds it: the chain of one recursion, forward product - sum over the waves - (pair exchange) - logits -
 // exchange - softmax - d(hidden) - backward product, four workgroup barriers long; the two large products are a
@@ -182,13 +184,16 @@ struct MlpPack {
 // there on compute the same numbers side by side; half 0 posts the logits and stores the
 // second layer at the end.
 // PAD: the width or the mini-batch does not fill its tiles.
-template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
+// SUB = 2: mini-batches of 33 .. 64 in two steps, samples 0 .. 31 and 32 .., on the same weights: the first step's
+// gradient sums are kept (in registers: where the second one's products start from), the second one's update takes both.
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD, int SUB>
 __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             int D, int H, int C, int G, int Brun, unsigned long long *__restrict__ xrec,
             unsigned long long *__restrict__ prec, unsigned long long *__restrict__ places, int skew,
             uint32_t tag0, int *__restrict__ errflag) {
     constexpr int B = 16 * NBT;
+    static_assert(SUB == 1 || (PAD && NBT == 2), "two steps of 32 samples, of which the second may be short");
     const int Br = PAD ? Brun : B;   // samples of the mini-batch
     // workgroup -> (client, unit group, half): consecutive workgroup ids go round the 8 XCDs,
     // so the workgroups of one client get ids that land on the same XCD and share its L2
@@ -318,8 +323,11 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     constexpr int AHEAD = TPW <= kMlpHalfTPW ? 2 : 1;
     f4 xreg[AHEAD][NBT][TPW];
     int lab_next = 0, lab_ahead = 0;   // labels of recursions u + 1 and u + AHEAD (of the wave that sees to the rows)
-    auto rows_of = [&](int u) -> uint32_t {
-        return lane < B ? sample_row(p.key, (uint64_t)(p.q0 + (int64_t)u * Br + min(lane, Br - 1)), p.n_samples) : 0u;
+    const int steps = SUB * p.m;
+    auto rows_of = [&](int u) -> uint32_t {   // of step u
+        const int64_t from = SUB == 1 ? (int64_t)u * Br : (int64_t)(u >> 1) * Br;
+        const int b = SUB == 1 ? lane : B * (u & 1) + lane;
+        return lane < B ? sample_row(p.key, (uint64_t)(p.q0 + from + min(b, Br - 1)), p.n_samples) : 0u;
     };
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) {
@@ -327,7 +335,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
             for (int tt = 0; tt < TPW; ++tt) xreg[k][bt][tt] = f4{0.f, 0.f, 0.f, 0.f};
-        if (k < p.m) {
+        if (k < steps) {
             const uint32_t rowv = rows_of(k);
             if (wave == kRowsWave && lane < B) {
                 const int lab = yg[rowv];
@@ -356,8 +364,12 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     __syncthreads();
     const bool one_xcd = __builtin_amdgcn_readfirstlane(lossacc[1] == 0.f);
 
-    // x: this recursion's rows; their registers take the rows of recursion u + AHEAD
-    auto recursion = [&](int u, f4 (&x)[NBT][TPW], const auto same) __attribute__((always_inline)) {   // same: whether the words stay in the L2 of one XCD
+    // the first of two steps' sums
+    f4 Gk[SUB == 2 ? TPW : 1], dW2k = {0.f, 0.f, 0.f, 0.f};
+    float db1k = 0.f, db2k = 0.f;
+    // x: this step's rows; their registers take the rows of step u + AHEAD (a step is a recursion, or, SUB = 2, half
+    // of one: part 0 or 1)
+    auto recursion = [&](int u, const int half, f4 (&x)[NBT][TPW], const auto same) __attribute__((always_inline)) {   // same: whether the words stay in the L2 of one XCD
         const int ntile = opaque_scalar(nt), tail = opaque_scalar(tail_tt);
         auto park_rows = [&]() {
 #pragma unroll
@@ -402,7 +414,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             for (int bt = 0; bt < NBT; ++bt) *reinterpret_cast<f4 *>(red + (wave * B + 16 * bt + li) * 16 + 4 * lg) = acc[bt];
         }
         __syncthreads();
-        const bool more = u + AHEAD < p.m;
+        const bool more = u + AHEAD < steps, updates = SUB == 1 || half == 1;
         // ---- h = relu(z1 + b1) ----------------------------------------------------------
         const uint32_t tag = tag0 + (uint32_t)u;
         const int par = u & 1;
@@ -529,11 +541,11 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             const float ex = o < C ? exp_of(z - zmax) : 0.f;
             const float sum = row16_sum(ex), lse = zmax + (PAD ? logf(sum) : __logf(sum));
             if (o == lab) lossb[b] = lse - z;
-            zs[b * 16 + o] = o < C && b < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
+            zs[b * 16 + o] = o < C && (SUB == 1 ? b : B * half + b) < Br ? exp_of(z - lse) - (o == lab ? 1.f : 0.f) : 0.f;
         }
         __syncthreads();
         // ---- small products on the matrix cores -----------------------------------------
-        f4 dW2acc = {0.f, 0.f, 0.f, 0.f};
+        f4 dW2acc = SUB == 2 && updates ? dW2k : f4{0.f, 0.f, 0.f, 0.f};
         if (wave < NBT) {
             // dh = (dz W2) * 1[h > 0] for samples 16*wave .. 16*wave+15
             const f4 dz = *reinterpret_cast<const f4 *>(zs + 16 * mt + 4 * lg);
@@ -553,16 +565,19 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             }
 #pragma unroll
             for (int s = 0; s < 4 * NBT; ++s) dW2acc = mfma16(za[s], hb[s], dW2acc);
+            if (!updates) dW2k = dW2acc;
         } else if (wave == 3) {
             // second-layer bias: column sums of dz
-            const float s = col_sum16<B>(zs, lane) * invB;
-            if (lane < C) {
+            float s = col_sum16<B>(zs, lane);
+            if (SUB == 2) s = updates ? db2k + s : (db2k = s);
+            s *= invB;
+            if (updates && lane < C) {
                 b2s[lane] -= p.eta * s;
                 Ub2s[lane] += s;
             }
         } else if (wave == 4) {
             // the recursion's mean loss
-            const float s = row16_sum(fold_rows(lane < Br ? lossb[lane] : 0.f));
+            const float s = row16_sum(fold_rows((SUB == 1 ? lane : B * half + lane) < Br && lane < B ? lossb[min(lane, B - 1)] : 0.f));
             if (lane == 0) lossacc[0] += s * invB;
         } else if (wave == kRowsWave && more) {
             // the rows that recursion u + AHEAD samples, for all waves, and their labels
@@ -590,7 +605,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             x[j % NBT][j / NBT] = piece;
         };
         // ---- second layer and first-layer bias: w <- w - eta g, U <- U + g ---------------
-        if (wave == 2) {
+        if (wave == 2 && updates) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int e = (4 * lg + r) * 16 + li;  // (o, j)
@@ -600,8 +615,10 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             }
         } else if (wave == 3) {
             // first-layer bias: column sums of dh
-            const float s = col_sum16<B>(dhs, lane) * invB;
-            if (lane < 16) {
+            float s = col_sum16<B>(dhs, lane);
+            if (SUB == 2) s = updates ? db1k + s : (db1k = s);
+            s *= invB;
+            if (updates && lane < 16) {
                 b1s[lane] -= p.eta * s;
                 Ub1s[lane] += s;
             }
@@ -630,15 +647,16 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                 if (FULL || tt < ntile) {
                     // two independent accumulation chains per tile
                     // (the first product of each chain takes the constant zero as its addend)
-                    f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], f4{0.f, 0.f, 0.f, 0.f});
+                    f4 acc0 = mfma16(xb[tt & 1][0], dhb[0], SUB == 2 && updates ? Gk[tt] : f4{0.f, 0.f, 0.f, 0.f});
                     f4 acc1 = mfma16(xb[tt & 1][1], dhb[1], f4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
                     for (int s = 2; s < 4 * NBT; s += 2) {
                         acc0 = mfma16(xb[tt & 1][s], dhb[s], acc0);
                         acc1 = mfma16(xb[tt & 1][s + 1], dhb[s + 1], acc1);
                     }
+                    if (!updates) Gk[tt] = acc0 + acc1;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
+                    for (int r = 0; r < 4 && updates; ++r) {
                         const float gsum = acc0[r] + acc1[r];
                         W1r[tt][r] -= eb * gsum;
                         U1r[tt][r] += invB * gsum;
@@ -652,15 +670,15 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         }
         // ---- the next recursion's labels ----------------------------------------------------
         if (AHEAD == 1) lab_next = lab_ahead;
-        if (wave == kRowsWave && lane < B && u + 1 < p.m) labs[lane] = lab_next;
+        if (wave == kRowsWave && lane < B && u + 1 < steps) labs[lane] = lab_next;
         lab_next = lab_ahead;
     };
     auto recursions = [&](const auto same) __attribute__((always_inline)) {
-        for (int u = 0; u < p.m; ++u) {
-            recursion(u, xreg[0], same);
+        for (int u = 0; u < steps; ++u) {
+            recursion(u, AHEAD == 2 ? 0 : u & 1, xreg[0], same);
             if constexpr (AHEAD == 2) {
-                if (++u == p.m) break;
-                recursion(u, xreg[1], same);
+                if (++u == steps) break;
+                recursion(u, 1, xreg[1], same);
             }
         }
     };
@@ -725,7 +743,7 @@ static size_t mlp_lds_bytes_tpw(int tpw, int B) {
 static size_t mlp_lds_bytes(int D, int B) { return mlp_lds_bytes_tpw(mlp_tpw(D), B); }
 
 bool mlp_round_supported(int D, int H, int C, int B) {
-    if (B < 1 || B > 32) return false;
+    if (B < 1 || B > 64) return false;
     if (H < 1 || H > 16 * kMlpMaxG || C < 1 || C > 16) return false;
     if (D < 1 || (D + 15) / 16 > kMlpWaves * kMlpMaxTPW) return false;
     return mlp_lds_bytes(D, B <= 16 ? 16 : 32) <= 160 * 1024;
@@ -747,6 +765,9 @@ bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0;
 //   250 units  96 (6)  0.87 .. 1.09   0.95 .. 0.99           0.91 .. 0.96
 //             256 (16) 1.76 .. 2.10   1.29 .. 1.42           0.93 .. 1.10           0.37 .. 0.46
 // (256 inputs, 250 units, 256 clients: 0.82 .. 0.89; 400: 0.67 .. 0.79.)
+// Mini-batches of 33 .. 64, which take two steps here and the same launches there, gain more: here / there at 64, 4, 48, 128
+// and 256 clients where the rule says here: 30 -> 10 0.24 0.25 0.58; 100 -> 100 0.34 0.51 0.67 0.85; 300 -> 250 0.37 0.66
+// 0.69; 784 -> 100 0.41 0.50 0.54 0.44; 890 -> 250 0.29 0.39 0.43 0.53 (33: 300 -> 250 0.39 0.74, 30 -> 10 0.28 0.29).
 bool mlp_padded_pays(int D, int H, int n_clients) {
     const int G = (H + 15) / 16, fit = resident_clusters(256, 8, G), per = fit < kMlpPack ? fit : kMlpPack;
     const int launches = (n_clients + per - 1) / per;
@@ -766,20 +787,20 @@ size_t mlp_round_scratch_bytes(int n_clients, int B) {
     return mlp_all_words(n_clients) * 8 + 256;
 }
 
-template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD, int SUB = 1>
 static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
     int dev = 0;
     const hipError_t e0 = hipGetDevice(&dev);
     if (e0 != hipSuccess) return e0;
     static PerDevice capacity;   // of this instantiation
     return capacity.get(dev, cap, [lds, dev](int *found) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD, SUB>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         int cus = 0, per_cu = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD>, kMlpThreads, lds);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD, SUB>, kMlpThreads, lds);
         *found = cus * per_cu;
         return e;
     });
@@ -787,7 +808,7 @@ static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
 
 // HF = 2 (two workgroups per unit group) is taken only when all active clients fit one
 // launch that way; otherwise *declined is set and nothing is launched.
-template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD>
+template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD, int SUB = 1>
 static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact, int max_m,
                              const float *Wg, int D, int H, int C, int Br, void *scratch, int n_clients,
                              uint32_t *epoch, bool *declined = nullptr) {
@@ -795,7 +816,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     const int G = (H + 15) / 16;
     const size_t lds = mlp_lds_bytes_tpw(TPW, B);
     int cap = 0, xcds = 0;
-    hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF, PAD>(lds, &cap);
+    hipError_t e = mlp_capacity<NBT, TPW, FAST, FULL, HF, PAD, SUB>(lds, &cap);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
     // Clusters per launch: every workgroup that polls must be resident together with its
@@ -815,7 +836,8 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     // earlier launch may have left in the records
     // A captured launch carries its tags into every replay, where the records still hold words
     // of the replay before with the same tags: there the records are cleared ahead of it.
-    const bool spent = *epoch == 0 || *epoch > 0xFFFFFFFFu - (uint32_t)max_m - 2u;
+    const uint32_t need = SUB * (uint32_t)max_m + 1u;
+    const bool spent = *epoch == 0 || *epoch > 0xFFFFFFFFu - need - 1u;
     if (spent || stream_is_capturing(s)) {
         k_zero_words<<<(unsigned)((mlp_all_words(n_clients) + 255) / 256), 256, 0, s>>>(xrec, mlp_all_words(n_clients));
         e = hipGetLastError();
@@ -823,7 +845,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     }
     if (spent) *epoch = 1;
     const uint32_t tag0 = *epoch;
-    *epoch += (uint32_t)max_m + 1u;
+    *epoch += need;
     for (int a0 = 0; a0 < nact; a0 += per_launch) {
         const int here = (nact - a0 < per_launch) ? nact - a0 : per_launch;
         const int groups = (here + 7) / 8;  // clients per XCD in this launch
@@ -831,7 +853,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, g_xcd_skew, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD, SUB><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, g_xcd_skew, tag0, errflag);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -848,11 +870,22 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     const bool full = D == 16 * kMlpWaves * mlp_tpw(D);   // no pad tiles
     // wide inputs: two workgroups per unit group, half of the columns each, when every active
     // client gets its 2 G workgroups resident in one launch
-    const bool pad = !mlp_round_exact(H, B);
+    const bool pad = !mlp_round_exact(H, B), half = !small && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW;
+    if (B > 32) {
+#define AET_MLP_TWO(tpw, fast_, hf, ...) mlp_launch<2, tpw, fast_, false, hf, true, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)
+        if (half) {
+            bool declined = false;
+            const hipError_t e = fast ? AET_MLP_TWO(kMlpHalfTPW, true, 2, &declined) : AET_MLP_TWO(kMlpHalfTPW, false, 2, &declined);
+            if (e != hipSuccess || !declined) return e;
+        }
+        if (small) return fast ? AET_MLP_TWO(2, true, 1) : AET_MLP_TWO(2, false, 1);
+        return fast ? AET_MLP_TWO(kMlpMaxTPW, true, 1) : AET_MLP_TWO(kMlpMaxTPW, false, 1);
+#undef AET_MLP_TWO
+    }
 #define AET_MLP(nbt, tpw, fast_, full_, hf, ...)                                                                            \
     (pad ? mlp_launch<nbt, tpw, fast_, full_, hf, true>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)   \
          : mlp_launch<nbt, tpw, fast_, full_, hf, false>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__))
-    if (!small && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW) {
+    if (half) {
         bool declined = false;
         hipError_t e;
         if (B <= 16) e = fast ? AET_MLP(1, kMlpHalfTPW, true, false, 2, &declined) : AET_MLP(1, kMlpHalfTPW, false, false, 2, &declined);

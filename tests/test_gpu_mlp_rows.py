@@ -46,3 +46,24 @@ def test_neighbouring_rows_stay_out(oracle_libs, d):
     run, orc = Run(wl), Oracle(wl, "f64")
     lockstep(wl, run, orc)
     run.close()
+
+
+@pytest.mark.parametrize("n,d,hidden,batch", [
+    (2, 20, 16, 33),     # one sample in the second step
+    (3, 256, 40, 64),    # both steps full, every wave has its two tiles
+    (2, 3, 5, 63),       # narrow rows
+    (2, 530, 100, 48),   # two workgroups per unit group, ragged columns
+    (2, 784, 32, 64),    # ... whole tiles
+    (9, 700, 256, 50),   # seven tiles a wave: sixteen unit groups, more clients than are resident two by two
+    (5, 150, 240, 37),   # more unit groups than are fetched at a time
+])
+def test_mini_batches_in_two_steps(oracle_libs, n, d, hidden, batch):
+    from oracle import Oracle
+    from paper_2112_13935_amd.runner import Run
+    from parity import lockstep
+    wl = W.config2(n_clients=n, n_total=n * 90, d=d, hidden=hidden, batch=batch, rounds=4, a=batch, b=0)
+    if n == 3:
+        wl.compute_factor = np.array([1, 2, 1], dtype=np.int32)
+    run, orc = Run(wl), Oracle(wl, "f64")
+    lockstep(wl, run, orc)
+    run.close()
