@@ -173,11 +173,12 @@ __device__ __forceinline__ float relu_pool(const float (&acc)[4], int &which) {
     return best;
 }
 
-// G28: the geometry of the 28 x 28 input (12 x 12 pooled maps, 8 x 8 conv-2 maps, 256 features)
-// as compile-time constants, so that the operand addresses of the convolution phases are
-// immediates; other input sizes take the sizes from d.
+// GEO: side of the input, 28 (12 x 12 pooled maps, 8 x 8 conv-2 maps, 256 features), 20 or 16: the geometry is
+// compile-time constants, so that the operand addresses of the convolution phases are
+// immediates.  With 16 and 20 as run-time sizes, us a job: 5 clients, 16 x 16, B = 4 1,668 -> 1,246; 59, 16 x 16, B = 16 754 ->
+// 567; 10, 20 x 20, B = 16 856 -> 674, B = 32 591 -> 498.
 // S: clusters of four workgroups per client; PAD: the mini-batch does not fill the S x 16 samples.
-template <bool G28, int S, bool PAD>
+template <int GEO, int S, bool PAD>
 __global__ void __launch_bounds__(kLnThreads, 1)
 k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const float *Wg, const LenetDims d, int Brun,
               u64 *__restrict__ xrec, u64 *__restrict__ places, int skew, uint32_t tag0, int *__restrict__ errflag) {
@@ -195,8 +196,8 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     const gci_ptr yg = as_global(p.y);
     const gf_ptr Wc = as_global(p.W), Uc = as_global(p.U);
     const int tid = threadIdx.x;
-    const int H0 = G28 ? 28 : d.H0, P1 = G28 ? 12 : d.P1, H2 = G28 ? 8 : d.H2, P2 = G28 ? 4 : d.P2, F0 = G28 ? 256 : d.F0;
-    const int lgF0 = G28 ? 8 : d.lgF0;
+    constexpr bool G28 = GEO == 28;
+    constexpr int H0 = GEO, P1 = (GEO - 4) / 2, H2 = P1 - 4, P2 = H2 / 2, F0 = 16 * P2 * P2, lgF0 = P2 == 4 ? 8 : P2 == 2 ? 6 : 4;
     const int nwin1 = P1 * P1, nwin2 = P2 * P2, npix = H0 * H0;
     const int P1S = 6 * nwin1 + 8;       // per-sample stride of the pooled conv-1 maps
     const int F0P = F0 + 4;              // row stride of arrays with F0 columns
@@ -1572,8 +1573,10 @@ bool lenet_dims(const LayerGeom *lay, int L, int B, LenetDims *d) {
     if (f1.oc != kF1 || !f1.relu || f2.oc != kF2 || !f2.relu || f3.oc != kNC || f3.relu) return false;
     d->H0 = c1.ih; d->P1 = q1.oh; d->H2 = c2.oh; d->P2 = q2.oh;
     d->F0 = 16 * d->P2 * d->P2;
-    if (d->H0 > 32 || (d->H0 * d->H0) % 4 || d->P1 > 12 || (d->P1 & 1) || d->H2 > 8) return false;
-    if (d->F0 != 16 && d->F0 != 64 && d->F0 != 256) return false;   // P2 = 1, 2 or 4
+    // (the geometries of the instantiations; others have odd maps, rows that are not whole 16-byte pieces, or more than
+    // 256 features)
+    if (d->H0 != 16 && d->H0 != 20 && d->H0 != 28) return false;
+    if (d->P1 != (d->H0 - 4) / 2 || d->H2 != d->P1 - 4 || d->P2 != d->H2 / 2) return false;
     d->lgF0 = d->F0 == 16 ? 4 : d->F0 == 64 ? 6 : 8;
     if ((int64_t)d->F0 != f1.in_size) return false;
     d->o_f1 = f1.w_off; d->o_f2 = f2.w_off; d->o_f3 = f3.w_off;
@@ -1591,12 +1594,13 @@ size_t lenet_lds_bytes(const LenetDims &d) {
     return fl * 4;
 }
 
-// the instantiations: 28 x 28 or any geometry; one or two clusters; exact or padded
+// the instantiations: side of the input; one or two clusters; exact or padded
 typedef void (*LenetKernel)(const RoundParams *, int, int, const float *, LenetDims, int, u64 *, u64 *, int, uint32_t, int *);
-LenetKernel lenet_kernel(bool g28, int S, bool pad) {
-    if (S == 2) return g28 ? k_lenet_round<true, 2, true> : k_lenet_round<false, 2, true>;
-    if (pad) return g28 ? k_lenet_round<true, 1, true> : k_lenet_round<false, 1, true>;
-    return g28 ? k_lenet_round<true, 1, false> : k_lenet_round<false, 1, false>;
+template <int GEO>
+LenetKernel lenet_kernel(int S, bool pad) {
+    if (S == 2) return k_lenet_round<GEO, 2, true>;
+    if (pad) return k_lenet_round<GEO, 1, true>;
+    return k_lenet_round<GEO, 1, false>;
 }
 static_assert(2 * kLnG <= kClusterMax, "a place for every workgroup");
 int lenet_clusters(int B) { return B > kLnB ? 2 : 1; }
@@ -1620,10 +1624,13 @@ bool lenet_round_exact(int B) { return B == kLnB; }
 
 // Padded samples cost as much as real ones; with many clients (launches of 64 or, two clusters
 // each, 32) the layer engine wins where they are most of the tile.  Time here / there per
-// recursion for mini-batches of 1, 4, 8, 15 | 17, 24, 32:
-//   128 clients  16 x 16  0.79 0.71 0.57 0.43 | 0.89 0.76 0.63   28 x 28  0.87 0.70 0.52 0.37 | 0.79 0.65 0.52
-//   192          20 x 20  1.18 1.00 0.75 0.57 | 1.14 0.95 0.78   28 x 28  1.09 0.79 0.59 0.40 | 0.86 0.68 0.53
-//   256          20 x 20  1.27 1.04 0.80 0.61 | 1.26 1.03 0.84   28 x 28  1.00 0.75 0.57 0.39 | 0.84 0.65 0.52
+// recursion for mini-batches of 1, 4, 7 (28 x 28: 8) | 17, 24:
+//   128 clients  28 x 28  0.87 0.70 0.52 | 0.79 0.65
+//   160          16 x 16  0.78 0.67 0.56 | 0.73 0.63   20 x 20  0.97 0.81 0.69 | 0.88 0.75
+//   192          16 x 16  0.76 0.65 0.50 | 0.81 0.68   20 x 20  0.93 0.78 0.61 | 0.93 0.77   28 x 28  1.09 0.79 0.59 | 0.86 0.68
+//   256          16 x 16  0.83 0.67 0.54 | 0.90 0.74   20 x 20  0.99 0.80 0.65 | 1.03 0.84   28 x 28  1.00 0.75 0.57 | 0.84 0.65
+// The line for 16 x 16 and 20 x 20 is that of the form with their sizes at run time (1.18 and 1.27 at 192 and 256 clients of
+// 20 x 20, mini-batch 1); it is on the safe side now.
 bool lenet_padded_pays(const LayerGeom &conv1, int B, int n_clients) {
     if (n_clients <= 128) return true;
     if (conv1.ih >= 28) return B >= 4;
@@ -1650,14 +1657,15 @@ hipError_t launch_lenet_round(hipStream_t s, Profiler *prof, const RoundParams *
     if (!lenet_dims(lay, L, B, &d)) return hipErrorInvalidValue;
     const size_t lds = lenet_lds_bytes(d);
     hipError_t e;
-    const bool g28 = d.H0 == 28 && d.P1 == 12 && d.H2 == 8 && d.P2 == 4 && d.F0 == 256 && d.lgF0 == 8;
     const int S = lenet_clusters(B);
-    const LenetKernel kernel = lenet_kernel(g28, S, !lenet_round_exact(B));
+    const int geo = d.H0 == 28 ? 0 : d.H0 == 20 ? 1 : 2;
+    const bool exact = lenet_round_exact(B);
+    const LenetKernel kernel = geo == 0 ? lenet_kernel<28>(S, !exact) : geo == 1 ? lenet_kernel<20>(S, !exact) : lenet_kernel<16>(S, !exact);
     int dev = 0, cus = 0, per_cu = 0, sized = 0;
     e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    static PerDevice lds_allowed[2][3];
-    e = lds_allowed[g28][S == 2 ? 2 : lenet_round_exact(B) ? 0 : 1].get(dev, &sized, [kernel](int *done) {
+    static PerDevice lds_allowed[3][3];
+    e = lds_allowed[geo][S == 2 ? 2 : exact ? 0 : 1].get(dev, &sized, [kernel](int *done) {
         *done = 1;
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
