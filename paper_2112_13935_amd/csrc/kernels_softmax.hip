@@ -68,11 +68,18 @@ __device__ __forceinline__ float row_sum_dpp(float v) {
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
     return v;
 }
+// (One instruction a step.  From fmaxf of a lane move the compiler makes three, the move, a maximum of the moved value with itself
+// for the sake of signalling NaNs, and the maximum.  Two wait states between a write and a lane move that reads it.)
 __device__ __forceinline__ float row_max_dpp(float v) {
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)));
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "+v"(v));
     return v;
 }
 
@@ -150,9 +157,10 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
                 U[j][q][r] = 0.f;
             }
     }
-    // lane o of every row of 16 looks after class o
+    // lane o of every row of 16 looks after class o; the lanes beyond have a bias and so a logit of minus infinity: their
+    // exponential and their dz are zero by themselves
     const bool real = cls < C;
-    float bias = real ? W0[(int64_t)C * D + cls] : 0.f, Ub = 0.f, dz = 0.f;
+    float bias = real ? W0[(int64_t)C * D + cls] : -INFINITY, Ub = 0.f, dz = 0.f;
     float loss_acc = 0.f;
 
     // Row numbers and labels come a block of kSmBlock recursions at a time: lane l hashes
@@ -225,11 +233,12 @@ k_softmax_round(const RoundParams *__restrict__ rp, const float *Wg, int D) {
             float z = bias;   // the waves' sums in wave order
 #pragma unroll
             for (int w = 0; w < NW; ++w) z += za[w >> 2][w & 3];
-            const float zmax = row_max_dpp(real ? z : -3.0e38f);
-            const float ex = real ? __expf(z - zmax) : 0.f;
-            const float lse = zmax + log_of_sum(row_sum_dpp(ex));
-            dz = real ? __expf(z - lse) - (cls == lab ? 1.f : 0.f) : 0.f;
+            const float zmax = row_max_dpp(z);
+            const float lse = zmax + log_of_sum(row_sum_dpp(__expf(z - zmax)));
+            dz = __expf(z - lse) - (cls == lab ? 1.f : 0.f);
+            __builtin_amdgcn_sched_barrier(0);
             rank1(W, -p.eta * dz, x);   // w <- w - eta g with g = dz x^T
+            __builtin_amdgcn_sched_barrier(0);   // (what the next logits do not need comes after it)
             bias -= p.eta * dz;
             Ub += dz;
             if (cls == lab) loss_acc += lse - z;
