@@ -111,30 +111,51 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
+// A client's exchange words, through a range-checked buffer: a word is a 32-bit number, and most of it an immediate or a
+// scalar, where a pointer takes three vector instructions for each of the many words of a thread.  The
+// scopes are cluster_post's.
+constexpr int kBufferFlags = 0x00020000;   // dword 3 of a raw buffer descriptor for 32-bit untyped accesses
+constexpr int kAgent = 16;                 // cache policy of agent scope: a load passes the L1 by, a store goes through to memory
+typedef int i2 __attribute__((ext_vector_type(2)));
+
 struct Waiter {
+    __amdgpu_buffer_rsrc_t words;
     uint32_t tag;
     int *errflag;
     bool dead;
     bool one_xcd;   // all workgroups of the client run on one XCD
 };
 
-__device__ __forceinline__ void xpost(u64 *p, const Waiter &w, float v) { cluster_post(p, w.tag, v, w.one_xcd); }
+__device__ __forceinline__ void xpost(int word, const Waiter &w, float v) {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const u2 both = {__float_as_uint(v), w.tag};
+    if (w.one_xcd) __builtin_amdgcn_raw_buffer_store_b64(both, w.words, 8 * word, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(both, w.words, 8 * word, 0, kAgent);
+}
+// {value, tag}
+__device__ __forceinline__ i2 xlook(int word, const Waiter &w) {
+    return __builtin_bit_cast(i2, __builtin_amdgcn_raw_buffer_load_b64(w.words, 8 * word, 0, kAgent));
+}
 
 // N words at once (the loads are in flight together); repeated until every needed word shows
-// the current step.  Words that are not needed still point at valid memory.
+// the current step.  Words that are not needed still are ones of the client.
 template <int N>
-__device__ __forceinline__ void xfetch(const u64 *(&p)[N], const bool (&need)[N], float (&out)[N], Waiter &w) {
+__device__ __forceinline__ void xfetch(const int (&p)[N], const bool (&need)[N], float (&out)[N], Waiter &w) {
     BoundedWait wait;
     for (;;) {
-        u64 v[N];
+        i2 v[N];
+        asm volatile("" ::: "memory");   // (to the compiler these are loads like any other: not to be moved out of the loop)
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = __hip_atomic_load(p[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < N; ++i) v[i] = xlook(p[i], w);
         bool ok = true;
 #pragma unroll
-        for (int i = 0; i < N; ++i) ok = ok && (!need[i] || (uint32_t)(v[i] >> 32) == w.tag);
+        for (int i = 0; i < N; ++i) ok = ok && (!need[i] || (uint32_t)v[i][1] == w.tag);
         if (ok || w.dead) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) out[i] = __uint_as_float((uint32_t)v[i]);
+            for (int i = 0; i < N; ++i) {
+                const int bits = v[i][0];
+                out[i] = __builtin_bit_cast(float, bits);
+            }
             return;
         }
         __builtin_amdgcn_s_sleep(1);
@@ -239,9 +260,9 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
     float *dp1 = h1;                               // [4][P1S]        delta at the pooled conv-1 outputs
     float *dpart = gsum;                           // [8][kDP]        partial sums of the dense forward products, one [32 units][17] slice per wave (over gsum, c1part)
 
-    u64 *const rec = xrec + (int64_t)(rec0 + a) * (S == 1 ? kXWords : kXWords2) + sub * kXB3;
-    u64 *const set0 = xrec + (int64_t)(rec0 + a) * kXWords2 + 2 * kXB3;   // S = 2
-    Waiter wt{tag0, errflag, false, false};
+    constexpr int kWords = S == 1 ? kXWords : kXWords2;
+    const int rec = sub * kXB3, set0 = 2 * kXB3;   // (set0: S = 2)
+    Waiter wt{__builtin_amdgcn_make_buffer_rsrc(xrec + (int64_t)(rec0 + a) * kWords, 0, 8 * kWords, kBufferFlags), tag0, errflag, false, false};
 
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL) ----
     const float *src = Wg ? Wg : p.W;
@@ -313,7 +334,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         int tq = opaque(tid);
         wt.tag = tag0 + (uint32_t)u;
         // filter-bank and (S = 2) dense gradients: this recursion's records
-        u64 *const set = set0 + (u & 1) * kXSet, *const recd = set + kXB3s;
+        const int set = set0 + (u & 1) * kXSet, recd = set + kXB3s;
         auto rec3 = [&](int i) { return S == 1 ? rec + kXB3 + i * 2576 : set + i * 2576; };   // of workgroup i
         constexpr int NP = kLnG * S;   // partials per filter-bank entry
         float gd1[S > 1 ? 16 : 1], gd2[S > 1 ? 8 : 1], gd3[S > 1 ? 2 : 1], gdb1 = 0.f, gdb2 = 0.f, gdb3 = 0.f, gloss = 0.f;   // S = 2: kept until the counterpart's are there
@@ -485,7 +506,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         }
         // the other workgroups' samples
         for (int e0 = tq; e0 < 16 * F0; e0 += 8 * kLnThreads) {
-            const u64 *ptr[8];
+            int ptr[8];
             bool need[8];
             float val[8];
             int dst[8];
@@ -557,19 +578,17 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             h1[b * kS1 + kU1 * g + ul] = h;
             xpost(rec + kXA2 + b * 128 + kU1 * g + ul, wt, h);
         }
-        for (int e0 = tq; e0 < 16 * kF1; e0 += 4 * kLnThreads) {
-            const u64 *ptr[4];
+        {   // (thread: unit k of samples b, b + 4, ...; places 120 .. 127 of a row are not posted)
+            const int k = tq & 127, b0 = tq >> 7;
+            int ptr[4];
             bool need[4];
             float val[4];
             int dst[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int e = e0 + kLnThreads * i;
-                const bool in = e < 16 * kF1;
-                const int b = in ? e / kF1 : 0, k = in ? e % kF1 : 0;
-                need[i] = in && k / kU1 != g;
-                ptr[i] = rec + kXA2 + b * 128 + k;
-                dst[i] = b * kS1 + k;
+                need[i] = k < kF1 && (unsigned)(k - kU1 * g) >= (unsigned)kU1;
+                ptr[i] = rec + kXA2 + tq + kLnThreads * i;
+                dst[i] = (b0 + 4 * i) * kS1 + k;
             }
             xfetch<4>(ptr, need, val, wt);
 #pragma unroll
@@ -621,23 +640,21 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             h2[b * kS2 + kU2 * g + ul] = h;
             xpost(rec + kXA3 + b * 96 + kU2 * g + ul, wt, h);
         }
-        for (int e0 = tq; e0 < 16 * kF2; e0 += 4 * kLnThreads) {
-            const u64 *ptr[4];
-            bool need[4];
-            float val[4];
-            int dst[4];
+        {   // (thread: words tq, tq + 512 and tq + 1,024 of the 16 rows of 96)
+            int ptr[3];
+            bool need[3];
+            float val[3];
+            int dst[3];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = e0 + kLnThreads * i;
-                const bool in = e < 16 * kF2;
-                const int b = in ? e / kF2 : 0, k = in ? e % kF2 : 0;
-                need[i] = in && k / kU2 != g;
-                ptr[i] = rec + kXA3 + b * 96 + k;
+            for (int i = 0; i < 3; ++i) {
+                const int e = tq + kLnThreads * i, b = e / 96, k = e - 96 * b;
+                need[i] = k < kF2 && (unsigned)(k - kU2 * g) >= (unsigned)kU2;
+                ptr[i] = rec + kXA3 + e;
                 dst[i] = b * kS2 + k;
             }
-            xfetch<4>(ptr, need, val, wt);
+            xfetch<3>(ptr, need, val, wt);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 3; ++i)
                 if (need[i]) h2[dst[i]] = val[i];
         }
         __syncthreads();
@@ -689,7 +706,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 lossacc[0] += s * invB;
             } else {
                 gloss = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 96, wt, s);
+                xpost(recd + gs * kXDw + 26 * 512 + 96, wt, s);
             }
         }
         __syncthreads();
@@ -732,7 +749,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                     U3[j] += gv;
                 } else {
                     gd3[j] = s;
-                    xpost(recd + (int64_t)gs * kXDw + (24 + j) * 512 + tq, wt, s);
+                    xpost(recd + gs * kXDw + (24 + j) * 512 + tq, wt, s);
                 }
             }
         }
@@ -746,7 +763,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U3b += gv;
             } else {
                 gdb3 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 64 + tq, wt, s);
+                xpost(recd + gs * kXDw + 26 * 512 + 64 + tq, wt, s);
             }
         }
         __syncthreads();
@@ -783,7 +800,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                             }
                         } else {
                             gd2[4 * mt + r] = acc[mt][r];
-                            if (ul < kU2) xpost(recd + (int64_t)gs * kXDw + (16 + 4 * mt + r) * 512 + tq, wt, acc[mt][r]);
+                            if (ul < kU2) xpost(recd + gs * kXDw + (16 + 4 * mt + r) * 512 + tq, wt, acc[mt][r]);
                         }
                     }
             }
@@ -798,14 +815,14 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U2b += gv;
             } else {
                 gdb2 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + 32 + tq, wt, s);
+                xpost(recd + gs * kXDw + 26 * 512 + 32 + tq, wt, s);
             }
         }
         // delta of the own units of dense 1: the four partials in workgroup order
         {
             const bool act = tq < kU1 * 16;
             const int ul = act ? tq >> 4 : 0, b = tq & 15, k = kU1 * g + ul;
-            const u64 *ptr[4];
+            int ptr[4];
             bool need[4];
             float val[4];
 #pragma unroll
@@ -916,7 +933,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                                 }
                             } else {
                                 gd1[(2 * nl + mt) * 4 + r] = acc[nl][mt][r];
-                                if (ul < kU1) xpost(recd + (int64_t)gs * kXDw + ((2 * nl + mt) * 4 + r) * 512 + tq, wt, acc[nl][mt][r]);
+                                if (ul < kU1) xpost(recd + gs * kXDw + ((2 * nl + mt) * 4 + r) * 512 + tq, wt, acc[nl][mt][r]);
                             }
                         }
                 }
@@ -932,13 +949,13 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                 U1b += gv;
             } else {
                 gdb1 = s;
-                xpost(recd + (int64_t)gs * kXDw + 26 * 512 + tq, wt, s);
+                xpost(recd + gs * kXDw + 26 * 512 + tq, wt, s);
             }
         }
         // delta at the own samples' pooled conv-2 outputs (masked by the ReLU): both elements of
         // a thread in one batch of loads
         {
-            const u64 *ptr[8];
+            int ptr[8];
             bool need[8];
             float val[8];
 #pragma unroll
@@ -1276,13 +1293,14 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         tq = opaque(tq);
         // the partial conv-2 gradients were posted before the last phase: ask for them now, the
         // words are looked at after the conv-1 gradient below (thread: elements 156 + tq + 512 j)
-        u64 early[5][NP];
+        i2 early[5][NP];
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int e = 156 + tq + kLnThreads * j;
 #pragma unroll
             for (int i = 0; i < NP; ++i)
-                early[j][i] = __hip_atomic_load(rec3(i) + (e < kConvP ? e : 156), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                early[j][i] = xlook(rec3(i) + (e < kConvP ? e : 156), wt);
         }
         // ---- conv-1 filter gradient over the own samples: thread = (window group, channel,
         // filter row); one position per window; the bias gradient is the sum of the deltas the
@@ -1339,7 +1357,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         if (more) store_rows(xr, labr);
         {   // the conv-1 part: threads 0 .. 155
             const bool act = tq < 156;
-            const u64 *ptr[NP];
+            int ptr[NP];
             bool need[NP];
             float val[NP];
 #pragma unroll
@@ -1365,11 +1383,12 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             bool ok = true;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                ok = ok && (uint32_t)(early[j][i] >> 32) == wt.tag;
-                val[i] = __uint_as_float((uint32_t)early[j][i]);
+                const int bits = early[j][i][0];
+                ok = ok && (uint32_t)early[j][i][1] == wt.tag;
+                val[i] = __builtin_bit_cast(float, bits);
             }
             if (act && !ok) {   // not there yet when asked: fetch again (rare)
-                const u64 *ptr[NP];
+                int ptr[NP];
                 bool need[NP];
 #pragma unroll
                 for (int i = 0; i < NP; ++i) {
@@ -1391,7 +1410,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         if constexpr (S > 1) {
             // dense slices: the counterpart's gradients, the two clusters' added in cluster order,
             // so that both copies get the same update
-            const u64 *theirs = recd + (int64_t)(gs ^ kLnG) * kXDw;
+            const int theirs = recd + (gs ^ kLnG) * kXDw;
             auto both = [&](float own, float other) { return (sub == 0 ? own + other : other + own) * invB; };
             const int wave = __builtin_amdgcn_readfirstlane(tq >> 6), n = tq & 15, kq = (tq & 63) >> 4;
             const int ntile = F0 >> 4;
@@ -1399,7 +1418,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             for (int nl = 0; nl < 2; ++nl) {
                 const int nt = wave + 8 * nl;
                 if (nt >= ntile) break;
-                const u64 *ptr[8];
+                int ptr[8];
                 bool need[8];
                 float val[8];
 #pragma unroll
@@ -1418,7 +1437,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             }
             {
                 const int k = 16 * wave + n;
-                const u64 *ptr[8];
+                int ptr[8];
                 bool need[8];
                 float val[8];
 #pragma unroll
@@ -1436,7 +1455,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                     }
             }
             {   // dense 3, the biases, the loss
-                const u64 *ptr[6];
+                int ptr[6];
                 bool need[6];
                 float val[6];
                 need[0] = tq < kNC * kF2;
