@@ -505,23 +505,23 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             }
         }
         // the other workgroups' samples
-        for (int e0 = tq; e0 < 16 * F0; e0 += 8 * kLnThreads) {
-            int ptr[8];
-            bool need[8];
-            float val[8];
-            int dst[8];
+        {
+            constexpr int NA = 16 * F0 > kLnThreads ? 16 * F0 / kLnThreads : 1;   // per thread
+            int ptr[NA];
+            bool need[NA];
+            float val[NA];
+            int dst[NA];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int e = e0 + kLnThreads * i;
-                const bool in = e < 16 * F0;
-                const int b = in ? e >> lgF0 : 0, f = in ? e & (F0 - 1) : 0;
-                need[i] = in && (b >> 2) != g;
+            for (int i = 0; i < NA; ++i) {
+                const int e = tq + kLnThreads * i;
+                const int b = (e >> lgF0) & 15, f = e & (F0 - 1);   // (16 samples; threads beyond them need nothing)
+                need[i] = (16 * F0 >= kLnThreads || e < 16 * F0) && (b >> 2) != g;
                 ptr[i] = rec + kXA1 + b * 256 + f;
                 dst[i] = b * F0P + f;
             }
-            xfetch<8>(ptr, need, val, wt);
+            xfetch<NA>(ptr, need, val, wt);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < NA; ++i)
                 if (need[i]) a0[dst[i]] = val[i];
         }
         __syncthreads();
@@ -533,31 +533,24 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         {
             const int wave = __builtin_amdgcn_readfirstlane(tq >> 6), lane = tq & 63;
             const int n = lane & 15, kq = lane >> 4;
-            const int nstep = F0 >> 2, per = (nstep + 7) >> 3;      // steps in all, steps per wave
-            const int t0 = wave * per, t1 = t0 + per < nstep ? t0 + per : nstep;
+            constexpr int nstep = F0 >> 2, per = (nstep + 7) >> 3;      // steps in all, steps per wave
+            const int t0 = wave * per;
             const float *ap = a0 + n * F0P + kq;
             const float *bp0 = w1s + n * F0P + kq, *bp1 = w1s + (16 + n < kU1 ? 16 + n : kU1 - 1) * F0P + kq;
             f4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            if (F0 == 256) {
-                float av[8], b0[8], b1[8];
+            if (nstep >= 8 || t0 < nstep) {   // (16 features: four waves have a step)
+                float av[per], b0[per], b1[per];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < per; ++i) {
                     av[i] = ap[4 * (t0 + i)];
                     b0[i] = bp0[4 * (t0 + i)];
                     b1[i] = bp1[4 * (t0 + i)];
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < per; ++i) {
                     acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], b0[i], acc0, 0, 0, 0);
                     acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], b1[i], acc1, 0, 0, 0);
-                }
-            } else {
-#pragma unroll 1
-                for (int t = t0; t < t1; ++t) {
-                    const float av = ap[4 * t];
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bp0[4 * t], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bp1[4 * t], acc1, 0, 0, 0);
                 }
             }
             // lane: unit n (and 16 + n), samples 4 kq .. 4 kq + 3; unit-major with a stride of 17
@@ -878,9 +871,10 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
             }
         }
         // which of the own pooled conv-2 outputs are positive (a0 is overwritten below)
-        bool alive2[2];
+        constexpr int NE = 4 * F0 > kLnThreads ? 4 * F0 / kLnThreads : 1;   // of them per thread
+        bool alive2[NE];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NE; ++j) {
             const int e = tq + kLnThreads * j;
             alive2[j] = e < 4 * F0 && a0[(4 * g + e / F0) * F0P + e % F0] > 0.f;
         }
@@ -955,11 +949,11 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         // delta at the own samples' pooled conv-2 outputs (masked by the ReLU): both elements of
         // a thread in one batch of loads
         {
-            int ptr[8];
-            bool need[8];
-            float val[8];
+            int ptr[4 * NE];
+            bool need[4 * NE];
+            float val[4 * NE];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NE; ++j) {
                 const int e = tq + kLnThreads * j;
                 const bool act = e < 4 * F0;
                 const int s = act ? e / F0 : 0, f = act ? e % F0 : 0;
@@ -969,9 +963,9 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                     need[4 * j + i] = act;
                 }
             }
-            xfetch<8>(ptr, need, val, wt);
+            xfetch<4 * NE>(ptr, need, val, wt);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NE; ++j) {
                 const int e = tq + kLnThreads * j;
                 if (e < 4 * F0) {
                     float t = val[4 * j];
@@ -1043,12 +1037,19 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 } else {
-                    const int rows = H2 == 4 ? 4 : 1;
-#pragma unroll 1
+                    constexpr int rows = H2 == 4 ? 4 : 1;
+                    float av[rows], b0[rows], b1[rows];
+#pragma unroll
                     for (int y = 0; y < rows; ++y) {
-                        const float a1 = ap[4 * y], c0 = bp0[y * P1];
-                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, c0, acc[0], 0, 0, 0);
-                        if (TWO) acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, bp1[y * P1], acc[1], 0, 0, 0);
+                        av[y] = ap[4 * y];
+                        b0[y] = bp0[y * P1];
+                        if (TWO) b1[y] = bp1[y * P1];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int y = 0; y < rows; ++y) {
+                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[y], b0[y], acc[0], 0, 0, 0);
+                        if (TWO) acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[y], b1[y], acc[1], 0, 0, 0);
                     }
                 }
             };
