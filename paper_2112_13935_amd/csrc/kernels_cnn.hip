@@ -19,8 +19,8 @@
 // gradients) are a quarter of a recursion.  Of its 130 K clocks (16 x 16 half-width CNN, mini-batch 16): forward 33 K,
 // backward-data 37 K, filter gradients 26 K, dense layers and softmax 19 K, update and barriers 13 K.  The layer
 // engine spends 13 - 15 launches on a recursion, each a launch boundary and two to four dependent trips through memory.
-// 6 clients of that CNN with compute factors, 6 rounds: 5.93 -> 3.65 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch
-// 5, 6 rounds: 1.94 -> 0.86 ms.  Sixteen waves of 128 registers: eight of 256 took 10 - 30 % longer in the
+// 6 clients of that CNN with compute factors, 6 rounds: 5.93 -> 3.63 ms; 12 x 12, 6 and 12 channels, 3 clients, mini-batch
+// 5, 6 rounds: 1.94 -> 0.84 ms.  Sixteen waves of 128 registers: eight of 256 took 10 - 30 % longer in the
 // products, which wait for LDS.  One body for both directions of the convolutions, and steps worked out by the
 // host: with each form written out the kernel had 84 KB of code, more than the instruction cache
 // holds, and took 1.7 times as long.  The update by whole waves, filters and dense layers side by side

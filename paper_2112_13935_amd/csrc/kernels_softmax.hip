@@ -108,15 +108,15 @@ __device__ __forceinline__ float log_of_sum(float v) {
 // data, and three instructions per 64 columns cover classes 0..11 (rows 10 and 11 stay
 // zero).  The vector ALU is left with the dot products, the reductions and the softmax.
 //
-// What bounds it: with many clients instruction issue (two waves per SIMD, some 150 vector and 36
+// What bounds it: with many clients instruction issue (two waves per SIMD, some 140 vector and 36
 // matrix instructions each per recursion at D = 3072), with few clients the chain dots - wave
 // reduction - LDS hop - softmax - update, the same for every width.  So what need not be on that
 // chain is off it: U of a recursion is added while the next one's partial logits travel through
 // LDS; row numbers are hashed 48 recursions at a time; rows are asked for three recursions
 // ahead, and no load stands behind a branch or goes through the scalar cache, so that nothing
 // waits for more than the row it needs.  Measured, 1,024 clients x 3,072 columns, 40 rounds:
-// 23.8 -> 19.0 ms (2.6 -> 3.3 TB/s of rows); 4 clients x 784 columns, 20 rounds: 1.73 -> 1.43
-// ms.  Four waves with twice the columns each, two rows ahead: slower; five ahead: no faster.
+// 23.8 -> 19.0 ms, with fewer instructions in the softmax 17.7 (2.6, 3.3 and 3.5 TB/s of rows); 4 clients x 784 columns,
+// 20 rounds: 1.73 -> 1.43 -> 1.30 ms.  Four waves with twice the columns each, two rows ahead: slower; five ahead: no faster.
 //
 // The arithmetic of dz = exp(z - lse) - onehot, its sums' order included, is fixed (the GPU tests
 // hold digests of it).  Its entries add up to an error that is not centred; with features of one
