@@ -17,6 +17,7 @@
 #include "aet_internal.h"
 #include "cluster_plan.h"
 #include "cluster_turns.h"
+#include "server_list.h"
 
 using namespace aet;
 
@@ -745,9 +746,11 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
 }
 
 // This tick's arrivals in (round, client) order, staged for a kernel: by value when the
-// list is short (*pack_out = &pack), else through the pinned ring into device memory (*dev_out).
+// list is short (*pack_out = &pack) or, for the server's kernel, fits its arguments (list not NULL, *list_out = list), else
+// through the pinned ring into device memory (*dev_out).
 static aet_status stage_arrivals(aet_ctx *ctx, float scale, std::vector<Msg> *arr_out, ArrivalPack *pack,
-                                 const ArrivalPack **pack_out, const Arrival **dev_out) {
+                                 const ArrivalPack **pack_out, ArrivalList *list, const ArrivalList **list_out,
+                                 const Arrival **dev_out) {
     std::vector<Msg> &arr = *arr_out;
     arr.clear();
     for (const Msg &m : ctx->queue)
@@ -755,8 +758,19 @@ static aet_status stage_arrivals(aet_ctx *ctx, float scale, std::vector<Msg> *ar
     std::sort(arr.begin(), arr.end(), [](const Msg &x, const Msg &y) { return x.k != y.k ? x.k < y.k : x.c < y.c; });
     const int na = (int)arr.size();
     *pack_out = nullptr;
+    *list_out = nullptr;
     *dev_out = nullptr;
     if (na == 0) return AET_OK;
+    if (list && na > kArrivalPack && na <= kArrivalList) {
+        list->base = ctx->Uslot(0);
+        list->stride = ctx->Ps;
+        for (int j = 0; j < na; ++j) {
+            list->a[j].slot = arr[j].slot;
+            list->a[j].scale = (float)((double)scale * (double)arr[j].eta);
+        }
+        *list_out = list;
+        return AET_OK;
+    }
     void *slot = pack->a;
     const bool by_value = na <= kArrivalPack;
     if (!by_value && ctx->static_ws) {
@@ -820,13 +834,17 @@ aet_status aet_server_aggregate(aet_ctx *ctx, float agg_scale, int32_t *n_applie
     if (!std::isfinite(agg_scale)) return fail(ctx, AET_EINVAL, "agg_scale is not finite");
     std::vector<Msg> arr;
     ArrivalPack pack;
+    ArrivalList list;
     const ArrivalPack *by_value = nullptr;
+    const ArrivalList *list_by_value = nullptr;
     const Arrival *on_device = nullptr;
-    const aet_status st = stage_arrivals(ctx, agg_scale, &arr, &pack, &by_value, &on_device);
+    const aet_status st = stage_arrivals(ctx, agg_scale, &arr, &pack, &by_value, &list, &list_by_value, &on_device);
     if (st != AET_OK) return st;
     const int na = (int)arr.size();
     if (by_value) {
         AET_HIP(ctx, launch_server_apply_small(ctx->stream, ctx->profp(), ctx->Wg(), *by_value, na, ctx->P));
+    } else if (list_by_value) {
+        AET_HIP(ctx, launch_server_reduce_list(ctx->stream, ctx->profp(), ctx->Wg(), *list_by_value, na, ctx->P));
     } else if (on_device) {
         AET_HIP(ctx, launch_server_reduce(ctx->stream, ctx->profp(), ctx->Wg(), on_device, na, ctx->P));
     }
@@ -907,8 +925,9 @@ aet_status aet_receive(aet_ctx *ctx, float scale, int32_t *n_applied, int32_t *a
     std::vector<Msg> arr;
     ArrivalPack pack;
     const ArrivalPack *by_value = nullptr;
+    const ArrivalList *no_list = nullptr;
     const Arrival *on_device = nullptr;
-    const aet_status st = stage_arrivals(ctx, scale, &arr, &pack, &by_value, &on_device);
+    const aet_status st = stage_arrivals(ctx, scale, &arr, &pack, &by_value, nullptr, &no_list, &on_device);
     if (st != AET_OK) return st;
     if (by_value || on_device)
         AET_HIP(ctx, launch_apply_neighbour_U(ctx->stream, ctx->profp(), ctx->Wc(0), ctx->Ps, ctx->P, ctx->n,
