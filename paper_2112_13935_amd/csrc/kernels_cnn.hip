@@ -59,8 +59,6 @@ constexpr int kCnChunk = 4 * kCnThreads * kCnPrefetch;   // floats of weights st
 constexpr int kCnRow = 4096 / kCnThreads;        // floats of the next sample that a thread has on the way
 constexpr int kCnBatch = 16;       // values of a sum over workgroups or samples on the way at a time
 constexpr int kCnRed = kCnWaves * 256;   // floats of the partial sums of split tiles; two such places take turns
-constexpr int kBufferFlags = 0x00020000;
-constexpr int kAgent = 16;         // cache policy of agent scope: a load passes the L1 by, a store goes through to memory
 constexpr int kNowhere = -2147483647 - 1;   // a byte offset beyond every buffer: reads zero, writes nothing
 
 typedef int i16v __attribute__((ext_vector_type(16)));

@@ -111,31 +111,20 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
-// A client's exchange words, through a range-checked buffer: a word is a 32-bit number, and most of it an immediate or a
-// scalar, where a pointer takes three vector instructions for each of the many words of a thread.  The
-// scopes are cluster_post's.
-constexpr int kBufferFlags = 0x00020000;   // dword 3 of a raw buffer descriptor for 32-bit untyped accesses
-constexpr int kAgent = 16;                 // cache policy of agent scope: a load passes the L1 by, a store goes through to memory
 typedef int i2 __attribute__((ext_vector_type(2)));
 
+// (A word's number is most of it an immediate, where a pointer takes three vector instructions for each of the many
+// words of a thread.)
 struct Waiter {
-    __amdgpu_buffer_rsrc_t words;
+    ClusterWords words;
     uint32_t tag;
     int *errflag;
     bool dead;
     bool one_xcd;   // all workgroups of the client run on one XCD
 };
 
-__device__ __forceinline__ void xpost(int word, const Waiter &w, float v) {
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-    const u2 both = {__float_as_uint(v), w.tag};
-    if (w.one_xcd) __builtin_amdgcn_raw_buffer_store_b64(both, w.words, 8 * word, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b64(both, w.words, 8 * word, 0, kAgent);
-}
-// {value, tag}
-__device__ __forceinline__ i2 xlook(int word, const Waiter &w) {
-    return __builtin_bit_cast(i2, __builtin_amdgcn_raw_buffer_load_b64(w.words, 8 * word, 0, kAgent));
-}
+__device__ __forceinline__ void xpost(int word, const Waiter &w, float v) { w.words.post(8 * word, 0, w.tag, v, w.one_xcd); }
+__device__ __forceinline__ i2 xlook(int word, const Waiter &w) { return w.words.get(8 * word, 0); }   // {value, tag}
 
 // N words at once (the loads are in flight together); repeated until every needed word shows
 // the current step.  Words that are not needed still are ones of the client.
@@ -144,7 +133,7 @@ __device__ __forceinline__ void xfetch(const int (&p)[N], const bool (&need)[N],
     BoundedWait wait;
     for (;;) {
         i2 v[N];
-        asm volatile("" ::: "memory");   // (to the compiler these are loads like any other: not to be moved out of the loop)
+        ClusterWords::look_again();
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = xlook(p[i], w);
         bool ok = true;
@@ -262,7 +251,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
 
     constexpr int kWords = S == 1 ? kXWords : kXWords2;
     const int rec = sub * kXB3, set0 = 2 * kXB3;   // (set0: S = 2)
-    Waiter wt{__builtin_amdgcn_make_buffer_rsrc(xrec + (int64_t)(rec0 + a) * kWords, 0, 8 * kWords, kBufferFlags), tag0, errflag, false, false};
+    Waiter wt{ClusterWords(xrec, (int64_t)(rec0 + a) * kWords, kWords), tag0, errflag, false, false};
 
     // ---- adopt the global model (server form) or go on from the own replica (Wg == NULL) ----
     const float *src = Wg ? Wg : p.W;
@@ -1295,7 +1284,7 @@ k_lenet_round(const RoundParams *__restrict__ rp, int nhere, int rec0, const flo
         // the partial conv-2 gradients were posted before the last phase: ask for them now, the
         // words are looked at after the conv-1 gradient below (thread: elements 156 + tq + 512 j)
         i2 early[5][NP];
-        asm volatile("" ::: "memory");
+        ClusterWords::look_again();
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int e = 156 + tq + kLnThreads * j;

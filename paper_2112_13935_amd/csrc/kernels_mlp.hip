@@ -78,8 +78,6 @@ constexpr int kMlpPair = 512;        // 64-bit words per pair record (B*16 <= 51
 static_assert(kMlpPair % kLineWords == 0, "whole lines");
 constexpr int kRowsWave = 5;         // the wave that works out which rows come next
 constexpr int kMlpHalfTPW = 4;       // K tiles per wave when two workgroups share the columns
-constexpr int kBufferFlags = 0x00020000;   // dword 3 of a raw buffer descriptor for 32-bit untyped accesses
-constexpr int kAgent = 16;           // cache policy of agent scope: a load passes the L1 by, a store goes through to memory
 
 // Hides a value from the optimiser so that addresses derived from it are computed where
 // they are used instead of being kept in registers across the whole recursion loop.
@@ -98,35 +96,6 @@ __device__ __forceinline__ int opaque_scalar(int x) {
 __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-// A client's exchange words through a range-checked buffer: the lane's own byte offset never changes, what differs from
-// record to record is a scalar, so that a post or a poll takes no address arithmetic.  The scopes are cluster_post's.
-struct Words {
-    __amdgpu_buffer_rsrc_t r;
-    __device__ __forceinline__ Words(unsigned long long *p, int n) : r(__builtin_amdgcn_make_buffer_rsrc(p, 0, 8 * n, kBufferFlags)) {}
-    // {value, tag}.  A poll loop needs look_again() in it: to the compiler this is a load like any other
-    __device__ __forceinline__ i2 get(int at, int base) const {
-        return __builtin_bit_cast(i2, __builtin_amdgcn_raw_buffer_load_b64(r, at, base, kAgent));
-    }
-    static __device__ __forceinline__ void look_again() { asm volatile("" ::: "memory"); }
-    __device__ __forceinline__ void post(int at, int base, uint32_t tag, const f4 &v, bool one_xcd) const {   // four neighbours
-        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-        const u4 a = {__float_as_uint(v[0]), tag, __float_as_uint(v[1]), tag}, b = {__float_as_uint(v[2]), tag, __float_as_uint(v[3]), tag};
-        if (one_xcd) {
-            __builtin_amdgcn_raw_buffer_store_b128(a, r, at, base, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(b, r, at + 16, base, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128(a, r, at, base, kAgent);
-            __builtin_amdgcn_raw_buffer_store_b128(b, r, at + 16, base, kAgent);
-        }
-    }
-    __device__ __forceinline__ void post(int at, int base, uint32_t tag, float v, bool one_xcd) const {
-        typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-        const u2 word = {__float_as_uint(v), tag};
-        if (one_xcd) __builtin_amdgcn_raw_buffer_store_b64(word, r, at, base, 0);
-        else __builtin_amdgcn_raw_buffer_store_b64(word, r, at, base, kAgent);
-    }
-};
-
 // sum / max over the 16 lanes of one sample (lanes 16k .. 16k+15 of the wave), with the
 // data-parallel-primitive lane permutations inside a row: neighbours in a quad, the other
 // pair of the quad, the mirrored half row, the mirrored row
@@ -351,9 +320,9 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         }
     }
     // logit records [step parity][unit group][sample][class]
-    const Words rec(xrec + (int64_t)(rec0 + a) * 2 * kMlpMaxG * kMlpRec, 2 * kMlpMaxG * kMlpRec);
+    const ClusterWords rec(xrec, (int64_t)(rec0 + a) * 2 * kMlpMaxG * kMlpRec, 2 * kMlpMaxG * kMlpRec);
     // pair records [client][unit group][step parity][half][B * 16]
-    const Words pair(prec + ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair, 4 * kMlpPair);
+    const ClusterWords pair(prec, ((int64_t)(rec0 + a) * kMlpMaxG + g) * 4 * kMlpPair, 4 * kMlpPair);
     int dead = 0;  // not 0: the poll expired: keep going, the host will see the flag (the same for the whole wave)
     {
         bool gone = false;
@@ -449,7 +418,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             i2 v;
             BoundedWait wait;
             for (;;) {
-                Words::look_again();
+                ClusterWords::look_again();
                 v = pair.get(8 * i, base + 8 * (1 - hf) * kMlpPair);
                 if (__all((uint32_t)v[1] == tag) || dead) break;
                 __builtin_amdgcn_s_sleep(1);
@@ -489,7 +458,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
                 const int at = 8 * (gg * kMlpRec + (16 * min(bt, NBT - 1) + 15) * 16 + (C - 1));
                 BoundedWait wait;
                 for (;;) {
-                    Words::look_again();
+                    ClusterWords::look_again();
                     const bool ok = bt >= NBT || (uint32_t)rec.get(at, recpar)[1] == tag;
                     if (__all(ok) || dead) break;
                     __builtin_amdgcn_s_sleep(2);
@@ -515,7 +484,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             auto fetch = [&](auto most) __attribute__((always_inline)) {
                 constexpr int GC = decltype(most)::value;
                 i2 v[GC];
-                Words::look_again();
+                ClusterWords::look_again();
 #pragma unroll
                 for (int gg = 0; gg < GC; ++gg) v[gg] = rec.get(at, recpar + 8 * min(gg, Gn - 1) * kMlpRec);
                 __builtin_amdgcn_sched_barrier(0);
