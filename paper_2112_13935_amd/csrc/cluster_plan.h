@@ -8,6 +8,7 @@
 // the first two XCDs: 36 workgroups for 32 places, and a cluster of which only a part
 // is resident polls until another one has finished its round.
 #pragma once
+#include <stdint.h>
 
 namespace aet {
 
@@ -31,6 +32,11 @@ constexpr int softmax_batch_record_words(int workgroups, int batch) {
 // Words of a client's workgroups about where they run: one each, and the last for their answer
 constexpr int kClusterMax = 32;   // workgroups of a cluster, at most
 constexpr int kPlaces = whole_lines(kClusterMax + 1);
+
+// Steps of a round, with one tag each: a round has up to 2^31 - 1 recursions, so two steps a recursion need all of 32 bits.
+constexpr uint32_t cluster_steps(int recursions, int steps_each) { return (uint32_t)recursions * (uint32_t)steps_each; }
+// Whether fewer than `need` tags are left from `next` on (0, the cleared state, is none)
+constexpr bool tags_spent(uint32_t next, uint32_t need) { return next == 0 || next - 1u > 0xFFFFFFFFu - need; }
 
 // How many times a workgroup polls for a peer's word before it gives up: 2.2 s with polls of the XCD's L2
 // (0.26 us), twice that with polls that go through memory.  (A count and not the clock, which goes on while

@@ -292,8 +292,9 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     constexpr int AHEAD = TPW <= kMlpHalfTPW ? 2 : 1;
     f4 xreg[AHEAD][NBT][TPW];
     int lab_next = 0, lab_ahead = 0;   // labels of recursions u + 1 and u + AHEAD (of the wave that sees to the rows)
-    const int steps = SUB * p.m;
-    auto rows_of = [&](int u) -> uint32_t {   // of step u
+    using Step = typename std::conditional<SUB == 2, uint32_t, int>::type;
+    const Step steps = (Step)cluster_steps(p.m, SUB);
+    auto rows_of = [&](Step u) -> uint32_t {   // of step u
         const int64_t from = SUB == 1 ? (int64_t)u * Br : (int64_t)(u >> 1) * Br;
         const int b = SUB == 1 ? lane : B * (u & 1) + lane;
         return lane < B ? sample_row(p.key, (uint64_t)(p.q0 + from + min(b, Br - 1)), p.n_samples) : 0u;
@@ -304,7 +305,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
             for (int tt = 0; tt < TPW; ++tt) xreg[k][bt][tt] = f4{0.f, 0.f, 0.f, 0.f};
-        if (k < steps) {
+        if ((Step)k < steps) {
             const uint32_t rowv = rows_of(k);
             if (wave == kRowsWave && lane < B) {
                 const int lab = yg[rowv];
@@ -338,7 +339,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     float db1k = 0.f, db2k = 0.f;
     // x: this step's rows; their registers take the rows of step u + AHEAD (a step is a recursion, or, SUB = 2, half
     // of one: part 0 or 1)
-    auto recursion = [&](int u, const int half, f4 (&x)[NBT][TPW], const auto same) __attribute__((always_inline)) {   // same: whether the words stay in the L2 of one XCD
+    auto recursion = [&](Step u, const int half, f4 (&x)[NBT][TPW], const auto same) __attribute__((always_inline)) {   // same: whether the words stay in the L2 of one XCD
         const int ntile = opaque_scalar(nt), tail = opaque_scalar(tail_tt);
         auto park_rows = [&]() {
 #pragma unroll
@@ -643,7 +644,7 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
         lab_next = lab_ahead;
     };
     auto recursions = [&](const auto same) __attribute__((always_inline)) {
-        for (int u = 0; u < steps; ++u) {
+        for (Step u = 0; u < steps; ++u) {
             recursion(u, AHEAD == 2 ? 0 : u & 1, xreg[0], same);
             if constexpr (AHEAD == 2) {
                 if (++u == steps) break;
@@ -805,8 +806,8 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     // earlier launch may have left in the records
     // A captured launch carries its tags into every replay, where the records still hold words
     // of the replay before with the same tags: there the records are cleared ahead of it.
-    const uint32_t need = SUB * (uint32_t)max_m + 1u;
-    const bool spent = *epoch == 0 || *epoch > 0xFFFFFFFFu - need - 1u;
+    const uint32_t need = cluster_steps(max_m, SUB) + 1u;
+    const bool spent = tags_spent(*epoch, need);
     if (spent || stream_is_capturing(s)) {
         k_zero_words<<<(unsigned)((mlp_all_words(n_clients) + 255) / 256), 256, 0, s>>>(xrec, mlp_all_words(n_clients));
         e = hipGetLastError();

@@ -18,7 +18,8 @@ def plan(tmp_path_factory):
         f.write('#include "cluster_plan.h"\n#include <cstdio>\nint main() {\n'
                 "    int c, x, s;\n"
                 '    while (scanf("%d %d %d", &c, &x, &s) == 3)\n'
-                '        printf("%d\\n", c > 0 ? aet::resident_clusters(c, x, s) : c == 0 ? aet::softmax_batch_record_words(x, s)\n'
+                '        if (c < -1) printf("%u\\n", c == -2 ? aet::cluster_steps(x, s) : (uint32_t)aet::tags_spent((uint32_t)x, (uint32_t)s));\n'
+                '        else printf("%d\\n", c > 0 ? aet::resident_clusters(c, x, s) : c == 0 ? aet::softmax_batch_record_words(x, s)\n'
                 '                                                                : aet::kWaitPolls);\n}\n')
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", exe, src], check=True)
 
@@ -92,3 +93,23 @@ def test_every_poll_of_a_peer_is_bounded_so(kernel):
 def test_the_launchers_take_their_clusters_from_the_plan(kernel):
     text = open(os.path.join(CSRC, f"kernels_{kernel}.hip")).read()
     assert "per_launch" in text and "resident_clusters(" in text
+
+
+def test_steps_and_tags_of_the_longest_round(plan):
+    """A round may have 2^31 - 1 recursions.  With two steps each their number, and the tags they take, just fit 32 bits
+    without a sign; tags run from the next one to 2^32 - 1."""
+    m = 2 ** 31 - 1
+    assert plan([(-2, m, 1), (-2, m, 2), (-2, 2 ** 30, 2), (-2, 0, 2)]) == [m, 2 * m, 2 ** 31, 0]
+
+    def signed(v):
+        return v - 2 ** 32 if v >= 2 ** 31 else v
+    for need in (1, 2, 7, m + 1, 2 * m + 1):
+        nexts = {0, 1, 2, 3, m, 2 ** 32 - need - 1, 2 ** 32 - need, 2 ** 32 - need + 1, 2 ** 32 - 1} & set(range(2 ** 32))
+        for nxt in nexts:
+            fits = nxt > 0 and nxt + need - 1 <= 2 ** 32 - 1
+            assert plan([(-3, signed(nxt), signed(need))]) == [0 if fits else 1], (nxt, need)
+
+
+def test_the_mlp_round_counts_its_steps_so():
+    text = open(os.path.join(CSRC, "kernels_mlp.hip")).read()
+    assert text.count("cluster_steps(") == 2 and "tags_spent(" in text and "SUB * p.m" not in text
