@@ -175,7 +175,7 @@ Engine pick_engine(const LayerGeom *lay, int L, int B, int n, bool padded_ok = t
     const bool padded = padded_ok && n <= kPaddedClients;
     if (L == 2 && lay[0].type == AET_DENSE && lay[1].type == AET_DENSE && lay[0].relu &&
         mlp_round_supported((int)lay[0].in_size, lay[0].oc, lay[1].oc, B) &&
-        (mlp_round_exact(lay[0].oc, B) || (padded && mlp_padded_pays((int)lay[0].in_size, lay[0].oc, n))))
+        (mlp_round_exact(lay[0].oc, B) || (padded && mlp_padded_pays((int)lay[0].in_size, lay[0].oc, B, n))))
         return ENGINE_MLP;
     if (L == 1 && lay[0].type == AET_DENSE && softmax_round_supported((int)lay[0].in_size, lay[0].oc, B))
         return ENGINE_SOFTMAX;

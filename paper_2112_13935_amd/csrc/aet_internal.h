@@ -211,7 +211,7 @@ const int *softmax_batch_error_flag_ptr(void *scratch, int n_clients, int D, int
 // fused round of dense-ReLU-dense models (kernels_mlp.hip)
 bool mlp_round_supported(int D, int H, int C, int B);
 bool mlp_round_exact(int H, int B);   // no padded units or samples
-bool mlp_padded_pays(int D, int H, int n_clients);   // else: faster than the layer engine
+bool mlp_padded_pays(int D, int H, int B, int n_clients);   // else: faster than the layer engine
 size_t mlp_round_scratch_bytes(int n_clients, int B);
 // hp: HOST array of the tick's round records (they are passed on in kernel arguments)
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact,

@@ -735,12 +735,30 @@ bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0;
 //   250 units  96 (6)  0.87 .. 1.09   0.95 .. 0.99           0.91 .. 0.96
 //             256 (16) 1.76 .. 2.10   1.29 .. 1.42           0.93 .. 1.10           0.37 .. 0.46
 // (256 inputs, 250 units, 256 clients: 0.82 .. 0.89; 400: 0.67 .. 0.79.)
-// Mini-batches of 33 .. 64, which take two steps here and the same launches there, gain more: here / there at 64, 4, 48, 128
-// and 256 clients where the rule says here: 30 -> 10 0.24 0.25 0.58; 100 -> 100 0.34 0.51 0.67 0.85; 300 -> 250 0.37 0.66
-// 0.69; 784 -> 100 0.41 0.50 0.54 0.44; 890 -> 250 0.29 0.39 0.43 0.53 (33: 300 -> 250 0.39 0.74, 30 -> 10 0.28 0.29).
-bool mlp_padded_pays(int D, int H, int n_clients) {
+// Mini-batches of 33 .. 64 take two steps a recursion here and the same launches there, where the time grows with the mini-batch,
+// so that the table above does not hold for them.  Here a recursion takes a time per launch that depends on a wave's column tiles and the
+// unit groups, however few clients the last launch has; there 28 us and what the products take.  Both in us, fitted to 2,040 shapes of 30 .. 896
+// inputs, 1 .. 256 units and 17 .. 256 clients (the first that needs one launch more, for each number of launches) at 33, 48, 56 and 64
+// samples.  Time here / there, lowest and highest over the inputs, at 33 samples:
+//   units        launches: 3   4          5          6          8          16
+//     1           .66 1.08     1.20 1.22  1.28 1.28  1.34 1.40
+//    17           .66 1.01     .80 1.11   .95 1.20   1.06 1.26
+//    33           .63 .93      .74 .99    .86 1.02   .95 1.14
+//    97           .59 .80      .71 .84    .77 .87    .80 .93    .81 1.03
+//   161           .67 .95      .81 .98    .97 1.09   1.01 1.16  1.08 1.33  .77 1.23   (16 clients a launch: 11 of 16 compute units at work)
+//   250           .62 .77      .72 .91    .74 .92    .68 .96    .79 1.06   .62 1.00
+// (at 56 samples 0.8 - 0.9 of that; two launches .41 - .96.)  With the line 3 % below the layer engine's time, 10 of the 1,600 that come here
+// are slower, by up to 6 %, and 69 of the others would be more than 8 % faster, by up to 1.4 times (130 to 170 units, over 176 clients).
+static bool mlp_two_steps_pay(int D, int H, int B, int n_clients, int G, int launches) {
+    const int tiles = ((D + 15) / 16 + kMlpWaves - 1) / kMlpWaves;
+    const double here = launches * (5.4 + (D > 256 ? 1.15 : 0) + 1.5 * tiles + (G > 4 ? 0.65 : 0) + (G > 8 ? 1.1 : 0));
+    const double there = 28.2 + n_clients * (5.9e-6 * H * D + 4.1e-6 * B * D + 1.8e-5 * B * H);
+    return launches <= 2 || here <= 0.97 * there;
+}
+bool mlp_padded_pays(int D, int H, int B, int n_clients) {
     const int G = (H + 15) / 16, fit = resident_clusters(256, 8, G), per = fit < kMlpPack ? fit : kMlpPack;
     const int launches = (n_clients + per - 1) / per;
+    if (B > 32 && !mlp_two_steps_pay(D, H, B, n_clients, G, launches)) return false;
     if (launches <= 3 || D >= 768) return true;
     return G > 1 && (launches <= 5 || D >= 384 || (D >= 256 && launches <= 12) || (D >= 100 && launches <= 8));
 }

@@ -254,6 +254,18 @@ def test_padded_mlp_where_it_is_the_faster_engine(gpu, n, d, hidden, launches):
     assert _launches(gpu, wl, "k_mlp_round") == launches
 
 
+@pytest.mark.parametrize("n,d,hidden,batch,launches", [
+    (256, 784, 10, 33, 0), (256, 784, 10, 48, 0), (192, 896, 10, 33, 0),   # 1.17, 1.04 and 1.0 of the layer engine's time
+    (241, 384, 17, 33, 0), (169, 256, 161, 33, 0), (169, 100, 160, 33, 0),   # 1.20, 1.35 and 1.20
+    (96, 784, 10, 33, 2), (144, 784, 10, 64, 3), (192, 784, 100, 33, 6),   # 0.66, 0.68 and 0.69
+    (144, 30, 10, 33, 3), (256, 784, 250, 33, 16), (48, 896, 16, 33, 1),
+    (49, 896, 1, 33, 2), (257, 784, 250, 64, 0),
+])
+def test_mini_batches_in_two_steps_where_they_are_faster(gpu, n, d, hidden, batch, launches):
+    wl = W.config2(n_clients=n, n_total=n * 8, d=d, hidden=hidden, batch=batch, rounds=1, a=0, b=batch)
+    assert _launches(gpu, wl, "k_mlp_round") == launches
+
+
 @pytest.mark.parametrize("n,hw,batch,launches", [
     (128, 16, 1, 2), (129, 16, 1, 0), (129, 16, 8, 3), (129, 20, 17, 0), (129, 16, 28, 5), (129, 28, 4, 3), (129, 28, 3, 0),
     (129, 28, 17, 5), (257, 28, 4, 0),
