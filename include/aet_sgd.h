@@ -302,8 +302,8 @@ aet_status aet_reset(aet_ctx *ctx);
  *     they run as below.
  *     PRECONDITION: all workgroups of a cluster must be resident on the GPU together.  The
  *     launcher sizes its launches for an otherwise idle GPU; contexts of one process on
- *     several streams take turns with these launches, except that those of small convolutional networks run
- *     side by side where every XCD has a compute unit for each of their workgroups there.  If other work occupies compute
+ *     several streams take turns with these launches, except that those of small convolutional networks and
+ *     dense-ReLU-dense models run side by side where every XCD has a compute unit for each of their workgroups there.  If other work occupies compute
  *     units at the same time for seconds (a long kernel, a compute-unit mask), or waits in
  *     the same way (another process with such a context, a graph of captured rounds replayed
  *     beside other rounds), a cluster may not become resident.  The wait of a workgroup for

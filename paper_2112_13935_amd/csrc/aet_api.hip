@@ -339,9 +339,10 @@ struct aet_ctx {
             return e != hipSuccess ? e : hipStreamWaitEvent(stream, ev, 0);
         }, launch);
     }
+    // clusters of one size, wherever the queue begins
     template <class Launch>
     hipError_t clustered(Launch launch) {
-        return clustered(ClusterTurns<hipStream_t>::Need(), [&](const ClusterTurns<hipStream_t>::Place &) { return launch(); });
+        return clustered(turn.need, [&](const ClusterTurns<hipStream_t>::Place &) { return launch(); });
     }
     std::string err;
     Profiler prof;
@@ -559,6 +560,10 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
     if (e == hipSuccess && ctx->engine == ENGINE_CNN)
         e = cnn_cluster_need(ctx->lay, ctx->L, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.least, &ctx->turn.need.most);
     ctx->turn.need.clients = n_clients;
+    if (e == hipSuccess && ctx->engine == ENGINE_MLP) {
+        e = mlp_cluster_need((int)ctx->lay[0].in_size, ctx->lay[0].oc, n_clients, &ctx->turn.need.cus, &ctx->turn.need.clients, &ctx->turn.need.least);
+        ctx->turn.need.most = ctx->turn.need.least;
+    }
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
         e = softmax_batch_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, (int)ctx->lay[0].in_size, ctx->B);
     // global model and every replica start as w0

@@ -217,6 +217,9 @@ size_t mlp_round_scratch_bytes(int n_clients, int B);
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact,
                             int max_m, const float *Wg, int D, int H, int C, int B, void *scratch,
                             int n_clients, uint32_t *epoch);
+// What a context's launches hold, for others to go beside them: compute units of an XCD (0: nothing goes beside them),
+// clients, each counted on the XCD that has most, and workgroups of a client
+hipError_t mlp_cluster_need(int D, int H, int n_clients, int *cus, int *clients, int *size);
 hipError_t mlp_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B);
 const int *mlp_error_flag_ptr(void *scratch, int n_clients, int B);
 // fused round of LeNet-5-style models (kernels_lenet.hip); dp: DEVICE array of round records

@@ -705,6 +705,8 @@ __global__ void k_zero_words(unsigned long long *p, size_t n) {
 }
 
 static int mlp_tpw(int D) { return (D + 15) / 16 <= 2 * kMlpWaves ? 2 : kMlpMaxTPW; }
+// whether launch_mlp_round gives a unit group two workgroups where there is room
+static bool mlp_halves(int D) { return mlp_tpw(D) != 2 && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW; }
 
 static size_t mlp_lds_bytes_tpw(int tpw, int B) {
     const int ld = 16 * kMlpWaves * tpw + 4;
@@ -858,7 +860,7 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     const bool full = D == 16 * kMlpWaves * mlp_tpw(D);   // no pad tiles
     // wide inputs: two workgroups per unit group, half of the columns each, when every active
     // client gets its 2 G workgroups resident in one launch
-    const bool pad = !mlp_round_exact(H, B), half = !small && ((D + 15) / 16 + 1) / 2 <= kMlpWaves * kMlpHalfTPW;
+    const bool pad = !mlp_round_exact(H, B), half = mlp_halves(D);
     if (B > 32) {
 #define AET_MLP_TWO(tpw, fast_, hf, ...) mlp_launch<2, tpw, fast_, false, hf, true, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)
         if (half) {
@@ -894,6 +896,19 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     AET_MLP_CASE(2, kMlpMaxTPW);
 #undef AET_MLP_CASE
 #undef AET_MLP
+}
+
+hipError_t mlp_cluster_need(int D, int H, int n_clients, int *cus, int *clients, int *size) {
+    int dev = 0, all = 0, xcds = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&all, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = device_xcds(&xcds);
+    if (e != hipSuccess) return e;
+    const ClusterHold hold = dense_cluster_hold(xcds == 8 ? all / xcds : 0, (H + 15) / 16, mlp_halves(D), n_clients);
+    *cus = hold.workgroups ? all / xcds : 0;
+    *clients = hold.clients;
+    *size = hold.workgroups;
+    return hipSuccess;
 }
 
 hipError_t mlp_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B) {

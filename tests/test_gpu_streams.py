@@ -35,6 +35,11 @@ MIXES = {
     "four alike": lambda: [cnn(6, 8, 16, 64, 8, 12) for _ in range(4)],
     # an XCD each
     "single clients": lambda: [cnn(1, 16, 16, 64, 32) for _ in range(3)] + [cnn(1, 8, 16, 64, 24), cnn(1, 12, 6, 18, 5)],
+    # dense models: beside each other where there is room; two steps a recursion in the first four
+    "dense models": lambda: [W.config2(n_clients=n, n_total=n * 70, d=d, hidden=h, batch=b, rounds=12, a=0, b=2 * b)
+                             for n, d, h, b in ((1, 30, 10, 64), (4, 100, 100, 48), (1, 784, 100, 64), (8, 784, 128, 33), (3, 50, 32, 16), (9, 300, 240, 20))],
+    "small CNNs and dense models": lambda: [cnn(3, 12, 6, 18, 5), cnn(1, 16, 16, 64, 32)] + [
+        W.config2(n_clients=n, n_total=n * 70, d=d, hidden=40, batch=b, rounds=8, a=0, b=2 * b) for n, d, b in ((2, 60, 64), (5, 530, 33))],
     "small CNNs and an MLP": lambda: [cnn(3, 12, 6, 18, 5), cnn(9, 8, 8, 32, 4),
                                       W.config2(n_clients=8, n_total=480, d=784, hidden=256, batch=16, rounds=6, a=16, b=32)],
 }
@@ -141,3 +146,39 @@ def test_contexts_on_their_own_streams(mix):
         assert torch.equal(a.cpu(), b)
         assert np.isfinite(b.numpy()).all()
         lib.aet_destroy()
+
+
+def test_dense_models_do_not_wait_for_each_other():
+    """A short job on another stream ends while a long one of one client is under way.  (Four hardware queues serve all
+    streams: one of several short ones has another queue than the long one.)"""
+    import torch
+    from paper_2112_13935_amd.binding import AetSgd
+    from paper_2112_13935_amd.runner import upload
+
+    def context(recursions):
+        wl = W.config2(n_clients=1, n_total=200, d=100, hidden=100, batch=64, rounds=1, a=0, b=64 * recursions)
+        X, y = upload(wl)
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        return wl, AetSgd(wl.model, X, y, wl.w0, wl.seed, max_inflight=1, max_rounds=1, stream=stream), stream
+
+    def job(wl, lib, stream):
+        with torch.cuda.stream(stream):
+            lib.aet_reset()
+            lib.aet_run_ticks(wl.a, wl.b, wl.rounds, wl.eta0, wl.beta, wl.power, wl.agg_scale)
+            return stream.record_event()
+    long_one, short = context(20000), [context(3) for _ in range(4)]   # 170 ms and 30 us
+    for j in [long_one] + short:
+        job(*j).synchronize()
+    end = job(*long_one)
+    ends = [job(*j) for j in short]
+    ahead = 0
+    for e in ends:
+        while not e.query():
+            pass
+        ahead += not end.query()
+    end.synchronize()
+    for _, lib, _ in [long_one] + short:
+        lib.aet_synchronize()
+        lib.aet_destroy()
+    assert ahead >= 1
