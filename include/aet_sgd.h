@@ -288,22 +288,23 @@ aet_status aet_reset(aet_ctx *ctx);
  *     workgroup per client runs the whole round with the replica in registers; the same
  *     with batch 2 to 64 and up to 512 inputs;
  *   - softmax regression with batch 2 to 64 and more inputs (up to 3072), dense-ReLU-dense
- *     models (batch up to 32, hidden width up to 256, up to 896 inputs, up to 16 classes),
+ *     models (batch up to 64, hidden width up to 256, up to 896 inputs, up to 16 classes),
  *     LeNet-5-style models (28 x 28, 20 x 20 or 16 x 16 images, batch up to 32) and small convolutional
  *     networks (up to seven 3 x 3 convolutions with padding 1 on maps of up to 32 x 32, each with
  *     or without a pooling layer behind it, then one hidden dense layer and up to 64 classes,
  *     where a sample's maps fit a compute unit's 160 KB of LDS): a CLUSTER of workgroups
  *     per client, up to 32 of them, which is a whole XCD, runs the whole round and exchanges partial sums
  *     or, small convolutional networks, gradients and weights through the workspace.
- *     Widths that are no multiple of 16 and batches other than 16 (and 32,
- *     dense-ReLU-dense) are padded: for up to 256 clients, where that is faster, and where
- *     the workspace has room (aet_workspace_bytes counts it); small convolutional networks run so
- *     where that is faster (which depends on widths, clients and batch) and where there is room; else
- *     they run as below.
+ *     Widths that are no multiple of 16 and batches other than 16 (and 32, dense-ReLU-dense) are padded; so are
+ *     dense-ReLU-dense batches of 33 to 64, which go in two steps of 32 samples.  Padded models run so for up to 256
+ *     clients, where that is faster, and where the workspace has room (aet_workspace_bytes counts it); small
+ *     convolutional networks run so where that is faster (which depends on widths, clients and batch) and where
+ *     there is room; else they run as below.
  *     PRECONDITION: all workgroups of a cluster must be resident on the GPU together.  The
  *     launcher sizes its launches for an otherwise idle GPU; contexts of one process on
  *     several streams take turns with these launches, except that those of small convolutional networks and
- *     dense-ReLU-dense models run side by side where every XCD has a compute unit for each of their workgroups there.  If other work occupies compute
+ *     dense-ReLU-dense models run side by side where every XCD has a compute unit for each of their
+ *     workgroups there.  If other work occupies compute
  *     units at the same time for seconds (a long kernel, a compute-unit mask), or waits in
  *     the same way (another process with such a context, a graph of captured rounds replayed
  *     beside other rounds), a cluster may not become resident.  The wait of a workgroup for

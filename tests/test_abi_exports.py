@@ -76,3 +76,25 @@ def test_room_for_split_weights_only_where_they_are_used():
     assert room(W.cnn32_model(64, hw=16, width=16), 32) == 32 * 27648 * (1 + 2 + 2)
     # too few tiles with every client at work
     assert room(W.cnn32_model(16, hw=16, width=16, fc=64), 6) == 0
+
+
+def test_header_names_the_batches_that_run_in_clusters():
+    """Callers of a model that runs in clusters have to know it: a precondition comes with it, and records in the workspace."""
+    import workloads as W
+    from paper_2112_13935_amd.binding import load_library, model_desc
+    lib = load_library()
+    text = re.sub(r"\n \* +", " ", open(os.path.join(ROOT, "include", "aet_sgd.h")).read())
+    dense = int(re.search(r"dense-ReLU-dense models \(batch up to (\d+),", text).group(1))
+    lenet = int(re.search(r"LeNet-5-style models \([^)]*batch up to (\d+)\)", text).group(1))
+
+    def records(model):
+        sizes = []
+        for layers in (0, 1):
+            lib.aet_test_select_kernels(layers, 0)
+            try:
+                sizes.append(lib.aet_workspace_bytes(ctypes.byref(model_desc(model)), 3, 1, 1))
+            finally:
+                lib.aet_test_select_kernels(0, 0)
+        return sizes[0] > sizes[1]
+    assert records(W.mlp_model(50, 20, 10, dense)) and not records(W.mlp_model(50, 20, 10, dense + 1))
+    assert records(W.lenet_model(lenet, 16)) and not records(W.lenet_model(lenet + 1, 16))
