@@ -22,6 +22,8 @@ CASES = {
     "softmax, mini-batch 20, clusters of 3": softmax_batch,
     "dense-ReLU-dense 50-32-10": lambda: W.config2(n_clients=4, n_total=200, d=50, hidden=32, batch=16, rounds=3, a=16, b=32),
     "padded 600-40-10": lambda: W.config2(n_clients=4, n_total=200, d=600, hidden=40, batch=20, rounds=3, a=20, b=40),
+    "two steps 50-32-10": lambda: W.config2(n_clients=4, n_total=200, d=50, hidden=32, batch=40, rounds=3, a=40, b=40),
+    "two steps 600-40-10": lambda: W.config2(n_clients=4, n_total=300, d=600, hidden=40, batch=64, rounds=3, a=64, b=64),
     "one round": lambda: W.config2(n_clients=4, n_total=200, d=600, hidden=40, batch=20, rounds=1, a=0, b=80),
     "LeNet 16 x 16, mini-batch 16": lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=16, rounds=2, a=16, b=32),
     "LeNet 16 x 16, mini-batch 20": lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=20, rounds=2, a=20, b=40),

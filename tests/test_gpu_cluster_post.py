@@ -20,6 +20,9 @@ CASES = {
     "mlp_one_group": lambda: W.config2(n_clients=9, n_total=9 * 100, d=50, hidden=16, rounds=4),
     "mlp_padded_17_groups_of_7": lambda: W.config2(n_clients=17, n_total=17 * 60, hidden=100, batch=20, rounds=3, a=20, b=20),
     "mlp_16_groups": lambda: W.config2(n_clients=2, n_total=2 * 60, d=300, hidden=256, batch=16, rounds=3, a=16, b=16),
+    "mlp_two_steps": lambda: W.config2(n_clients=9, n_total=9 * 80, d=50, hidden=100, batch=48, rounds=3, a=48, b=48),
+    "mlp_two_steps_two_halves": lambda: W.config2(n_clients=3, n_total=3 * 80, d=784, hidden=128, batch=64, rounds=3, a=64, b=64),
+    "mlp_two_steps_seven_tiles": lambda: W.config2(n_clients=9, n_total=9 * 80, d=688, hidden=256, batch=50, rounds=3, a=50, b=50),
     "lenet": lambda: W.config3(n_clients=3, n_per=60, rounds=3),
     "lenet_two_clusters": lambda: W.config3(n_clients=3, n_per=60, batch=20, rounds=3, a=20, b=20),
     "softmax_cluster_of_six": lambda: _softmax(3, 3072, 20),

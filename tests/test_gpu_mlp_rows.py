@@ -56,6 +56,8 @@ def test_neighbouring_rows_stay_out(oracle_libs, d):
     (2, 784, 32, 64),    # ... whole tiles
     (9, 700, 256, 50),   # seven tiles a wave: sixteen unit groups, more clients than are resident two by two
     (5, 150, 240, 37),   # more unit groups than are fetched at a time
+    (9, 688, 256, 50),   # seven tiles a wave in whole pieces
+    (48, 784, 100, 64),  # ... seven unit groups, two launches
 ])
 def test_mini_batches_in_two_steps(oracle_libs, n, d, hidden, batch):
     from oracle import Oracle
@@ -64,6 +66,19 @@ def test_mini_batches_in_two_steps(oracle_libs, n, d, hidden, batch):
     wl = W.config2(n_clients=n, n_total=n * 90, d=d, hidden=hidden, batch=batch, rounds=4, a=batch, b=0)
     if n == 3:
         wl.compute_factor = np.array([1, 2, 1], dtype=np.int32)
+    run, orc = Run(wl), Oracle(wl, "f64")
+    lockstep(wl, run, orc)
+    run.close()
+
+
+@pytest.mark.parametrize("n,d,hidden,batch", [(4, 60, 40, 50), (3, 784, 100, 33), (9, 688, 256, 64)])
+def test_mini_batches_in_two_steps_on_a_ring(oracle_libs, n, d, hidden, batch):
+    """Peer to peer: rounds that go on from the own replica."""
+    from oracle import Oracle
+    from paper_2112_13935_amd.runner import Run
+    from parity import lockstep
+    wl = W.config2(n_clients=n, n_total=n * 90, d=d, hidden=hidden, batch=batch, rounds=3, a=batch, b=batch)
+    wl.topology = W.ring_topology(n)
     run, orc = Run(wl), Oracle(wl, "f64")
     lockstep(wl, run, orc)
     run.close()

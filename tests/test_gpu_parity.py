@@ -103,8 +103,9 @@ def small_cases():
     cases["softmax_1024_columns"] = wl
     wl = W.config1(n_clients=2, n_per=40, d=513, rounds=3, a=2, b=2)
     cases["softmax_513_columns"] = wl
-    # layer engine, dense layers with 16-byte aligned rows (the float4 kernels) and mini-batches
-    # of 32 (two of four sample tiles real) and 64 (all four)
+    # dense layers with 16-byte aligned rows and mini-batches of 32 and 64.  (The names are from when these and the
+    # next two ran on the layer engine; they are padded rounds of the dense-ReLU-dense kernel now, 64 samples in two
+    # steps.  test_gpu_round_edges.py has the same shapes on the layer engine.)
     wl = W.config2(n_clients=3, n_total=3 * 90, d=52, hidden=24, batch=32, rounds=3, a=32, b=32)
     cases["mlp_layers_aligned_b32"] = wl
     wl = W.config2(n_clients=2, n_total=2 * 150, d=36, hidden=40, batch=64, rounds=3, a=64, b=64)

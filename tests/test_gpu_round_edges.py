@@ -143,7 +143,8 @@ def test_conv_backward_in_one_launch(gpu, oracle_libs, layer_engine, n, hw, widt
     lambda: W.config2(n_clients=3, n_total=150, d=50, hidden=24, batch=4, rounds=3, a=4, b=8),
     lambda: W.config3(n_clients=2, n_per=40, hw=16, batch=20, rounds=2, a=20, b=20),
     lambda: _mini_batch_softmax(n=3, d=1100, batch=20),
-], ids=["cnn", "mlp", "lenet", "softmax"])
+    lambda: W.config2(n_clients=3, n_total=300, d=50, hidden=24, batch=50, rounds=3, a=50, b=50),
+], ids=["cnn", "mlp", "lenet", "softmax", "mlp_two_steps"])
 def test_smallest_workspace(gpu, oracle_libs, monkeypatch, make):
     """A workspace that holds the layer engine's needs and nothing more is still accepted: the
     exchange records of the padded rounds and the partial sums of every layer apart are taken
@@ -313,7 +314,8 @@ def test_mini_batch_softmax_keeps_the_precision_of_the_layer_engine(gpu, n, d, b
     lambda: W.config2(n_clients=60, n_total=60 * 100, d=60, hidden=30, batch=4, rounds=8, a=4, b=20),
     lambda: W.config2(n_clients=64, n_total=64 * 100, d=100, hidden=60, batch=20, rounds=8, a=20, b=20),
     lambda: W.config3(n_clients=32, n_per=100, hw=16, batch=4, rounds=6, a=8, b=8),
-], ids=["mlp_b4", "mlp_b20", "lenet_b4"])
+    lambda: W.config2(n_clients=64, n_total=64 * 100, d=100, hidden=60, batch=50, rounds=8, a=50, b=50),
+], ids=["mlp_b4", "mlp_b20", "lenet_b4", "mlp_b50"])
 def test_padded_rounds_keep_the_precision_of_the_layer_engine(gpu, make):
     """The entries of d(logits) should add up to zero, so the sum of the last layer's biases should
     stay; what it drifts by is the rounding of exp and log, not centred.  The padded rounds took
