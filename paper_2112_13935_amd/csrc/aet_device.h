@@ -33,6 +33,17 @@ __device__ __forceinline__ gcf_ptr as_global(const float *p) { return (gcf_ptr)p
 __device__ __forceinline__ gf_ptr as_global(float *p) { return (gf_ptr)p; }
 __device__ __forceinline__ gci_ptr as_global(const int32_t *p) { return (gci_ptr)p; }
 
+// Hides a value from the optimiser, so that what follows from it (addresses) is worked out where it is used
+// instead of being kept in registers across a loop; the same for a scalar, by scalar instructions.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ int opaque_scalar(int x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -128,14 +128,6 @@ __device__ __forceinline__ void put1(__amdgpu_buffer_rsrc_t r, int at, int base,
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, at, 4 * base, kAgent);
 }
 
-// Hides a scalar from the optimiser: a step's third record is then loaded where it is used.  All three at once fill half of
-// the scalar registers, and what they push out comes back through vector ones.  Us a job: 3 clients, 12 x 12 images, 6 channels 853 ->
-// 841; 8, 8 x 8, 6 channels 592 -> 582; 6, 16 x 16, 16 channels 3,662 -> 3,630; 20, 12 x 12, 24 channels 1,403 -> 1,389.
-__device__ __forceinline__ int scalar(int x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
 __device__ __forceinline__ f4 mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // ---- sums over the lanes of a wave: lane swaps of gfx950 between rows, DPP inside a row of 16 -----------
@@ -668,7 +660,10 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, int first, cons
                             }
                         });
                 // ---- gradient of the filters ---------------------------------------------------------------------
-                const i16v Q = g.step[scalar(t)].g;
+                // (hidden, so that a step's third record is loaded here: all three at once fill half of the scalar registers, and what they
+                // push out comes back through vector ones.  Us a job: 3 clients, 12 x 12 images, 6 channels 853 -> 841; 8, 8 x 8, 6
+                // channels 592 -> 582; 6, 16 x 16, 16 channels 3,662 -> 3,630; 20, 12 x 12, 24 channels 1,403 -> 1,389.)
+                const i16v Q = g.step[opaque_scalar(t)].g;
                 if (Q[G_TILES]) {
                     const int ni = Q[G_NI], per = Q[G_PER];
                     deal_tiles(Q[G_TILES], Q[G_LG], lds + g.red + kCnRed,

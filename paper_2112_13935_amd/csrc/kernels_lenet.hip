@@ -86,7 +86,7 @@ constexpr int kXWords2 = 2 * kXB3 + 2 * kXSet;
 static_assert(kXWords % kLineWords == 0 && kXWords2 % kLineWords == 0, "whole lines");
 
 struct LenetDims {
-    int H0, P1, H2, P2, F0, lgF0;    // input side, sides after pool 1 / conv 2 / pool 2, F0 = 16 P2^2 = 2^lgF0
+    int H0, P1, H2, P2, F0;          // input side, sides after pool 1 / conv 2 / pool 2, F0 = 16 P2^2
     int64_t o_f1, o_f2, o_f3;        // offsets of the dense layers in the flat parameter vector
 };
 
@@ -103,12 +103,6 @@ __device__ __forceinline__ float row16_max_ln(float v) {
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)));
     v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)));
     return v;
-}
-
-// Hides a value from the optimiser so that what is derived from it is computed where it is used.
-__device__ __forceinline__ int opaque(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
 }
 
 typedef int i2 __attribute__((ext_vector_type(2)));
@@ -1586,7 +1580,6 @@ bool lenet_dims(const LayerGeom *lay, int L, int B, LenetDims *d) {
     // 256 features)
     if (d->H0 != 16 && d->H0 != 20 && d->H0 != 28) return false;
     if (d->P1 != (d->H0 - 4) / 2 || d->H2 != d->P1 - 4 || d->P2 != d->H2 / 2) return false;
-    d->lgF0 = d->F0 == 16 ? 4 : d->F0 == 64 ? 6 : 8;
     if ((int64_t)d->F0 != f1.in_size) return false;
     d->o_f1 = f1.w_off; d->o_f2 = f2.w_off; d->o_f3 = f3.w_off;
     if (c1.w_off != 0 || c1.b_off != 150 || c2.w_off != 156 || c2.b_off != 2556 || f1.w_off != kConvP) return false;
@@ -1638,8 +1631,9 @@ bool lenet_round_exact(int B) { return B == kLnB; }
 //   160          16 x 16  0.78 0.67 0.56 | 0.73 0.63   20 x 20  0.97 0.81 0.69 | 0.88 0.75
 //   192          16 x 16  0.76 0.65 0.50 | 0.81 0.68   20 x 20  0.93 0.78 0.61 | 0.93 0.77   28 x 28  1.09 0.79 0.59 | 0.86 0.68
 //   256          16 x 16  0.83 0.67 0.54 | 0.90 0.74   20 x 20  0.99 0.80 0.65 | 1.03 0.84   28 x 28  1.00 0.75 0.57 | 0.84 0.65
-// The line for 16 x 16 and 20 x 20 is that of the form with their sizes at run time (1.18 and 1.27 at 192 and 256 clients of
-// 20 x 20, mini-batch 1); it is on the safe side now.
+// The line for 16 x 16 and 20 x 20 was drawn for a form with their sizes at run time (1.18 and 1.27 at 192 and 256 clients of
+// 20 x 20, mini-batch 1).  By the present figures, 0.50 - 0.99 at mini-batches up to 16, it could lie further out: it stays where it is
+// because models beyond it would get other bits, not for speed.
 bool lenet_padded_pays(const LayerGeom &conv1, int B, int n_clients) {
     if (n_clients <= 128) return true;
     if (conv1.ih >= 28) return B >= 4;

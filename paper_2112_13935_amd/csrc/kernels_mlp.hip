@@ -79,20 +79,6 @@ static_assert(kMlpPair % kLineWords == 0, "whole lines");
 constexpr int kRowsWave = 5;         // the wave that works out which rows come next
 constexpr int kMlpHalfTPW = 4;       // K tiles per wave when two workgroups share the columns
 
-// Hides a value from the optimiser so that addresses derived from it are computed where
-// they are used instead of being kept in registers across the whole recursion loop.
-__device__ __forceinline__ int opaque(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
-// The same for a scalar: what follows from it is worked out by scalar instructions where it is used (kept across the loop
-// it would fill the scalar registers, and what is spilled comes back through vector ones).
-__device__ __forceinline__ int opaque_scalar(int x) {
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
 __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -723,7 +709,8 @@ bool mlp_round_supported(int D, int H, int C, int B) {
 
 bool mlp_round_exact(int H, int B) { return (B == 16 || B == 32) && H % 16 == 0; }
 
-// (The ratios are those of the form that had one mini-batch ahead; the present one is 1.05 to 1.6 times as fast.)
+// (The ratios are those of the form that had one mini-batch ahead; the present one is 1.05 to 1.6 times as fast, so the line could lie
+// further out.  It stays because models beyond it would get other bits.)
 // The layer engine's launches take all clients, these as many as are resident (at most kMlpPack)
 // and follow one another, so it catches up with many clients, the sooner the smaller the
 // model.  Time here / there per recursion at mini-batches of 1 to 31, launches in brackets:

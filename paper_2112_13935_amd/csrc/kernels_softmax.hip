@@ -85,9 +85,9 @@ __device__ __forceinline__ float row_max_dpp(float v) {
     return v;
 }
 
-// __logf of a sum of exponentials, bit for bit: ln 2 in two parts times the unit's base-2 logarithm.  The scaling for
-// arguments below 2^-126 is left out, five instructions of the chain: the largest exponential is 1, so the sum is
-// 1 .. 10 (0 where every logit lies below -3e38, or NaN).  Us a job: 4 clients x 784 columns 1,435 -> 1,424; 5 x 60 943 -> 909;
+// __logf of a sum of exponentials, bit for bit as the AMD compiler expands it: the unit's base-2 logarithm times ln 2 in two parts,
+// the products' rounding caught by fused multiply-adds.  Its scaling for arguments below 2^-126 is left out, five instructions of the chain:
+// the largest exponential is 1, so the sum is 1 .. 10, or NaN where the largest logit is not finite.  Us a job: 4 clients x 784 columns 1,435 -> 1,424; 5 x 60 943 -> 909;
 // 346 x 114 1,487 -> 1,428; 1,024 x 3,072, 10 rounds 1,852 -> 1,833.
 __device__ __forceinline__ float log_of_sum(float v) {
     const float y = __builtin_amdgcn_logf(v), ln2 = __uint_as_float(0x3f317217u), rest = __uint_as_float(0x3377d1cfu);

@@ -15,6 +15,7 @@ struct ArrivalList {
         float scale;
     } a[kArrivalList];
 };
+static_assert(sizeof(ArrivalList) + 24 <= 4096, "the kernel's other arguments: a model, two lengths");
 
 // launch_server_reduce with the list by value, kArrivalPack < n_arr <= kArrivalList
 hipError_t launch_server_reduce_list(hipStream_t s, Profiler *prof, float *Wg, const ArrivalList &list, int n_arr, int64_t P);
