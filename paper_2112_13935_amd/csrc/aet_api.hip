@@ -314,7 +314,7 @@ struct aet_ctx {
     struct Turn : ClusterTurns<hipStream_t>::Member {
         ClusterTurns<hipStream_t> *among = nullptr;
         ClusterTurns<hipStream_t>::Need need;
-        hipEvent_t ev = nullptr, mark = nullptr;   // none in a context on the library's own workspace; mark: only of launches that go beside others
+        hipEvent_t ev = nullptr, mark = nullptr;   // none in a context on the library's own workspace; mark: only of launches that hold now more, now less beside others
     };
     Turn turn;
     // The cluster launch, beside those that other contexts made on other streams or behind them.  (Under
