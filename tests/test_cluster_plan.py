@@ -104,8 +104,8 @@ def test_steps_and_tags_of_the_longest_round(plan):
     def signed(v):
         return v - 2 ** 32 if v >= 2 ** 31 else v
     for need in (1, 2, 7, m + 1, 2 * m + 1):
-        nexts = {0, 1, 2, 3, m, 2 ** 32 - need - 1, 2 ** 32 - need, 2 ** 32 - need + 1, 2 ** 32 - 1} & set(range(2 ** 32))
-        for nxt in nexts:
+        nexts = {0, 1, 2, 3, m, 2 ** 32 - need - 1, 2 ** 32 - need, 2 ** 32 - need + 1, 2 ** 32 - 1}
+        for nxt in (x for x in nexts if 0 <= x < 2 ** 32):
             fits = nxt > 0 and nxt + need - 1 <= 2 ** 32 - 1
             assert plan([(-3, signed(nxt), signed(need))]) == [0 if fits else 1], (nxt, need)
 
