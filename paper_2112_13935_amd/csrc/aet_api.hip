@@ -314,6 +314,7 @@ struct aet_ctx {
     struct Turn : ClusterTurns<hipStream_t>::Member {
         ClusterTurns<hipStream_t> *among = nullptr;
         ClusterTurns<hipStream_t>::Need need;
+        int begins = -1;   // the XCD of the present launch's first client, or below 0: wherever the queue begins
         hipEvent_t ev = nullptr, mark = nullptr;   // none in a context on the library's own workspace; mark: only of launches that hold now more, now less beside others
     };
     Turn turn;
@@ -339,10 +340,13 @@ struct aet_ctx {
             return e != hipSuccess ? e : hipStreamWaitEvent(stream, ev, 0);
         }, launch);
     }
-    // clusters of one size, wherever the queue begins
+    // clusters of one size; turn.begins: where
     template <class Launch>
     hipError_t clustered(Launch launch) {
-        return clustered(turn.need, [&](const ClusterTurns<hipStream_t>::Place &) { return launch(); });
+        return clustered(turn.need, [&](const ClusterTurns<hipStream_t>::Place &place) {
+            turn.begins = place.first;
+            return launch();
+        });
     }
     std::string err;
     Profiler prof;
@@ -549,7 +553,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess && (dev < 0 || dev >= kMaxDevices)) e = hipErrorInvalidDevice;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->turn.ev, hipEventDisableTiming);
-        if (e == hipSuccess && ctx->engine == ENGINE_CNN) e = hipEventCreateWithFlags(&ctx->turn.mark, hipEventDisableTiming);
+        if (e == hipSuccess && (ctx->engine == ENGINE_CNN || ctx->engine == ENGINE_MLP)) e = hipEventCreateWithFlags(&ctx->turn.mark, hipEventDisableTiming);
     }
     if (e == hipSuccess && ctx->engine == ENGINE_MLP)
         e = mlp_clear_error_flag(ctx->stream, ctx->ws + ctx->lo.fused, n_clients, ctx->B);
@@ -561,7 +565,7 @@ static aet_status init_context(aet_ctx **out, const aet_model_desc *model, int32
         e = cnn_cluster_need(ctx->lay, ctx->L, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.least, &ctx->turn.need.most);
     ctx->turn.need.clients = n_clients;
     if (e == hipSuccess && ctx->engine == ENGINE_MLP) {
-        e = mlp_cluster_need((int)ctx->lay[0].in_size, ctx->lay[0].oc, n_clients, &ctx->turn.need.cus, &ctx->turn.need.clients, &ctx->turn.need.least);
+        e = mlp_cluster_need((int)ctx->lay[0].in_size, ctx->lay[0].oc, ctx->B, n_clients, &ctx->turn.need.cus, &ctx->turn.need.clients, &ctx->turn.need.least);
         ctx->turn.need.most = ctx->turn.need.least;
     }
     if (e == hipSuccess && ctx->engine == ENGINE_SOFTMAX_BATCH)
@@ -708,7 +712,7 @@ aet_status aet_run_round(aet_ctx *ctx, const aet_threshold *thr, const aet_eta *
         if (ctx->engine == ENGINE_MLP) {
             AET_HIP(ctx, ctx->clustered([&] {
                 return launch_mlp_round(ctx->stream, ctx->profp(), dp, nact, (int)max_m, start, (int)ctx->lay[0].in_size,
-                                        ctx->lay[0].oc, ctx->lay[1].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, &ctx->epoch);
+                                        ctx->lay[0].oc, ctx->lay[1].oc, ctx->B, ctx->ws + ctx->lo.fused, ctx->n, ctx->turn.begins, &ctx->epoch);
             }));
         } else if (ctx->engine == ENGINE_SOFTMAX) {
             AET_HIP(ctx, launch_softmax_round(ctx->stream, ctx->profp(), dp, nact, start, (int)ctx->lay[0].in_size, ctx->lay[0].oc));

@@ -213,13 +213,14 @@ bool mlp_round_supported(int D, int H, int C, int B);
 bool mlp_round_exact(int H, int B);   // no padded units or samples
 bool mlp_padded_pays(int D, int H, int B, int n_clients);   // else: faster than the layer engine
 size_t mlp_round_scratch_bytes(int n_clients, int B);
-// hp: HOST array of the tick's round records (they are passed on in kernel arguments)
+// hp: HOST array of the tick's round records (they are passed on in kernel arguments); first: the XCD of the first client, or below 0:
+// wherever the queue begins
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact,
                             int max_m, const float *Wg, int D, int H, int C, int B, void *scratch,
-                            int n_clients, uint32_t *epoch);
-// What a context's launches hold, for others to go beside them: compute units of an XCD (0: nothing goes beside them),
-// clients, each counted on the XCD that has most, and workgroups of a client
-hipError_t mlp_cluster_need(int D, int H, int n_clients, int *cus, int *clients, int *size);
+                            int n_clients, int first, uint32_t *epoch);
+// Of a context's launches, for others to go beside them: compute units of an XCD (0: nothing does), clients (round the XCDs from `first`
+// on; a multiple of eight, every XCD counted as the fullest, where the kernel does not take `first`) and workgroups of a client
+hipError_t mlp_cluster_need(int D, int H, int B, int n_clients, int *cus, int *clients, int *size);
 hipError_t mlp_clear_error_flag(hipStream_t s, void *scratch, int n_clients, int B);
 const int *mlp_error_flag_ptr(void *scratch, int n_clients, int B);
 // fused round of LeNet-5-style models (kernels_lenet.hip); dp: DEVICE array of round records

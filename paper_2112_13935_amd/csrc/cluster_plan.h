@@ -18,15 +18,12 @@ inline int resident_clusters(int capacity, int xcds, int cluster_size) {
     return xcds * ((capacity / xcds) / cluster_size);
 }
 
-// Compute units of an XCD that a context of dense-ReLU-dense models may hold, for those on other streams to go beside it
-// (cluster_turns.h), as workgroups of a client and clients: `clients` of them at `groups` workgroups each, or twice as many where a launch that
-// has room gives every unit group two (`halves`).  Which XCD a launch begins with is not known, so every XCD counts as having as many
-// clients as any.  0 workgroups: nothing goes beside it, an XCD's `cus` compute units do not hold them (or, with halves, a launch of fewer
-// clients, of which each takes twice as many).
-struct ClusterHold { int workgroups, clients; };
-inline ClusterHold dense_cluster_hold(int cus, int groups, bool halves, int clients) {
-    const int there = (clients + 7) / 8, size = halves ? 2 * groups : groups;
-    return {size * there <= cus ? size : 0, 8 * there};
+// Workgroups that a client of a dense-ReLU-dense context may have, for contexts on other streams to go beside it (cluster_turns.h):
+// `groups`, or twice as many where a launch that has room gives every unit group two (`halves`).  0: nothing goes beside it, an XCD's `cus`
+// compute units do not hold them (or, with halves, a tick of fewer clients may have twice as many of each).
+inline int dense_cluster_size(int cus, int groups, bool halves, int clients) {
+    const int size = halves ? 2 * groups : groups;
+    return size * ((clients + 7) / 8) <= cus ? size : 0;
 }
 
 // Words that stay in an XCD's L2 are seen by that XCD alone (cluster_post.h): a line of memory that

@@ -37,6 +37,21 @@ __device__ __forceinline__ void cluster_announce(unsigned long long *places, int
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same word, and a claim, where the workgroup has taken its place by the XCD that it runs on: false, for the whole
+// workgroup, if another one was there before.  (Should the ids not go round the XCDs; some other place stays empty then, and the bounded waits
+// say so.)  claims: as places, but never NULL; lds: a word that is free
+__device__ __forceinline__ bool cluster_claim(unsigned long long *claims, int me, uint32_t tag, int skew, float *lds) {
+    if (threadIdx.x == 0) {
+        const unsigned long long word = ((unsigned long long)tag << 32) | (unsigned)(xcc_id() + (me == 0 ? skew : 0));
+        const unsigned long long was = __hip_atomic_exchange(claims + me, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *lds = (uint32_t)(was >> 32) == tag ? 1.f : 0.f;
+    }
+    __syncthreads();
+    const bool taken = *lds != 0.f;
+    __syncthreads();
+    return !taken;
+}
+
 // The bounded wait of a poll loop: gave_up() after every poll in vain.  Once this or another workgroup's
 // wait has expired the error flag is set and the answer is yes.
 struct BoundedWait {

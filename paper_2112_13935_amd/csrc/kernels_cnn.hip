@@ -296,20 +296,8 @@ k_cnn_round(const RoundParams *__restrict__ rp, int nact, int G, int first, cons
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     bool dead = false;
     u64 *const place = places ? places + (size_t)p.client * kPlaces : nullptr;
-    if (first < 0) {
-        cluster_announce(place, me, tag0, skew);
-    } else {
-        // the same word, and a claim: a second workgroup in this place, should the ids not go round the XCDs, goes
-        if (tid == 0) {
-            const u64 word = ((u64)tag0 << 32) | (unsigned)(xcc_id() + (me == 0 ? skew : 0));
-            const u64 was = __hip_atomic_exchange(claims + (size_t)p.client * kPlaces + me, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            lds[0] = (uint32_t)(was >> 32) == tag0 ? 1.f : 0.f;
-        }
-        __syncthreads();
-        const bool taken = lds[0] != 0.f;
-        __syncthreads();
-        if (taken) return;
-    }
+    if (first < 0) cluster_announce(place, me, tag0, skew);
+    else if (!cluster_claim(claims + (size_t)p.client * kPlaces, me, tag0, skew, lds)) return;
 
     float *const mine = scratch + (size_t)p.client * g.client_floats;   // the client's scratch memory
     const gf_ptr U = as_global(p.U);

@@ -146,19 +146,23 @@ __global__ void __launch_bounds__(kMlpThreads, 1)
 k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
             int D, int H, int C, int G, int Brun, unsigned long long *__restrict__ xrec,
             unsigned long long *__restrict__ prec, unsigned long long *__restrict__ places, int skew,
-            uint32_t tag0, int *__restrict__ errflag) {
+            uint32_t tag0, int *__restrict__ errflag, unsigned long long *claims, int first) {
     constexpr int B = 16 * NBT;
     static_assert(SUB == 1 || (PAD && NBT == 2), "two steps of 32 samples, of which the second may be short");
     const int Br = PAD ? Brun : B;   // samples of the mini-batch
+    extern __shared__ float smem[];
     // workgroup -> (client, unit group, half): consecutive workgroup ids go round the 8 XCDs,
     // so the workgroups of one client get ids that land on the same XCD and share its L2
-    // for the mini-batch rows and the exchanges.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    // for the mini-batch rows and the exchanges.  Which XCD begins differs from queue to queue: where the launch has
+    // to know (others are beside it), client 0 is on XCD `first` and the workgroup asks where it is.  (The forms of
+    // one step a recursion do not ask: 784 -> 100, B = 20 1,908 -> 1,972 us a job, other registers and spills in the whole kernel.)
+    const int xcd = SUB == 2 ? opaque_scalar((first < 0 ? (int)blockIdx.x : xcc_id() - first) & 7) : (int)blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int a = xcd + 8 * (slot / (G * HF));  // index into this launch's records
     const int g = (slot % (G * HF)) / HF, hf = slot % HF;
     if (a >= nhere) return;
     if (places) places += (int64_t)(rec0 + a) * kPlaces;
-    cluster_announce(places, g * HF + hf, tag0, skew);
+    if (SUB == 1 || first < 0) cluster_announce(places, g * HF + hf, tag0, skew);
+    else if (!cluster_claim(claims + (int64_t)(rec0 + a) * kPlaces, g * HF + hf, tag0, skew, smem)) return;
     const RoundParams p = pack.p[a];
     const gcf_ptr Xg = as_global(p.X);
     const gci_ptr yg = as_global(p.y);
@@ -184,7 +188,6 @@ k_mlp_round(const MlpPack pack, int nhere, int rec0, const float *Wg,
     const int col0 = 16 * TPW * wave;         // first column of the wave's slots in the staged rows
     const int gcol0 = 16 * (tbase + t0);      // first own column in the sample / weight rows
 
-    extern __shared__ float smem[];
     // the small arrays come first so that their addresses fit the 16-bit offset field of
     // the LDS instructions; the big mini-batch tile follows
     float *red = smem;                // [waves][B][16]
@@ -788,7 +791,7 @@ static hipError_t mlp_capacity(size_t lds, int *cap) {   // resident workgroups
 template <int NBT, int TPW, bool FAST, bool FULL, int HF, bool PAD, int SUB = 1>
 static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact, int max_m,
                              const float *Wg, int D, int H, int C, int Br, void *scratch, int n_clients,
-                             uint32_t *epoch, bool *declined = nullptr) {
+                             int first, uint32_t *epoch, bool *declined = nullptr) {
     constexpr int B = 16 * NBT;
     const int G = (H + 15) / 16;
     const size_t lds = mlp_lds_bytes_tpw(TPW, B);
@@ -807,7 +810,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
     }
     if (per_launch < 1) return hipErrorLaunchOutOfResources;
     unsigned long long *xrec = static_cast<unsigned long long *>(scratch);
-    unsigned long long *prec = xrec + mlp_rec_words(n_clients), *places = g_posts_to_memory ? nullptr : prec + mlp_pair_words(n_clients);
+    unsigned long long *prec = xrec + mlp_rec_words(n_clients), *claims = prec + mlp_pair_words(n_clients), *places = g_posts_to_memory ? nullptr : claims;
     int *errflag = reinterpret_cast<int *>(xrec + mlp_all_words(n_clients));
     // step tags of this launch: never 0 (the cleared state) and never a tag that an
     // earlier launch may have left in the records
@@ -830,7 +833,7 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
         MlpPack pack;
         for (int j = 0; j < here; ++j) pack.p[j] = hp[a0 + j];
         if (prof && prof->on[F_MLP_ROUND]) prof->before(F_MLP_ROUND, s);
-        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD, SUB><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, g_xcd_skew, tag0, errflag);
+        k_mlp_round<NBT, TPW, FAST, FULL, HF, PAD, SUB><<<grid, kMlpThreads, lds, s>>>(pack, here, a0, Wg, D, H, C, G, Br, xrec, prec, places, g_xcd_skew, tag0, errflag, claims, first);
         if (prof && prof->on[F_MLP_ROUND]) prof->after(F_MLP_ROUND, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -840,8 +843,9 @@ static hipError_t mlp_launch(hipStream_t s, Profiler *prof, const RoundParams *h
 
 hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp, int nact, int max_m,
                             const float *Wg, int D, int H, int C, int B, void *scratch,
-                            int n_clients, uint32_t *epoch) {
+                            int n_clients, int first, uint32_t *epoch) {
     if (nact <= 0) return hipSuccess;
+    if (first > 7 || (first >= 0 && B <= 32)) return hipErrorInvalidValue;
     const bool small = mlp_tpw(D) == 2;  // at most 2 K tiles per wave
     const bool fast = (D & 15) == 0;
     const bool full = D == 16 * kMlpWaves * mlp_tpw(D);   // no pad tiles
@@ -849,7 +853,7 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
     // client gets its 2 G workgroups resident in one launch
     const bool pad = !mlp_round_exact(H, B), half = mlp_halves(D);
     if (B > 32) {
-#define AET_MLP_TWO(tpw, fast_, hf, ...) mlp_launch<2, tpw, fast_, false, hf, true, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)
+#define AET_MLP_TWO(tpw, fast_, hf, ...) mlp_launch<2, tpw, fast_, false, hf, true, 2>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, first, epoch, ##__VA_ARGS__)
         if (half) {
             bool declined = false;
             const hipError_t e = fast ? AET_MLP_TWO(kMlpHalfTPW, true, 2, &declined) : AET_MLP_TWO(kMlpHalfTPW, false, 2, &declined);
@@ -860,8 +864,8 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
 #undef AET_MLP_TWO
     }
 #define AET_MLP(nbt, tpw, fast_, full_, hf, ...)                                                                            \
-    (pad ? mlp_launch<nbt, tpw, fast_, full_, hf, true>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__)   \
-         : mlp_launch<nbt, tpw, fast_, full_, hf, false>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, epoch, ##__VA_ARGS__))
+    (pad ? mlp_launch<nbt, tpw, fast_, full_, hf, true>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, first, epoch, ##__VA_ARGS__)   \
+         : mlp_launch<nbt, tpw, fast_, full_, hf, false>(s, prof, hp, nact, max_m, Wg, D, H, C, B, scratch, n_clients, first, epoch, ##__VA_ARGS__))
     if (half) {
         bool declined = false;
         hipError_t e;
@@ -885,16 +889,15 @@ hipError_t launch_mlp_round(hipStream_t s, Profiler *prof, const RoundParams *hp
 #undef AET_MLP
 }
 
-hipError_t mlp_cluster_need(int D, int H, int n_clients, int *cus, int *clients, int *size) {
+hipError_t mlp_cluster_need(int D, int H, int B, int n_clients, int *cus, int *clients, int *size) {
     int dev = 0, all = 0, xcds = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&all, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = device_xcds(&xcds);
     if (e != hipSuccess) return e;
-    const ClusterHold hold = dense_cluster_hold(xcds == 8 ? all / xcds : 0, (H + 15) / 16, mlp_halves(D), n_clients);
-    *cus = hold.workgroups ? all / xcds : 0;
-    *clients = hold.clients;
-    *size = hold.workgroups;
+    *size = dense_cluster_size(xcds == 8 ? all / xcds : 0, (H + 15) / 16, mlp_halves(D), n_clients);
+    *cus = *size ? all / xcds : 0;
+    *clients = B > 32 ? n_clients : (n_clients + 7) / 8 * 8;
     return hipSuccess;
 }
 

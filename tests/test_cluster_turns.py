@@ -235,58 +235,66 @@ int main() {
 """
 
 
-# Contexts of dense-ReLU-dense models: clusters of one size, on whichever XCD.
+# Contexts of dense-ReLU-dense models: clusters of one size.
 DENSE = r"""
 #include "cluster_plan.h"
 #include "cluster_turns.h"
 #include <cstdio>
 #define CHECK(x) do { if (!(x)) { std::printf("failed: %s (line %d)\n", #x, __LINE__); return 1; } } while (0)
 using Turns = aet::ClusterTurns<int>;
-// launches of k contexts in turn, none of which is done: the most that are ahead of nothing, and whether one had a place of its own
-int beside(int k, int groups, bool halves, int clients, bool *fixed) {
+// launches of k contexts in turn, each under way while the others make theirs: how many wait for nothing once all know of each other (bad: more
+// workgroups on an XCD than it holds, or another size)
+int beside(int k, int groups, bool halves, int clients, bool *bad) {
     Turns turns;
     std::vector<Turns::Member> m(k);
-    const aet::ClusterHold hold = aet::dense_cluster_hold(32, groups, halves, clients);
+    const int size = aet::dense_cluster_size(32, groups, halves, clients);
     Turns::Need need;
-    if (hold.workgroups) need = {32, hold.clients, hold.workgroups, hold.workgroups};
-    int free = 0;
+    if (size) need = {32, clients, size, size};
+    int free = 0, held[8] = {};
     for (int i = 0; i < k; ++i) { m[i].stream = i; turns.join(&m[i]); }
-    for (int round = 0; round < 3; ++round)
+    for (int round = 0; round < 5; ++round)
         for (int i = 0; i < k; ++i) {
             bool ordered = false;
-            turns.take(&m[i], need, [](Turns::Member *) { return false; }, [](Turns::Member *) { return 1; }, [](Turns::Member *) { return false; },
+            turns.take(&m[i], need, [](Turns::Member *) { return false; }, [](Turns::Member *) { return 0; }, [](Turns::Member *) { return true; },
                        [&](Turns::Member *) { ordered = true; return 0; },
                        [&](const Turns::Place &p) {
-                           *fixed = *fixed || p.first >= 0 || (hold.workgroups && p.size != hold.workgroups);
+                           *bad = *bad || (size && p.size != size);
+                           for (int x = 0; x < 8 && round == 4 && !ordered && size; ++x) {
+                               for (int c = 0; c < clients; ++c) held[x] += p.first < 0 ? (c % 8 == 0) * size : ((p.first + c) % 8 == x) * size;
+                               *bad = *bad || held[x] > 32;
+                           }
                            return 0;
                        });
-            free += round == 0 && !ordered;
+            free += round == 4 && !ordered;
         }
     return free;
 }
 int main() {
-    bool fixed = false;
-    CHECK(beside(8, 1, false, 1, &fixed) == 8);     // 30 -> 10
-    CHECK(beside(8, 7, false, 8, &fixed) == 4);     // 100 -> 100: 28 of 32 compute units
-    CHECK(beside(8, 7, false, 9, &fixed) == 2);
-    CHECK(beside(8, 7, true, 1, &fixed) == 2);      // 784 -> 100, two workgroups a unit group
-    CHECK(beside(4, 8, true, 8, &fixed) == 2);
-    CHECK(beside(4, 8, true, 16, &fixed) == 1);     // the whole GPU
-    CHECK(beside(4, 8, true, 17, &fixed) == 1);     // unit groups have one workgroup, or two in a tick of fewer clients
-    CHECK(beside(4, 16, false, 17, &fixed) == 1);   // more than one launch
-    CHECK(!fixed);
+    bool bad = false;
+    CHECK(beside(8, 1, false, 1, &bad) == 8);     // 30 -> 10
+    CHECK(beside(4, 7, false, 8, &bad) == 4);     // 100 -> 100: 28 of 32 compute units
+    CHECK(beside(5, 7, false, 8, &bad) < 5);
+    CHECK(beside(8, 7, true, 1, &bad) == 8);      // 784 -> 100, two workgroups a unit group
+    CHECK(beside(8, 16, true, 1, &bad) == 8);     // 784 -> 250: an XCD each
+    CHECK(beside(4, 16, true, 2, &bad) == 4);
+    CHECK(beside(5, 16, true, 2, &bad) < 5);
+    CHECK(beside(2, 8, true, 8, &bad) == 2);
+    CHECK(beside(2, 8, true, 16, &bad) < 2);      // the whole GPU
+    CHECK(beside(2, 8, true, 17, &bad) < 2);      // unit groups have one workgroup, or two in a tick of fewer clients
+    CHECK(beside(2, 16, false, 17, &bad) < 2);    // more than one launch
+    CHECK(!bad);
     for (int groups = 1; groups <= 16; ++groups)
         for (int halves = 0; halves < 2; ++halves)
             for (int clients = 1; clients < 300; ++clients) {
-                const aet::ClusterHold h = aet::dense_cluster_hold(32, groups, halves, clients);
+                const int size = aet::dense_cluster_size(32, groups, halves, clients), there = (clients + 7) / 8;
                 // as many as launches of these clients, or of some of them, can have on an XCD, or nothing goes beside them
                 int most = 0;
                 for (int now = 1; now <= clients; ++now)
                     most = std::max(most, (now + 7) / 8 * groups * (halves && now <= aet::resident_clusters(256, 8, 2 * groups) ? 2 : 1));
-                CHECK(h.workgroups == 0 || (h.clients / 8 * h.workgroups >= most && h.clients / 8 * h.workgroups <= 32));
-                CHECK(h.workgroups || most > 16);
+                CHECK(size == 0 || (there * size >= most && there * size <= 32));
+                CHECK(size || most > 16);
             }
-    CHECK(aet::dense_cluster_hold(0, 1, false, 1).workgroups == 0);
+    CHECK(aet::dense_cluster_size(0, 1, false, 1) == 0);
     std::puts("ok");
 }
 """

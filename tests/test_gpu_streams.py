@@ -46,7 +46,10 @@ MIXES = {
 
 
 @pytest.mark.parametrize("mode,variants", [(2, 0), (0, 1)])
-def test_contexts_beside_each_other_by_the_other_ways_of_exchange(mode, variants):
+@pytest.mark.parametrize("make", [lambda n: cnn(n, 8, 5, 12, 5),
+                                  lambda n: W.config2(n_clients=n, n_total=n * 70, d=784, hidden=100, batch=40, rounds=6, a=40, b=80)],
+                         ids=["cnn", "two steps"])
+def test_contexts_beside_each_other_by_the_other_ways_of_exchange(make, mode, variants):
     """Words through memory, without asking and because one workgroup of each client names another XCD, with the XCD of
     the first client given: the bits of a context that is alone."""
     import torch
@@ -61,7 +64,7 @@ def test_contexts_beside_each_other_by_the_other_ways_of_exchange(mode, variants
         return ctx.aet_get_weights_device(-1)
     jobs = []
     for n in (1, 3, 2):
-        wl = cnn(n, 8, 5, 12, 5)
+        wl = make(n)
         X, y = upload(wl)
         stream = torch.cuda.Stream()
         torch.cuda.synchronize()
